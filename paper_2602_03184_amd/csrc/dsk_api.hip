@@ -43,8 +43,12 @@ CompressWs compress_ws_layout(const dsk_compress_args& a) {
     ws.jump_stride = (a.total_tokens + 15) / 16 * 16;
   }
   ws.seg_jump = off;   off += align_up((size_t)ws.jump_levels * ws.jump_stride * sizeof(uint16_t) + 32);
-  const size_t n_samp = (size_t)a.B * (a.n_class > 0 ? a.n_class : 0) * (a.M > 0 ? a.M : 0);
-  ws.imp_part = off;   off += align_up(n_samp * (size_t)a.Hkv * 2 * sizeof(float));
+  ws.imp_plan = ws.imp_part = off;
+  if (a.n_class > 0 && a.M > 0) {
+    const ImpLayout l = importance_layout(a.B, a.n_class * a.M, a.W > 0 ? a.W : 1, a.Hq, a.Hkv);
+    off += align_up(l.plan_ints * sizeof(int32_t));
+    ws.imp_part = off;   off += align_up(l.part_rows * sizeof(float4));
+  }
   ws.total = off;
   return ws;
 }

@@ -28,7 +28,8 @@ struct CompressWs {
   size_t tile_count;  // i32 [n_cand_tiles + 1]      candidates per tile, then exclusive scan
   size_t seg_cand;    // i32 [2 * n_tiles]           candidates per segmentation tile, then their offsets in the sequence
   size_t seg_jump;    // u16 [jump_levels][jump_stride]  position in the tile 2, 4, 8 .. chunks after each token
-  size_t imp_part;    // f32 [B * n_class * M * Hkv] per-(sample, kv head) partial sums
+  size_t imp_plan;    // i32 [ImpLayout::plan_ints]   plan of the importance launch
+  size_t imp_part;    // float4 [ImpLayout::part_rows] softmax statistics of a piece's query rows
   size_t total;
   int tiles_per_seq;  // ceil(max_seqlen / kSegTile)
   int map_row;        // min(C + delta, kSegTile)
@@ -37,6 +38,19 @@ struct CompressWs {
   int jump_stride;    // total_tokens rounded up to 16
 };
 CompressWs compress_ws_layout(const dsk_compress_args& a);
+
+// ---- stage IMPORTANCE ----------------------------------------------------------------------
+constexpr int kImpRows = 256;          // query rows that share the key tiles of a workgroup
+constexpr int kImpMaxSamples = DSK_MAX_CLASSES * kMaxSamplesPerClass;   // samples of a sequence
+constexpr int kImpMaxItems = 4096;     // items of all KV heads planned in one launch (unless one sequence has more)
+constexpr int kImpMaxSeqs = 256;       // sequences planned in one launch
+constexpr int kImpPieces = 512;        // workgroups of a launch: two per CU
+struct ImpLayout {
+  int seqs;            // sequences per launch
+  int items;           // upper bound of the groups of kImpRows query rows of one KV head in a launch
+  size_t plan_ints, part_rows;
+};
+ImpLayout importance_layout(int B, int n_samp, int W, int Hq, int Hkv);
 
 hipError_t launch_candidates(const dsk_compress_args& a, const CompressWs& ws, hipStream_t st);
 hipError_t launch_importance(const dsk_compress_args& a, const CompressWs& ws, hipStream_t st);

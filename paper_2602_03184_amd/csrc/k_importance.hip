@@ -2,22 +2,37 @@
 // layer, for the sampled candidates, followed by the class-mean -> weight-in-tenths map.
 //
 // For a sampled candidate at position t the W queries that follow it, for the G query heads of
-// one KV head, form a [W*G x D] block; its logits against keys 0..t+W are a real dense
-// contraction, so they run on the matrix cores: S^T tile [32 keys x 32 query rows] =
-// K tile [32 x 128] . Q^T [128 x 32] as 8 MFMA 32x32x16 bf16 steps.  Keys are the MFMA "A" rows
-// so that a lane ends up holding 16 keys of ONE query row: the softmax statistics (running max,
-// total mass, mass on the retained region O_t, mass on the discarded region D_t) then
-// accumulate per lane with no cross-lane traffic until the very end.  K rows are read straight
-// from HBM into the A-operand layout: the contraction index is permuted so that lane half
-// hf = lane/32 owns channels [64*hf, 64*hf+64) of its key row, i.e. eight contiguous 16-byte
-// loads; Q^T (staged in LDS once per workgroup) is read with the same permutation, so the sum
-// over channels is unchanged.  Every key tile a wavefront fetches is multiplied with the query
-// windows of 3 or 4 sample slots (fetching a tile per sample made the operand loads, one key row
-// per lane, the bound), the next tile is requested before the current one is used, and tiles that
-// lie wholly in a sample's discarded region (nearly all of them) take an unmasked path: one running
-// sum feeds the total and the discarded mass.  With that a wavefront no longer waits for loads;
-// what remains is the vector-ALU work of the running softmax (16 exponentials and about 90 other
-// instructions per lane and product, next to 8 MFMAs), two wavefronts per SIMD.
+// one KV head, are W*G query rows; their logits against keys 0..t+W are a real dense contraction,
+// so they run on the matrix cores: S^T tile [32 keys x 32 query rows] = K tile [32 x 128] .
+// Q^T [128 x 32] as 8 MFMA 32x32x16 bf16 steps.  Keys are the MFMA "A" rows so that a lane ends up
+// holding 16 keys of ONE query row: the softmax statistics (mass of all keys, of the retained region
+// O_t, of the discarded region D_t) accumulate per lane with no cross-lane traffic until the very end.
+//
+// What bounds it: the vector ALU.  Per product of a key tile and a row tile a lane has 16 exponentials
+// (a quarter of the issue rate), 16 multiply-adds and 16 adds = 384 cycles of a SIMD, next to 256 cycles
+// of MFMA, which run in their shadow when the two are interleaved.  Everything else is kept off that path:
+//  - The samples of a sequence are ranked by position (latest first) and their rows packed back to back,
+//    so that row tiles are full for any W*G and the samples of a workgroup end at about the same key.
+//  - A workgroup (8 wavefronts x kImpNS row tiles, query operands in registers) shares every key tile
+//    through LDS (two buffers of 64 rows, 16-byte chunks permuted by the row number so that the operand
+//    reads touch all banks), loaded coalesced and once per kImpRows query rows.
+//  - The work line -- for every KV head, every item (kImpRows rows of one sequence), every stage of 64
+//    keys -- is cut into equal pieces, one per workgroup, wherever the cuts fall; a piece leaves its rows'
+//    statistics in the workspace and the finishing kernel merges them.  (One workgroup per group of
+//    samples left the chip idle half of the time: the latest sample has 2.5 times the mean's keys.)
+//  - The exponentials are taken relative to a reference that is only moved when a tile's sum exceeds
+//    kImpRescaleAt (at first, and seldom afterwards), so the usual tile has no maximum and no rescaling.
+//  - The products of the next tile are issued in between the exponentials of the current one; with both
+//    workgroups of a CU at work a product takes about 585 cycles of a SIMD (440 when the other one idles).
+//    Holding the products of both row tiles at once spilled registers, leaving the MFMAs in front of the
+//    branch on the kind of a tile serialised them (1.2 instead of 0.8 us per key tile).
+//  - Tiles that cross a region's edge (two or three per row tile, 2.5 times the work) are left out of that
+//    loop and done by each wavefront on its own, so that it does not hold up the others at a barrier.
+// Measured (stage IMPORTANCE, 32 query / 8 KV heads, W = 8): 128 samples of a 128K sequence 92.7 -> 57.7 us,
+// 1024 samples of eight sequences of 24K to 64K tokens 360 -> 233 us (740 TFLOP/s of q.k products), against
+// one workgroup per 3 or 4 consecutive samples with the key tiles fetched by each wavefront.
+#include <type_traits>
+
 #include "dsk_common.hpp"
 #include "dsk_internal.hpp"
 
@@ -29,7 +44,7 @@ typedef __attribute__((ext_vector_type(16))) float f32x16_t;
 constexpr float kImpLog2e = 1.4426950408889634f;
 
 struct RowStat {       // online-softmax statistics of one query row over a subset of keys
-  float m;             // running max of logits (log2 units)
+  float m;             // reference the sums are relative to (log2 units), -inf: no key seen
   float zt, zo, zd;    // sum of 2^(z-m): all causal keys, retained region, discarded region
 };
 
@@ -43,220 +58,639 @@ __device__ __forceinline__ void stat_merge(RowStat& a, const RowStat& b) {
   a.m = m;
 }
 
-// Sample slots sharing the key tiles a wavefront loads (consecutive slots: mostly the same class,
-// neighbouring positions).  Their Q^T operands live in LDS (rows of 128 channels padded to 136 so
-// that the 16-byte reads of 16 consecutive query rows cover all banks), which leaves the registers
-// to the key tiles and the statistics.
-// 4 slots per group with 8 wavefronts when the launch is small (one sequence: 32 groups x 8 KV heads
-// fill the 256 CUs in one round, 90 instead of 118 us at 128 windows), 3 with 4 wavefronts when
-// there are many workgroups anyway (4 and 6 were measured there: 617 and 551 against 554 us).
-constexpr int kImpQRow = DSK_HEAD_DIM + 8;   // bf16 elements per query row in LDS
+constexpr int kImpThreads = 256;
+constexpr int kImpWaves = kImpThreads / DSK_WAVE;
+constexpr int kImpNS = kImpRows / 32 / kImpWaves;     // row tiles per wavefront
+constexpr int kImpStage = 64;                         // keys per LDS buffer
+constexpr int kImpMinStages = 4;                      // a piece shorter than this does not pay for its start
+constexpr int kImpItemCost = 5;                       // start of an item and its tiles at the regions' edges, in stages
+constexpr float kImpRescaleAt = 64.0f;
+constexpr float kImpHeadroom = 4.0f;                  // log2 units a new reference lies above the largest logit seen
+static_assert(kImpNS == 2, "the row tiles of a wavefront are written out below");
 
-// grid: (group of kImpSamples sample slots, kv head, sequence)
-template <int kImpThreads, int kImpSamples>
-__global__ __launch_bounds__(kImpThreads) void importance_kernel(
+// low position bits left out of a sample's sort key (19 bits of it are in)
+__device__ __forceinline__ int imp_slack(int L) { return L > (1 << 19) ? 13 - __clz(L - 1) : 0; }
+
+// Lengths and cuts of the work line.  Piece w covers [seg_lo(w), seg_lo(w + 1)).
+struct ImpLine {
+  uint32_t per, extra;   // the first `extra` pieces have per + 1 stages, the others per
+  __device__ __forceinline__ uint64_t lo(uint32_t w) const { return (uint64_t)w * per + (w < extra ? w : extra); }
+  __device__ __forceinline__ uint32_t piece_of(uint64_t x) const {
+    const uint64_t head = (uint64_t)extra * (per + 1);
+    if (x < head) return (uint32_t)((x >> 32) ? x / (per + 1) : (uint32_t)x / (per + 1));
+    const uint64_t y = x - head;
+    return extra + (uint32_t)((y >> 32) ? y / per : (uint32_t)y / per);
+  }
+};
+
+// exclusive prefix sum over the workgroup (one value per thread); *total = sum of all
+__device__ __forceinline__ int block_excl_scan(int v, int* sm_wave, int* total) {
+  const int lane = threadIdx.x & (DSK_WAVE - 1), wave = threadIdx.x / DSK_WAVE;
+  const int incl = wave_incl_scan_i(v, lane);
+  __syncthreads();                                    // earlier readers of sm_wave are done
+  if (lane == DSK_WAVE - 1) sm_wave[wave] = incl;
+  __syncthreads();
+  int before = 0, all = 0;
+#pragma unroll
+  for (int w = 0; w < kImpWaves; ++w) {
+    before += w < wave ? sm_wave[w] : 0;
+    all += sm_wave[w];
+  }
+  *total = all;
+  return before + incl - v;
+}
+
+// logits of a key tile against one row tile: kf[u] = channels [64*hf + 8u, +8) of key `col`
+__device__ __forceinline__ f32x16_t imp_product(const bf16x8_t (&kf)[8], const bf16x8_t (&qf)[8]) {
+  f32x16_t acc;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
+#pragma unroll
+  for (int u = 0; u < 8; ++u) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[u], qf[u], acc, 0, 0, 0);
+  return acc;
+}
+
+__device__ __forceinline__ float imp_tile_sum(const f32x16_t& acc, float scale_log2, float m) {
+  float e[16];
+#pragma unroll
+  for (int r = 0; r < 16; ++r) e[r] = __builtin_amdgcn_exp2f(fmaf(acc[r], scale_log2, -m));
+  float a = e[0], b = e[1], c = e[2], d = e[3];       // four chains of four, fixed order
+#pragma unroll
+  for (int r = 4; r < 16; r += 4) { a += e[r]; b += e[r + 1]; c += e[r + 2]; d += e[r + 3]; }
+  return (a + b) + (c + d);
+}
+
+struct RowAcc {          // of one lane: 16 keys in 32 of one query row
+  float m, zf;           // reference; mass of tiles that lie wholly in the discarded region
+  float zt, zo, zd;      // masses from the other tiles
+};
+
+// the tile's sum is too large for the reference (or there is none yet): move it above the largest logit
+__device__ __forceinline__ void imp_move_reference(RowAcc& st, const f32x16_t& acc, float scale_log2) {
+  float top = acc[0] * scale_log2;
+#pragma unroll
+  for (int r = 1; r < 16; ++r) top = fmaxf(top, acc[r] * scale_log2);
+  const float mn = top > st.m ? top + kImpHeadroom : st.m;
+  const float f = mn == st.m ? 1.0f : __builtin_amdgcn_exp2f(st.m - mn);   // 0 while there is none
+  st.zf *= f; st.zt *= f; st.zo *= f; st.zd *= f;
+  st.m = mn;
+}
+
+__device__ __forceinline__ bool imp_too_large(float sum) { return __any(!(sum <= kImpRescaleAt)); }
+
+// a tile that crosses a region's edge, the causal edge or the end of the sequence.  Bounds count from
+// the lane's first key of the tile: keys <= kmax exist, >= o_lo and <= t are retained, <= d_hi discarded.
+__device__ __forceinline__ void imp_masked_tile(RowAcc& st, f32x16_t z, float scale_log2, int kmax, int o_lo, int t,
+                                                int d_hi) {
+#pragma unroll
+  for (int r = 0; r < 16; ++r) z[r] = kmax >= 8 * (r / 4) + (r % 4) ? z[r] : -__builtin_inff();
+  float zt, zo, zd;
+  auto sums = [&]() {
+    zt = zo = zd = 0.0f;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int k = 8 * (r / 4) + (r % 4);
+      float e = __builtin_amdgcn_exp2f(fmaf(z[r], scale_log2, -st.m));
+      zt += e;
+      zd += d_hi >= k ? e : 0.0f;
+      e = t >= k ? e : 0.0f;
+      zo += o_lo <= k ? e : 0.0f;
+    }
+  };
+  sums();
+  if (imp_too_large(zt)) {
+    imp_move_reference(st, z, scale_log2);
+    sums();
+    // a lane without any key so far still has no reference and no number here; it adds nothing
+    if (st.m == -__builtin_inff()) zt = zo = zd = 0.0f;
+  }
+  st.zt += zt; st.zo += zo; st.zd += zd;
+}
+
+// The plan, in the workspace (ints):
+//   head [0] stages of all items of one KV head, [1] pieces, [2] items of one KV head
+//   n_valid [nseq], first item of each sequence [nseq + 1], first unit of each item [items + 1]
+//   rank of each sample [nseq * n_samp] (-1 = absent), samples by rank [nseq * n_samp], their positions
+struct ImpPlan {
+  int32_t *head, *n_valid, *item_base, *item_at, *rank, *order, *pos;
+};
+__host__ __device__ __forceinline__ ImpPlan imp_plan(int32_t* w, int nseq, int n_samp, int items) {
+  ImpPlan p;
+  p.head = w;
+  p.n_valid = w + 4;
+  p.item_base = p.n_valid + nseq;
+  p.item_at = p.item_base + nseq + 1;
+  p.rank = p.item_at + items + 1;
+  p.order = p.rank + (int64_t)nseq * n_samp;
+  p.pos = p.order + (int64_t)nseq * n_samp;
+  return p;
+}
+
+// sort key of a sample at position t: position, then the smaller index; 0 = absent
+__device__ __forceinline__ uint32_t imp_key(bool have, int t, int slack, int i) {
+  return have ? (((uint32_t)t >> slack) + 1u) << 12 | (uint32_t)(4095 - i) : 0u;
+}
+
+// keys among quads [lo, hi) of a table that are larger than `key`
+__device__ __forceinline__ int imp_count_larger(const uint32_t* table, int lo, int hi, uint32_t key) {
+  const uint4* keys = reinterpret_cast<const uint4*>(table);
+  int c = 0;
+  for (int j = lo; j < hi; ++j) {
+    const uint4 o = keys[j];
+    c += (o.x > key ? 1 : 0) + (o.y > key ? 1 : 0) + (o.z > key ? 1 : 0) + (o.w > key ? 1 : 0);
+  }
+  return c;
+}
+
+// The samples of a sequence ranked by position, latest first: 64 samples per workgroup, counted by its
+// four wavefronts against a quarter of the sequence's samples each.  grid: (64 samples, sequence)
+__global__ __launch_bounds__(kImpThreads) void importance_rank_kernel(
+    const int32_t* __restrict__ samp_pos, const int32_t* __restrict__ cu_seqlens, int seq_first, int nseq, int n_samp,
+    int items, int32_t* __restrict__ plan) {
+  __shared__ __attribute__((aligned(16))) uint32_t sm_key[kImpMaxSamples];
+  __shared__ int sm_rank[DSK_WAVE], sm_n;
+  const ImpPlan pl = imp_plan(plan, nseq, n_samp, items);
+  const int s = blockIdx.y;
+  const int tid = threadIdx.x;
+  const int lane = tid & (DSK_WAVE - 1), wave = tid / DSK_WAVE;
+  const int ns4 = (n_samp + 3) & ~3;
+  const int seq0 = cu_seqlens[seq_first + s];
+  const int L = cu_seqlens[seq_first + s + 1] - seq0;
+  const int slack = imp_slack(L);
+  const int32_t* pos = samp_pos + (int64_t)(seq_first + s) * n_samp;
+  if (tid < DSK_WAVE) sm_rank[tid] = 0;
+  if (tid == 0) sm_n = 0;
+  __syncthreads();
+  int n = 0;
+  for (int i = tid; i < ns4; i += kImpThreads) {
+    const int tg = i < n_samp ? pos[i] : -1;
+    const bool have = tg >= 0 && tg - seq0 >= 0 && tg - seq0 < L;
+    sm_key[i] = imp_key(have, tg - seq0, slack, i);
+    n += have ? 1 : 0;
+  }
+  if (n > 0) atomicAdd(&sm_n, n);
+  __syncthreads();
+  const int i = blockIdx.x * DSK_WAVE + lane;
+  const uint32_t key = i < n_samp ? sm_key[i] : 0u;
+  const int quads = ns4 / 4;
+  const int c = imp_count_larger(sm_key, wave * quads / kImpWaves, (wave + 1) * quads / kImpWaves, key);
+  atomicAdd(&sm_rank[lane], c);
+  __syncthreads();
+  if (wave == 0 && i < n_samp) {
+    const int r = sm_rank[lane];
+    pl.rank[s * n_samp + i] = key != 0 ? r : -1;
+    if (key != 0) {
+      pl.order[s * n_samp + r] = i;
+      pl.pos[s * n_samp + r] = pos[i] - seq0;
+    }
+  }
+  if (blockIdx.x == 0 && tid == 0) pl.n_valid[s] = sm_n;
+}
+
+// grid: persistent workgroups, one piece of the work line each.  OWN_RANK (one sequence of at most
+// kImpThreads samples): every workgroup ranks the samples itself, which takes it 1 us, instead of a
+// launch in front (63.0 -> 57.7 us for the stage at 128 samples of a 128K sequence, 32 heads).
+template <bool OWN_RANK>
+__global__ __launch_bounds__(kImpThreads, 2) void importance_kernel(
     const uint16_t* __restrict__ K, int64_t kst, int64_t ksh, const uint16_t* __restrict__ qwin,
-    const int32_t* __restrict__ samp_pos, const int32_t* __restrict__ cu_seqlens, int n_samp, int W, int R,
-    int Hq, int G, float alpha, float scale_log2, float* __restrict__ imp_part, int Hkv) {
-  constexpr int kImpWaves = kImpThreads / DSK_WAVE;
-  __shared__ RowStat sm_stat[kImpSamples][kImpWaves][32];
-  __shared__ float sm_val[kImpSamples][32];
-  __shared__ __attribute__((aligned(16))) uint16_t sm_q[kImpSamples][32][kImpQRow];
-  const int hk = blockIdx.y;
-  const int s = blockIdx.z;
-  const int lane = threadIdx.x & (DSK_WAVE - 1);
-  const int wave = threadIdx.x / DSK_WAVE;
-  const int col = lane & 31;        // query row of the tile this lane accumulates
+    const int32_t* __restrict__ samp_pos, const int32_t* __restrict__ cu_seqlens, int seq_first, int nseq, int n_samp, int items, int W, int R, int Hq, int G,
+    int Hkv, float scale_log2, int32_t* __restrict__ plan, float4* __restrict__ part) {
+  __shared__ __attribute__((aligned(16))) uint16_t sm_k[2][kImpStage][DSK_HEAD_DIM];
+  __shared__ int sm_ib[kImpMaxSeqs + 1];         // first item of each sequence
+  __shared__ int sm_nv[kImpMaxSeqs];             // its samples
+  __shared__ int sm_wave[kImpWaves];
+  __shared__ int sm_cur[2];
+
+  const ImpPlan pl = imp_plan(plan, nseq, n_samp, items);
+  const int tid = threadIdx.x;
+  const int lane = tid & (DSK_WAVE - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(tid / DSK_WAVE);
+  const int rps = W * G;                          // query rows of one (sample, KV head)
+
+  __shared__ uint16_t sm_order[OWN_RANK ? kImpThreads : 1];   // the plan's order and positions
+  __shared__ int sm_pos[OWN_RANK ? kImpThreads : 1];
+  auto order_of = [&](int s, int j) { return OWN_RANK ? (int)sm_order[j] : pl.order[s * n_samp + j]; };
+  auto pos_of = [&](int s, int j) { return OWN_RANK ? sm_pos[j] : pl.pos[s * n_samp + j]; };
+  int own_valid = 0;
+  if constexpr (OWN_RANK) {
+    uint32_t* sm_key = reinterpret_cast<uint32_t*>(&sm_k[0][0][0]);
+    const int seq0 = cu_seqlens[seq_first];
+    const int L = cu_seqlens[seq_first + 1] - seq0;
+    const int tg = tid < n_samp ? samp_pos[(int64_t)seq_first * n_samp + tid] : -1;
+    const int t = tg - seq0;
+    const bool have = tg >= 0 && t >= 0 && t < L;
+    const uint32_t key = imp_key(have, t, imp_slack(L), tid);
+    sm_key[tid] = key;
+    const int in_wave = __popcll(__ballot(have));
+    if (lane == 0) sm_wave[wave] = in_wave;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < kImpWaves; ++w) own_valid += sm_wave[w];
+    const int rank = imp_count_larger(sm_key, 0, (n_samp + 3) / 4, key);
+    if (have) { sm_order[rank] = (uint16_t)tid; sm_pos[rank] = t; }
+    if (blockIdx.x == 0 && tid < n_samp) pl.rank[tid] = have ? rank : -1;
+    __syncthreads();
+  }
+
+  // ---- the work line, the same in every workgroup ----------------------------------------------
+  int n_list;                                     // items of one KV head
+  {
+    const int nv = OWN_RANK ? (tid == 0 ? own_valid : 0) : (tid < nseq ? pl.n_valid[tid] : 0);
+    const int at = block_excl_scan((nv * rps + kImpRows - 1) / kImpRows, sm_wave, &n_list);
+    if (tid < nseq) { sm_ib[tid] = at; sm_nv[tid] = nv; }
+    if (tid == 0) sm_ib[nseq] = n_list;
+  }
+  __syncthreads();
+  if (n_list == 0) {                              // no sample anywhere
+    if (blockIdx.x == 0 && tid < 4) pl.head[tid] = 0;
+    return;
+  }
+  auto seq_of = [&](int item) {
+    int a = 0, b = nseq - 1;
+    while (a < b) {
+      const int mid = (a + b + 1) >> 1;
+      if (sm_ib[mid] <= item) a = mid; else b = mid - 1;
+    }
+    return a;
+  };
+  // stages of 64 keys up to the item's latest query, and its length on the line
+  auto stages_of = [&](int item, int s) {
+    const int j0 = (item - sm_ib[s]) * kImpRows / rps;
+    const int L = cu_seqlens[seq_first + s + 1] - cu_seqlens[seq_first + s];
+    const int t = pos_of(s, j0) | ((1 << imp_slack(L)) - 1);   // no later one in the item
+    return (t < L - 1 - W ? t + W : L - 1) / kImpStage + 1;
+  };
+  const int per_thread = (n_list + kImpThreads - 1) / kImpThreads;
+  const int item_lo = tid * per_thread < n_list ? tid * per_thread : n_list;
+  const int item_hi = item_lo + per_thread < n_list ? item_lo + per_thread : n_list;
+  int own = 0;
+  for (int it = item_lo; it < item_hi; ++it) own += stages_of(it, seq_of(it)) + kImpItemCost;
+  int T1;
+  const int own_at = block_excl_scan(own, sm_wave, &T1);
+  const uint64_t T = (uint64_t)T1 * Hkv;
+  uint32_t nw = gridDim.x;
+  if (T / kImpMinStages < nw) nw = T / kImpMinStages > 0 ? (uint32_t)(T / kImpMinStages) : 1u;
+  if (nw >= 8) nw &= ~7u;
+  ImpLine line;
+  line.per = (uint32_t)(T / nw);
+  line.extra = (uint32_t)(T % nw);
+  if (blockIdx.x == 0) {
+    if (tid == 0) { pl.head[0] = T1; pl.head[1] = (int)nw; pl.head[2] = n_list; }
+    for (int s = tid; s <= nseq; s += kImpThreads) pl.item_base[s] = sm_ib[s];
+    int at = own_at;
+    for (int it = item_lo; it < item_hi; ++it) { pl.item_at[it] = at; at += stages_of(it, seq_of(it)) + kImpItemCost; }
+    if (tid == 0) pl.item_at[n_list] = T1;
+  }
+  if (blockIdx.x >= nw) return;                   // uniform over the workgroup
+  // workgroup 8j + i runs on XCD i: neighbouring pieces, which read the same keys, go to one L2
+  const uint32_t piece = nw >= 8 ? (blockIdx.x & 7) * (nw >> 3) + (blockIdx.x >> 3) : blockIdx.x;
+  uint64_t x = line.lo(piece);
+  const uint64_t x_end = line.lo(piece + 1);
+  int hk = (int)(x / (uint32_t)T1);
+  {
+    const int rem = (int)(x - (uint64_t)hk * T1);
+    if (rem >= own_at && rem < own_at + own) {
+      int at = own_at;
+      for (int it = item_lo; it < item_hi; ++it) {
+        const int len = stages_of(it, seq_of(it)) + kImpItemCost;
+        if (rem < at + len) { sm_cur[0] = it; sm_cur[1] = rem - at; break; }
+        at += len;
+      }
+    }
+  }
+  __syncthreads();
+  int item = __builtin_amdgcn_readfirstlane(sm_cur[0]);
+  int at = __builtin_amdgcn_readfirstlane(sm_cur[1]);        // units into the item
+
+  // the later row tiles of an item have fewer keys: the second workgroup of a CU deals its tiles to the
+  // SIMDs the other way round
+  const int own_tile = (blockIdx.x * 2 >= gridDim.x ? kImpWaves - 1 - wave : wave) * kImpNS;
+  const int col = lane & 31;        // query row of the tile this lane accumulates; key row of its A operand
   const int hf = lane >> 5;         // channel half / key sub-row selector
+  // LDS: chunk c (16 bytes) of key row r lies in slot c ^ (r & 15) of the row
+  const int ld_row = tid >> 4, ld_slot = ((tid & 15) ^ ld_row) * 8;   // rows ld_row + 0, 16, 32, 48
+  static_assert(kImpThreads == 256 && kImpStage == 64, "a thread stages four 16-byte chunks");
+  const int rd_slot = (hf * 8) ^ (col & 15);
 
-  const int seq0 = cu_seqlens[s];
-  const int L = cu_seqlens[s + 1] - seq0;
-  int jn[kImpSamples], t[kImpSamples], o_lo[kImpSamples], d_hi[kImpSamples], last_key[kImpSamples];
-  bool have[kImpSamples];
-  int n_tiles = 0;
-#pragma unroll
-  for (int p = 0; p < kImpSamples; ++p) {
-    jn[p] = blockIdx.x * kImpSamples + p;
-    const int tg = jn[p] < n_samp ? samp_pos[(int64_t)s * n_samp + jn[p]] : -1;
-    t[p] = tg - seq0;
-    have[p] = tg >= 0 && t[p] >= 0 && t[p] < L;
-    if (!have[p]) t[p] = 0;
-    o_lo[p] = t[p] - R + 1 > 0 ? t[p] - R + 1 : 0;          // retained region [o_lo, t]
-    d_hi[p] = t[p] - R > 0 ? t[p] - R : 0;                  // discarded region [0, d_hi]
-    last_key[p] = have[p] ? (t[p] + W < L - 1 ? t[p] + W : L - 1) : -1;
-    const int nt = last_key[p] / 32 + 1;
-    if (have[p] && nt > n_tiles) n_tiles = nt;
-    if (!have[p] && jn[p] < n_samp && threadIdx.x == 0)     // no such sample
-      imp_part[((int64_t)s * n_samp + jn[p]) * Hkv + hk] = 0.0f;
-  }
-  if (n_tiles == 0) return;                                 // uniform over the workgroup
-  const int rows = W * G;                                   // query rows of one (sample, kv head)
-  const uint16_t* Kh = K + (int64_t)hk * ksh + (int64_t)seq0 * kst + hf * 64;
-  float total[kImpSamples];
-#pragma unroll
-  for (int p = 0; p < kImpSamples; ++p) total[p] = 0.0f;
+  while (x < x_end) {
+    const int s = __builtin_amdgcn_readfirstlane(seq_of(item));
+    const int seq = seq_first + s;
+    const int seq0 = __builtin_amdgcn_readfirstlane(cu_seqlens[seq]);
+    const int L = __builtin_amdgcn_readfirstlane(cu_seqlens[seq + 1]) - seq0;
+    const int item_st = __builtin_amdgcn_readfirstlane(stages_of(item, s));
+    // a cut among the units of the item's cost, behind its stages, leaves the next piece no stage of it
+    const int end = (uint64_t)(item_st + kImpItemCost - at) < x_end - x ? item_st + kImpItemCost : at + (int)(x_end - x);
+    const int st_at = at < item_st ? at : item_st;
+    const int st_end = end < item_st ? end : item_st;
+    const uint16_t* Kh = K + (int64_t)hk * ksh + (int64_t)seq0 * kst + (tid & 15) * 8;
 
-  for (int row0 = 0; row0 < rows; row0 += 32) {
-    // Q^T operands of the group's samples -> LDS: row r of sample p is query row row0 + r (window
-    // position w = row / G, head g = row % G), zero for rows or samples that do not exist
-    for (int idx = threadIdx.x; idx < kImpSamples * 32 * 16; idx += kImpThreads) {
-      const int p = idx / (32 * 16);
-      const int r = (idx / 16) & 31;
-      const int c16 = idx & 15;
-      const int rowq = row0 + r;
-      uint4 raw = make_uint4(0, 0, 0, 0);
-      if (rowq < rows && have[p]) {
-        const int wq_ = rowq / G, gq_ = rowq % G;
-        raw = *reinterpret_cast<const uint4*>(
-            qwin + ((((int64_t)s * n_samp + jn[p]) * W + wq_) * Hq + hk * G + gq_) * DSK_HEAD_DIM + c16 * 8);
+    // first stage -> registers
+    uint4 kreg0, kreg1, kreg2, kreg3;
+    auto load_row = [&](int row) {
+      row = row < L ? row : L - 1;                // stay inside the sequence; masked below
+      return *reinterpret_cast<const uint4*>(Kh + (int64_t)row * kst);
+    };
+    auto load_stage = [&](int st) {
+      kreg0 = load_row(st * kImpStage + ld_row);
+      kreg1 = load_row(st * kImpStage + ld_row + 16);
+      kreg2 = load_row(st * kImpStage + ld_row + 32);
+      kreg3 = load_row(st * kImpStage + ld_row + 48);
+    };
+    auto store_stage = [&](int buf) {
+      *reinterpret_cast<uint4*>(&sm_k[buf][ld_row][ld_slot]) = kreg0;
+      *reinterpret_cast<uint4*>(&sm_k[buf][ld_row + 16][ld_slot]) = kreg1;
+      *reinterpret_cast<uint4*>(&sm_k[buf][ld_row + 32][ld_slot]) = kreg2;
+      *reinterpret_cast<uint4*>(&sm_k[buf][ld_row + 48][ld_slot]) = kreg3;
+    };
+    load_stage(st_at);
+
+    // this wavefront's row tiles: row rho of the sequence's packed rows is row rho % rps of the
+    // (rho / rps)-th latest sample -- window position w = r / G, head g = r % G
+    bf16x8_t qf[kImpNS][8];
+    int tt[kImpNS], kmax[kImpNS];                 // per lane: position of the sample, last key of the row (-1: no row)
+    int t_lo[kImpNS], t_hi[kImpNS], last[kImpNS]; // per tile: smallest and largest position, last key of any row
+    // (first qf[p][i] = row 4i + lane / 16 of the tile, chunk lane % 16)
+#pragma unroll
+    for (int p = 0; p < kImpNS; ++p) {
+      const int rho = (item - sm_ib[s]) * kImpRows + (own_tile + p) * 32 + col;
+      const int j = rho / rps;
+      const bool ok = j < sm_nv[s];               // the packed rows end with the last sample's
+      const int jn = ok ? order_of(s, j) : 0;
+      const int t = ok ? pos_of(s, j) : 0;
+      const int r = rho - j * rps;
+      const int w = ok ? r / G : 0, g = ok ? r - (r / G) * G : 0;
+      tt[p] = t;
+      kmax[p] = ok ? (t < L - 2 - w ? t + 1 + w : L - 1) : -1;
+      t_lo[p] = (int)wave_min_u(ok ? (uint32_t)t : 0x7FFFFFFFu);
+      t_hi[p] = (int)wave_max_u((uint32_t)t);
+      last[p] = (int)wave_max_u((uint32_t)(kmax[p] + 1)) - 1;
+      // the row among all query rows
+      const int64_t row_at = (((int64_t)seq * n_samp + jn) * W + w) * Hq + hk * G + g;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const int from = 4 * i + (lane >> 4);
+        const int64_t at_i = (int64_t)__shfl((int)(row_at >> 32), from, DSK_WAVE) << 32 |
+                             (uint32_t)__shfl((int)row_at, from, DSK_WAVE);
+        qf[p][i] = *reinterpret_cast<const bf16x8_t*>(qwin + at_i * DSK_HEAD_DIM + (lane & 15) * 8);
       }
-      *reinterpret_cast<uint4*>(&sm_q[p][r][c16 * 8]) = raw;
     }
-    const int row = row0 + col;
-    const bool row_ok = row < rows;
-    const int w = row_ok ? row / G : 0;
-    int qpos[kImpSamples];
-    RowStat st[kImpSamples];
+    __syncthreads();                              // readers of the previous piece are done
+    // rows -> operand layout through the wavefront's own quarter of the key buffers
+    uint16_t* sm_own = &sm_k[0][0][0] + wave * (32 * DSK_HEAD_DIM);
+    static_assert(sizeof(sm_k) == kImpWaves * 32 * DSK_HEAD_DIM * sizeof(uint16_t), "a row tile per wavefront");
 #pragma unroll
-    for (int p = 0; p < kImpSamples; ++p) {
-      qpos[p] = t[p] + 1 + w;               // position of this query; attends keys 0..qpos
-      st[p].m = -__builtin_inff();
-      st[p].zt = st[p].zo = st[p].zd = 0.0f;
+    for (int p = 0; p < kImpNS; ++p) {
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const int row = 4 * i + (lane >> 4);
+        *reinterpret_cast<bf16x8_t*>(sm_own + row * DSK_HEAD_DIM + ((lane & 15) ^ (row & 15)) * 8) = qf[p][i];
+      }
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        qf[p][u] = *reinterpret_cast<const bf16x8_t*>(sm_own + col * DSK_HEAD_DIM + (rd_slot ^ u) * 8);
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
     }
+    RowAcc acc_st[kImpNS];
+#pragma unroll
+    for (int p = 0; p < kImpNS; ++p) {
+      acc_st[p].m = -__builtin_inff();
+      acc_st[p].zf = acc_st[p].zt = acc_st[p].zo = acc_st[p].zd = 0.0f;
+    }
+
     __syncthreads();
-    // the rows of the wave's next tile are requested before the current tile is multiplied
-    uint4 knext[8];
-    {
-      int krow = wave * 32 + col;           // A operand row of this lane
-      krow = krow < L ? krow : L - 1;       // stay inside the sequence; masked below
-      const uint16_t* kp = Kh + (int64_t)krow * kst;
+    store_stage(0);
+    if (st_at + 1 < st_end) load_stage(st_at + 1);
+    __syncthreads();
+
+    auto read_keys = [&](bf16x8_t (&kf)[8], int buf, int tile) {
 #pragma unroll
-      for (int u = 0; u < 8; ++u) knext[u] = *reinterpret_cast<const uint4*>(kp + u * 8);
-    }
-    for (int tile = wave; tile < n_tiles; tile += kImpWaves) {
-      const int k0 = tile * 32;
-      uint4 kraw[8];
+      for (int u = 0; u < 8; ++u)
+        kf[u] = *reinterpret_cast<const bf16x8_t*>(&sm_k[buf][tile * 32 + col][(rd_slot ^ u) * 8]);
+    };
+    // what a tile is to row tile p: nothing (0), wholly discarded (1) or retained (2) by all rows, mixed (3)
+    auto kind_of = [&](int p, int k0) {
+      if (k0 > last[p]) return 0;
+      if (k0 + 31 <= (t_lo[p] - R > 0 ? t_lo[p] - R : 0)) return 1;
+      return k0 > t_hi[p] - R && k0 + 31 <= t_lo[p] && k0 > 0 ? 2 : 3;   // key 0 may be in both regions
+    };
+    // statistics of the tile at key k0 for row tile p (logits cur) in the shadow of the products that the
+    // caller's next half step needs: nxt = keys kf against row tile o.  FRESH: kf was only just requested
+    // from LDS, so the products are held back behind the first exponentials.
+    auto half_step = [&](auto fresh, int p, int o, int k0, const f32x16_t& cur, f32x16_t& nxt, const bf16x8_t (&kf)[8]) {
+      const int kind = kind_of(p, k0);
+      if (kind == 1 || kind == 2) {
+        // no masks: one sum per row feeds the total and one of the regions
+        nxt = imp_product(kf, qf[o]);
+        float sum = imp_tile_sum(cur, scale_log2, acc_st[p].m);
+        if constexpr (decltype(fresh)::value) {
+          __builtin_amdgcn_sched_group_barrier(0x2, 8, 0);      // vector ALU
+          __builtin_amdgcn_sched_group_barrier(0x400, 6, 0);    // exponentials
+          __builtin_amdgcn_sched_group_barrier(0x2, 4, 0);
 #pragma unroll
-      for (int u = 0; u < 8; ++u) kraw[u] = knext[u];
-      {
-        int krow = k0 + kImpWaves * 32 + col;
-        krow = krow < L ? krow : L - 1;     // past the last tile: a harmless re-read inside the sequence
-        const uint16_t* kp = Kh + (int64_t)krow * kst;
-#pragma unroll
-        for (int u = 0; u < 8; ++u) knext[u] = *reinterpret_cast<const uint4*>(kp + u * 8);
-      }
-#pragma unroll
-      for (int p = 0; p < kImpSamples; ++p) {
-        if (k0 > last_key[p]) continue;     // this sample's keys ended before the tile (uniform)
-        f32x16_t acc;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-          // lane (col, hf) supplies channels [64*hf + 8u, +8) of query row col
-          const bf16x8_t qb = *reinterpret_cast<const bf16x8_t*>(&sm_q[p][col][hf * 64 + u * 8]);
-          acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<bf16x8_t*>(&kraw[u]), qb, acc, 0, 0, 0);
-        }
-        // acc[r] = logit of key k0 + 8*(r/4) + 4*hf + r%4 against query row `col`
-        if (k0 + 31 <= d_hi[p]) {
-          // the whole tile lies in the discarded region (hence before every query of the window
-          // and outside the retained region): no masks, one sum feeds both totals
-          float amax = acc[0];
-#pragma unroll
-          for (int r = 1; r < 16; ++r) amax = fmaxf(amax, acc[r]);
-          const float mn = fmaxf(st[p].m, amax * scale_log2);
-          const float f = __builtin_amdgcn_exp2f(st[p].m - mn);   // 0 while st.m is still -inf
-          float esum = 0.0f;
-#pragma unroll
-          for (int r = 0; r < 16; ++r) esum += __builtin_amdgcn_exp2f(fmaf(acc[r], scale_log2, -mn));
-          st[p].zt = fmaf(st[p].zt, f, esum);
-          st[p].zd = fmaf(st[p].zd, f, esum);
-          st[p].zo *= f;
-          st[p].m = mn;
-          continue;
-        }
-        float z[16];
-        float tmax = -__builtin_inff();
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int kpos = k0 + 8 * (r / 4) + 4 * hf + (r % 4);
-          z[r] = (kpos <= qpos[p] && kpos <= last_key[p]) ? acc[r] * scale_log2 : -__builtin_inff();
-          tmax = fmaxf(tmax, z[r]);
-        }
-        if (tmax != -__builtin_inff()) {
-          const float mn = fmaxf(st[p].m, tmax);
-          const float f = st[p].m == -__builtin_inff() ? 0.0f : exp2f(st[p].m - mn);
-          st[p].zt *= f; st[p].zo *= f; st[p].zd *= f;
-#pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            const int kpos = k0 + 8 * (r / 4) + 4 * hf + (r % 4);
-            const float e = __builtin_amdgcn_exp2f(z[r] - mn);   // z <= mn; 0 for masked keys (-inf)
-            st[p].zt += e;
-            st[p].zo += (kpos >= o_lo[p] && kpos <= t[p]) ? e : 0.0f;
-            st[p].zd += (kpos <= d_hi[p]) ? e : 0.0f;
+          for (int i = 0; i < 8; ++i) {
+            __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);    // MFMA
+            __builtin_amdgcn_sched_group_barrier(0x400, 2, 0);
+            __builtin_amdgcn_sched_group_barrier(0x2, 3, 0);
           }
-          st[p].m = mn;
         }
+        if (imp_too_large(sum)) {
+          imp_move_reference(acc_st[p], cur, scale_log2);
+          sum = imp_tile_sum(cur, scale_log2, acc_st[p].m);
+        }
+        if (kind == 1) {
+          acc_st[p].zf += sum;
+        } else {
+          acc_st[p].zt += sum;
+          acc_st[p].zo += sum;
+        }
+      } else if (k0 <= last[o]) {
+        nxt = imp_product(kf, qf[o]);
       }
+    };
+    constexpr std::true_type kFresh{};
+    constexpr std::false_type kReady{};
+    bf16x8_t kf[8];
+    f32x16_t c0, c1;
+    read_keys(kf, 0, 0);
+    c0 = imp_product(kf, qf[0]);
+    c1 = c0;
+    for (int st = st_at; st < st_end; ++st) {
+      const int buf = (st - st_at) & 1;
+      const int k0 = st * kImpStage;
+      half_step(kReady, 0, 1, k0, c0, c1, kf);
+      read_keys(kf, buf, 1);
+      half_step(kFresh, 1, 0, k0, c1, c0, kf);
+      half_step(kReady, 0, 1, k0 + 32, c0, c1, kf);
+      if (st + 1 < st_end) store_stage(buf ^ 1);  // read last before the previous barrier
+      __syncthreads();
+      if (st + 2 < st_end) load_stage(st + 2);
+      read_keys(kf, buf ^ 1, 0);                  // past the end: old keys, their products are not used
+      half_step(kFresh, 1, 0, k0 + 32, c1, c0, kf);
     }
-    // halves of a wave hold disjoint keys of the same row; then waves; fixed order
+    // the mixed tiles, two or three per row tile: each wavefront on its own, so that it holds up no other one
+    auto next_mixed = [&](int p, int tile) {
+      while (tile < 2 * st_end && tile * 32 <= last[p] && kind_of(p, tile * 32) != 3) ++tile;
+      return tile < 2 * st_end && tile * 32 <= last[p] ? tile : -1;
+    };
+    auto first_mixed = [&](int p) {
+      const int open = ((t_lo[p] - R > 0 ? t_lo[p] - R : 0) + 1) >> 5;      // the first that is not discarded
+      return next_mixed(p, open > 2 * st_at ? open : 2 * st_at);
+    };
+    auto fetch_keys = [&](int tile) {
+      int row = tile * 32 + col;
+      row = row < L ? row : L - 1;
+      const uint16_t* kp = K + (int64_t)hk * ksh + (int64_t)(seq0 + row) * kst + hf * 64;
 #pragma unroll
-    for (int p = 0; p < kImpSamples; ++p) {
-      RowStat other;
-      other.m = shfl_xor_f(st[p].m, 32);
-      other.zt = shfl_xor_f(st[p].zt, 32);
-      other.zo = shfl_xor_f(st[p].zo, 32);
-      other.zd = shfl_xor_f(st[p].zd, 32);
-      if (hf == 0) {
-        stat_merge(st[p], other);
-        sm_stat[p][wave][col] = st[p];
-      }
+      for (int u = 0; u < 8; ++u) kf[u] = *reinterpret_cast<const bf16x8_t*>(kp + u * 8);
+    };
+    int m0 = first_mixed(0), m1 = first_mixed(1);
+    if (m0 >= 0 || m1 >= 0) fetch_keys(m0 >= 0 ? m0 : m1);
+    // tile m of row tile p, whose keys are in kf; the keys of the next one are requested behind its products
+    auto mixed_tile = [&](int p, int& m, const int& other) {
+      c0 = imp_product(kf, qf[p]);
+      const int tile = m;
+      m = next_mixed(p, tile + 1);
+      if (m >= 0 || other >= 0) fetch_keys(other >= 0 ? other : m);
+      const int key0 = tile * 32 + 4 * hf;
+      imp_masked_tile(acc_st[p], c0, scale_log2, kmax[p] - key0, (tt[p] - R + 1 > 0 ? tt[p] - R + 1 : 0) - key0,
+                      tt[p] - key0, (tt[p] - R > 0 ? tt[p] - R : 0) - key0);
+    };
+    while (m0 >= 0 || m1 >= 0) {
+      if (m0 >= 0) mixed_tile(0, m0, m1);
+      if (m1 >= 0) mixed_tile(1, m1, m0);
     }
-    __syncthreads();
-    if (threadIdx.x < 32 * kImpSamples) {
-      const int p = threadIdx.x >> 5;
-      RowStat a = sm_stat[p][0][col];
+
+    // halves of a wave hold disjoint keys of the same row
+    float4* out = part + ((int64_t)piece + (int64_t)hk * n_list + item) * kImpRows;
 #pragma unroll
-      for (int wv = 1; wv < kImpWaves; ++wv) stat_merge(a, sm_stat[p][wv][col]);
-      const float v = (row0 + col < rows && a.zt > 0.0f) ? (a.zo - alpha * a.zd) / a.zt : 0.0f;
-      sm_val[p][col] = v;
+    for (int p = 0; p < kImpNS; ++p) {
+      RowStat a, o;
+      a.m = acc_st[p].m;
+      a.zt = acc_st[p].zt + acc_st[p].zf;
+      a.zo = acc_st[p].zo;
+      a.zd = acc_st[p].zd + acc_st[p].zf;
+      o.m = shfl_xor_f(a.m, 32);
+      o.zt = shfl_xor_f(a.zt, 32);
+      o.zo = shfl_xor_f(a.zo, 32);
+      o.zd = shfl_xor_f(a.zd, 32);
+      stat_merge(a, o);
+      if (hf == 0) out[(own_tile + p) * 32 + col] = make_float4(a.m, a.zt, a.zo, a.zd);
     }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-#pragma unroll
-      for (int p = 0; p < kImpSamples; ++p)
-        for (int c2 = 0; c2 < 32; ++c2) total[p] += sm_val[p][c2];   // fixed order
-    }
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) {
-#pragma unroll
-    for (int p = 0; p < kImpSamples; ++p)
-      if (have[p]) imp_part[((int64_t)s * n_samp + jn[p]) * Hkv + hk] = total[p];
+    x += (uint64_t)(end - at);
+    at = 0;
+    if (++item == n_list) { item = 0; ++hk; }
   }
 }
 
-// one wavefront per (class, sequence), one lane per sample of the class (M <= 64): the lanes sum
-// their KV-head partials side by side (same order per sample as a serial loop), lane 0 then adds
-// the sample scores in sample order
-__global__ __launch_bounds__(DSK_WAVE) void importance_finalize_kernel(
-    const float* __restrict__ imp_part, const int32_t* __restrict__ samp_pos, int n_class, int M, int Hkv,
-    int Hq, int W, float alpha, uint8_t* __restrict__ class_weight_q, float* __restrict__ class_mean,
-    float* __restrict__ samp_score, float* __restrict__ samp_score_sum, int layers) {
+// grid: (class, sequence).  The wavefronts are dealt to the class's samples; their lanes merge the pieces
+// of the sample's rows over all KV heads and sum the row values, thread 0 then adds the sample scores in
+// sample order (every sum in a fixed order).
+constexpr int kImpFinThreads = 1024;
+constexpr int kImpFinWaves = kImpFinThreads / DSK_WAVE;
+constexpr int kImpFinRows = 2;       // rows of a lane in flight together,
+constexpr int kImpFinBatch = 8;      // and pieces of each
+constexpr int kImpFinItems = 1024;   // items whose places on the line are fetched ahead
+__global__ __launch_bounds__(kImpFinThreads) void importance_finalize_kernel(
+    int32_t* __restrict__ plan, const float4* __restrict__ part, const int32_t* __restrict__ samp_pos,
+    int seq_first, int nseq, int items, int n_class, int M, int Hkv, int G, int W, float alpha,
+    uint8_t* __restrict__ class_weight_q, float* __restrict__ class_mean, float* __restrict__ samp_score,
+    float* __restrict__ samp_score_sum, int layers) {
+  __shared__ float sm_sum[kMaxSamplesPerClass * kImpFinWaves];
   __shared__ float sm_score[kMaxSamplesPerClass];
   __shared__ int sm_have[kMaxSamplesPerClass];
+  __shared__ int sm_item[kImpFinItems];
   const int c = blockIdx.x;
-  const int s = blockIdx.y;
-  const int m = threadIdx.x;
+  const int sl = blockIdx.y, s = seq_first + sl;
+  const int lane = threadIdx.x & (DSK_WAVE - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / DSK_WAVE);
   const int n_samp = n_class * M;
-  if (m < M) {
-    const int64_t js = (int64_t)s * n_samp + c * M + m;
-    const bool have = samp_pos[js] >= 0;
-    float st = 0.0f;
-    if (have) {
-      for (int hk = 0; hk < Hkv; ++hk) st += imp_part[js * Hkv + hk];
-      st /= (float)(Hq * W);
+  const int rps = W * G;
+  const ImpPlan pl = imp_plan(plan, nseq, n_samp, items);
+  const int T1 = pl.head[0], n_list = pl.head[2];
+  const uint32_t nw = (uint32_t)pl.head[1];
+  const int ib = pl.item_base[sl];
+  const int32_t* rank = pl.rank + (int64_t)sl * n_samp;
+  // everything that does not depend on the plan's values goes out in one round trip
+  if (threadIdx.x <= items && threadIdx.x < kImpFinItems) sm_item[threadIdx.x] = pl.item_at[threadIdx.x];
+  if (threadIdx.x < M) sm_have[threadIdx.x] = samp_pos[(int64_t)s * n_samp + c * M + threadIdx.x] >= 0 ? 1 : 0;
+  static_assert(kImpFinItems <= kImpFinThreads, "one load each");
+  auto item_at = [&](int i) { return (uint32_t)(i < kImpFinItems ? sm_item[i] : pl.item_at[i]); };
+  ImpLine line;
+  line.per = line.extra = 0;
+  if (nw > 0) {
+    const uint64_t T = (uint64_t)T1 * Hkv;
+    line.per = (uint32_t)(T / nw);
+    line.extra = (uint32_t)(T % nw);
+  }
+  __syncthreads();
+  const int per_sample = M < kImpFinWaves ? kImpFinWaves / M : 1;   // wavefronts of one sample
+  for (int m = wave / per_sample; m < M; m += kImpFinWaves / per_sample) {
+    const int rk = rank[c * M + m];
+    float sum = 0.0f;
+    if (rk >= 0 && nw > 0) {
+      const int n_rows = rps * Hkv, stride = per_sample * DSK_WAVE;
+      for (int idx = (wave % per_sample) * DSK_WAVE + lane; idx < n_rows; idx += kImpFinRows * stride) {
+        const float4* rows[kImpFinRows];
+        int n[kImpFinRows], most = 0;                  // pieces of the row's item
+        RowStat a[kImpFinRows];
+#pragma unroll
+        for (int i = 0; i < kImpFinRows; ++i) {
+          const int x = idx + i * stride < n_rows ? idx + i * stride : idx;
+          const int hk = x / rps;
+          const int rho = rk * rps + (x - hk * rps);
+          const int item = ib + rho / kImpRows;
+          const uint64_t x0 = (uint64_t)hk * T1 + item_at(item), x1 = (uint64_t)hk * T1 + item_at(item + 1);
+          const uint32_t w0 = line.piece_of(x0);
+          rows[i] = part + ((int64_t)w0 + (int64_t)hk * n_list + item) * kImpRows + rho % kImpRows;
+          n[i] = idx + i * stride < n_rows ? (int)(line.piece_of(x1 - 1) - w0) + 1 : 0;
+          most = n[i] > most ? n[i] : most;
+          a[i] = {-__builtin_inff(), 0.0f, 0.0f, 0.0f};
+        }
+        for (int w = 0; w < most; w += kImpFinBatch) {
+          float4 v[kImpFinRows][kImpFinBatch];
+#pragma unroll
+          for (int i = 0; i < kImpFinRows; ++i)
+#pragma unroll
+            for (int j = 0; j < kImpFinBatch; ++j) v[i][j] = rows[i][(int64_t)(w + j < n[i] ? w + j : 0) * kImpRows];
+#pragma unroll
+          for (int i = 0; i < kImpFinRows; ++i)
+#pragma unroll
+            for (int j = 0; j < kImpFinBatch; ++j) pin_loaded(v[i][j]);
+#pragma unroll
+          for (int i = 0; i < kImpFinRows; ++i) {
+            float m = a[i].m;
+#pragma unroll
+            for (int j = 0; j < kImpFinBatch; ++j) m = fmaxf(m, w + j < n[i] ? v[i][j].x : -__builtin_inff());
+            const float ref = m == -__builtin_inff() ? 0.0f : m;     // no key anywhere yet: all factors 0
+            const float f = __builtin_amdgcn_exp2f(a[i].m - ref);
+            a[i] = {m, a[i].zt * f, a[i].zo * f, a[i].zd * f};
+#pragma unroll
+            for (int j = 0; j < kImpFinBatch; ++j) {
+              const float g = w + j < n[i] ? __builtin_amdgcn_exp2f(v[i][j].x - ref) : 0.0f;
+              a[i].zt = fmaf(v[i][j].y, g, a[i].zt);
+              a[i].zo = fmaf(v[i][j].z, g, a[i].zo);
+              a[i].zd = fmaf(v[i][j].w, g, a[i].zd);
+            }
+          }
+        }
+#pragma unroll
+        for (int i = 0; i < kImpFinRows; ++i) sum += a[i].zt > 0.0f ? (a[i].zo - alpha * a[i].zd) / a[i].zt : 0.0f;
+      }
     }
+    sum = wave_sum(sum);
+    if (lane == 0) sm_sum[m * kImpFinWaves + wave % per_sample] = sum;
+  }
+  __syncthreads();
+  if ((int)threadIdx.x < M) {
+    const int m = threadIdx.x;
+    const int64_t js = (int64_t)s * n_samp + c * M + m;
+    const bool have = sm_have[m] != 0;
+    float st = 0.0f;
+    for (int i = 0; i < per_sample; ++i) st += sm_sum[m * kImpFinWaves + i];
+    st /= (float)(G * Hkv * W);
     if (samp_score) samp_score[js] = have ? st : __builtin_nanf("");
     if (samp_score_sum != nullptr && have) {      // expectation over layers: this layer joins the running sum
       const float tot = samp_score_sum[js] + st;
@@ -264,10 +698,9 @@ __global__ __launch_bounds__(DSK_WAVE) void importance_finalize_kernel(
       st = tot / (float)layers;
     }
     sm_score[m] = st;
-    sm_have[m] = have ? 1 : 0;
   }
   __syncthreads();
-  if (m != 0) return;
+  if (threadIdx.x != 0) return;
   float sum = 0.0f;
   int cnt = 0;
   for (int i = 0; i < M; ++i)
@@ -284,29 +717,54 @@ __global__ __launch_bounds__(DSK_WAVE) void importance_finalize_kernel(
   }
 }
 
+ImpLayout importance_layout(int B, int n_samp, int W, int Hq, int Hkv) {
+  ImpLayout l;
+  const int64_t rps = (int64_t)W * (Hq / Hkv);
+  const int64_t per_seq = ((int64_t)n_samp * rps + kImpRows - 1) / kImpRows;
+  int64_t seqs = kImpMaxItems / (per_seq * Hkv > 0 ? per_seq * Hkv : 1);    // bounds the workspace
+  if (seqs < 1) seqs = 1;
+  if (seqs > kImpMaxSeqs) seqs = kImpMaxSeqs;
+  if (seqs > B) seqs = B;
+  l.seqs = (int)seqs;
+  l.items = (int)(seqs * per_seq);
+  l.plan_ints = (size_t)4 + 2 * l.seqs + 1 + l.items + 1 + 3 * (size_t)l.seqs * n_samp;
+  l.part_rows = ((size_t)kImpPieces + (size_t)l.items * Hkv) * kImpRows;
+  return l;
+}
+
 hipError_t launch_importance(const dsk_compress_args& a, const CompressWs& ws, hipStream_t st) {
-  float* imp_part = reinterpret_cast<float*>(static_cast<unsigned char*>(a.workspace) + ws.imp_part);
+  unsigned char* w = static_cast<unsigned char*>(a.workspace);
+  int32_t* plan = reinterpret_cast<int32_t*>(w + ws.imp_plan);
+  float4* part = reinterpret_cast<float4*>(w + ws.imp_part);
   const int n_samp = a.n_class * a.M;
+  const int G = a.Hq / a.Hkv;
   const float scale = a.imp_scale != 0.0f ? a.imp_scale : 0.08838834764831845f;   // 128^-1/2
-  const int64_t heads_seqs = (int64_t)a.Hkv * a.B;
-#define DSK_IMP_ARGS                                                                                          \
-  static_cast<const uint16_t*>(a.K), a.k_stride_tok, a.k_stride_head, static_cast<const uint16_t*>(a.qwin),    \
-      a.samp_pos, a.cu_seqlens, n_samp, a.W, a.R, a.Hq, a.Hq / a.Hkv, a.alpha_imp, scale * kImpLog2e, imp_part, \
-      a.Hkv
-  if ((int64_t)((n_samp + 3) / 4) * heads_seqs < 1024) {
-    const dim3 grid((unsigned)((n_samp + 3) / 4), (unsigned)a.Hkv, (unsigned)a.B);
-    importance_kernel<512, 4><<<grid, dim3(512), 0, st>>>(DSK_IMP_ARGS);
-  } else {
-    const dim3 grid((unsigned)((n_samp + 2) / 3), (unsigned)a.Hkv, (unsigned)a.B);
-    importance_kernel<256, 3><<<grid, dim3(256), 0, st>>>(DSK_IMP_ARGS);
-  }
+  const ImpLayout l = importance_layout(a.B, n_samp, a.W, a.Hq, a.Hkv);
+  for (int s = 0; s < a.B; s += l.seqs) {
+    const int nseq = a.B - s < l.seqs ? a.B - s : l.seqs;
+    hipError_t err;
+#define DSK_IMP_ARGS                                                                                              \
+  static_cast<const uint16_t*>(a.K), a.k_stride_tok, a.k_stride_head, static_cast<const uint16_t*>(a.qwin),       \
+      a.samp_pos, a.cu_seqlens, s, nseq, n_samp, l.items, a.W, a.R, a.Hq, G, a.Hkv, scale * kImpLog2e, plan, part
+    if (nseq == 1 && n_samp <= kImpThreads) {
+      importance_kernel<true><<<dim3(kImpPieces), dim3(kImpThreads), 0, st>>>(DSK_IMP_ARGS);
+    } else {
+      importance_rank_kernel<<<dim3((unsigned)((n_samp + DSK_WAVE - 1) / DSK_WAVE), (unsigned)nseq), dim3(kImpThreads), 0,
+                               st>>>(a.samp_pos, a.cu_seqlens, s, nseq, n_samp, l.items, plan);
+      err = hipGetLastError();
+      if (err != hipSuccess) return err;
+      importance_kernel<false><<<dim3(kImpPieces), dim3(kImpThreads), 0, st>>>(DSK_IMP_ARGS);
+    }
 #undef DSK_IMP_ARGS
-  hipError_t err = hipGetLastError();
-  if (err != hipSuccess) return err;
-  importance_finalize_kernel<<<dim3((unsigned)a.n_class, (unsigned)a.B), dim3(DSK_WAVE), 0, st>>>(
-      imp_part, a.samp_pos, a.n_class, a.M, a.Hkv, a.Hq, a.W, a.alpha_imp, a.class_weight_q, a.class_mean,
-      a.samp_score, a.samp_score_sum, a.imp_layers > 0 ? a.imp_layers : 1);
-  return hipGetLastError();
+    err = hipGetLastError();
+    if (err != hipSuccess) return err;
+    importance_finalize_kernel<<<dim3((unsigned)a.n_class, (unsigned)nseq), dim3(kImpFinThreads), 0, st>>>(
+        plan, part, a.samp_pos, s, nseq, l.items, a.n_class, a.M, a.Hkv, G, a.W, a.alpha_imp, a.class_weight_q,
+        a.class_mean, a.samp_score, a.samp_score_sum, a.imp_layers > 0 ? a.imp_layers : 1);
+    err = hipGetLastError();
+    if (err != hipSuccess) return err;
+  }
+  return hipSuccess;
 }
 
 }  // namespace dsk

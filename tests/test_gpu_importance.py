@@ -241,3 +241,63 @@ def test_importance_at_full_128k_context_both_launch_shapes():
             worst = max(worst, abs(got - want[j]))
             assert abs(got - want[j]) <= SCORE_TOL, (j, int(t_all[j]), got, want[j])
     print("128K importance worst |s_gpu - s_oracle| = %.2e over %d samples" % (worst, len(checked)))
+
+
+# ---------------------------------------------------------------------------------------------
+# stage IMPORTANCE on positions given by the caller, where the packing of the query rows, the
+# ranking of the samples and the cuts of the key ranges have their edges
+# ---------------------------------------------------------------------------------------------
+@pytest.mark.parametrize(
+    "B, L, Hq, Hkv, n_class, M, W, R, spread, imp_scale",
+    [
+        (1, 700, 1, 1, 1, 1, 1, 1, 1.0, 0.0),            # one row; the regions meet at every position
+        (1, 1500, 4, 4, 3, 7, 8, 20, 1.0, 0.0),          # several samples in a row tile, regions narrower than a tile
+        (1, 2100, 6, 2, 5, 3, 5, 100, 1.0, 0.0),         # 15 rows per sample: samples straddle row tiles
+        (1, 1300, 8, 1, 2, 2, 64, 128, 1.0, 0.0),        # 512 rows per sample: a sample fills two items
+        (1, 900, 2, 2, 16, 16, 2, 64, 1.0, 0.0),         # 256 samples: the largest ranked inside the kernel
+        (1, 900, 2, 2, 16, 17, 2, 64, 1.0, 0.0),         # 272: ranked by the launch in front
+        (3, 1100, 4, 1, 4, 3, 8, 128, 1.0, 0.0),         # several sequences
+        (270, 90, 1, 1, 1, 2, 3, 16, 1.0, 0.0),          # more sequences than one launch plans
+        (1, 3000, 4, 1, 4, 4, 8, 128, 40.0, 0.0),        # logits of hundreds: the reference moves often
+        (1, 1200, 4, 1, 4, 4, 8, 128, 1.0, 0.5),         # a caller's logit scale
+    ])
+def test_importance_given_positions(B, L, Hq, Hkv, n_class, M, W, R, spread, imp_scale):
+    import paper_2602_03184_amd as dsk
+    from workloads import f32_to_bf16_bits
+    r = np.random.default_rng(B * L + Hq + M)
+    n_samp = n_class * M
+    lens = np.full(B, L)
+    if B > 1:
+        lens[1::2] = L // 2 + 7
+    cu = np.concatenate([[0], np.cumsum(lens)])
+    t = np.stack([r.integers(0, n, size=n_samp) for n in lens])       # also t < R and windows cut by the end
+    t[:, 0] = lens - 1                                                # no key behind the sample but its own
+    if n_samp > 3:
+        t[:, 1] = 0
+        t[:, 2] = t[:, 3]                                             # equal positions
+    samp = t + cu[:-1, None]
+    if n_samp > 4:
+        samp[0, 4] = -1                                               # an absent sample
+    if B > 1:
+        samp[B - 1] = -1                                              # a sequence without samples
+    K_bits = f32_to_bf16_bits(r.standard_normal((Hkv, int(cu[-1]), 128), dtype=np.float32) * np.float32(spread))
+    q_bits = f32_to_bf16_bits(r.standard_normal((B, n_samp, W, Hq, 128), dtype=np.float32))
+    wq = dev_u8(np.full((B, n_class), 3, np.uint8))
+    kw = dict(cu_seqlens=dev_i32(cu), max_seqlen=int(lens.max()), Hq=Hq, K=dev_bf16(K_bits), V=None,
+              stages=dsk.DSK_STAGE_IMPORTANCE, n_class=n_class, M=M, W=W, R=R, alpha_imp=1.0, imp_scale=imp_scale,
+              samp_pos=dev_i32(samp.reshape(B, n_class, M)), qwin=dev_bf16(q_bits), class_weight_q=wq)
+    got = dsk.compress(**kw).samp_score.cpu().numpy().reshape(B, n_samp)
+    again = dsk.compress(**kw).samp_score.cpu().numpy().reshape(B, n_samp)
+    np.testing.assert_array_equal(got, again)                         # fixed reduction orders
+    Kf = O.widen_bf16(K_bits)
+    scale = imp_scale if imp_scale != 0.0 else 1.0 / math.sqrt(128.0)
+    # the logits' rounding (fp32, up to |z| units) is the error of the exponentials
+    tol = SCORE_TOL * max(1.0, spread / 4)
+    seqs = range(B) if B < 8 else (0, 1, 2, 255, 256, B - 2, B - 1)
+    for s in seqs:
+        for j in (range(n_samp) if n_samp < 30 else (0, 1, 2, 3, 4, n_samp // 2, n_samp - 1)):
+            if samp[s, j] < 0:
+                assert math.isnan(got[s, j])
+                continue
+            want = O.delimiter_importance(O.widen_bf16(q_bits[s, j]), Kf[:, cu[s]: cu[s + 1]], int(t[s, j]), R, 1.0, scale)
+            assert abs(float(got[s, j]) - want) <= tol, (s, j, int(t[s, j]), float(got[s, j]), want)
