@@ -11,9 +11,25 @@ constexpr int kSumThreads = 256;
 constexpr int kSumWaves = kSumThreads / DSK_WAVE;
 constexpr int kSumUnroll = 8;  // row-groups of 4 rows in flight per wave
 
+// STREAM (the full pass): the records are stored past the cache's replacement order.  Written through it
+// they leave it one by one between the reads, which costs far more than their bytes: K and V summaries of
+// eight sequences, 24K to 64K tokens, 8 heads: 361 -> 345 us for the pass from the larger grid, -> 307 us from
+// these stores.  (Streaming loads of the rows took another 23 us off, and put 30 us on the decode step that
+// follows, which then finds none of K in the memory-side cache: not used.)
+typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
+template <bool STREAM>
+__device__ __forceinline__ void store_record16(uint4* at, uint32_t x, uint32_t y, uint32_t z, uint32_t w) {
+  if constexpr (!STREAM) {
+    *at = make_uint4(x, y, z, w);
+  } else {
+    const u32x4_t v = {x, y, z, w};
+    __builtin_nontemporal_store(v, reinterpret_cast<u32x4_t*>(at));
+  }
+}
+
 // min / max (or mean) of rows [0, len) of one head, `base` pointing at row 0 of the block, written
 // to the 512-byte record `o`.  All 64 lanes of a wavefront call it with wave-uniform arguments.
-template <bool MEAN>
+template <bool MEAN, bool STREAM>
 __device__ __forceinline__ void summarize_block(const uint16_t* base, int len, int64_t stride_tok, unsigned ustride,
                                                 uint16_t* o, int g, int c) {
   // MEAN: mn[] holds this lane's running sums instead
@@ -65,16 +81,15 @@ __device__ __forceinline__ void summarize_block(const uint16_t* base, int len, i
     }
   }
   if (g == 0) {
-    reinterpret_cast<uint4*>(o)[c] = make_uint4(pack_bf16_exact(mn[0], mn[1]), pack_bf16_exact(mn[2], mn[3]),
-                                                pack_bf16_exact(mn[4], mn[5]), pack_bf16_exact(mn[6], mn[7]));
+    store_record16<STREAM>(reinterpret_cast<uint4*>(o) + c, pack_bf16_exact(mn[0], mn[1]), pack_bf16_exact(mn[2], mn[3]),
+                           pack_bf16_exact(mn[4], mn[5]), pack_bf16_exact(mn[6], mn[7]));
   } else if (g == 1) {
-    reinterpret_cast<uint4*>(o)[16 + c] = make_uint4(pack_bf16_exact(mx[0], mx[1]), pack_bf16_exact(mx[2], mx[3]),
-                                                     pack_bf16_exact(mx[4], mx[5]), pack_bf16_exact(mx[6], mx[7]));
+    store_record16<STREAM>(reinterpret_cast<uint4*>(o) + 16 + c, pack_bf16_exact(mx[0], mx[1]),
+                           pack_bf16_exact(mx[2], mx[3]), pack_bf16_exact(mx[4], mx[5]), pack_bf16_exact(mx[6], mx[7]));
   }
 }
 
-// 8 waves per SIMD (32 per CU) so that one launch keeps every wave of the grid resident
-template <bool MEAN>
+template <bool MEAN, bool STREAM>
 __global__ __launch_bounds__(kSumThreads) void summaries_kernel(
     const uint16_t* __restrict__ X, int64_t stride_tok, int64_t stride_head, int Hkv,
     const int32_t* __restrict__ block_start, const int32_t* __restrict__ cu_blocks, int B,
@@ -122,7 +137,7 @@ __global__ __launch_bounds__(kSumThreads) void summaries_kernel(
       if (lane == 0) set_status(dev_status, DSK_ERR_SHAPE);
     } else {
       const uint16_t* base = X + (int64_t)h * stride_head + (int64_t)s * stride_tok;   // uniform
-      summarize_block<MEAN>(base, len, stride_tok, ustride, o, g, c);
+      summarize_block<MEAN, STREAM>(base, len, stride_tok, ustride, o, g, c);
     }
     if (nitem >= items) break;
     item = nitem; h = nh; i = ni; s = ns; e = ne;
@@ -134,17 +149,25 @@ static hipError_t launch_summaries_impl(const dsk_compress_args& a, hipStream_t 
   const int64_t max_items = (int64_t)a.Hkv * a.max_blocks_total;
   if (max_items <= 0) return hipSuccess;
   int64_t wgs = (max_items + kSumWaves - 1) / kSumWaves;
-  const int64_t max_wgs = 256 * 8;   // 8 workgroups (32 waves) per CU keeps HBM requests deep
+  // One or two blocks per wavefront where there are many: workgroups dealt out as others end stay close
+  // together in memory, while a persistent grid of 256 * 8 drifts apart (128K tokens, 8 heads: 79 -> 73 us
+  // for the pass with the streamed records).  The capacity may be a multiple of the blocks there are, and an
+  // empty workgroup is not free, so the grid follows twice the blocks of chunks of C tokens (four times where
+  // sequences have a C of their own, below this bound).
+  // (C is only a hint here: a call of this stage alone may leave it unset.)
+  int64_t max_wgs = a.C > 0 ? (a.C_per_seq != nullptr ? 4 : 2) * (int64_t)a.Hkv * (a.total_tokens / a.C + a.B) / kSumWaves : 0;
+  if (max_wgs < 256 * 8) max_wgs = 256 * 8;
+  if (max_wgs > 256 * 128) max_wgs = 256 * 128;
   if (wgs > max_wgs) wgs = max_wgs;
   const int out_rows = a.sum_stride_blocks > 0 ? a.sum_stride_blocks : a.max_blocks_total;
-  summaries_kernel<MEAN><<<dim3((unsigned)wgs), dim3(kSumThreads), 0, st>>>(
+  summaries_kernel<MEAN, true><<<dim3((unsigned)wgs), dim3(kSumThreads), 0, st>>>(
       static_cast<const uint16_t*>(a.K), a.k_stride_tok, a.k_stride_head, a.Hkv, a.block_start,
       a.cu_blocks, a.B, nullptr, a.max_blocks_total, out_rows, a.total_tokens, static_cast<uint16_t*>(a.ksum),
       a.dev_status);
   hipError_t err = hipGetLastError();
   if (err != hipSuccess) return err;
   if (a.vsum != nullptr) {
-    summaries_kernel<MEAN><<<dim3((unsigned)wgs), dim3(kSumThreads), 0, st>>>(
+    summaries_kernel<MEAN, true><<<dim3((unsigned)wgs), dim3(kSumThreads), 0, st>>>(
         static_cast<const uint16_t*>(a.V), a.v_stride_tok, a.v_stride_head, a.Hkv, a.block_start,
         a.cu_blocks, a.B, nullptr, a.max_blocks_total, out_rows, a.total_tokens, static_cast<uint16_t*>(a.vsum),
         a.dev_status);
@@ -166,11 +189,11 @@ hipError_t launch_summaries_range(const void* X, int64_t stride_tok, int64_t str
   int64_t wgs = (max_items + kSumWaves - 1) / kSumWaves;
   if (wgs > 256 * 8) wgs = 256 * 8;
   if (summary_mode == DSK_SUMMARY_MEAN)
-    summaries_kernel<true><<<dim3((unsigned)wgs), dim3(kSumThreads), 0, st>>>(
+    summaries_kernel<true, false><<<dim3((unsigned)wgs), dim3(kSumThreads), 0, st>>>(
         static_cast<const uint16_t*>(X), stride_tok, stride_head, Hkv, block_start, nullptr, 0, blk_range, cap, cap,
         total_tokens, static_cast<uint16_t*>(out), dev_status);
   else
-    summaries_kernel<false><<<dim3((unsigned)wgs), dim3(kSumThreads), 0, st>>>(
+    summaries_kernel<false, false><<<dim3((unsigned)wgs), dim3(kSumThreads), 0, st>>>(
         static_cast<const uint16_t*>(X), stride_tok, stride_head, Hkv, block_start, nullptr, 0, blk_range, cap, cap,
         total_tokens, static_cast<uint16_t*>(out), dev_status);
   return hipGetLastError();
@@ -201,7 +224,7 @@ __global__ __launch_bounds__(kSumThreads) void summaries_batch_ranges_kernel(
       if (lane == 0) set_status(dev_status, DSK_ERR_SHAPE);
     } else {
       const uint16_t* base = X + (int64_t)h * stride_head + ((int64_t)rg.z + s) * stride_tok;
-      summarize_block<MEAN>(base, len, stride_tok, (unsigned)stride_tok, o, g, c);
+      summarize_block<MEAN, false>(base, len, stride_tok, (unsigned)stride_tok, o, g, c);
     }
   }
 }
