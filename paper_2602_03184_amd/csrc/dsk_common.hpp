@@ -35,6 +35,26 @@ __device__ __forceinline__ void unpack8(const uint4& v, float (&f)[8]) {
   f[6] = bf16_lo(v.w); f[7] = bf16_hi(v.w);
 }
 
+// ---- 16-byte loads and stores ------------------------------------------------------------------
+// STREAM marks data that is not used again before much else has passed (non-temporal): it is not kept
+// in the caches, and what is there stays.
+typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
+template <bool STREAM>
+__device__ __forceinline__ uint4 load16(const void* at) {
+  if constexpr (!STREAM) return *static_cast<const uint4*>(at);
+  const u32x4_t v = __builtin_nontemporal_load(static_cast<const u32x4_t*>(at));
+  return make_uint4(v.x, v.y, v.z, v.w);
+}
+template <bool STREAM>
+__device__ __forceinline__ void store16(void* at, const uint4& v) {
+  if constexpr (!STREAM) {
+    *static_cast<uint4*>(at) = v;
+  } else {
+    const u32x4_t w = {v.x, v.y, v.z, v.w};
+    __builtin_nontemporal_store(w, static_cast<u32x4_t*>(at));
+  }
+}
+
 // ---- keeping a batch of independent loads in flight together -------------------------------
 // The compiler sinks loads towards their first use, which turns a batch of independent loads
 // into a chain of memory round trips in latency-bound kernels.  pin_loaded(x) is an empty asm

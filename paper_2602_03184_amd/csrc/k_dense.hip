@@ -14,7 +14,7 @@ constexpr int kDenseWaves = 4;
 constexpr int kDenseThreads = kDenseWaves * DSK_WAVE;
 constexpr int kDenseStep = kDenseWaves * 32;              // token ranges are multiples of this
 
-template <int GT, int NS>
+template <int GT, int NS, bool STREAM>
 __global__ __launch_bounds__(kDenseThreads) void dense_attn_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ K, const uint16_t* __restrict__ V,
     int64_t kst, int64_t ksh, int64_t vst, int64_t vsh, int Hq, int G, int total_tokens,
@@ -80,13 +80,13 @@ __global__ __launch_bounds__(kDenseThreads) void dense_attn_kernel(
     for (int u = 0; u < NS; ++u) {
       int r = 4 * u + grp;
       r = r < nvalid ? r : nvalid - 1;                         // padding rows re-read a real row
-      kv[u] = *reinterpret_cast<const uint4*>(Kh + (int64_t)(r0 + r) * kst);
+      kv[u] = load16<STREAM>(Kh + (int64_t)(r0 + r) * kst);
     }
 #pragma unroll
     for (int u = 0; u < NS; ++u) {
       int r = 4 * u + grp;
       r = r < nvalid ? r : nvalid - 1;
-      vv[u] = *reinterpret_cast<const uint4*>(Vh + (int64_t)(r0 + r) * vst);
+      vv[u] = load16<STREAM>(Vh + (int64_t)(r0 + r) * vst);
     }
 #pragma unroll
     for (int j = 0; j < GT; ++j) fold_loaded<NS>(st[j], qf[j], kv, vv, nvalid, grp, scale_log2);
@@ -177,9 +177,22 @@ hipError_t launch_dense_attn(const dsk_dense_attn_args& a, const DenseWs& ws, hi
       static_cast<uint16_t*>(a.out_bf16), a.lse
   // 32-row tiles: 16- and 8-row tiles raise occupancy but were measured slower (the per-tile
   // rescale of four heads' states is vector-ALU work the kernel has little room for)
-  if (ws.group_tile == 4) dense_attn_kernel<4, 8><<<grid, dim3(kDenseThreads), 0, st>>>(DSK_DENSE_ARGS);
-  else if (ws.group_tile == 2) dense_attn_kernel<2, 8><<<grid, dim3(kDenseThreads), 0, st>>>(DSK_DENSE_ARGS);
-  else dense_attn_kernel<1, 8><<<grid, dim3(kDenseThreads), 0, st>>>(DSK_DENSE_ARGS);
+  // K and V that together exceed the 256 MB memory-side cache are not found there again by the next step, so
+  // they are read past it (128K tokens, 8 heads, 537 MB: 96.2 -> 90.8 us for the call, 5.6 -> 5.9 TB/s).  Not
+  // where the passes of a group wider than the tile share the rows.  (The sparse step's summaries and rows
+  // are smaller: streaming them gains 3 to 8 % on caches that are cold, and loses 6 to 14 % where steps follow
+  // each other on one cache.)
+  constexpr int64_t kStreamCacheBytes = 256ll << 20;
+  const bool stream = tiles_g == 1 && (int64_t)a.total_tokens * a.Hkv * (4 * DSK_HEAD_DIM) >= kStreamCacheBytes;
+#define DSK_DENSE_LAUNCH(gt)                                                                              \
+  do {                                                                                                    \
+    if (stream) dense_attn_kernel<gt, 8, true><<<grid, dim3(kDenseThreads), 0, st>>>(DSK_DENSE_ARGS);      \
+    else dense_attn_kernel<gt, 8, false><<<grid, dim3(kDenseThreads), 0, st>>>(DSK_DENSE_ARGS);            \
+  } while (0)
+  if (ws.group_tile == 4) DSK_DENSE_LAUNCH(4);
+  else if (ws.group_tile == 2) DSK_DENSE_LAUNCH(2);
+  else DSK_DENSE_LAUNCH(1);
+#undef DSK_DENSE_LAUNCH
 #undef DSK_DENSE_ARGS
   hipError_t err = hipGetLastError();
   if (err != hipSuccess || ws.nsplit <= 1) return err;

@@ -11,24 +11,13 @@ constexpr int kSumThreads = 256;
 constexpr int kSumWaves = kSumThreads / DSK_WAVE;
 constexpr int kSumUnroll = 8;  // row-groups of 4 rows in flight per wave
 
+// min / max (or mean) of rows [0, len) of one head, `base` pointing at row 0 of the block, written
+// to the 512-byte record `o`.  All 64 lanes of a wavefront call it with wave-uniform arguments.
 // STREAM (the full pass): the records are stored past the cache's replacement order.  Written through it
 // they leave it one by one between the reads, which costs far more than their bytes: K and V summaries of
 // eight sequences, 24K to 64K tokens, 8 heads: 361 -> 345 us for the pass from the larger grid, -> 307 us from
 // these stores.  (Streaming loads of the rows took another 23 us off, and put 30 us on the decode step that
 // follows, which then finds none of K in the memory-side cache: not used.)
-typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
-template <bool STREAM>
-__device__ __forceinline__ void store_record16(uint4* at, uint32_t x, uint32_t y, uint32_t z, uint32_t w) {
-  if constexpr (!STREAM) {
-    *at = make_uint4(x, y, z, w);
-  } else {
-    const u32x4_t v = {x, y, z, w};
-    __builtin_nontemporal_store(v, reinterpret_cast<u32x4_t*>(at));
-  }
-}
-
-// min / max (or mean) of rows [0, len) of one head, `base` pointing at row 0 of the block, written
-// to the 512-byte record `o`.  All 64 lanes of a wavefront call it with wave-uniform arguments.
 template <bool MEAN, bool STREAM>
 __device__ __forceinline__ void summarize_block(const uint16_t* base, int len, int64_t stride_tok, unsigned ustride,
                                                 uint16_t* o, int g, int c) {
@@ -81,11 +70,13 @@ __device__ __forceinline__ void summarize_block(const uint16_t* base, int len, i
     }
   }
   if (g == 0) {
-    store_record16<STREAM>(reinterpret_cast<uint4*>(o) + c, pack_bf16_exact(mn[0], mn[1]), pack_bf16_exact(mn[2], mn[3]),
-                           pack_bf16_exact(mn[4], mn[5]), pack_bf16_exact(mn[6], mn[7]));
+    store16<STREAM>(reinterpret_cast<uint4*>(o) + c,
+                    make_uint4(pack_bf16_exact(mn[0], mn[1]), pack_bf16_exact(mn[2], mn[3]),
+                               pack_bf16_exact(mn[4], mn[5]), pack_bf16_exact(mn[6], mn[7])));
   } else if (g == 1) {
-    store_record16<STREAM>(reinterpret_cast<uint4*>(o) + 16 + c, pack_bf16_exact(mx[0], mx[1]),
-                           pack_bf16_exact(mx[2], mx[3]), pack_bf16_exact(mx[4], mx[5]), pack_bf16_exact(mx[6], mx[7]));
+    store16<STREAM>(reinterpret_cast<uint4*>(o) + 16 + c,
+                    make_uint4(pack_bf16_exact(mx[0], mx[1]), pack_bf16_exact(mx[2], mx[3]),
+                               pack_bf16_exact(mx[4], mx[5]), pack_bf16_exact(mx[6], mx[7])));
   }
 }
 
