@@ -57,18 +57,33 @@ __device__ __forceinline__ void half_wave_reduce(float (&v)[N], int lane, int& i
   }
 }
 
+// dot product of the 8 channels of a summary (widened) with the q+ or q- of a head, in channel order
+__device__ __forceinline__ float dot8_f32(const float (&q)[8], const float (&k)[8]) {
+  float acc = 0.0f;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) acc = fmaf(q[i], k[i], acc);
+  return acc;
+}
+
 // value index = block_in_group * G + g.  GROUPMAX: one row per KV head, the largest of the G
 // heads' scores (selection shared by the group); the G values of a block sit in lanes that
 // differ only in log2(G) consecutive lane bits, so the maximum is a few exchanges.
-template <int G, bool GROUPMAX = false>
+// PADDED: group widths that are no power of two (and above 8): G is the width of a tile of the group's heads,
+// the real width `group` comes from the launch, blockIdx.y counts (KV head, tile), and the heads that a tile
+// does not have repeat its first one and are not written.  The products of this variant are single-precision
+// multiply-adds in channel order, so that its scores are those of the one-block-at-a-time kernel bit by bit.
+template <int G, bool GROUPMAX = false, bool PADDED = false>
 __global__ __launch_bounds__(kScoreThreads) void scores_kernel(
     const uint16_t* __restrict__ ksum, const uint16_t* __restrict__ q, const int32_t* __restrict__ cu_blocks,
     const int32_t* __restrict__ blocks_used, int B, int Hq, int cap, int bound, int stride,
-    float* __restrict__ scores, float* __restrict__ user) {
+    float* __restrict__ scores, float* __restrict__ user, int group) {
   constexpr int NB = score_blocks_per_half(G);
   constexpr int V = NB * G;
   static_assert(V <= 32 && (V & (V - 1)) == 0, "one finished value per lane");
-  const int hk = blockIdx.y;
+  const int tiles = PADDED ? (group + G - 1) / G : 1;
+  const int hk = PADDED ? (int)blockIdx.y / tiles : (int)blockIdx.y;
+  const int h0 = PADDED ? hk * group + ((int)blockIdx.y - hk * tiles) * G : hk * G;   // first head of the tile
+  const int heads = PADDED ? ((hk + 1) * group - h0 < G ? (hk + 1) * group - h0 : G) : G;
   const int half = threadIdx.x >> 5;          // 0..7 within the workgroup
   const int c = threadIdx.x & 31;             // 16-byte column of the summary
   const bool is_max = c >= 16;                // lanes 0-15: kmin, 16-31: kmax
@@ -122,7 +137,7 @@ __global__ __launch_bounds__(kScoreThreads) void scores_kernel(
   uint4 qv[G];
 #pragma unroll
   for (int g = 0; g < G; ++g)
-    qv[g] = *reinterpret_cast<const uint4*>(q + ((int64_t)s_first * Hq + hk * G + g) * DSK_HEAD_DIM + d0);
+    qv[g] = *reinterpret_cast<const uint4*>(q + ((int64_t)s_first * Hq + h0 + (g < heads ? g : 0)) * DSK_HEAD_DIM + d0);
 #pragma unroll
   for (int u = 0; u < NB; ++u) pin_loaded(kv[u]);
 #pragma unroll
@@ -140,7 +155,7 @@ __global__ __launch_bounds__(kScoreThreads) void scores_kernel(
     if (s_first != s_before) {
 #pragma unroll
       for (int g = 0; g < G; ++g)
-        qv[g] = *reinterpret_cast<const uint4*>(q + ((int64_t)s_first * Hq + hk * G + g) * DSK_HEAD_DIM + d0);
+        qv[g] = *reinterpret_cast<const uint4*>(q + ((int64_t)s_first * Hq + h0 + (g < heads ? g : 0)) * DSK_HEAD_DIM + d0);
     }
   }
   // One pass per sequence the group touches (nearly always one): the group's summaries stay in
@@ -159,26 +174,42 @@ __global__ __launch_bounds__(kScoreThreads) void scores_kernel(
       // q+ (lanes holding kmax) or q- (lanes holding kmin) as packed bf16 pairs: the halves whose
       // sign does not fit are zeroed, both are exact in bf16; the products then run on the packed
       // bf16 dot instruction with neither operand widened
-      uint32_t qp[G][4];
-#pragma unroll
-      for (int g = 0; g < G; ++g) {
-        const uint32_t wds[4] = {qv[g].x, qv[g].y, qv[g].z, qv[g].w};
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          const uint32_t neg = ((uint32_t)((int32_t)(wds[k] << 16) >> 31) & 0xFFFFu) |
-                               ((uint32_t)((int32_t)wds[k] >> 31) & 0xFFFF0000u);   // ones over negative halves
-          qp[g][k] = wds[k] & (is_max ? ~neg : neg);
-        }
-      }
       float v[V];
-#pragma unroll
-      for (int u = 0; u < NB; ++u) {
+      if constexpr (PADDED) {
 #pragma unroll
         for (int g = 0; g < G; ++g) {
-          float acc = dot2_bf16(qp[g][0], kv[u].x, 0.0f);
-          acc = dot2_bf16(qp[g][1], kv[u].y, acc);
-          acc = dot2_bf16(qp[g][2], kv[u].z, acc);
-          v[u * G + g] = dot2_bf16(qp[g][3], kv[u].w, acc);
+          float qs[8];
+          unpack8(qv[g], qs);
+#pragma unroll
+          for (int k = 0; k < 8; ++k) qs[k] = is_max ? fmaxf(qs[k], 0.0f) : fminf(qs[k], 0.0f);
+#pragma unroll
+          for (int u = 0; u < NB; ++u) {
+            float f[8];
+            unpack8(kv[u], f);
+            v[u * G + g] = dot8_f32(qs, f);
+          }
+        }
+      } else {
+        uint32_t qp[G][4];
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+          const uint32_t wds[4] = {qv[g].x, qv[g].y, qv[g].z, qv[g].w};
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            const uint32_t neg = ((uint32_t)((int32_t)(wds[k] << 16) >> 31) & 0xFFFFu) |
+                                 ((uint32_t)((int32_t)wds[k] >> 31) & 0xFFFF0000u);   // ones over negative halves
+            qp[g][k] = wds[k] & (is_max ? ~neg : neg);
+          }
+        }
+#pragma unroll
+        for (int u = 0; u < NB; ++u) {
+#pragma unroll
+          for (int g = 0; g < G; ++g) {
+            float acc = dot2_bf16(qp[g][0], kv[u].x, 0.0f);
+            acc = dot2_bf16(qp[g][1], kv[u].y, acc);
+            acc = dot2_bf16(qp[g][2], kv[u].z, acc);
+            v[u * G + g] = dot2_bf16(qp[g][3], kv[u].w, acc);
+          }
         }
       }
       int idx = 0;
@@ -188,16 +219,16 @@ __global__ __launch_bounds__(kScoreThreads) void scores_kernel(
       if constexpr (GROUPMAX) {
         // the G heads of a block: value indices that differ in their low log2(G) bits, i.e. lanes
         // that differ in lane bits log2(V / G) .. log2(V) - 1
-        float best = v[0];
+        float best = PADDED && g >= heads ? -__builtin_inff() : v[0];
 #pragma unroll
         for (int m = V / G; m < V; m <<= 1) best = fmaxf(best, shfl_xor_f(best, m));
         if (writer && g == 0 && i0 + u >= cur && i0 + u < seg_end) {
           scores[(int64_t)hk * stride + i0 + u] = best;
           if (user) user[(int64_t)hk * cap + i0 + u] = best;
         }
-      } else if (writer && i0 + u >= cur && i0 + u < seg_end) {
-        scores[(int64_t)(hk * G + g) * stride + i0 + u] = v[0];
-        if (user) user[(int64_t)(hk * G + g) * cap + i0 + u] = v[0];
+      } else if (writer && g < heads && i0 + u >= cur && i0 + u < seg_end) {
+        scores[(int64_t)(h0 + g) * stride + i0 + u] = v[0];
+        if (user) user[(int64_t)(h0 + g) * cap + i0 + u] = v[0];
       }
       cur = seg_end;
     }
@@ -205,11 +236,12 @@ __global__ __launch_bounds__(kScoreThreads) void scores_kernel(
     ++s;
 #pragma unroll
     for (int g = 0; g < G; ++g)
-      qv[g] = *reinterpret_cast<const uint4*>(q + ((int64_t)s * Hq + hk * G + g) * DSK_HEAD_DIM + d0);
+      qv[g] = *reinterpret_cast<const uint4*>(q + ((int64_t)s * Hq + h0 + (g < heads ? g : 0)) * DSK_HEAD_DIM + d0);
   }
 }
 
-// any group width: one block per half-wave step, q re-read per block (it stays in the vector cache)
+// one selection per KV head on groups of more than 8 heads: one block per half-wave step, q re-read per block
+// (it stays in the vector cache)
 __global__ __launch_bounds__(kScoreThreads) void scores_kernel_anyg(
     const uint16_t* __restrict__ ksum, const uint16_t* __restrict__ q, const int32_t* __restrict__ cu_blocks,
     int B, int Hq, int G, int cap, int stride, bool group_max, float* __restrict__ scores,
@@ -257,14 +289,26 @@ __global__ __launch_bounds__(kScoreThreads) void scores_kernel_anyg(
 hipError_t launch_scores(const dsk_select_args& a, float* scores, int stride, hipStream_t st) {
   if (a.max_blocks_total <= 0) return hipSuccess;
   const int G = a.Hq / a.Hkv;
-  const int per_wg = kHalvesPerWg * score_blocks_per_half(G);
+  const bool shared = (a.flags & DSK_SELECT_SHARED_BY_KV_GROUP) != 0 && G > 1;
+  // group widths that are no power of two or above 8: tiles of 4 (G = 3) or 8 heads (decode step at 20K tokens
+  // against the one-block-at-a-time kernel: 28 / 4 heads 35.4 -> 19.1 us, 40 / 8 31.3 -> 19.8, 16 / 1 61 -> 23).
+  // The maximum over a group needs all of its heads in one tile.
+  const bool padded = G != 1 && G != 2 && G != 4 && G != 8 && (!shared || G <= 8);
+  const int width = padded ? (G == 3 ? 4 : 8) : G;
+  const int per_wg = kHalvesPerWg * score_blocks_per_half(width);
   const int bound = a.max_blocks_used > 0 ? a.max_blocks_used : a.max_blocks_total;
-  const dim3 grid((unsigned)((bound + per_wg - 1) / per_wg), (unsigned)a.Hkv);
+  const dim3 grid((unsigned)((bound + per_wg - 1) / per_wg), (unsigned)(a.Hkv * (padded ? (G + width - 1) / width : 1)));
   const dim3 block(kScoreThreads);
   const uint16_t* ksum = static_cast<const uint16_t*>(a.ksum);
   const uint16_t* q = static_cast<const uint16_t*>(a.q);
-  const bool shared = (a.flags & DSK_SELECT_SHARED_BY_KV_GROUP) != 0 && G > 1;
-#define DSK_SCORE_ARGS ksum, q, a.cu_blocks, a.blocks_used, a.B, a.Hq, a.max_blocks_total, bound, stride, scores, a.scores
+#define DSK_SCORE_ARGS ksum, q, a.cu_blocks, a.blocks_used, a.B, a.Hq, a.max_blocks_total, bound, stride, scores, a.scores, G
+  if (padded) {
+    if (width == 4 && shared) scores_kernel<4, true, true><<<grid, block, 0, st>>>(DSK_SCORE_ARGS);
+    else if (width == 4) scores_kernel<4, false, true><<<grid, block, 0, st>>>(DSK_SCORE_ARGS);
+    else if (shared) scores_kernel<8, true, true><<<grid, block, 0, st>>>(DSK_SCORE_ARGS);
+    else scores_kernel<8, false, true><<<grid, block, 0, st>>>(DSK_SCORE_ARGS);
+    return hipGetLastError();
+  }
   switch (shared ? -G : G) {
     case 1: scores_kernel<1><<<grid, block, 0, st>>>(DSK_SCORE_ARGS); break;
     case 2: scores_kernel<2><<<grid, block, 0, st>>>(DSK_SCORE_ARGS); break;

@@ -135,3 +135,49 @@ def test_shared_selection_tiled_gather(cfg_id, Hq, Hkv, B):
                     T=128 * (32 if cfg_id == 3 else 16))
     assert case.cfg.B * case.cfg.Hkv * case.cfg.k >= 4096
     _check_shared(case, 1, [0, 1, 2, B - 1], sorted({0, Hkv - 1}), "tiled G=%d" % (Hq // Hkv))
+
+
+# group widths that are no power of two, or above 8: the tiled score kernel on padded tiles of heads
+@pytest.mark.parametrize("lens", [[13], [700], [1, 0, 350, 97, 33]])
+@pytest.mark.parametrize("Hq, Hkv, shared", [(3, 1, False), (3, 1, True), (10, 2, False), (10, 2, True), (6, 1, True),
+                                             (7, 1, False), (14, 2, True), (9, 1, False), (16, 1, False), (26, 2, False),
+                                             (12, 1, True)])
+def test_scores_of_any_group_width(Hq, Hkv, shared, lens):
+    import paper_2602_03184_amd as dsk
+    G, B, total = Hq // Hkv, len(lens), sum(lens)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(100 * Hq + total)
+    K = torch.randn(Hkv, total, 128, generator=g, device="cuda").bfloat16()
+    q = torch.randn(B, Hq, 128, generator=g, device="cuda").bfloat16()
+    cu = [0]
+    for n in lens:
+        cu.append(cu[-1] + n)
+    tok = torch.randint(0, 40, (total,), generator=g, device="cuda", dtype=torch.int32)
+    comp = dsk.compress(cu_seqlens=torch.tensor(cu, dtype=torch.int32, device="cuda"), max_seqlen=max(lens), Hq=Hq, K=K,
+                        stages=dsk.DSK_STAGE_CANDIDATES | dsk.DSK_STAGE_SEGMENT | dsk.DSK_STAGE_SUMMARIES, token_ids=tok,
+                        delim_ids=torch.tensor([3, 7], dtype=torch.int32, device="cuda"), n_class=2,
+                        class_weight_q=torch.full((B, 2), 7, dtype=torch.uint8, device="cuda"), C_=5, delta=2, b=4)
+    sel = dsk.select_topk(comp, q, 16, want_scores=True, shared=shared)
+    torch.cuda.synchronize()
+    assert int(comp.dev_status.item()) == 0
+    cub = comp.cu_blocks.cpu().tolist()
+    ks = comp.ksum.double().cpu()
+    qd = q.double().cpu()
+    for s in range(B):
+        rec = ks[:, cub[s]: cub[s + 1]]                                       # [Hkv, n, 2, D]
+        for h in range(Hq):
+            lo, hi = qd[s, h] * rec[h // G, :, 0], qd[s, h] * rec[h // G, :, 1]
+            terms = torch.maximum(lo, hi)
+            # 8 multiply-adds and 5 additions in fp32 on every path to the sum, rounded with 2^-24 each
+            tol = 14 * 2.0 ** -24 * torch.maximum(lo.abs(), hi.abs()).sum(-1)
+            want = terms.sum(-1)
+            if shared:
+                if h % G == 0:
+                    best, best_tol = want, tol
+                else:
+                    best, best_tol = torch.maximum(best, want), torch.maximum(best_tol, tol)
+                if h % G != G - 1:
+                    continue
+                want, tol = best, best_tol
+            got = sel.scores[h // G if shared else h, cub[s]: cub[s + 1]].double().cpu()
+            assert bool(((got - want).abs() <= tol).all()), (s, h, float((got - want).abs().max()))
