@@ -137,7 +137,14 @@ __global__ __launch_bounds__(kDenseThreads) void dense_attn_kernel(
 DenseWs dense_ws_layout(const dsk_dense_attn_args& a) {
   DenseWs ws;
   const int G = a.Hq / a.Hkv;
-  ws.group_tile = (G % 4 == 0) ? 4 : (G % 2 == 0 ? 2 : 1);
+  // Heads folded per pass over the rows.  A width that 4 does not divide is cut into tiles of 4 all the same
+  // where the rows are many (the last pass repeats a head): every pass less is a read of K and V less --
+  // 28 / 4 heads, four sequences of 16K to 33K tokens 208 -> 82 us, 40 / 8 250 -> 141, 24 / 8 178 -> 87,
+  // 48 / 8 181 -> 141.  Below, the smaller tiles' workgroups and fewer repeated heads win: 24 / 8 at 16K tokens
+  // (64 MB) 18.8 against 20.2 us, at 8K 13.3 against 15.5; 48 / 8 at 16K 22.7 against 25.6, at 60K (246 MB) even.
+  const int64_t row_bytes = (int64_t)a.total_tokens * a.Hkv * (4 * DSK_HEAD_DIM);
+  const bool tiles_of_4 = G % 4 == 0 || (G > 2 && row_bytes >= (G % 2 ? 64ll << 20 : 256ll << 20));
+  ws.group_tile = tiles_of_4 ? 4 : (G % 2 == 0 ? 2 : 1);
   const int64_t passes = (int64_t)a.B * a.Hkv * ((G + ws.group_tile - 1) / ws.group_tile);
   // about 4096 workgroups (16 per CU) when the cache is long enough, 128 tokens at least each;
   // at most kDenseMaxSplit ranges per sequence, since the merge runs one workgroup per head and

@@ -172,3 +172,34 @@ def test_token_major_padded_layout_gives_identical_results():
     got = run(Kv, Vv)
     for a, b_ in zip(ref, got):
         assert a.shape == b_.shape and torch.equal(a, b_)
+
+
+@pytest.mark.parametrize("Hq, Hkv", [(3, 1), (5, 1), (7, 1), (24, 4)])
+def test_dense_large_cache_group_widths_that_4_does_not_divide(Hq, Hkv):
+    """From 64 MB (odd widths) or 256 MB of K and V on, such groups run in tiles of 4 heads whose last tile
+    repeats a head."""
+    import paper_2602_03184_amd as dsk
+    lens = [70001, 0, 60031, 33, 1100]
+    total = sum(lens)
+    G = Hq // Hkv
+    assert total * Hkv * 512 >= (64 << 20 if G % 2 else 256 << 20)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(Hq)
+    K = torch.randn(Hkv, total, 128, generator=g, device="cuda").bfloat16()
+    V = torch.randn(Hkv, total, 128, generator=g, device="cuda").bfloat16()
+    q = torch.randn(len(lens), Hq, 128, generator=g, device="cuda").bfloat16()
+    cu = [0]
+    for n in lens:
+        cu.append(cu[-1] + n)
+    att = dsk.dense_decode_attn(q, K, V, torch.tensor(cu, dtype=torch.int32, device="cuda"), max(lens))
+    for s, n in enumerate(lens):
+        if n == 0:
+            assert bool((att.out[s] == 0).all()) and bool(torch.isneginf(att.lse[s]).all())
+            continue
+        rows = slice(cu[s], cu[s + 1])
+        z = q[s].double().view(Hkv, G, 128) @ K[:, rows].double().transpose(1, 2).contiguous() / 128 ** 0.5
+        want = (torch.softmax(z, -1) @ V[:, rows].double()).view(Hq, 128)
+        z = z.view(Hq, n)
+        # fp32 logits, exponentials and sums: a few units of 2^-24 each, far below the bar of bf16 inputs
+        assert float((att.out[s].double() - want).norm() / want.norm()) <= 1e-5
+        assert float((att.lse[s].double() - torch.logsumexp(z, 1)).abs().max()) <= 1e-5
