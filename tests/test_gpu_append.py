@@ -187,3 +187,20 @@ def test_append_reports_capacity_and_table_mismatch():
     seq.app.args.len_old, seq.app.args.len_new = 0, 10
     seq.app.args.delta = seq.app.args.C
     assert dsk.dsk_append_tokens(seq.app.args, check=False) == dsk.DSK_ERR_PARAM
+
+
+@pytest.mark.parametrize("C, delta, share, a_num, steps", [
+    (40, 39, 1.0, 10, [1, 1, 3]),            # chunks of one token: more open chunks than one ballot covers
+    (700, 600, 0.05, 5, [1, 2, 400]),        # more searched tokens than the window holds
+    (24, 12, 0.04, 5, [1000, 1001, 1]),      # 2 * delta + new tokens: as many as the window holds, and one more
+    (24, 12, 0.04, 5, [1, 255, 256, 257]),   # full and partial rounds of window loads
+])
+def test_append_token_window_edges(C, delta, share, a_num, steps):
+    r = np.random.default_rng(C + delta)
+    L0 = 2500
+    total = L0 + sum(steps)
+    K = r.integers(0x3F00, 0x4000, size=(1, total, 128)).astype(np.uint16)
+    tok = np.where(r.random(total) < share, r.integers(0, 3, size=total), 9)
+    q = _Seq(K, K, tok, [0, 1, 2], [10, 10, 7] if share < 1.0 else [10, 10, 10], L0, C, delta, a_num, 10, 16)
+    for n in steps:
+        q.check_tables(*q.append(n))
