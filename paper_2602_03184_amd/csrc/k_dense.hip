@@ -185,7 +185,7 @@ hipError_t launch_dense_attn(const dsk_dense_attn_args& a, const DenseWs& ws, hi
   // 32-row tiles: 16- and 8-row tiles raise occupancy but were measured slower (the per-tile
   // rescale of four heads' states is vector-ALU work the kernel has little room for)
   // K and V that together exceed the 256 MB memory-side cache are not found there again by the next step, so
-  // they are read past it (128K tokens, 8 heads, 537 MB: 96.2 -> 90.8 us for the call, 5.6 -> 5.9 TB/s).  Not
+  // they are read past it (128K tokens, 8 heads, 537 MB: 95.5 -> 91.0 us for the call, 5.6 -> 5.9 TB/s).  Not
   // where the passes of a group wider than the tile share the rows.  (The sparse step's summaries and rows
   // are smaller: streaming them gains 3 to 8 % on caches that are cold, and loses 6 to 14 % where steps follow
   // each other on one cache.)

@@ -13,7 +13,7 @@
 // of MFMA, which run in their shadow when the two are interleaved.  Everything else is kept off that path:
 //  - The samples of a sequence are ranked by position (latest first) and their rows packed back to back,
 //    so that row tiles are full for any W*G and the samples of a workgroup end at about the same key.
-//  - A workgroup (8 wavefronts x kImpNS row tiles, query operands in registers) shares every key tile
+//  - A workgroup (4 wavefronts x kImpNS row tiles, query operands in registers) shares every key tile
 //    through LDS (two buffers of 64 rows, 16-byte chunks permuted by the row number so that the operand
 //    reads touch all banks), loaded coalesced and once per kImpRows query rows.
 //  - The work line -- for every KV head, every item (kImpRows rows of one sequence), every stage of 64
@@ -28,8 +28,8 @@
 //    branch on the kind of a tile serialised them (1.2 instead of 0.8 us per key tile).
 //  - Tiles that cross a region's edge (two or three per row tile, 2.5 times the work) are left out of that
 //    loop and done by each wavefront on its own, so that it does not hold up the others at a barrier.
-// Measured (stage IMPORTANCE, 32 query / 8 KV heads, W = 8): 128 samples of a 128K sequence 92.7 -> 57.7 us,
-// 1024 samples of eight sequences of 24K to 64K tokens 360 -> 233 us (740 TFLOP/s of q.k products), against
+// Measured (stage IMPORTANCE, 32 query / 8 KV heads, W = 8): 128 samples of a 128K sequence 98.3 -> 57.0 us,
+// 1024 samples of eight sequences of 24K to 64K tokens 379 -> 237 us, against
 // one workgroup per 3 or 4 consecutive samples with the key tiles fetched by each wavefront.
 #include <type_traits>
 
