@@ -45,6 +45,8 @@ constexpr int kImpMaxSamples = DSK_MAX_CLASSES * kMaxSamplesPerClass;   // sampl
 constexpr int kImpMaxItems = 4096;     // items of all KV heads planned in one launch (unless one sequence has more)
 constexpr int kImpMaxSeqs = 256;       // sequences planned in one launch
 constexpr int kImpPieces = 512;        // workgroups of a launch: two per CU
+constexpr int kImpFewKeys = 4096;      // keys of a range of the kernel for few query rows,
+constexpr int kImpFewRanges = 32;      // of which there are at most so many (longer ones then)
 struct ImpLayout {
   int seqs;            // sequences per launch
   int items;           // upper bound of the groups of kImpRows query rows of one KV head in a launch

@@ -26,8 +26,12 @@
 //    workgroups of a CU at work a product takes about 585 cycles of a SIMD (440 when the other one idles).
 //    Holding the products of both row tiles at once spilled registers, leaving the MFMAs in front of the
 //    branch on the kind of a tile serialised them (1.2 instead of 0.8 us per key tile).
-//  - Tiles that cross a region's edge (two or three per row tile, 2.5 times the work) are left out of that
-//    loop and done by each wavefront on its own, so that it does not hold up the others at a barrier.
+//  - Tiles that cross a region's edge of some row (2.5 times the work) are left out of that loop and done by
+//    each wavefront on its own, so that it does not hold up the others at a barrier.  A row tile of one sample has
+//    two or three of them.  With fewer than 32 rows per sample a row tile holds several samples, and every tile
+//    between their edges counts: 14 on average for 4 samples a row tile (128 samples of a long text), more
+//    for samples far apart, which the flat kImpItemCost does not follow.
+//  - Calls with few rows or short sequences run on a kernel of their own, importance_few_kernel below.
 // Measured (stage IMPORTANCE, 32 query / 8 KV heads, W = 8): 128 samples of a 128K sequence 98.3 -> 57.0 us,
 // 1024 samples of eight sequences of 24K to 64K tokens 379 -> 237 us, against
 // one workgroup per 3 or 4 consecutive samples with the key tiles fetched by each wavefront.
@@ -530,7 +534,7 @@ __global__ __launch_bounds__(kImpThreads, 2) void importance_kernel(
       read_keys(kf, buf ^ 1, 0);                  // past the end: old keys, their products are not used
       half_step(kFresh, 1, 0, k0 + 32, c1, c0, kf);
     }
-    // the mixed tiles, two or three per row tile: each wavefront on its own, so that it holds up no other one
+    // the mixed tiles: each wavefront on its own, so that it holds up no other one
     auto next_mixed = [&](int p, int tile) {
       while (tile < 2 * st_end && tile * 32 <= last[p] && kind_of(p, tile * 32) != 3) ++tile;
       return tile < 2 * st_end && tile * 32 <= last[p] ? tile : -1;
@@ -585,119 +589,225 @@ __global__ __launch_bounds__(kImpThreads, 2) void importance_kernel(
   }
 }
 
-// grid: (class, sequence).  The wavefronts are dealt to the class's samples; their lanes merge the pieces
-// of the sample's rows over all KV heads and sum the row values, thread 0 then adds the sample scores in
-// sample order (every sum in a fixed order).
-constexpr int kImpFinThreads = 1024;
-constexpr int kImpFinWaves = kImpFinThreads / DSK_WAVE;
-constexpr int kImpFinRows = 2;       // rows of a lane in flight together,
-constexpr int kImpFinBatch = 8;      // and pieces of each
-constexpr int kImpFinItems = 1024;   // items whose places on the line are fetched ahead
-__global__ __launch_bounds__(kImpFinThreads) void importance_finalize_kernel(
-    int32_t* __restrict__ plan, const float4* __restrict__ part, const int32_t* __restrict__ samp_pos,
-    int seq_first, int nseq, int items, int n_class, int M, int Hkv, int G, int W, float alpha,
-    uint8_t* __restrict__ class_weight_q, float* __restrict__ class_mean, float* __restrict__ samp_score,
-    float* __restrict__ samp_score_sum, int layers) {
-  __shared__ float sm_sum[kMaxSamplesPerClass * kImpFinWaves];
-  __shared__ float sm_score[kMaxSamplesPerClass];
-  __shared__ int sm_have[kMaxSamplesPerClass];
-  __shared__ int sm_item[kImpFinItems];
-  const int c = blockIdx.x;
-  const int sl = blockIdx.y, s = seq_first + sl;
+// ---- calls with few query rows ------------------------------------------------------------------
+// The packed kernel pays for its plan, and shares key tiles among kImpRows query rows of a sequence.  Where a
+// sequence has far fewer rows, or few keys, one workgroup per kSamples samples of one KV head does better: its
+// wavefronts take every kWaves-th key tile, straight from memory (one key row per lane), against the
+// samples' operands in LDS.  What bounds it is the latency of that chain, so the keys are cut into
+// ranges of `range_keys` that workgroups of their own take.  A range in which none of the samples has a key
+// ends at once.  A sample that ends in the first range is finished here (imp_part), of the others the
+// statistics of their rows (part) are left to the finishing kernel.
+// grid: (group of kSamples samples, KV head, range x sequence): the ranges are the slowest, so that the few
+// workgroups with work, the first range's, spread over all XCDs
+__device__ __forceinline__ int imp_few_ranges(int last_key, int ranges, int range_keys) {   // that hold a sample's keys
+  const int n = last_key / range_keys + 1;
+  return n < ranges ? n : ranges;
+}
+constexpr int kImpQRow = DSK_HEAD_DIM + 8;   // bf16 elements per query row in LDS: 16 rows' 16-byte reads cover all banks
+template <int kThreads, int kSamples, bool SPLIT>
+__global__ __launch_bounds__(kThreads) void importance_few_kernel(
+    const uint16_t* __restrict__ K, int64_t kst, int64_t ksh, const uint16_t* __restrict__ qwin,
+    const int32_t* __restrict__ samp_pos, const int32_t* __restrict__ cu_seqlens, int n_samp, int ranges, int range_keys, int W,
+    int R, int Hq, int G, int Hkv, float alpha, float scale_log2, int B, float* __restrict__ imp_part, float4* __restrict__ part) {
+  constexpr int kWaves = kThreads / DSK_WAVE;
+  __shared__ RowStat sm_stat[kSamples][kWaves][32];
+  __shared__ float sm_val[kSamples][32];
+  __shared__ __attribute__((aligned(16))) uint16_t sm_q[kSamples][32][kImpQRow];
+  const int group = blockIdx.x;
+  const int hk = blockIdx.y;
+  const int range = SPLIT ? blockIdx.z / B : 0, s = SPLIT ? blockIdx.z - range * B : blockIdx.z;
   const int lane = threadIdx.x & (DSK_WAVE - 1);
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / DSK_WAVE);
-  const int n_samp = n_class * M;
-  const int rps = W * G;
-  const ImpPlan pl = imp_plan(plan, nseq, n_samp, items);
-  const int T1 = pl.head[0], n_list = pl.head[2];
-  const uint32_t nw = (uint32_t)pl.head[1];
-  const int ib = pl.item_base[sl];
-  const int32_t* rank = pl.rank + (int64_t)sl * n_samp;
-  // everything that does not depend on the plan's values goes out in one round trip
-  if (threadIdx.x <= items && threadIdx.x < kImpFinItems) sm_item[threadIdx.x] = pl.item_at[threadIdx.x];
-  if (threadIdx.x < M) sm_have[threadIdx.x] = samp_pos[(int64_t)s * n_samp + c * M + threadIdx.x] >= 0 ? 1 : 0;
-  static_assert(kImpFinItems <= kImpFinThreads, "one load each");
-  auto item_at = [&](int i) { return (uint32_t)(i < kImpFinItems ? sm_item[i] : pl.item_at[i]); };
-  ImpLine line;
-  line.per = line.extra = 0;
-  if (nw > 0) {
-    const uint64_t T = (uint64_t)T1 * Hkv;
-    line.per = (uint32_t)(T / nw);
-    line.extra = (uint32_t)(T % nw);
+  const int wave = threadIdx.x / DSK_WAVE;
+  const int col = lane & 31;        // query row of the tile this lane accumulates
+  const int hf = lane >> 5;         // channel half / key sub-row selector
+
+  const int seq0 = cu_seqlens[s];
+  const int L = cu_seqlens[s + 1] - seq0;
+  int jn[kSamples], t[kSamples], o_lo[kSamples], d_hi[kSamples], last_key[kSamples];
+  int n_tiles = 0;
+#pragma unroll
+  for (int p = 0; p < kSamples; ++p) {
+    jn[p] = group * kSamples + p;
+    const int tg = jn[p] < n_samp ? samp_pos[(int64_t)s * n_samp + jn[p]] : -1;
+    t[p] = tg - seq0;
+    const bool have = tg >= 0 && t[p] >= 0 && t[p] < L;
+    if (!have) t[p] = 0;
+    o_lo[p] = t[p] - R + 1 > 0 ? t[p] - R + 1 : 0;          // retained region [o_lo, t]
+    d_hi[p] = t[p] - R > 0 ? t[p] - R : 0;                  // discarded region [0, d_hi]
+    last_key[p] = have ? (t[p] < L - 1 - W ? t[p] + W : L - 1) : -1;
+    if (have && last_key[p] / 32 + 1 > n_tiles) n_tiles = last_key[p] / 32 + 1;
   }
-  __syncthreads();
-  const int per_sample = M < kImpFinWaves ? kImpFinWaves / M : 1;   // wavefronts of one sample
-  for (int m = wave / per_sample; m < M; m += kImpFinWaves / per_sample) {
-    const int rk = rank[c * M + m];
-    float sum = 0.0f;
-    if (rk >= 0 && nw > 0) {
-      const int n_rows = rps * Hkv, stride = per_sample * DSK_WAVE;
-      for (int idx = (wave % per_sample) * DSK_WAVE + lane; idx < n_rows; idx += kImpFinRows * stride) {
-        const float4* rows[kImpFinRows];
-        int n[kImpFinRows], most = 0;                  // pieces of the row's item
-        RowStat a[kImpFinRows];
+  // the last range takes what is left, whatever the host expected
+  const int tile0 = range * (range_keys / 32);
+  if (SPLIT && range + 1 < ranges && n_tiles > tile0 + range_keys / 32) n_tiles = tile0 + range_keys / 32;
+  if (tile0 >= n_tiles) return;                             // uniform over the workgroup
+  const int rows = W * G;                                   // query rows of one (sample, kv head)
+  const uint16_t* Kh = K + (int64_t)hk * ksh + (int64_t)seq0 * kst + hf * 64;
+  float total[kSamples];
 #pragma unroll
-        for (int i = 0; i < kImpFinRows; ++i) {
-          const int x = idx + i * stride < n_rows ? idx + i * stride : idx;
-          const int hk = x / rps;
-          const int rho = rk * rps + (x - hk * rps);
-          const int item = ib + rho / kImpRows;
-          const uint64_t x0 = (uint64_t)hk * T1 + item_at(item), x1 = (uint64_t)hk * T1 + item_at(item + 1);
-          const uint32_t w0 = line.piece_of(x0);
-          rows[i] = part + ((int64_t)w0 + (int64_t)hk * n_list + item) * kImpRows + rho % kImpRows;
-          n[i] = idx + i * stride < n_rows ? (int)(line.piece_of(x1 - 1) - w0) + 1 : 0;
-          most = n[i] > most ? n[i] : most;
-          a[i] = {-__builtin_inff(), 0.0f, 0.0f, 0.0f};
+  for (int p = 0; p < kSamples; ++p) total[p] = 0.0f;
+
+  for (int row0 = 0; row0 < rows; row0 += 32) {
+    // Q^T operands of the group's samples -> LDS: row r of sample p is query row row0 + r (window
+    // position w = row / G, head g = row % G), zero for rows or samples that do not exist
+    for (int idx = threadIdx.x; idx < kSamples * 32 * 16; idx += kThreads) {
+      const int p = idx / (32 * 16);
+      const int r = (idx / 16) & 31;
+      const int c16 = idx & 15;
+      const int rowq = row0 + r;
+      uint4 raw = make_uint4(0, 0, 0, 0);
+      if (rowq < rows && last_key[p] >= 0) {
+        const int wq_ = rowq / G, gq_ = rowq % G;
+        raw = *reinterpret_cast<const uint4*>(
+            qwin + ((((int64_t)s * n_samp + jn[p]) * W + wq_) * Hq + hk * G + gq_) * DSK_HEAD_DIM + c16 * 8);
+      }
+      *reinterpret_cast<uint4*>(&sm_q[p][r][c16 * 8]) = raw;
+    }
+    const int row = row0 + col;
+    const int w = row < rows ? row / G : 0;
+    int qpos[kSamples];
+    RowStat st[kSamples];
+#pragma unroll
+    for (int p = 0; p < kSamples; ++p) {
+      qpos[p] = t[p] + 1 + w;               // position of this query; attends keys 0..qpos
+      st[p].m = -__builtin_inff();
+      st[p].zt = st[p].zo = st[p].zd = 0.0f;
+    }
+    __syncthreads();
+    // the rows of the wave's next tile are requested before the current tile is multiplied
+    uint4 knext[8];
+    auto request = [&](int tile) {
+      int krow = tile * 32 + col;           // A operand row of this lane
+      krow = krow < L ? krow : L - 1;       // stay inside the sequence; masked below, or past the last tile
+      const uint16_t* kp = Kh + (int64_t)krow * kst;
+#pragma unroll
+      for (int u = 0; u < 8; ++u) knext[u] = *reinterpret_cast<const uint4*>(kp + u * 8);
+    };
+    request(tile0 + wave);
+    for (int tile = tile0 + wave; tile < n_tiles; tile += kWaves) {
+      const int k0 = tile * 32;
+      uint4 kraw[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) kraw[u] = knext[u];
+      request(tile + kWaves);
+#pragma unroll
+      for (int p = 0; p < kSamples; ++p) {
+        if (k0 > last_key[p]) continue;     // this sample's keys ended before the tile (uniform)
+        f32x16_t acc;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          // lane (col, hf) supplies channels [64*hf + 8u, +8) of query row col
+          const bf16x8_t qb = *reinterpret_cast<const bf16x8_t*>(&sm_q[p][col][hf * 64 + u * 8]);
+          acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<bf16x8_t*>(&kraw[u]), qb, acc, 0, 0, 0);
         }
-        for (int w = 0; w < most; w += kImpFinBatch) {
-          float4 v[kImpFinRows][kImpFinBatch];
+        // acc[r] = logit of key k0 + 8*(r/4) + 4*hf + r%4 against query row `col`
+        if (k0 + 31 <= d_hi[p]) {
+          // the whole tile lies in the discarded region (hence before every query of the window
+          // and outside the retained region): no masks, one sum feeds both totals
+          float amax = acc[0];
 #pragma unroll
-          for (int i = 0; i < kImpFinRows; ++i)
+          for (int r = 1; r < 16; ++r) amax = fmaxf(amax, acc[r]);
+          const float mn = fmaxf(st[p].m, amax * scale_log2);
+          const float f = __builtin_amdgcn_exp2f(st[p].m - mn);   // 0 while st.m is still -inf
+          float esum = 0.0f;
 #pragma unroll
-            for (int j = 0; j < kImpFinBatch; ++j) v[i][j] = rows[i][(int64_t)(w + j < n[i] ? w + j : 0) * kImpRows];
+          for (int r = 0; r < 16; ++r) esum += __builtin_amdgcn_exp2f(fmaf(acc[r], scale_log2, -mn));
+          st[p].zt = fmaf(st[p].zt, f, esum);
+          st[p].zd = fmaf(st[p].zd, f, esum);
+          st[p].zo *= f;
+          st[p].m = mn;
+          continue;
+        }
+        float z[16];
+        float tmax = -__builtin_inff();
 #pragma unroll
-          for (int i = 0; i < kImpFinRows; ++i)
+        for (int r = 0; r < 16; ++r) {
+          const int kpos = k0 + 8 * (r / 4) + 4 * hf + (r % 4);
+          z[r] = (kpos <= qpos[p] && kpos <= last_key[p]) ? acc[r] * scale_log2 : -__builtin_inff();
+          tmax = fmaxf(tmax, z[r]);
+        }
+        if (tmax != -__builtin_inff()) {
+          const float mn = fmaxf(st[p].m, tmax);
+          const float f = st[p].m == -__builtin_inff() ? 0.0f : exp2f(st[p].m - mn);
+          st[p].zt *= f; st[p].zo *= f; st[p].zd *= f;
 #pragma unroll
-            for (int j = 0; j < kImpFinBatch; ++j) pin_loaded(v[i][j]);
-#pragma unroll
-          for (int i = 0; i < kImpFinRows; ++i) {
-            float m = a[i].m;
-#pragma unroll
-            for (int j = 0; j < kImpFinBatch; ++j) m = fmaxf(m, w + j < n[i] ? v[i][j].x : -__builtin_inff());
-            const float ref = m == -__builtin_inff() ? 0.0f : m;     // no key anywhere yet: all factors 0
-            const float f = __builtin_amdgcn_exp2f(a[i].m - ref);
-            a[i] = {m, a[i].zt * f, a[i].zo * f, a[i].zd * f};
-#pragma unroll
-            for (int j = 0; j < kImpFinBatch; ++j) {
-              const float g = w + j < n[i] ? __builtin_amdgcn_exp2f(v[i][j].x - ref) : 0.0f;
-              a[i].zt = fmaf(v[i][j].y, g, a[i].zt);
-              a[i].zo = fmaf(v[i][j].z, g, a[i].zo);
-              a[i].zd = fmaf(v[i][j].w, g, a[i].zd);
-            }
+          for (int r = 0; r < 16; ++r) {
+            const int kpos = k0 + 8 * (r / 4) + 4 * hf + (r % 4);
+            const float e = __builtin_amdgcn_exp2f(z[r] - mn);   // z <= mn; 0 for masked keys (-inf)
+            st[p].zt += e;
+            st[p].zo += (kpos >= o_lo[p] && kpos <= t[p]) ? e : 0.0f;
+            st[p].zd += (kpos <= d_hi[p]) ? e : 0.0f;
           }
+          st[p].m = mn;
         }
-#pragma unroll
-        for (int i = 0; i < kImpFinRows; ++i) sum += a[i].zt > 0.0f ? (a[i].zo - alpha * a[i].zd) / a[i].zt : 0.0f;
       }
     }
-    sum = wave_sum(sum);
-    if (lane == 0) sm_sum[m * kImpFinWaves + wave % per_sample] = sum;
+    // halves of a wave hold disjoint keys of the same row; then waves; fixed order
+#pragma unroll
+    for (int p = 0; p < kSamples; ++p) {
+      RowStat other;
+      other.m = shfl_xor_f(st[p].m, 32);
+      other.zt = shfl_xor_f(st[p].zt, 32);
+      other.zo = shfl_xor_f(st[p].zo, 32);
+      other.zd = shfl_xor_f(st[p].zd, 32);
+      if (hf == 0) {
+        stat_merge(st[p], other);
+        sm_stat[p][wave][col] = st[p];
+      }
+    }
+    __syncthreads();
+    if (threadIdx.x < 32 * kSamples) {
+      const int p = threadIdx.x >> 5;
+      RowStat a = sm_stat[p][0][col];
+#pragma unroll
+      for (int wv = 1; wv < kWaves; ++wv) stat_merge(a, sm_stat[p][wv][col]);
+      sm_val[p][col] = row0 + col < rows && a.zt > 0.0f ? (a.zo - alpha * a.zd) / a.zt : 0.0f;
+      if constexpr (SPLIT) {
+        int j = 0, last = -1;
+#pragma unroll
+        for (int i = 0; i < kSamples; ++i)
+          if (i == p) { j = jn[i]; last = last_key[i]; }
+        if (row0 + col < rows && last >= tile0 * 32 && imp_few_ranges(last, ranges, range_keys) > 1)
+          part[((((int64_t)s * n_samp + j) * Hkv + hk) * rows + row0 + col) * ranges + range] =
+              make_float4(a.m, a.zt, a.zo, a.zd);
+      }
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+#pragma unroll
+      for (int p = 0; p < kSamples; ++p)
+        for (int c2 = 0; c2 < 32; ++c2) total[p] += sm_val[p][c2];   // fixed order
+    }
+    __syncthreads();
   }
-  __syncthreads();
+  if (threadIdx.x == 0) {
+#pragma unroll
+    for (int p = 0; p < kSamples; ++p)
+      if (last_key[p] >= 0 && (!SPLIT || (range == 0 && imp_few_ranges(last_key[p], ranges, range_keys) == 1)))
+        imp_part[((int64_t)s * n_samp + jn[p]) * Hkv + hk] = total[p];
+  }
+}
+
+// what the finishing kernels end with, on the sum `st` of a sample's rows (thread m < M: the class's m-th
+// sample, have: its position is not -1): sample scores, class mean, class weight; sums in sample order
+__device__ __forceinline__ void imp_class_weight(float st, bool have, int c, int s, int n_class, int M, int n_rows,
+                                                 float alpha, uint8_t* class_weight_q, float* class_mean,
+                                                 float* samp_score, float* samp_score_sum, int layers) {
+  __shared__ float sm_score[kMaxSamplesPerClass];
+  __shared__ int sm_have[kMaxSamplesPerClass];
   if ((int)threadIdx.x < M) {
-    const int m = threadIdx.x;
-    const int64_t js = (int64_t)s * n_samp + c * M + m;
-    const bool have = sm_have[m] != 0;
-    float st = 0.0f;
-    for (int i = 0; i < per_sample; ++i) st += sm_sum[m * kImpFinWaves + i];
-    st /= (float)(G * Hkv * W);
+    const int64_t js = ((int64_t)s * n_class + c) * M + threadIdx.x;
+    st /= (float)n_rows;
     if (samp_score) samp_score[js] = have ? st : __builtin_nanf("");
     if (samp_score_sum != nullptr && have) {      // expectation over layers: this layer joins the running sum
       const float tot = samp_score_sum[js] + st;
       samp_score_sum[js] = tot;
       st = tot / (float)layers;
     }
-    sm_score[m] = st;
+    sm_score[threadIdx.x] = st;
+    sm_have[threadIdx.x] = have ? 1 : 0;
   }
   __syncthreads();
   if (threadIdx.x != 0) return;
@@ -717,6 +827,186 @@ __global__ __launch_bounds__(kImpFinThreads) void importance_finalize_kernel(
   }
 }
 
+// grid: (class, sequence), one lane per sample (M <= 64): the samples that importance_few_kernel finished
+__global__ __launch_bounds__(DSK_WAVE) void importance_few_finalize_kernel(
+    const float* __restrict__ imp_part, const int32_t* __restrict__ samp_pos, const int32_t* __restrict__ cu_seqlens,
+    int n_class, int M, int Hkv, int G, int W, float alpha, uint8_t* __restrict__ class_weight_q,
+    float* __restrict__ class_mean, float* __restrict__ samp_score, float* __restrict__ samp_score_sum, int layers) {
+  const int c = blockIdx.x, s = blockIdx.y, m = threadIdx.x;
+  const int seq0 = cu_seqlens[s], end = cu_seqlens[s + 1];
+  float st = 0.0f;
+  bool have = false;
+  if (m < M) {
+    const int64_t js = ((int64_t)s * n_class + c) * M + m;
+    const int tg = samp_pos[js];
+    have = tg >= 0;
+    if (have && tg >= seq0 && tg < end)           // a position outside the sequence counts with 0
+      for (int hk = 0; hk < Hkv; ++hk) st += imp_part[js * Hkv + hk];
+  }
+  imp_class_weight(st, have, c, s, n_class, M, G * Hkv * W, alpha, class_weight_q, class_mean, samp_score, samp_score_sum,
+                   layers);
+}
+
+constexpr int kImpFinThreads = 1024;
+constexpr int kImpFinWaves = kImpFinThreads / DSK_WAVE;
+constexpr int kImpFinRows = 2;       // rows of a lane in flight together,
+constexpr int kImpFinBatch = 8;      // and pieces of each
+// The rows idx, idx + stride .. of a sample's n_rows: their pieces' statistics merged, the row values summed.
+// locate(row, n): the first of the row's n pieces, `pitch` entries apart.
+template <typename Locate>
+__device__ __forceinline__ float imp_rows_sum(Locate locate, int pitch, int idx, int stride, int n_rows, float alpha) {
+  float sum = 0.0f;
+  for (; idx < n_rows; idx += kImpFinRows * stride) {
+    const float4* rows[kImpFinRows];
+    int n[kImpFinRows], most = 0;
+    RowStat a[kImpFinRows];
+#pragma unroll
+    for (int i = 0; i < kImpFinRows; ++i) {
+      const bool own = idx + i * stride < n_rows;
+      rows[i] = locate(own ? idx + i * stride : idx, n[i]);
+      n[i] = own ? n[i] : 0;
+      most = n[i] > most ? n[i] : most;
+      a[i] = {-__builtin_inff(), 0.0f, 0.0f, 0.0f};
+    }
+    for (int w = 0; w < most; w += kImpFinBatch) {
+      float4 v[kImpFinRows][kImpFinBatch];
+#pragma unroll
+      for (int i = 0; i < kImpFinRows; ++i)
+#pragma unroll
+        for (int j = 0; j < kImpFinBatch; ++j) v[i][j] = rows[i][(int64_t)(w + j < n[i] ? w + j : 0) * pitch];
+#pragma unroll
+      for (int i = 0; i < kImpFinRows; ++i)
+#pragma unroll
+        for (int j = 0; j < kImpFinBatch; ++j) pin_loaded(v[i][j]);
+#pragma unroll
+      for (int i = 0; i < kImpFinRows; ++i) {
+        float m = a[i].m;
+#pragma unroll
+        for (int j = 0; j < kImpFinBatch; ++j) m = fmaxf(m, w + j < n[i] ? v[i][j].x : -__builtin_inff());
+        const float ref = m == -__builtin_inff() ? 0.0f : m;     // no key anywhere yet: all factors 0
+        const float f = __builtin_amdgcn_exp2f(a[i].m - ref);
+        a[i] = {m, a[i].zt * f, a[i].zo * f, a[i].zd * f};
+#pragma unroll
+        for (int j = 0; j < kImpFinBatch; ++j) {
+          const float g = w + j < n[i] ? __builtin_amdgcn_exp2f(v[i][j].x - ref) : 0.0f;
+          a[i].zt = fmaf(v[i][j].y, g, a[i].zt);
+          a[i].zo = fmaf(v[i][j].z, g, a[i].zo);
+          a[i].zd = fmaf(v[i][j].w, g, a[i].zd);
+        }
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < kImpFinRows; ++i) sum += a[i].zt > 0.0f ? (a[i].zo - alpha * a[i].zd) / a[i].zt : 0.0f;
+  }
+  return sum;
+}
+
+// grid: (class, sequence).  The wavefronts are dealt to the class's samples; their lanes merge the pieces
+// of the sample's rows over all KV heads and sum the row values, thread 0 then adds the sample scores in
+// sample order (every sum in a fixed order).
+constexpr int kImpFinItems = 1024;   // items whose places on the line are fetched ahead
+__global__ __launch_bounds__(kImpFinThreads) void importance_finalize_kernel(
+    int32_t* __restrict__ plan, const float4* __restrict__ part, const int32_t* __restrict__ samp_pos,
+    int seq_first, int nseq, int items, int n_class, int M, int Hkv, int G, int W, float alpha,
+    uint8_t* __restrict__ class_weight_q, float* __restrict__ class_mean, float* __restrict__ samp_score,
+    float* __restrict__ samp_score_sum, int layers) {
+  __shared__ float sm_sum[kMaxSamplesPerClass * kImpFinWaves];
+  __shared__ int sm_item[kImpFinItems];
+  const int c = blockIdx.x;
+  const int sl = blockIdx.y, s = seq_first + sl;
+  const int lane = threadIdx.x & (DSK_WAVE - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / DSK_WAVE);
+  const int n_samp = n_class * M;
+  const int rps = W * G;
+  const ImpPlan pl = imp_plan(plan, nseq, n_samp, items);
+  const int T1 = pl.head[0], n_list = pl.head[2];
+  const uint32_t nw = (uint32_t)pl.head[1];
+  const int ib = pl.item_base[sl];
+  const int32_t* rank = pl.rank + (int64_t)sl * n_samp;
+  // everything that does not depend on the plan's values goes out in one round trip
+  if (threadIdx.x <= items && threadIdx.x < kImpFinItems) sm_item[threadIdx.x] = pl.item_at[threadIdx.x];
+  const bool have = (int)threadIdx.x < M && samp_pos[(int64_t)s * n_samp + c * M + threadIdx.x] >= 0;
+  static_assert(kImpFinItems <= kImpFinThreads, "one load each");
+  auto item_at = [&](int i) { return (uint32_t)(i < kImpFinItems ? sm_item[i] : pl.item_at[i]); };
+  ImpLine line;
+  line.per = line.extra = 0;
+  if (nw > 0) {
+    const uint64_t T = (uint64_t)T1 * Hkv;
+    line.per = (uint32_t)(T / nw);
+    line.extra = (uint32_t)(T % nw);
+  }
+  __syncthreads();
+  const int per_sample = M < kImpFinWaves ? kImpFinWaves / M : 1;   // wavefronts of one sample
+  for (int m = wave / per_sample; m < M; m += kImpFinWaves / per_sample) {
+    const int rk = rank[c * M + m];
+    float sum = 0.0f;
+    if (rk >= 0 && nw > 0) {
+      sum = imp_rows_sum(
+          [&](int x, int& n) {
+            const int hk = x / rps;
+            const int rho = rk * rps + (x - hk * rps);
+            const int item = ib + rho / kImpRows;
+            const uint64_t x0 = (uint64_t)hk * T1 + item_at(item), x1 = (uint64_t)hk * T1 + item_at(item + 1);
+            const uint32_t w0 = line.piece_of(x0);
+            n = (int)(line.piece_of(x1 - 1) - w0) + 1;
+            return part + ((int64_t)w0 + (int64_t)hk * n_list + item) * kImpRows + rho % kImpRows;
+          },
+          kImpRows, (wave % per_sample) * DSK_WAVE + lane, per_sample * DSK_WAVE, rps * Hkv, alpha);
+    }
+    sum = wave_sum(sum);
+    if (lane == 0) sm_sum[m * kImpFinWaves + wave % per_sample] = sum;
+  }
+  __syncthreads();
+  float st = 0.0f;
+  if ((int)threadIdx.x < M)
+    for (int i = 0; i < per_sample; ++i) st += sm_sum[threadIdx.x * kImpFinWaves + i];
+  imp_class_weight(st, have, c, s, n_class, M, G * Hkv * W, alpha, class_weight_q, class_mean, samp_score, samp_score_sum,
+                   layers);
+}
+
+// grid: (class, sequence): the same behind importance_few_kernel with several key ranges
+constexpr int kImpFewWaves = 4;
+__global__ __launch_bounds__(kImpFewWaves * DSK_WAVE) void importance_few_merge_kernel(
+    const float* __restrict__ imp_part, const float4* __restrict__ part, const int32_t* __restrict__ samp_pos,
+    const int32_t* __restrict__ cu_seqlens, int ranges, int range_keys, int n_class, int M, int Hkv, int G, int W,
+    float alpha, uint8_t* __restrict__ class_weight_q, float* __restrict__ class_mean, float* __restrict__ samp_score,
+    float* __restrict__ samp_score_sum, int layers) {
+  __shared__ float sm_sum[kMaxSamplesPerClass * kImpFewWaves];
+  const int c = blockIdx.x, s = blockIdx.y;
+  const int lane = threadIdx.x & (DSK_WAVE - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / DSK_WAVE);
+  const int n_rows = W * G * Hkv;
+  const int seq0 = cu_seqlens[s], L = cu_seqlens[s + 1] - seq0;
+  const int64_t js = ((int64_t)s * n_class + c) * M;
+  const bool have = (int)threadIdx.x < M && samp_pos[js + threadIdx.x] >= 0;
+  const int per_sample = M < kImpFewWaves ? kImpFewWaves / M : 1;   // wavefronts of one sample
+  for (int m = wave / per_sample; m < M; m += kImpFewWaves / per_sample) {
+    const int tg = samp_pos[js + m], t = tg - seq0, part_of = wave % per_sample;
+    float sum = 0.0f;
+    if (tg >= 0 && t >= 0 && t < L) {             // a position outside the sequence counts with 0
+      const int n_ranges = imp_few_ranges(t < L - 1 - W ? t + W : L - 1, ranges, range_keys);
+      if (n_ranges == 1) {
+        for (int hk = part_of * DSK_WAVE + lane; hk < Hkv; hk += per_sample * DSK_WAVE) sum += imp_part[(js + m) * Hkv + hk];
+      } else {
+        sum = imp_rows_sum(
+            [&](int x, int& n) {
+              n = n_ranges;
+              return part + ((js + m) * n_rows + x) * ranges;
+            },
+            1, part_of * DSK_WAVE + lane, per_sample * DSK_WAVE, n_rows, alpha);
+      }
+    }
+    sum = wave_sum(sum);
+    if (lane == 0) sm_sum[m * kImpFewWaves + part_of] = sum;
+  }
+  __syncthreads();
+  float st = 0.0f;
+  if ((int)threadIdx.x < M)
+    for (int i = 0; i < per_sample; ++i) st += sm_sum[threadIdx.x * kImpFewWaves + i];
+  imp_class_weight(st, have, c, s, n_class, M, G * Hkv * W, alpha, class_weight_q, class_mean, samp_score, samp_score_sum,
+                   layers);
+}
+
 ImpLayout importance_layout(int B, int n_samp, int W, int Hq, int Hkv) {
   ImpLayout l;
   const int64_t rps = (int64_t)W * (Hq / Hkv);
@@ -732,6 +1022,49 @@ ImpLayout importance_layout(int B, int n_samp, int W, int Hq, int Hkv) {
   return l;
 }
 
+// The kernel for few rows: whether the call takes it, its key ranges, and where the rows' statistics lie
+// behind the sums of the (sample, KV head) pairs.
+struct ImpFew {
+  bool take;
+  int ranges, keys;
+  size_t sums;           // float4 entries
+};
+static ImpFew importance_few(const dsk_compress_args& a, const ImpLayout& l) {
+  ImpFew f;
+  const int64_t n_samp = (int64_t)a.n_class * a.M;
+  const int64_t rps = (int64_t)a.W * (a.Hq / a.Hkv), row_tiles = (rps + 31) / 32;
+  const int64_t wgs = (n_samp + 3) / 4 * a.Hkv * a.B;
+  // The rule bounds the work of this kernel, in products of four samples' row tiles with a key tile, and the chain of
+  // samples with several row tiles.  It counts with the keys that the samples of stage CANDIDATES reach, the first
+  // M occurrences of every class (delimiters are some tens of tokens apart), not with the sequence's length: on
+  // positions further back this kernel is up to three times slower than the packed one, which is up to 2.9 times
+  // slower than this one on early positions or short sequences.  Several sequences cost the packed kernel a
+  // ranking launch and time for its plan, and items of a few rows leave most of its wavefronts idle.
+  // Measured at its sides, packed against this kernel: 128 samples of 300 tokens, 32 / 8 heads 29.3 against 16.9 us;
+  // 4 samples in each of 8 sequences of 8K tokens, 32 / 32 heads 224 against 93; 128 samples spread over 8K
+  // tokens, 32 / 8 heads 62.8 against 71.8 (packed).
+  const bool own_rank = a.B == 1 && n_samp <= kImpThreads;
+  int64_t keys = (int64_t)a.R + a.W + 48 * n_samp;
+  if (keys > a.max_seqlen) keys = a.max_seqlen;
+  const int64_t work = wgs * row_tiles * ((keys + 31) / 32);
+  f.take = (work <= (own_rank ? 16384 : 26000 + 300 * (int64_t)a.B) && (row_tiles == 1 || row_tiles * keys <= 1024)) ||
+           (row_tiles == 1 && n_samp <= 8 && n_samp * rps <= 64);
+  // Key ranges only where the samples alone occupy at most half of the CUs (a sequence of 128K tokens, 4 samples
+  // spread over it, 8 / 8 heads: 859 us in one range, 56 in 32; 40 samples in each of 3 sequences of 5.3K, 240
+  // workgroups: 53 against 62 in 2), and as far as their statistics have room.
+  const int64_t rows = a.B * n_samp * rps * a.Hkv;
+  f.sums = (size_t)(((int64_t)a.B * n_samp * a.Hkv + 3) / 4);
+  int64_t ranges = ((int64_t)a.max_seqlen + kImpFewKeys - 1) / kImpFewKeys;
+  if (ranges > kImpFewRanges) ranges = kImpFewRanges;
+  if (wgs > 128) ranges = 1;
+  else if (ranges * wgs > 1024) ranges = 1024 / wgs;
+  if (ranges > 1 && (int64_t)f.sums + ranges * rows > (int64_t)l.part_rows) ranges = ((int64_t)l.part_rows - (int64_t)f.sums) / rows;
+  if (ranges < 1) ranges = 1;
+  f.ranges = (int)ranges;
+  f.keys = (int)((((int64_t)a.max_seqlen + ranges - 1) / ranges + 31) / 32 * 32);
+  return f;
+}
+
 hipError_t launch_importance(const dsk_compress_args& a, const CompressWs& ws, hipStream_t st) {
   unsigned char* w = static_cast<unsigned char*>(a.workspace);
   int32_t* plan = reinterpret_cast<int32_t*>(w + ws.imp_plan);
@@ -740,6 +1073,39 @@ hipError_t launch_importance(const dsk_compress_args& a, const CompressWs& ws, h
   const int G = a.Hq / a.Hkv;
   const float scale = a.imp_scale != 0.0f ? a.imp_scale : 0.08838834764831845f;   // 128^-1/2
   const ImpLayout l = importance_layout(a.B, n_samp, a.W, a.Hq, a.Hkv);
+  const int layers = a.imp_layers > 0 ? a.imp_layers : 1;
+  const ImpFew few = importance_few(a, l);
+  if (few.take && few.sums <= l.part_rows) {
+    float* sums = reinterpret_cast<float*>(part);     // of each (sample, KV head), in front of the statistics
+    float4* stats = part + few.sums;
+#define DSK_IMP_ARGS                                                                                             \
+  static_cast<const uint16_t*>(a.K), a.k_stride_tok, a.k_stride_head, static_cast<const uint16_t*>(a.qwin),      \
+      a.samp_pos, a.cu_seqlens, n_samp, few.ranges, few.keys, a.W, a.R, a.Hq, G, a.Hkv, a.alpha_imp,         \
+      scale * kImpLog2e, a.B, sums, stats
+#define DSK_IMP_FEW(threads, samples)                                                                             \
+  do {                                                                                                           \
+    const dim3 grid((unsigned)((n_samp + samples - 1) / samples), (unsigned)a.Hkv, (unsigned)(a.B * few.ranges)); \
+    if (few.ranges > 1) importance_few_kernel<threads, samples, true><<<grid, dim3(threads), 0, st>>>(DSK_IMP_ARGS); \
+    else importance_few_kernel<threads, samples, false><<<grid, dim3(threads), 0, st>>>(DSK_IMP_ARGS);           \
+  } while (0)
+    // 4 samples and 8 wavefronts per workgroup where these are few, 3 and 4 where there are many
+    if ((int64_t)((n_samp + 3) / 4) * a.Hkv * a.B < 1024) DSK_IMP_FEW(512, 4);
+    else DSK_IMP_FEW(256, 3);
+#undef DSK_IMP_FEW
+#undef DSK_IMP_ARGS
+    hipError_t err = hipGetLastError();
+    if (err != hipSuccess) return err;
+    const dim3 grid((unsigned)a.n_class, (unsigned)a.B);
+    if (few.ranges == 1)
+      importance_few_finalize_kernel<<<grid, dim3(DSK_WAVE), 0, st>>>(
+          sums, a.samp_pos, a.cu_seqlens, a.n_class, a.M, a.Hkv, G, a.W, a.alpha_imp, a.class_weight_q, a.class_mean,
+          a.samp_score, a.samp_score_sum, layers);
+    else
+      importance_few_merge_kernel<<<grid, dim3(kImpFewWaves * DSK_WAVE), 0, st>>>(
+          sums, stats, a.samp_pos, a.cu_seqlens, few.ranges, few.keys, a.n_class, a.M, a.Hkv, G, a.W, a.alpha_imp,
+          a.class_weight_q, a.class_mean, a.samp_score, a.samp_score_sum, layers);
+    return hipGetLastError();
+  }
   for (int s = 0; s < a.B; s += l.seqs) {
     const int nseq = a.B - s < l.seqs ? a.B - s : l.seqs;
     hipError_t err;
@@ -760,7 +1126,7 @@ hipError_t launch_importance(const dsk_compress_args& a, const CompressWs& ws, h
     if (err != hipSuccess) return err;
     importance_finalize_kernel<<<dim3((unsigned)a.n_class, (unsigned)nseq), dim3(kImpFinThreads), 0, st>>>(
         plan, part, a.samp_pos, s, nseq, l.items, a.n_class, a.M, a.Hkv, G, a.W, a.alpha_imp, a.class_weight_q,
-        a.class_mean, a.samp_score, a.samp_score_sum, a.imp_layers > 0 ? a.imp_layers : 1);
+        a.class_mean, a.samp_score, a.samp_score_sum, layers);
     err = hipGetLastError();
     if (err != hipSuccess) return err;
   }

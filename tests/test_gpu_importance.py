@@ -301,3 +301,117 @@ def test_importance_given_positions(B, L, Hq, Hkv, n_class, M, W, R, spread, imp
                 continue
             want = O.delimiter_importance(O.widen_bf16(q_bits[s, j]), Kf[:, cu[s]: cu[s + 1]], int(t[s, j]), R, 1.0, scale)
             assert abs(float(got[s, j]) - want) <= tol, (s, j, int(t[s, j]), float(got[s, j]), want)
+
+
+# ---------------------------------------------------------------------------------------------
+# both kernels of the stage at the sizes where they can go wrong, against plain torch in 64 bits
+# ---------------------------------------------------------------------------------------------
+def _on_the_few_rows_kernel(B, L, Hq, Hkv, n, W, R):
+    """The launch rule, on the keys that a calibration's first occurrences reach: a bound on the work (row tiles of
+    four samples times key tiles) and on the chain of a sample with several row tiles, or a handful of rows."""
+    rows = W * (Hq // Hkv)
+    row_tiles, keys = -(-rows // 32), min(L, R + W + 48 * n)
+    limit = 16384 if B == 1 and n <= 256 else 26000 + 300 * B
+    work = -(-n // 4) * Hkv * B * row_tiles * -(-keys // 32)
+    return ((work <= limit and (row_tiles == 1 or row_tiles * keys <= 1024))
+            or (row_tiles == 1 and n <= 8 and n * rows <= 64))
+
+
+def _score64(q, K, t, R, alpha, scale):
+    """s_t of one sample: q [W, Hq, D], K [Hkv, L, D]."""
+    W_, Hq, D = q.shape
+    Hkv, L, _ = K.shape
+    n = min(t + W_, L - 1) + 1
+    qg = q.double().view(W_, Hkv, Hq // Hkv, D).permute(1, 2, 0, 3).reshape(Hkv, -1, D)
+    z = (qg @ K[:, :n].double().transpose(1, 2).contiguous() * scale).view(Hkv, Hq // Hkv, W_, n)
+    pos = torch.arange(n, device=K.device)
+    reach = pos[None] <= t + 1 + torch.arange(W_, device=K.device)[:, None]
+    p = torch.softmax(z.masked_fill(~reach, float("-inf")), -1)
+    kept = p[..., max(0, t - R + 1): t + 1].sum(-1)
+    lost = p[..., : max(0, t - R) + 1].sum(-1)
+    return float((kept - alpha * lost).mean())
+
+
+def _compare_with_64_bits(B, L, Hq, Hkv, n_class, M, W, R, positions, few, spread=1.0, imp_scale=0.0, check=40, alpha=1.0):
+    import paper_2602_03184_amd as dsk
+    n = n_class * M
+    assert _on_the_few_rows_kernel(B, L, Hq, Hkv, n, W, R) == few
+    r = np.random.default_rng(L + Hq + n)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(L + n)
+    lens = np.full(B, L)
+    lens[1::2] = max(1, L // 2)
+    cu = np.concatenate([[0], np.cumsum(lens)])
+    t = np.stack([r.integers(0, x, size=n) for x in lens])
+    t[0, : len(positions)] = positions
+    samp = t + cu[:-1, None]
+    if n > 4:
+        samp[0, n - 1] = -1                                           # an absent sample
+    K = (torch.randn(Hkv, int(cu[-1]), 128, generator=g, device="cuda") * spread).bfloat16()
+    q = torch.randn(B, n, W, Hq, 128, generator=g, device="cuda").bfloat16()
+    wq = dev_u8(np.full((B, n_class), 3, np.uint8))
+    kw = dict(cu_seqlens=dev_i32(cu), max_seqlen=L, Hq=Hq, K=K, V=None, stages=dsk.DSK_STAGE_IMPORTANCE,
+              n_class=n_class, M=M, W=W, R=R, alpha_imp=alpha, imp_scale=imp_scale,
+              samp_pos=dev_i32(samp.reshape(B, n_class, M)), qwin=q, class_weight_q=wq)
+    comp = dsk.compress(**kw)
+    got = comp.samp_score.cpu().numpy().reshape(B, n)
+    np.testing.assert_array_equal(got, dsk.compress(**kw).samp_score.cpu().numpy().reshape(B, n))
+    mean = comp.class_mean.cpu().numpy()
+    scale = imp_scale if imp_scale != 0.0 else 1.0 / math.sqrt(128.0)
+    tol = SCORE_TOL * max(1.0, spread / 4)                            # rounding of logits of that size, as above
+    for s in (range(B) if B < 8 else (0, 1, B // 2, B - 1)):
+        for j in (range(n) if n <= check else sorted(set(range(len(positions))) | {n // 2, n - 2, n - 1})):
+            if samp[s, j] < 0:
+                assert math.isnan(got[s, j])
+                continue
+            want = _score64(q[s, j], K[:, cu[s]: cu[s + 1]], int(t[s, j]), R, alpha, scale)
+            assert abs(float(got[s, j]) - want) <= tol, (s, j, int(t[s, j]), float(got[s, j]), want)
+        # the means add the scores in sample order, in 32 bits
+        np.testing.assert_allclose(mean[s], np.nanmean(got[s].reshape(n_class, M).astype(np.float64), axis=1), atol=1e-6)
+
+
+@pytest.mark.parametrize(
+    "B, L, Hq, Hkv, n_class, M, W, R, positions",
+    [
+        (1, 700, 1, 1, 1, 3, 1, 1, [0, 699]),                             # one row a sample, a group that is not full
+        (1, 900, 4, 2, 2, 3, 8, 128, [0, 31, 32, 899, 891]),              # second group of two samples, windows cut
+        (1, 510, 8, 1, 2, 2, 8, 64, [0, 200, 509]),                       # two row tiles a sample
+        (3, 300, 2, 2, 3, 4, 8, 300, [299, 0]),                           # ragged; nothing is discarded but key 0
+        (32, 100, 32, 32, 1, 4, 8, 16, [99]),                             # 1024 groups: 3 samples and 4 wavefronts
+        (1, 4096, 8, 2, 2, 2, 8, 128, [4095, 4087, 2000]),                # the longest in one range
+        (1, 4097, 8, 2, 2, 2, 8, 128, [4096, 2079, 2080, 2071]),          # two ranges: 2080 keys, then the rest
+        (1, 20000, 4, 4, 1, 5, 8, 5000, [19999, 3991, 3992, 3999, 4000]), # five ranges, retained over two
+        (2, 20000, 8, 2, 2, 1, 4, 128, [7999, 12345]),                    # two sequences over ranges of 4000
+        (1, 131072, 8, 8, 2, 2, 8, 128, [131071, 70000, 4095, 200]),      # 32 ranges
+    ])
+def test_importance_few_rows(B, L, Hq, Hkv, n_class, M, W, R, positions):
+    """Calls on the kernel for few query rows, whole and in key ranges."""
+    _compare_with_64_bits(B, L, Hq, Hkv, n_class, M, W, R, positions, few=True, alpha=0.75)
+
+
+@pytest.mark.parametrize(
+    "B, L, Hq, Hkv, n_class, M, W, R, spread, imp_scale",
+    [
+        (1, 8300, 1, 1, 16, 16, 1, 128, 1.0, 0.0),       # 256 samples of one row: the largest ranked inside the kernel
+        (1, 14000, 2, 2, 16, 17, 2, 20, 1.0, 0.0),       # 272: ranked by the launch in front; narrow regions
+        (1, 8300, 6, 2, 16, 12, 5, 100, 1.0, 0.0),       # 15 rows per sample: samples straddle row tiles
+        (3, 3000, 8, 8, 16, 4, 8, 128, 1.0, 0.0),        # several sequences
+        (270, 180, 4, 1, 1, 2, 64, 16, 1.0, 0.0),        # more sequences than one launch plans
+        (1, 3000, 4, 1, 4, 4, 16, 128, 40.0, 0.0),       # logits of hundreds: the reference moves often
+        (1, 3000, 4, 1, 4, 4, 16, 128, 1.0, 0.5),        # a caller's logit scale
+        (1, 500, 8, 1, 16, 40, 64, 128, 1.0, 0.0),       # 1280 items: several per thread of the plan, past the table's LDS
+        (1, 3000, 1, 1, 64, 64, 1, 64, 1.0, 0.0),        # the most samples of a sequence
+    ])
+def test_importance_packed_rows(B, L, Hq, Hkv, n_class, M, W, R, spread, imp_scale):
+    """Calls on the kernel that packs the rows, where its packing, ranking and plan have their edges."""
+    n = n_class * M
+    positions = [L - 1, 0, L // 3, L // 3][: min(n, 4)]
+    _compare_with_64_bits(B, L, Hq, Hkv, n_class, M, W, R, positions, few=False, spread=spread, imp_scale=imp_scale)
+
+
+def test_importance_ranks_positions_beyond_19_bits():
+    """A sequence of more than 2^19 tokens: the sort keys leave out the lowest bit of a position, so neighbours
+    tie and an item's length counts from the later one."""
+    L = 600001
+    positions = [L - 1, L - 2, L - 10, 524288, 524289, 524287, 300, 64 * 9000 + 55]
+    _compare_with_64_bits(1, L, 1, 1, 1, 8, 64, 128, positions, few=False)
