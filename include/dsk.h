@@ -295,8 +295,10 @@ typedef struct dsk_attn_args {
  * full-KV baseline the method is compared with (Sec. 5, GPU Inference analysis, Figure 8), on
  * the same device and the same K/V layout, so that a decode step of the sparse path can be set
  * against it.  The heads of a GQA group share one pass over their K/V rows (every K/V byte is
- * read once per call when Hq/Hkv is 1, 2 or 4, and once per 4 heads of a wider group; small caches
- * whose ratio 4 does not divide are read once per 2 heads or per head instead).
+ * read once per call when Hq/Hkv is 1, 2 or 4, and once per 4 heads of a wider group; where 4 does
+ * not divide the ratio and the cache is small or in few ranges, once per 2 heads or per head).
+ * dsk_dense_attn_workspace_bytes does not depend on total_tokens: one workspace serves a cache that
+ * grows within max_seqlen.
  * bf16 inputs, fp32 accumulation, split over tokens with an online-softmax merge in a fixed
  * order.  A sequence of length 0 gets out = 0 and lse = -inf.
  * ---------------------------------------------------------------------------------------- */

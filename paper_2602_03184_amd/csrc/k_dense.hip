@@ -13,6 +13,12 @@ namespace dsk {
 constexpr int kDenseWaves = 4;
 constexpr int kDenseThreads = kDenseWaves * DSK_WAVE;
 constexpr int kDenseStep = kDenseWaves * 32;              // token ranges are multiples of this
+// K and V that together exceed the 256 MB memory-side cache by an eighth are hardly found there again by the next step,
+// so they are read past it.  8 / 8 heads: 264 MB 51.5 us through it, 55.7 past it, 288 MB 60.3 / 59.0, 320 MB 68.9 / 64.5,
+// 512 MB 106 / 96; 32 / 8 heads: 256 MB 49.6 / 51.2, 288 MB 58.3 / 56.5, 512 MB 96.4 / 90.9.  Not where the passes of a
+// group wider than the tile share the rows.  (The sparse step's summaries and rows are smaller: streaming them gains 3
+// to 8 % on caches that are cold, and loses 6 to 14 % where steps follow each other on one cache.)
+constexpr int64_t kDenseStreamBytes = 288ll << 20;
 
 template <int GT, int NS, bool STREAM>
 __global__ __launch_bounds__(kDenseThreads) void dense_attn_kernel(
@@ -134,36 +140,68 @@ __global__ __launch_bounds__(kDenseThreads) void dense_attn_kernel(
   }
 }
 
+// tokens that a call can read per KV head: total_tokens may be the capacity of a buffer
+static int64_t dense_tokens(const dsk_dense_attn_args& a) {
+  const int64_t most = (int64_t)a.B * a.max_seqlen;
+  return most < a.total_tokens ? most : a.total_tokens;
+}
+static int64_t dense_kv_bytes(const dsk_dense_attn_args& a) { return dense_tokens(a) * a.Hkv * (4 * DSK_HEAD_DIM); }
+
 DenseWs dense_ws_layout(const dsk_dense_attn_args& a) {
-  DenseWs ws;
+  struct Split {
+    int64_t passes, tps, nsplit;   // passes over a (sequence, KV head)'s rows; token ranges of a sequence
+    int64_t wgs, reads;            // workgroups; passes of a range that find its rows in no other one's L2
+  };
   const int G = a.Hq / a.Hkv;
-  // Heads folded per pass over the rows.  A width that 4 does not divide is cut into tiles of 4 all the same
-  // where the rows are many (the last pass repeats a head): every pass less is a read of K and V less --
-  // 28 / 4 heads, four sequences of 16K to 33K tokens 208 -> 82 us, 40 / 8 250 -> 141, 24 / 8 178 -> 87,
-  // 48 / 8 181 -> 141.  Below, the smaller tiles' workgroups and fewer repeated heads win: 24 / 8 at 16K tokens
-  // (64 MB) 18.8 against 20.2 us, at 8K 13.3 against 15.5; 48 / 8 at 16K 22.7 against 25.6, at 60K (246 MB) even.
-  const int64_t row_bytes = (int64_t)a.total_tokens * a.Hkv * (4 * DSK_HEAD_DIM);
-  const bool tiles_of_4 = G % 4 == 0 || (G > 2 && row_bytes >= (G % 2 ? 64ll << 20 : 256ll << 20));
-  ws.group_tile = tiles_of_4 ? 4 : (G % 2 == 0 ? 2 : 1);
-  const int64_t passes = (int64_t)a.B * a.Hkv * ((G + ws.group_tile - 1) / ws.group_tile);
   // about 4096 workgroups (16 per CU) when the cache is long enough, 128 tokens at least each;
   // at most kDenseMaxSplit ranges per sequence, since the merge runs one workgroup per head and
   // its time grows with the partials it reads (measured: 32 beats 16, 24, 64, 128 and 256 at
   // batch 1 with 32K and 128K tokens)
   constexpr int64_t kDenseMaxSplit = 32;
-  int64_t want_split = (4096 + passes - 1) / passes;
-  if (want_split < 1) want_split = 1;
-  if (want_split > kDenseMaxSplit) want_split = kDenseMaxSplit;
-  int64_t tps = ((int64_t)a.max_seqlen + want_split - 1) / want_split;
-  tps = (tps + kDenseStep - 1) / kDenseStep * kDenseStep;
-  if (tps < kDenseStep) tps = kDenseStep;
-  ws.tokens_per_split = (int)tps;
-  ws.nsplit = (int)(((int64_t)a.max_seqlen + tps - 1) / tps);
-  if (ws.nsplit < 1) ws.nsplit = 1;
-  const size_t n = (size_t)a.B * a.Hq * ws.nsplit;
+  auto split_of = [&](int tile) {
+    Split s;
+    s.passes = (G + tile - 1) / tile;
+    const int64_t heads = (int64_t)a.B * a.Hkv;
+    int64_t want_split = (4096 + heads * s.passes - 1) / (heads * s.passes);
+    if (want_split < 1) want_split = 1;
+    if (want_split > kDenseMaxSplit) want_split = kDenseMaxSplit;
+    s.tps = ((int64_t)a.max_seqlen + want_split - 1) / want_split;
+    s.tps = (s.tps + kDenseStep - 1) / kDenseStep * kDenseStep;
+    if (s.tps < kDenseStep) s.tps = kDenseStep;
+    s.nsplit = ((int64_t)a.max_seqlen + s.tps - 1) / s.tps;
+    if (s.nsplit < 1) s.nsplit = 1;
+    s.wgs = heads * s.passes * s.nsplit;
+    // workgroups go to the 8 XCDs in turn, ranges fastest: the passes of a range meet on 8 / gcd(nsplit, 8) of them
+    const int64_t xcds = s.nsplit % 8 == 0 ? 1 : (s.nsplit % 4 == 0 ? 2 : (s.nsplit % 2 == 0 ? 4 : 8));
+    s.reads = s.passes < xcds ? s.passes : xcds;
+    return s;
+  };
+  // Heads folded per pass over the rows.  A group width that 4 does not divide is cut into tiles of 4 all the same
+  // (the last pass repeats a head) where that saves reads of many rows: from 64 MB of K and V on, and while the
+  // fewer workgroups still occupy most of the chip, when the passes over a range share an L2 less with the smaller
+  // tile.  For odd widths, which are cut into single heads otherwise, also when the rows fill most of the
+  // memory-side cache, or when both tiles share alike and 7 passes become 2.  Smaller against tiles of 4:
+  //   28 / 4 heads, 4 sequences of 32K tokens (256 MB) 92 / 68 us, 24 / 8, 80K (320 MB) 83 / 61, 40 / 8, 4 x 20K (320 MB)
+  //   245 / 96, 28 / 4, 6 x 42K (497 MB) 217 / 156
+  //   and not 9 / 3 heads, 64K (96 MB, 96 workgroups with 4 heads) 36 / 43, 24 / 8, 4 x 8K (128 MB, L2 shared) 29 / 32,
+  //   40 / 8, 4 x 12K (192 MB, L2 shared) 53 / 56, 48 / 8, 64K (256 MB) 63 / 69, 12 / 2, 256K (250 MB) 100 / 142.
+  const int small = G % 4 == 0 ? 4 : (G % 2 == 0 ? 2 : 1);
+  const Split few = split_of(4), more = split_of(small);
+  const int64_t kv = dense_kv_bytes(a);
+  const bool saves = few.reads < more.reads ||
+                     (G % 2 == 1 && (kv >= 224ll << 20 || (few.reads == more.reads && 2 * more.passes >= 7 * few.passes)));
+  const bool tiles_of_4 = small == 4 || (G > 2 && kv >= 64ll << 20 && few.wgs >= 180 && saves);
+  const Split& use = tiles_of_4 ? few : more;
+  DenseWs ws;
+  ws.group_tile = tiles_of_4 ? 4 : small;
+  ws.tokens_per_split = (int)use.tps;
+  ws.nsplit = (int)use.nsplit;
+  // The size does not follow the choice: a workspace made for the longest sequences serves a cache that grows.
+  const size_t heads = (size_t)a.B * a.Hq, n = heads * ws.nsplit;
+  const size_t most = heads * (size_t)(few.nsplit > more.nsplit ? few.nsplit : more.nsplit);
   ws.part_ml = 0;
   ws.part_acc = align_up(n * sizeof(float2));
-  ws.total = ws.part_acc + align_up(n * DSK_HEAD_DIM * sizeof(float));
+  ws.total = align_up(most * sizeof(float2)) + align_up(most * DSK_HEAD_DIM * sizeof(float));
   return ws;
 }
 
@@ -184,13 +222,7 @@ hipError_t launch_dense_attn(const dsk_dense_attn_args& a, const DenseWs& ws, hi
       static_cast<uint16_t*>(a.out_bf16), a.lse
   // 32-row tiles: 16- and 8-row tiles raise occupancy but were measured slower (the per-tile
   // rescale of four heads' states is vector-ALU work the kernel has little room for)
-  // K and V that together exceed the 256 MB memory-side cache are not found there again by the next step, so
-  // they are read past it (128K tokens, 8 heads, 537 MB: 95.5 -> 91.0 us for the call, 5.6 -> 5.9 TB/s).  Not
-  // where the passes of a group wider than the tile share the rows.  (The sparse step's summaries and rows
-  // are smaller: streaming them gains 3 to 8 % on caches that are cold, and loses 6 to 14 % where steps follow
-  // each other on one cache.)
-  constexpr int64_t kStreamCacheBytes = 256ll << 20;
-  const bool stream = tiles_g == 1 && (int64_t)a.total_tokens * a.Hkv * (4 * DSK_HEAD_DIM) >= kStreamCacheBytes;
+  const bool stream = tiles_g == 1 && dense_kv_bytes(a) >= kDenseStreamBytes;
 #define DSK_DENSE_LAUNCH(gt)                                                                              \
   do {                                                                                                    \
     if (stream) dense_attn_kernel<gt, 8, true><<<grid, dim3(kDenseThreads), 0, st>>>(DSK_DENSE_ARGS);      \

@@ -283,3 +283,17 @@ def test_binding_never_imports_the_oracle(dsk):
                    if "paper_2602_03184_amd" in (getattr(sys.modules[m], "__package__", "") or ""))
     src = open(os.path.join(ROOT, "paper_2602_03184_amd", "binding.py")).read()
     assert "oracle" not in src.replace("no CPU fallback", "")
+
+
+@pytest.mark.parametrize("Hq, Hkv, B", [(28, 4, 8), (24, 8, 8), (40, 8, 6), (48, 8, 16), (32, 8, 4), (7, 7, 3)])
+def test_dense_workspace_serves_a_cache_that_grows(dsk, Hq, Hkv, B):
+    """The workspace follows B, the heads and max_seqlen alone: the tokens in the cache grow from step to step, and a
+    kept workspace has to do for all of them."""
+    a = dsk.dsk_dense_attn_args()
+    a.struct_size = C.sizeof(a)
+    a.B, a.Hq, a.Hkv, a.D, a.max_seqlen = B, Hq, Hkv, 128, 16384
+    sizes = set()
+    for total in (1, 1000, 16384, 16384 * B, 1 << 20, 1 << 24):
+        a.total_tokens = total
+        sizes.add(dsk.dsk_dense_attn_workspace_bytes(a))
+    assert len(sizes) == 1 and 0 not in sizes

@@ -174,10 +174,10 @@ def test_token_major_padded_layout_gives_identical_results():
         assert a.shape == b_.shape and torch.equal(a, b_)
 
 
-@pytest.mark.parametrize("Hq, Hkv", [(3, 1), (5, 1), (7, 1), (24, 4)])
+@pytest.mark.parametrize("Hq, Hkv", [(3, 1), (5, 1), (7, 1), (24, 4), (9, 3)])
 def test_dense_large_cache_group_widths_that_4_does_not_divide(Hq, Hkv):
-    """From 64 MB (odd widths) or 256 MB of K and V on, such groups run in tiles of 4 heads whose last tile
-    repeats a head."""
+    """From 64 MB of K and V on, such groups run in tiles of 4 heads whose last tile repeats a head, if the
+    workgroups are enough (not on one KV head with 3 query heads)."""
     import paper_2602_03184_amd as dsk
     lens = [70001, 0, 60031, 33, 1100]
     total = sum(lens)
@@ -203,3 +203,20 @@ def test_dense_large_cache_group_widths_that_4_does_not_divide(Hq, Hkv):
         # fp32 logits, exponentials and sums: a few units of 2^-24 each, far below the bar of bf16 inputs
         assert float((att.out[s].double() - want).norm() / want.norm()) <= 1e-5
         assert float((att.lse[s].double() - torch.logsumexp(z, 1)).abs().max()) <= 1e-5
+
+
+def test_dense_does_not_depend_on_the_room_behind_the_sequences():
+    """total_tokens may be the capacity of the buffers: the split of the work, and with it every bit of the result,
+    follows the tokens that the sequences can have."""
+    dsk = _dsk()
+    B, Hq, Hkv, n, room = 8, 28, 4, 4095, 65536
+    g = torch.Generator(device="cuda")
+    g.manual_seed(3)
+    K = torch.randn(Hkv, room, 128, generator=g, device="cuda").bfloat16()
+    V = torch.randn(Hkv, room, 128, generator=g, device="cuda").bfloat16()
+    q = torch.randn(B, Hq, 128, generator=g, device="cuda").bfloat16()
+    cu = torch.arange(0, (B + 1) * n, n, dtype=torch.int32, device="cuda")
+    a = dsk.dense_decode_attn(q, K[:, : B * n], V[:, : B * n], cu, n)
+    b = dsk.dense_decode_attn(q, K, V, cu, n)
+    torch.cuda.synchronize()
+    assert torch.equal(a.out, b.out) and torch.equal(a.lse, b.lse)
