@@ -15,6 +15,11 @@ static bool geometry_ok(int B, int Hq, int Hkv, int D) {
   return B >= 1 && Hq >= 1 && Hkv >= 1 && Hq % Hkv == 0 && D == DSK_HEAD_DIM && B <= 65535 && Hq <= 65535;
 }
 
+// classes, samples per class and window of stage IMPORTANCE
+static bool importance_args_ok(const dsk_compress_args& a) {
+  return a.n_class >= 1 && a.n_class <= DSK_MAX_CLASSES && a.M >= 1 && a.M <= kMaxSamplesPerClass && a.W >= 1 && a.W <= 64;
+}
+
 CompressWs compress_ws_layout(const dsk_compress_args& a) {
   CompressWs ws;
   ws.tiles_per_seq = (a.max_seqlen + kSegTile - 1) / kSegTile;
@@ -43,9 +48,11 @@ CompressWs compress_ws_layout(const dsk_compress_args& a) {
     ws.jump_stride = (a.total_tokens + 15) / 16 * 16;
   }
   ws.seg_jump = off;   off += align_up((size_t)ws.jump_levels * ws.jump_stride * sizeof(uint16_t) + 32);
-  ws.imp_plan = ws.imp_part = off;
-  if (a.n_class > 0 && a.M > 0) {
-    const ImpLayout l = importance_layout(a.B, a.n_class * a.M, a.W > 0 ? a.W : 1, a.Hq, a.Hkv);
+  // Stage IMPORTANCE alone uses what follows.  The query counts it whatever the stages, since the struct may be
+  // used again for other stages, unless the arguments are none that the stage takes.
+  ws.imp_plan = ws.imp_part = ws.without_imp = off;
+  if (importance_args_ok(a) && geometry_ok(a.B, a.Hq, a.Hkv, a.D)) {
+    const ImpLayout l = importance_layout(a.B, a.n_class * a.M, a.W, a.Hq, a.Hkv);
     off += align_up(l.plan_ints * sizeof(int32_t));
     ws.imp_part = off;   off += align_up(l.part_rows * sizeof(float4));
   }
@@ -84,7 +91,7 @@ static dsk_status validate_compress(const dsk_compress_args* a) {
   if (st_imp) {
     if (a->samp_pos == nullptr || a->qwin == nullptr || a->class_weight_q == nullptr || a->K == nullptr)
       return DSK_ERR_NULL;
-    if (a->M < 1 || a->M > kMaxSamplesPerClass || a->W < 1 || a->W > 64 || a->R < 1) return DSK_ERR_PARAM;
+    if (!importance_args_ok(*a) || a->R < 1) return DSK_ERR_PARAM;
     if (!(a->alpha_imp >= 0.0f) || !(a->alpha_imp <= 1.0e6f) || !(a->imp_scale >= 0.0f)) return DSK_ERR_PARAM;
     if (!aligned16(a->qwin)) return DSK_ERR_ALIGN;
     if (a->samp_score_sum != nullptr && a->imp_layers < 1) return DSK_ERR_PARAM;
@@ -123,7 +130,7 @@ static dsk_status validate_compress(const dsk_compress_args* a) {
   }
   const CompressWs ws = compress_ws_layout(*a);
   if (st_cand || st_imp || st_seg) {
-    if (a->workspace == nullptr || a->workspace_bytes < ws.total) return DSK_ERR_WORKSPACE;
+    if (a->workspace == nullptr || a->workspace_bytes < (st_imp ? ws.total : ws.without_imp)) return DSK_ERR_WORKSPACE;
     if (!aligned256(a->workspace)) return DSK_ERR_ALIGN;
   }
   return DSK_OK;

@@ -30,6 +30,7 @@ struct CompressWs {
   size_t seg_jump;    // u16 [jump_levels][jump_stride]  position in the tile 2, 4, 8 .. chunks after each token
   size_t imp_plan;    // i32 [ImpLayout::plan_ints]   plan of the importance launch
   size_t imp_part;    // float4 [ImpLayout::part_rows] softmax statistics of a piece's query rows
+  size_t without_imp; // bytes that the other stages need
   size_t total;
   int tiles_per_seq;  // ceil(max_seqlen / kSegTile)
   int map_row;        // min(C + delta, kSegTile)
@@ -50,7 +51,7 @@ constexpr int kImpFewRanges = 32;      // of which there are at most so many (lo
 struct ImpLayout {
   int seqs;            // sequences per launch
   int items;           // upper bound of the groups of kImpRows query rows of one KV head in a launch
-  size_t plan_ints, part_rows;
+  size_t plan_ints, part_rows;   // space; it does not shrink when B, the samples or W grow
 };
 ImpLayout importance_layout(int B, int n_samp, int W, int Hq, int Hkv);
 

@@ -1017,8 +1017,13 @@ ImpLayout importance_layout(int B, int n_samp, int W, int Hq, int Hkv) {
   if (seqs > B) seqs = B;
   l.seqs = (int)seqs;
   l.items = (int)(seqs * per_seq);
-  l.plan_ints = (size_t)4 + 2 * l.seqs + 1 + l.items + 1 + 3 * (size_t)l.seqs * n_samp;
-  l.part_rows = ((size_t)kImpPieces + (size_t)l.items * Hkv) * kImpRows;
+  // sequences and items of a launch at most, for these arguments and for smaller ones (fewer rows per sequence can
+  // mean more sequences in a launch, and more items)
+  const int64_t most_seqs = B < kImpMaxSeqs ? B : kImpMaxSeqs;
+  int64_t most_items = kImpMaxItems / Hkv > per_seq ? kImpMaxItems / Hkv : per_seq;
+  if (most_items > most_seqs * per_seq) most_items = most_seqs * per_seq;
+  l.plan_ints = (size_t)(4 + 2 * most_seqs + 1 + most_items + 1 + 3 * most_seqs * n_samp);
+  l.part_rows = (size_t)(kImpPieces + most_items * Hkv) * kImpRows;
   return l;
 }
 

@@ -297,3 +297,57 @@ def test_dense_workspace_serves_a_cache_that_grows(dsk, Hq, Hkv, B):
         a.total_tokens = total
         sizes.add(dsk.dsk_dense_attn_workspace_bytes(a))
     assert len(sizes) == 1 and 0 not in sizes
+
+
+def _compress_args(dsk, **kw):
+    """Arguments that pass every check up to the workspace's (its pointer is misaligned, so nothing is launched)."""
+    a = dsk.dsk_compress_args()
+    a.struct_size = C.sizeof(a)
+    a.B, a.Hq, a.Hkv, a.D, a.total_tokens, a.max_seqlen = 4, 32, 8, 128, 20000, 8000
+    a.k_stride_tok, a.k_stride_head = 128, 128 * 20000
+    a.n_class, a.M, a.W, a.R, a.alpha_imp = 16, 8, 8, 128, 1.0
+    a.C, a.delta, a.alpha_num, a.alpha_den, a.b = 32, 16, 5, 10, 16
+    a.max_blocks_total, a.max_cand_total = 2000, 20000
+    for f in ("cu_seqlens", "K", "token_ids", "delim_ids", "cand_pos", "cand_class", "cand_cu", "samp_pos", "qwin",
+              "class_weight_q", "block_start", "cu_blocks", "slot_base", "ksum"):
+        setattr(a, f, 4096)
+    a.workspace = 4096 + 8
+    for k, v in kw.items():
+        setattr(a, k, v)
+    return a
+
+
+def test_compress_needs_the_importance_space_for_that_stage_only(dsk):
+    """The statistics of stage IMPORTANCE are asked of the calls that run it: sampling takes windows that the stage does
+    not, and a segmentation reads neither M nor W."""
+    query = dsk.dsk_compress_workspace_bytes
+    base = query(_compress_args(dsk, M=0))
+    for kw in (dict(stages=dsk.DSK_STAGE_CANDIDATES), dict(stages=dsk.DSK_STAGE_CANDIDATES, W=1024),
+               dict(stages=dsk.DSK_STAGE_SEGMENT, M=1 << 26, W=1 << 30, n_class=64),
+               dict(stages=dsk.DSK_STAGE_SEGMENT, M=-5, W=-7)):
+        a = _compress_args(dsk, workspace_bytes=base, **kw)
+        assert dsk.dsk_compress(a, 0, check=False) == dsk.DSK_ERR_ALIGN, kw      # the size was enough
+        a.workspace_bytes = base - 1
+        assert dsk.dsk_compress(a, 0, check=False) == dsk.DSK_ERR_WORKSPACE, kw
+    assert query(_compress_args(dsk, stages=dsk.DSK_STAGE_CANDIDATES, W=1024)) == base
+    assert query(_compress_args(dsk, stages=dsk.DSK_STAGE_SEGMENT, M=1 << 26, n_class=64)) == base
+    # one workspace for a struct whose stages are run one by one
+    full = query(_compress_args(dsk, stages=dsk.DSK_STAGE_CANDIDATES))
+    assert full > base and full == query(_compress_args(dsk, stages=dsk.DSK_STAGE_IMPORTANCE))
+    a = _compress_args(dsk, stages=dsk.DSK_STAGE_IMPORTANCE, workspace_bytes=full)
+    assert dsk.dsk_compress(a, 0, check=False) == dsk.DSK_ERR_ALIGN
+    a.workspace_bytes = full - 1
+    assert dsk.dsk_compress(a, 0, check=False) == dsk.DSK_ERR_WORKSPACE
+
+
+@pytest.mark.parametrize("Hq, Hkv", [(32, 8), (8, 8), (28, 4), (1, 1)])
+def test_compress_workspace_does_for_smaller_calls(dsk, Hq, Hkv):
+    """A workspace made for the largest batch, sample count and window serves the smaller ones."""
+    def size(B, M, W):
+        return dsk.dsk_compress_workspace_bytes(_compress_args(dsk, Hq=Hq, Hkv=Hkv, B=B, M=M, W=W, max_seqlen=5))
+    for B in (1, 7, 40, 300):
+        for M in (1, 5, 8, 13):
+            for W in range(1, 65):
+                assert size(B, M, W) <= min(size(B + 1, M, W), size(B, M + 1, W))
+                if W < 64:
+                    assert size(B, M, W) <= size(B, M, W + 1), (B, M, W)
