@@ -109,14 +109,18 @@ __device__ __forceinline__ bool append_segment_one(
       const int lo = s_e - delta;                          // > s_c because delta < C
       const int hi = s_e + delta < len_new ? s_e + delta : len_new;
       unsigned long long best = 0ull;                      // 0 = nothing offered
-      for (int e = lo + lane; e <= hi; e += DSK_WAVE) {
+      for (int e0 = lo; e0 <= hi; e0 += DSK_WAVE) {        // all lanes stay: the class ids are read across them
+        const int e = e0 + lane;
+        const bool in = e <= hi;
         int w = -1;                                        // the delimiter at e-1 offers the boundary e
         if (windowed) {
-          w = offered[e - 1 - w0];
+          if (in) w = offered[e - 1 - w0];
         } else {
-          const int tok = token_ids[e - 1];
-          for (int c = n_class - 1; c >= 0; --c)
-            if (tok == __builtin_amdgcn_readlane(my_id, c)) w = __builtin_amdgcn_readlane(my_weight, c);
+          const int tok = token_ids[(in ? e : hi) - 1];
+          for (int c = n_class - 1; c >= 0; --c) {
+            const int id = __builtin_amdgcn_readlane(my_id, c), wc = __builtin_amdgcn_readlane(my_weight, c);
+            w = in && tok == id ? wc : w;
+          }
         }
         if (w >= 0) {
           const int dist = e > s_e ? e - s_e : s_e - e;

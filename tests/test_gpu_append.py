@@ -204,3 +204,15 @@ def test_append_token_window_edges(C, delta, share, a_num, steps):
     q = _Seq(K, K, tok, [0, 1, 2], [10, 10, 7] if share < 1.0 else [10, 10, 10], L0, C, delta, a_num, 10, 16)
     for n in steps:
         q.check_tables(*q.append(n))
+
+
+@pytest.mark.parametrize("n_class, delta", [(16, 2), (64, 0), (64, 4), (64, 31), (20, 9)])
+def test_append_more_classes_than_searched_positions(n_class, delta):
+    """More new tokens than the window holds, so that the search classifies them itself, with fewer positions in a
+    search range than there are classes: the ids and weights of the lanes without a position count too."""
+    r = np.random.default_rng(n_class + delta)
+    L0, new = 700, 1500
+    K = r.integers(0x3F00, 0x4000, size=(1, L0 + new, 128)).astype(np.uint16)
+    tok = np.where(r.random(L0 + new) < 0.5, r.integers(0, n_class, size=L0 + new), 9999)
+    q = _Seq(K, K, tok, np.arange(n_class), r.integers(0, 11, size=n_class).astype(np.uint8), L0, 32, delta, 7, 10, 16)
+    q.check_tables(*q.append(new))
