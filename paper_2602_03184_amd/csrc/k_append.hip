@@ -4,6 +4,8 @@
 // lanes score the positions of the search range (token id -> delimiter class -> integer score)
 // and a wave-wide maximum of packed (score, smaller-e-wins) keys picks the boundary.  The
 // summaries of the rewritten chunks are then recomputed by the summaries kernel on that range.
+#include <type_traits>
+
 #include "dsk_common.hpp"
 #include "dsk_internal.hpp"
 
@@ -29,14 +31,14 @@ constexpr int kAppendWindow = 1024;
 //
 // The update is a chain of memory latencies, so everything whose address is known goes out together: the
 // caller's parameters, then here the last 64 entries of both tables and the tokens that the open chunks
-// search (two round trips in front of the walk instead of seven: 5.2 -> 4.3 us for a token appended to each of
+// search (two round trips in front of the walk instead of seven: 5.3 -> 4.8 us for a token appended to each of
 // eight sequences).
 __device__ __forceinline__ bool append_segment_one(
     const int32_t* __restrict__ token_ids, int my_id, int my_weight, int n_class, int nblk, int len_old, int len_new,
     int C, int delta, int a_num, int a_den, int b, int cap, int32_t* __restrict__ block_start,
     int32_t* __restrict__ n_blocks, int32_t* __restrict__ slot_base, int blk_base, int32_t* __restrict__ range,
     int32_t* __restrict__ first_recomputed, int32_t* __restrict__ first_stale_slot, int32_t* dev_status) {
-  __shared__ int16_t offered[kAppendWindow];                // weight of the delimiter at a token, -1 = no delimiter
+  __shared__ int32_t window[kAppendWindow];                 // token ids; from the first search on offered weights
   const int lane = threadIdx.x;
   if (nblk < 0) nblk = 0;
   if (nblk > cap) nblk = cap;
@@ -47,28 +49,55 @@ __device__ __forceinline__ bool append_segment_one(
   // len_old - 2 * delta
   const int w0 = len_old - 2 * delta > 0 ? len_old - 2 * delta : 0;
   const bool windowed = (int64_t)len_new - w0 <= kAppendWindow;
-  if (windowed) {
-    for (int t0 = w0; t0 < len_new; t0 += 4 * DSK_WAVE) {
-      int tok[4];
+  const int n_win = windowed ? len_new - w0 : 0;
+  for (int t0 = 0; t0 < n_win; t0 += 4 * DSK_WAVE) {
+    int tok[4];
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int t = t0 + r * DSK_WAVE + lane;
-        tok[r] = token_ids[t < len_new ? t : len_new - 1];
-      }
-      int w[4] = {-1, -1, -1, -1};
-      for (int c = n_class - 1; c >= 0; --c) {             // the lowest class index wins
-        const int id = __builtin_amdgcn_readlane(my_id, c), wc = __builtin_amdgcn_readlane(my_weight, c);
+    for (int r = 0; r < 4; ++r) {
+      const int t = t0 + r * DSK_WAVE + lane;
+      tok[r] = token_ids[w0 + (t < n_win ? t : n_win - 1)];
+    }
 #pragma unroll
-        for (int r = 0; r < 4; ++r) w[r] = tok[r] == id ? wc : w[r];
-      }
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int t = t0 + r * DSK_WAVE + lane;
-        if (t < len_new) offered[t - w0] = (int16_t)w[r];
-      }
+    for (int r = 0; r < 4; ++r) {
+      const int t = t0 + r * DSK_WAVE + lane;
+      if (t < n_win) window[t] = tok[r];
     }
   }
   __syncthreads();
+  // Token id -> weight of the delimiter, -1 = none, for every token of the window, several tokens a lane side by side.
+  // Left until a chunk searches, since often none does: a token appended at C = 256, delta = 128 with 64 classes takes
+  // 13.1 us with the rewinds of its table, 21.1 classified ahead; at C = 600, delta = 500, where several chunks
+  // search the same tokens, 34.9 against 56.7 classified by every search.
+  bool classified = false;
+  auto classify_rows = [&](auto rows, int t0) {              // rows * 64 tokens side by side
+    constexpr int kRows = decltype(rows)::value;
+    int tok[kRows], w[kRows];
+#pragma unroll
+    for (int r = 0; r < kRows; ++r) {
+      const int t = t0 + r * DSK_WAVE + lane;
+      tok[r] = window[t < n_win ? t : n_win - 1];
+      w[r] = -1;
+    }
+    for (int c = n_class - 1; c >= 0; --c) {               // the lowest class index wins
+      const int id = __builtin_amdgcn_readlane(my_id, c), wc = __builtin_amdgcn_readlane(my_weight, c);
+#pragma unroll
+      for (int r = 0; r < kRows; ++r) w[r] = tok[r] == id ? wc : w[r];
+    }
+    __syncthreads();                                       // lanes past the end read another one's entry
+#pragma unroll
+    for (int r = 0; r < kRows; ++r) {
+      const int t = t0 + r * DSK_WAVE + lane;
+      if (t < n_win) window[t] = w[r];
+    }
+  };
+  auto classify = [&]() {
+    int t0 = 0;
+    for (; n_win - t0 > 2 * DSK_WAVE; t0 += 4 * DSK_WAVE) classify_rows(std::integral_constant<int, 4>{}, t0);
+    if (n_win - t0 > DSK_WAVE) classify_rows(std::integral_constant<int, 2>{}, t0);
+    else if (n_win > t0) classify_rows(std::integral_constant<int, 1>{}, t0);
+    __syncthreads();
+    classified = true;
+  };
 
   const int table_end = __builtin_amdgcn_readlane(bs, 0);
   if (table_end != len_old || first != 0) {                // not the table this call was sized for
@@ -109,12 +138,13 @@ __device__ __forceinline__ bool append_segment_one(
       const int lo = s_e - delta;                          // > s_c because delta < C
       const int hi = s_e + delta < len_new ? s_e + delta : len_new;
       unsigned long long best = 0ull;                      // 0 = nothing offered
+      if (windowed && !classified) classify();
       for (int e0 = lo; e0 <= hi; e0 += DSK_WAVE) {        // all lanes stay: the class ids are read across them
         const int e = e0 + lane;
         const bool in = e <= hi;
         int w = -1;                                        // the delimiter at e-1 offers the boundary e
         if (windowed) {
-          if (in) w = offered[e - 1 - w0];
+          if (in) w = window[e - 1 - w0];
         } else {
           const int tok = token_ids[(in ? e : hi) - 1];
           for (int c = n_class - 1; c >= 0; --c) {
