@@ -71,7 +71,7 @@ __device__ __forceinline__ float dot8_f32(const float (&q)[8], const float (&k)[
 // PADDED: group widths that are no power of two (and above 8): G is the width of a tile of the group's heads,
 // the real width `group` comes from the launch, blockIdx.y counts (KV head, tile), and the heads that a tile
 // does not have repeat its first one and are not written.  The products of this variant are single-precision
-// multiply-adds in channel order, so that its scores are those of the one-block-at-a-time kernel bit by bit.
+// multiply-adds in channel order, so that its scores are those of scores_kernel_wide_shared bit by bit.
 template <int G, bool GROUPMAX = false, bool PADDED = false>
 __global__ __launch_bounds__(kScoreThreads) void scores_kernel(
     const uint16_t* __restrict__ ksum, const uint16_t* __restrict__ q, const int32_t* __restrict__ cu_blocks,
@@ -242,10 +242,10 @@ __global__ __launch_bounds__(kScoreThreads) void scores_kernel(
 
 // one selection per KV head on groups of more than 8 heads: one block per half-wave step, q re-read per block
 // (it stays in the vector cache)
-__global__ __launch_bounds__(kScoreThreads) void scores_kernel_anyg(
+constexpr int kWideBlocks = 8;   // blocks of a half-wave, one after the other
+__global__ __launch_bounds__(kScoreThreads) void scores_kernel_wide_shared(
     const uint16_t* __restrict__ ksum, const uint16_t* __restrict__ q, const int32_t* __restrict__ cu_blocks,
-    int B, int Hq, int G, int cap, int stride, bool group_max, float* __restrict__ scores,
-    float* __restrict__ user) {
+    int B, int Hq, int G, int cap, int stride, float* __restrict__ scores, float* __restrict__ user) {
   const int hk = blockIdx.y;
   int nblk = cu_blocks[B];
   if (nblk > cap) nblk = cap;
@@ -253,10 +253,10 @@ __global__ __launch_bounds__(kScoreThreads) void scores_kernel_anyg(
   const int c = threadIdx.x & 31;
   const bool is_max = c >= 16;
   const int d0 = (c & 15) * 8;
-  const int first = (blockIdx.x * kHalvesPerWg + half) * 8;
+  const int first = (blockIdx.x * kHalvesPerWg + half) * kWideBlocks;
   const uint16_t* kh = ksum + (int64_t)hk * cap * (2 * DSK_HEAD_DIM);
   int s = 0;
-  for (int it = 0; it < 8; ++it) {
+  for (int it = 0; it < kWideBlocks; ++it) {
     const int i = first + it;
     if (i >= nblk) break;
     while (s + 1 < B && cu_blocks[s + 1] <= i) ++s;
@@ -274,12 +274,8 @@ __global__ __launch_bounds__(kScoreThreads) void scores_kernel_anyg(
       acc = group16_sum(acc);
       acc += shfl_xor_f(acc, 16);
       best = fmaxf(best, acc);
-      if (c == 0 && !group_max) {
-        scores[(int64_t)(hk * G + g) * stride + i] = acc;
-        if (user) user[(int64_t)(hk * G + g) * cap + i] = acc;
-      }
     }
-    if (c == 0 && group_max) {
+    if (c == 0) {
       scores[(int64_t)hk * stride + i] = best;
       if (user) user[(int64_t)hk * cap + i] = best;
     }
@@ -291,11 +287,12 @@ hipError_t launch_scores(const dsk_select_args& a, float* scores, int stride, hi
   const int G = a.Hq / a.Hkv;
   const bool shared = (a.flags & DSK_SELECT_SHARED_BY_KV_GROUP) != 0 && G > 1;
   // group widths that are no power of two or above 8: tiles of 4 (G = 3) or 8 heads (decode step at 20K tokens
-  // against the one-block-at-a-time kernel: 28 / 4 heads 35.4 -> 19.1 us, 40 / 8 31.3 -> 19.8, 16 / 1 61 -> 23).
+  // against one block at a time: 28 / 4 heads 35.4 -> 19.1 us, 40 / 8 31.3 -> 19.8, 16 / 1 61 -> 23).
   // The maximum over a group needs all of its heads in one tile.
   const bool padded = G != 1 && G != 2 && G != 4 && G != 8 && (!shared || G <= 8);
   const int width = padded ? (G == 3 ? 4 : 8) : G;
-  const int per_wg = kHalvesPerWg * score_blocks_per_half(width);
+  const bool wide_shared = shared && G > 8;
+  const int per_wg = kHalvesPerWg * (wide_shared ? kWideBlocks : score_blocks_per_half(width));
   const int bound = a.max_blocks_used > 0 ? a.max_blocks_used : a.max_blocks_total;
   const dim3 grid((unsigned)((bound + per_wg - 1) / per_wg), (unsigned)(a.Hkv * (padded ? (G + width - 1) / width : 1)));
   const dim3 block(kScoreThreads);
@@ -309,6 +306,11 @@ hipError_t launch_scores(const dsk_select_args& a, float* scores, int stride, hi
     else scores_kernel<8, false, true><<<grid, block, 0, st>>>(DSK_SCORE_ARGS);
     return hipGetLastError();
   }
+  if (wide_shared) {
+    scores_kernel_wide_shared<<<grid, block, 0, st>>>(ksum, q, a.cu_blocks, a.B, a.Hq, G, a.max_blocks_total, stride, scores,
+                                                      a.scores);
+    return hipGetLastError();
+  }
   switch (shared ? -G : G) {
     case 1: scores_kernel<1><<<grid, block, 0, st>>>(DSK_SCORE_ARGS); break;
     case 2: scores_kernel<2><<<grid, block, 0, st>>>(DSK_SCORE_ARGS); break;
@@ -317,9 +319,6 @@ hipError_t launch_scores(const dsk_select_args& a, float* scores, int stride, hi
     case -2: scores_kernel<2, true><<<grid, block, 0, st>>>(DSK_SCORE_ARGS); break;
     case -4: scores_kernel<4, true><<<grid, block, 0, st>>>(DSK_SCORE_ARGS); break;
     case -8: scores_kernel<8, true><<<grid, block, 0, st>>>(DSK_SCORE_ARGS); break;
-    default:
-      scores_kernel_anyg<<<grid, block, 0, st>>>(ksum, q, a.cu_blocks, a.B, a.Hq, G, a.max_blocks_total, stride, shared,
-                                                 scores, a.scores);
   }
 #undef DSK_SCORE_ARGS
   return hipGetLastError();
