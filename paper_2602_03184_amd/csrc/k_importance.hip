@@ -608,10 +608,9 @@ template <int kThreads, int kSamples, bool SPLIT>
 __global__ __launch_bounds__(kThreads) void importance_few_kernel(
     const uint16_t* __restrict__ K, int64_t kst, int64_t ksh, const uint16_t* __restrict__ qwin,
     const int32_t* __restrict__ samp_pos, const int32_t* __restrict__ cu_seqlens, int n_samp, int ranges, int range_keys, int W,
-    int R, int Hq, int G, int Hkv, float alpha, float scale_log2, int B, float* __restrict__ imp_part, float4* __restrict__ part) {
+    int R, int Hq, int G, int Hkv, float alpha, float scale_log2, int B, double* __restrict__ imp_part, float4* __restrict__ part) {
   constexpr int kWaves = kThreads / DSK_WAVE;
   __shared__ RowStat sm_stat[kSamples][kWaves][32];
-  __shared__ float sm_val[kSamples][32];
   __shared__ __attribute__((aligned(16))) uint16_t sm_q[kSamples][32][kImpQRow];
   const int group = blockIdx.x;
   const int hk = blockIdx.y;
@@ -643,9 +642,8 @@ __global__ __launch_bounds__(kThreads) void importance_few_kernel(
   if (tile0 >= n_tiles) return;                             // uniform over the workgroup
   const int rows = W * G;                                   // query rows of one (sample, kv head)
   const uint16_t* Kh = K + (int64_t)hk * ksh + (int64_t)seq0 * kst + hf * 64;
-  float total[kSamples];
-#pragma unroll
-  for (int p = 0; p < kSamples; ++p) total[p] = 0.0f;
+  // of sample threadIdx / 32: the row values are near -alpha each, so 32-bit sums would round away a bit of the mean
+  double total = 0.0;
 
   for (int row0 = 0; row0 < rows; row0 += 32) {
     // Q^T operands of the group's samples -> LDS: row r of sample p is query row row0 + r (window
@@ -711,9 +709,7 @@ __global__ __launch_bounds__(kThreads) void importance_few_kernel(
           for (int r = 1; r < 16; ++r) amax = fmaxf(amax, acc[r]);
           const float mn = fmaxf(st[p].m, amax * scale_log2);
           const float f = __builtin_amdgcn_exp2f(st[p].m - mn);   // 0 while st.m is still -inf
-          float esum = 0.0f;
-#pragma unroll
-          for (int r = 0; r < 16; ++r) esum += __builtin_amdgcn_exp2f(fmaf(acc[r], scale_log2, -mn));
+          const float esum = imp_tile_sum(acc, scale_log2, mn);
           st[p].zt = fmaf(st[p].zt, f, esum);
           st[p].zd = fmaf(st[p].zd, f, esum);
           st[p].zo *= f;
@@ -763,7 +759,10 @@ __global__ __launch_bounds__(kThreads) void importance_few_kernel(
       RowStat a = sm_stat[p][0][col];
 #pragma unroll
       for (int wv = 1; wv < kWaves; ++wv) stat_merge(a, sm_stat[p][wv][col]);
-      sm_val[p][col] = row0 + col < rows && a.zt > 0.0f ? (a.zo - alpha * a.zd) / a.zt : 0.0f;
+      double v = row0 + col < rows && a.zt > 0.0f ? (a.zo - alpha * a.zd) / a.zt : 0.0f;
+#pragma unroll
+      for (int m = 1; m < 32; m <<= 1) v += __shfl_xor(v, m, DSK_WAVE);   // the sample's 32 rows, in a fixed order
+      total += v;
       if constexpr (SPLIT) {
         int j = 0, last = -1;
 #pragma unroll
@@ -775,31 +774,27 @@ __global__ __launch_bounds__(kThreads) void importance_few_kernel(
       }
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
-#pragma unroll
-      for (int p = 0; p < kSamples; ++p)
-        for (int c2 = 0; c2 < 32; ++c2) total[p] += sm_val[p][c2];   // fixed order
-    }
-    __syncthreads();
   }
-  if (threadIdx.x == 0) {
+  if (threadIdx.x < 32 * kSamples && col == 0) {
+    int j = 0, last = -1;
 #pragma unroll
-    for (int p = 0; p < kSamples; ++p)
-      if (last_key[p] >= 0 && (!SPLIT || (range == 0 && imp_few_ranges(last_key[p], ranges, range_keys) == 1)))
-        imp_part[((int64_t)s * n_samp + jn[p]) * Hkv + hk] = total[p];
+    for (int i = 0; i < kSamples; ++i)
+      if (i == (int)threadIdx.x >> 5) { j = jn[i]; last = last_key[i]; }
+    if (last >= 0 && (!SPLIT || (range == 0 && imp_few_ranges(last, ranges, range_keys) == 1)))
+      imp_part[((int64_t)s * n_samp + j) * Hkv + hk] = total;
   }
 }
 
-// what the finishing kernels end with, on the sum `st` of a sample's rows (thread m < M: the class's m-th
+// what the finishing kernels end with, on the sum of a sample's rows (thread m < M: the class's m-th
 // sample, have: its position is not -1): sample scores, class mean, class weight; sums in sample order
-__device__ __forceinline__ void imp_class_weight(float st, bool have, int c, int s, int n_class, int M, int n_rows,
+__device__ __forceinline__ void imp_class_weight(double sum_rows, bool have, int c, int s, int n_class, int M, int n_rows,
                                                  float alpha, uint8_t* class_weight_q, float* class_mean,
                                                  float* samp_score, float* samp_score_sum, int layers) {
   __shared__ float sm_score[kMaxSamplesPerClass];
   __shared__ int sm_have[kMaxSamplesPerClass];
   if ((int)threadIdx.x < M) {
     const int64_t js = ((int64_t)s * n_class + c) * M + threadIdx.x;
-    st /= (float)n_rows;
+    float st = (float)(sum_rows / n_rows);
     if (samp_score) samp_score[js] = have ? st : __builtin_nanf("");
     if (samp_score_sum != nullptr && have) {      // expectation over layers: this layer joins the running sum
       const float tot = samp_score_sum[js] + st;
@@ -829,12 +824,12 @@ __device__ __forceinline__ void imp_class_weight(float st, bool have, int c, int
 
 // grid: (class, sequence), one lane per sample (M <= 64): the samples that importance_few_kernel finished
 __global__ __launch_bounds__(DSK_WAVE) void importance_few_finalize_kernel(
-    const float* __restrict__ imp_part, const int32_t* __restrict__ samp_pos, const int32_t* __restrict__ cu_seqlens,
+    const double* __restrict__ imp_part, const int32_t* __restrict__ samp_pos, const int32_t* __restrict__ cu_seqlens,
     int n_class, int M, int Hkv, int G, int W, float alpha, uint8_t* __restrict__ class_weight_q,
     float* __restrict__ class_mean, float* __restrict__ samp_score, float* __restrict__ samp_score_sum, int layers) {
   const int c = blockIdx.x, s = blockIdx.y, m = threadIdx.x;
   const int seq0 = cu_seqlens[s], end = cu_seqlens[s + 1];
-  float st = 0.0f;
+  double st = 0.0;
   bool have = false;
   if (m < M) {
     const int64_t js = ((int64_t)s * n_class + c) * M + m;
@@ -843,8 +838,8 @@ __global__ __launch_bounds__(DSK_WAVE) void importance_few_finalize_kernel(
     if (have && tg >= seq0 && tg < end)           // a position outside the sequence counts with 0
       for (int hk = 0; hk < Hkv; ++hk) st += imp_part[js * Hkv + hk];
   }
-  imp_class_weight(st, have, c, s, n_class, M, G * Hkv * W, alpha, class_weight_q, class_mean, samp_score, samp_score_sum,
-                   layers);
+  imp_class_weight(st, have, c, s, n_class, M, G * Hkv * W, alpha, class_weight_q, class_mean, samp_score,
+                   samp_score_sum, layers);
 }
 
 constexpr int kImpFinThreads = 1024;
@@ -967,11 +962,11 @@ __global__ __launch_bounds__(kImpFinThreads) void importance_finalize_kernel(
 // grid: (class, sequence): the same behind importance_few_kernel with several key ranges
 constexpr int kImpFewWaves = 4;
 __global__ __launch_bounds__(kImpFewWaves * DSK_WAVE) void importance_few_merge_kernel(
-    const float* __restrict__ imp_part, const float4* __restrict__ part, const int32_t* __restrict__ samp_pos,
+    const double* __restrict__ imp_part, const float4* __restrict__ part, const int32_t* __restrict__ samp_pos,
     const int32_t* __restrict__ cu_seqlens, int ranges, int range_keys, int n_class, int M, int Hkv, int G, int W,
     float alpha, uint8_t* __restrict__ class_weight_q, float* __restrict__ class_mean, float* __restrict__ samp_score,
     float* __restrict__ samp_score_sum, int layers) {
-  __shared__ float sm_sum[kMaxSamplesPerClass * kImpFewWaves];
+  __shared__ double sm_sum[kMaxSamplesPerClass * kImpFewWaves];
   const int c = blockIdx.x, s = blockIdx.y;
   const int lane = threadIdx.x & (DSK_WAVE - 1);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / DSK_WAVE);
@@ -982,7 +977,7 @@ __global__ __launch_bounds__(kImpFewWaves * DSK_WAVE) void importance_few_merge_
   const int per_sample = M < kImpFewWaves ? kImpFewWaves / M : 1;   // wavefronts of one sample
   for (int m = wave / per_sample; m < M; m += kImpFewWaves / per_sample) {
     const int tg = samp_pos[js + m], t = tg - seq0, part_of = wave % per_sample;
-    float sum = 0.0f;
+    double sum = 0.0;
     if (tg >= 0 && t >= 0 && t < L) {             // a position outside the sequence counts with 0
       const int n_ranges = imp_few_ranges(t < L - 1 - W ? t + W : L - 1, ranges, range_keys);
       if (n_ranges == 1) {
@@ -996,11 +991,12 @@ __global__ __launch_bounds__(kImpFewWaves * DSK_WAVE) void importance_few_merge_
             1, part_of * DSK_WAVE + lane, per_sample * DSK_WAVE, n_rows, alpha);
       }
     }
-    sum = wave_sum(sum);
+#pragma unroll
+    for (int i = 1; i < DSK_WAVE; i <<= 1) sum += __shfl_xor(sum, i, DSK_WAVE);
     if (lane == 0) sm_sum[m * kImpFewWaves + part_of] = sum;
   }
   __syncthreads();
-  float st = 0.0f;
+  double st = 0.0;
   if ((int)threadIdx.x < M)
     for (int i = 0; i < per_sample; ++i) st += sm_sum[threadIdx.x * kImpFewWaves + i];
   imp_class_weight(st, have, c, s, n_class, M, G * Hkv * W, alpha, class_weight_q, class_mean, samp_score, samp_score_sum,
@@ -1058,7 +1054,7 @@ static ImpFew importance_few(const dsk_compress_args& a, const ImpLayout& l) {
   // spread over it, 8 / 8 heads: 859 us in one range, 56 in 32; 40 samples in each of 3 sequences of 5.3K, 240
   // workgroups: 53 against 62 in 2), and as far as their statistics have room.
   const int64_t rows = a.B * n_samp * rps * a.Hkv;
-  f.sums = (size_t)(((int64_t)a.B * n_samp * a.Hkv + 3) / 4);
+  f.sums = (size_t)(((int64_t)a.B * n_samp * a.Hkv + 1) / 2);
   int64_t ranges = ((int64_t)a.max_seqlen + kImpFewKeys - 1) / kImpFewKeys;
   if (ranges > kImpFewRanges) ranges = kImpFewRanges;
   if (wgs > 128) ranges = 1;
@@ -1081,7 +1077,7 @@ hipError_t launch_importance(const dsk_compress_args& a, const CompressWs& ws, h
   const int layers = a.imp_layers > 0 ? a.imp_layers : 1;
   const ImpFew few = importance_few(a, l);
   if (few.take && few.sums <= l.part_rows) {
-    float* sums = reinterpret_cast<float*>(part);     // of each (sample, KV head), in front of the statistics
+    double* sums = reinterpret_cast<double*>(part);   // of each (sample, KV head), in front of the statistics
     float4* stats = part + few.sums;
 #define DSK_IMP_ARGS                                                                                             \
   static_cast<const uint16_t*>(a.K), a.k_stride_tok, a.k_stride_head, static_cast<const uint16_t*>(a.qwin),      \
