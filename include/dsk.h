@@ -102,6 +102,9 @@ enum {
  *   [0,1] by (mean + alpha_imp) / (1 + alpha_imp), clamped, and rounded half-up to tenths.
  *   Classes without a sample keep the value already in class_weight_q.  One call covers one
  *   layer; samp_score_sum carries the mean over several layers from call to call.
+ *   The same call gives the same bits; the last bits of a sample's s_t may differ with what else the call
+ *   holds (sums are in 32 bits, cut and grouped by the work of the whole call), and with them a
+ *   weight whose mean lies next to a rounding edge of the tenths.
  * Stage SEGMENT (Sec. 4.1, Dynamic Segmentation Procedure; Sec. 4.2 variable-to-fixed map):
  *   a candidate at position t offers the boundary e = t+1.  From s_c (0 at first):
  *   s_e = s_c + C; if s_e >= L the last chunk ends at L; else the offered boundary in
@@ -498,7 +501,9 @@ const char* dsk_strerror(dsk_status status);
  * (Sec. 4.1): floor(total_tokens / min_chunk) + B.  Returns -1 on bad arguments. */
 int64_t dsk_block_capacity(int32_t total_tokens, int32_t B, int32_t min_chunk);
 
-/* Workspace sizes in bytes for the given arguments (0 on invalid geometry). */
+/* Workspace sizes in bytes for the given arguments (0 on invalid geometry).  That of dsk_compress counts stage
+ * IMPORTANCE whatever `stages` says, if the stage takes n_class, M and W: one workspace serves a struct whose
+ * stages are run one after the other.  A call without that stage needs only what the query says for M = 0. */
 size_t dsk_compress_workspace_bytes(const dsk_compress_args* args);
 size_t dsk_select_workspace_bytes(const dsk_select_args* args);
 size_t dsk_attn_workspace_bytes(const dsk_attn_args* args);

@@ -93,7 +93,7 @@ def test_shared_selection_parity_full_size(cfg_id):
 
 @pytest.mark.parametrize("Hq,Hkv", [(4, 2), (16, 2), (6, 2), (10, 2)])
 def test_shared_selection_group_widths(Hq, Hkv):
-    """Group widths 2 and 8 (the register-tiled score kernel), 3 and 5 (the any-width one)."""
+    """Group widths 2 and 8 (tiles of the group's own width in the score kernel), 3 and 5 (padded tiles of 4 and 8)."""
     case = gpu_case(2, Hq=Hq, Hkv=Hkv, seqlens=[5000], T=512, n_queries=2)
     _check_shared(case, 2, [0], [0, 1], "G=%d shared" % (Hq // Hkv))
 
@@ -137,7 +137,8 @@ def test_shared_selection_tiled_gather(cfg_id, Hq, Hkv, B):
     _check_shared(case, 1, [0, 1, 2, B - 1], sorted({0, Hkv - 1}), "tiled G=%d" % (Hq // Hkv))
 
 
-# group widths that are no power of two, or above 8: the tiled score kernel on padded tiles of heads
+# group widths that are no power of two, or above 8: the tiled score kernel on padded tiles of heads, and for a
+# shared selection on more than 8 heads (12 / 1) the one that takes a block at a time
 @pytest.mark.parametrize("lens", [[13], [700], [1, 0, 350, 97, 33]])
 @pytest.mark.parametrize("Hq, Hkv, shared", [(3, 1, False), (3, 1, True), (10, 2, False), (10, 2, True), (6, 1, True),
                                              (7, 1, False), (14, 2, True), (9, 1, False), (16, 1, False), (26, 2, False),

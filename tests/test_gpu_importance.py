@@ -170,22 +170,24 @@ def test_importance_mean_over_layers():
 
 
 # ---------------------------------------------------------------------------------------------
-# the many-workgroup launch shape (3 sample slots x 4 wavefronts), taken when
-# ceil(n_samp / 4) * Hkv * B >= 1024, and Alg. 1 at the full 128K context
+# the kernel that packs the query rows, with the samples ranked by a launch in front (several
+# sequences, or more than 256 samples) and by itself, and Alg. 1 at the full 128K context
 # ---------------------------------------------------------------------------------------------
 def test_importance_many_workgroups_gqa_batch():
-    """Llama-3-8B head shape, 4 sequences, 16 classes x 8 samples: 32 * 8 * 4 = 1024 sample groups."""
+    """Llama-3-8B head shape, 4 sequences of 16 classes x 8 samples: ranked by the launch in front."""
     wl, comp, prior = _run(5, B=4, seqlens=[3300, 2100, 4000, 2600])
     cfg = wl.cfg
-    assert (cfg.n_class * cfg.M + 3) // 4 * cfg.Hkv * cfg.B >= 1024
+    assert not _on_the_few_rows_kernel(cfg.B, 4000, cfg.Hq, cfg.Hkv, cfg.n_class * cfg.M, cfg.W, cfg.R)
     print("many-workgroup GQA batch worst = %.2e" % _check(wl, comp, prior))
 
 
 def test_importance_many_workgroups_mha():
-    """Llama2-13B head shape (40 KV heads, no grouping), one sequence: 32 * 40 = 1280 sample groups."""
+    """Llama2-13B head shape (40 KV heads, no grouping), one sequence: ranked by the kernel itself, four samples
+    in a row tile."""
     wl, comp, prior = _run(4, seqlens=[6000])
     cfg = wl.cfg
-    assert (cfg.n_class * cfg.M + 3) // 4 * cfg.Hkv * cfg.B >= 1024
+    assert cfg.n_class * cfg.M <= 256
+    assert not _on_the_few_rows_kernel(1, 6000, cfg.Hq, cfg.Hkv, cfg.n_class * cfg.M, cfg.W, cfg.R)
     print("many-workgroup MHA worst = %.2e" % _check(wl, comp, prior))
 
 
@@ -193,8 +195,8 @@ def test_importance_at_full_128k_context_both_launch_shapes():
     """Stage IMPORTANCE alone at 131072 tokens with sample positions given by the caller, spread
     over the whole context (the first and the last admissible position, the middle, tile edges),
     so that the key loop runs thousands of tiles and nearly all of them lie in the discarded
-    region.  512 samples take the many-workgroup launch, a 6-sample call the other one; a
-    handful of samples (all 32 heads, every window query) is compared with the oracle."""
+    region.  512 samples run packed, ranked by the launch in front, a 6-sample call on the kernel for few
+    rows, in key ranges; a handful of samples (all 32 heads, every window query) is compared with the oracle."""
     import paper_2602_03184_amd as dsk
     from workloads import f32_to_bf16_bits
     wl = make_workload(3, with_kv=True, with_qwin=False)
@@ -203,7 +205,8 @@ def test_importance_at_full_128k_context_both_launch_shapes():
     assert L == 131072
     n_class, M = 16, 32
     n_samp = n_class * M
-    assert (n_samp + 3) // 4 * cfg.Hkv >= 1024
+    assert n_samp > 256 and not _on_the_few_rows_kernel(1, L, cfg.Hq, cfg.Hkv, n_samp, cfg.W, cfg.R)
+    assert _on_the_few_rows_kernel(1, L, cfg.Hq, cfg.Hkv, 6, cfg.W, cfg.R)
     r = np.random.default_rng(2024)
     t_all = r.integers(cfg.R, L - cfg.W, size=n_samp).astype(np.int64)
     t_all[0] = cfg.R                      # first admissible position
@@ -232,9 +235,9 @@ def test_importance_at_full_128k_context_both_launch_shapes():
         assert int(comp.dev_status.item()) == 0
         return comp.samp_score.cpu().numpy().reshape(-1)
 
-    big = run(np.arange(n_samp), n_class, M)              # many-workgroup launch
+    big = run(np.arange(n_samp), n_class, M)              # packed
     assert np.isfinite(big).all() and (big >= -cfg.alpha_imp - 1e-5).all() and (big <= 1.0 + 1e-5).all()
-    small = run(np.asarray(checked), 2, 3)                # few-workgroup launch on the checked samples
+    small = run(np.asarray(checked), 2, 3)                # few rows: the checked samples alone
     worst = 0.0
     for i, j in enumerate(checked):
         for got in (float(big[j]), float(small[i])):
@@ -244,21 +247,21 @@ def test_importance_at_full_128k_context_both_launch_shapes():
 
 
 # ---------------------------------------------------------------------------------------------
-# stage IMPORTANCE on positions given by the caller, where the packing of the query rows, the
-# ranking of the samples and the cuts of the key ranges have their edges
+# stage IMPORTANCE on positions given by the caller, odd shapes (all on the kernel for few rows but the one with
+# 512 rows per sample; the packed kernel's edges are in test_importance_packed_rows)
 # ---------------------------------------------------------------------------------------------
 @pytest.mark.parametrize(
     "B, L, Hq, Hkv, n_class, M, W, R, spread, imp_scale",
     [
         (1, 700, 1, 1, 1, 1, 1, 1, 1.0, 0.0),            # one row; the regions meet at every position
-        (1, 1500, 4, 4, 3, 7, 8, 20, 1.0, 0.0),          # several samples in a row tile, regions narrower than a tile
-        (1, 2100, 6, 2, 5, 3, 5, 100, 1.0, 0.0),         # 15 rows per sample: samples straddle row tiles
+        (1, 1500, 4, 4, 3, 7, 8, 20, 1.0, 0.0),          # 8 rows per sample, regions narrower than a tile
+        (1, 2100, 6, 2, 5, 3, 5, 100, 1.0, 0.0),         # 15 rows per sample
         (1, 1300, 8, 1, 2, 2, 64, 128, 1.0, 0.0),        # 512 rows per sample: a sample fills two items
-        (1, 900, 2, 2, 16, 16, 2, 64, 1.0, 0.0),         # 256 samples: the largest ranked inside the kernel
-        (1, 900, 2, 2, 16, 17, 2, 64, 1.0, 0.0),         # 272: ranked by the launch in front
+        (1, 900, 2, 2, 16, 16, 2, 64, 1.0, 0.0),         # 256 samples
+        (1, 900, 2, 2, 16, 17, 2, 64, 1.0, 0.0),         # 272
         (3, 1100, 4, 1, 4, 3, 8, 128, 1.0, 0.0),         # several sequences
-        (270, 90, 1, 1, 1, 2, 3, 16, 1.0, 0.0),          # more sequences than one launch plans
-        (1, 3000, 4, 1, 4, 4, 8, 128, 40.0, 0.0),        # logits of hundreds: the reference moves often
+        (270, 90, 1, 1, 1, 2, 3, 16, 1.0, 0.0),          # many sequences
+        (1, 3000, 4, 1, 4, 4, 8, 128, 40.0, 0.0),        # logits of hundreds: the maximum moves often
         (1, 1200, 4, 1, 4, 4, 8, 128, 1.0, 0.5),         # a caller's logit scale
     ])
 def test_importance_given_positions(B, L, Hq, Hkv, n_class, M, W, R, spread, imp_scale):
