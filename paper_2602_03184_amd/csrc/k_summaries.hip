@@ -16,8 +16,10 @@ constexpr int kSumUnroll = 8;  // row-groups of 4 rows in flight per wave
 // STREAM (the full pass): the records are stored past the cache's replacement order.  Written through it
 // they leave it one by one between the reads, which costs far more than their bytes: K and V summaries of
 // eight sequences, 24K to 64K tokens, 8 heads: 361 -> 345 us for the pass from the larger grid, -> 307 us from
-// these stores.  (Streaming loads of the rows took another 23 us off, and put 30 us on the decode step that
-// follows, which then finds none of K in the memory-side cache: not used.)
+// these stores.  The first selection that follows reads them from memory instead of the memory-side cache: one
+// sequence of 128K tokens, 8 heads, chunks of 32: pass 66.6 -> 62.6 us, pass and selection 78.4 -> 74.7; chunks of 8:
+// pass unchanged, both 180 -> 183.  (Streaming loads of the rows took another 23 us off, and put 30 us on the
+// decode step that follows, which then finds none of K in the memory-side cache: not used.)
 template <bool MEAN, bool STREAM>
 __device__ __forceinline__ void summarize_block(const uint16_t* base, int len, int64_t stride_tok, unsigned ustride,
                                                 uint16_t* o, int g, int c) {
@@ -140,11 +142,12 @@ static hipError_t launch_summaries_impl(const dsk_compress_args& a, hipStream_t 
   const int64_t max_items = (int64_t)a.Hkv * a.max_blocks_total;
   if (max_items <= 0) return hipSuccess;
   int64_t wgs = (max_items + kSumWaves - 1) / kSumWaves;
-  // One or two blocks per wavefront where there are many: workgroups dealt out as others end stay close
-  // together in memory, while a persistent grid of 256 * 8 drifts apart (128K tokens, 8 heads: 79 -> 73 us
-  // for the pass with the streamed records).  The capacity may be a multiple of the blocks there are, and an
-  // empty workgroup is not free, so the grid follows twice the blocks of chunks of C tokens (four times where
-  // sequences have a C of their own, below this bound).
+  // A wavefront per block where there are many: workgroups dealt out as others end stay close together in
+  // memory, while a persistent grid of 256 * 8 drifts apart (128K tokens, 8 heads: 79 -> 73 us for the pass
+  // with the streamed records).  The capacity may be a multiple of the blocks there are, and an empty workgroup
+  // is not free, so the grid is bounded by wavefronts for twice the blocks of chunks of C tokens (four times
+  // where sequences have a C of their own, below this bound).  Where chunks are C tokens long half of them find no
+  // block and leave: 69 920 wavefronts for 32 608 blocks at 128K tokens, C = 30.
   // (C is only a hint here: a call of this stage alone may leave it unset.)
   int64_t max_wgs = a.C > 0 ? (a.C_per_seq != nullptr ? 4 : 2) * (int64_t)a.Hkv * (a.total_tokens / a.C + a.B) / kSumWaves : 0;
   if (max_wgs < 256 * 8) max_wgs = 256 * 8;
