@@ -32,9 +32,9 @@
 //    between their edges counts: 14 on average for 4 samples a row tile (128 samples of a long text), more
 //    for samples far apart, which the flat kImpItemCost does not follow.
 //  - Calls with few rows or short sequences run on a kernel of their own, importance_few_kernel below.
-// Measured (stage IMPORTANCE, 32 query / 8 KV heads, W = 8): 128 samples of a 128K sequence 98.3 -> 57.0 us,
-// 1024 samples of eight sequences of 24K to 64K tokens 379 -> 237 us, against
-// one workgroup per 3 or 4 consecutive samples with the key tiles fetched by each wavefront.
+// Measured (stage IMPORTANCE, 32 query / 8 KV heads, W = 8): 128 samples of a 128K sequence 97.7 -> 57.9 us (58 to 66
+// over the GPUs seen), 1024 samples of eight sequences of 24K to 64K tokens 370 -> 243 us, against one workgroup per
+// 3 or 4 consecutive samples with the key tiles fetched by each wavefront.
 #include <type_traits>
 
 #include "dsk_common.hpp"
@@ -1041,9 +1041,10 @@ static ImpFew importance_few(const dsk_compress_args& a, const ImpLayout& l) {
   // positions further back this kernel is up to three times slower than the packed one, which is up to 2.9 times
   // slower than this one on early positions or short sequences.  Several sequences cost the packed kernel a
   // ranking launch and time for its plan, and items of a few rows leave most of its wavefronts idle.
-  // Measured at its sides, packed against this kernel: 128 samples of 300 tokens, 32 / 8 heads 29.3 against 16.9 us;
-  // 4 samples in each of 8 sequences of 8K tokens, 32 / 32 heads 224 against 93; 128 samples spread over 8K
-  // tokens, 32 / 8 heads 62.8 against 71.8 (packed).
+  // Measured at its sides, packed against this kernel: 128 samples of 300 tokens, 32 / 8 heads 30.4 against 17.3 us;
+  // 4 samples in each of 512 sequences of 300 tokens, 1 / 1 head 75 against 28, in each of 8 of 8K tokens, 32 / 32
+  // heads 224 against 92; 16 samples of 128K tokens, 32 / 8 heads 24.3 against 19.2 where they lie early, 127 against
+  // 183 spread over all of it (864 with one range); 128 samples spread over 8K tokens 67.6 against 77.7 (packed).
   const bool own_rank = a.B == 1 && n_samp <= kImpThreads;
   int64_t keys = (int64_t)a.R + a.W + 48 * n_samp;
   if (keys > a.max_seqlen) keys = a.max_seqlen;
