@@ -51,7 +51,7 @@ CompressWs compress_ws_layout(const dsk_compress_args& a) {
   // Stage IMPORTANCE alone uses what follows.  The query counts it whatever the stages, since the struct may be
   // used again for other stages, unless the arguments are none that the stage takes.
   ws.imp_plan = ws.imp_part = ws.without_imp = off;
-  if (importance_args_ok(a) && geometry_ok(a.B, a.Hq, a.Hkv, a.D)) {
+  if (importance_args_ok(a) && a.Hkv >= 1 && a.Hq >= a.Hkv) {
     const ImpLayout l = importance_layout(a.B, a.n_class * a.M, a.W, a.Hq, a.Hkv);
     off += align_up(l.plan_ints * sizeof(int32_t));
     ws.imp_part = off;   off += align_up(l.part_rows * sizeof(float4));

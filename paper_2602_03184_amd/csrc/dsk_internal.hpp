@@ -52,6 +52,7 @@ struct ImpLayout {
   int seqs;            // sequences per launch
   int items;           // upper bound of the groups of kImpRows query rows of one KV head in a launch
   size_t plan_ints, part_rows;   // space; it does not shrink when B, the samples or W grow
+  size_t sum_rows;               // entries at the start of part that calls with few rows use for sums of samples
 };
 ImpLayout importance_layout(int B, int n_samp, int W, int Hq, int Hkv);
 

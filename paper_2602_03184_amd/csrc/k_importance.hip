@@ -1020,15 +1020,16 @@ ImpLayout importance_layout(int B, int n_samp, int W, int Hq, int Hkv) {
   if (most_items > most_seqs * per_seq) most_items = most_seqs * per_seq;
   l.plan_ints = (size_t)(4 + 2 * most_seqs + 1 + most_items + 1 + 3 * most_seqs * n_samp);
   l.part_rows = (size_t)(kImpPieces + most_items * Hkv) * kImpRows;
+  // calls with few rows: a sum of 8 bytes for each (sample, KV head) of all sequences
+  l.sum_rows = ((size_t)B * n_samp * Hkv + 1) / 2;
+  if (l.part_rows < l.sum_rows) l.part_rows = l.sum_rows;
   return l;
 }
 
-// The kernel for few rows: whether the call takes it, its key ranges, and where the rows' statistics lie
-// behind the sums of the (sample, KV head) pairs.
+// The kernel for few rows: whether the call takes it, and its key ranges.
 struct ImpFew {
   bool take;
   int ranges, keys;
-  size_t sums;           // float4 entries
 };
 static ImpFew importance_few(const dsk_compress_args& a, const ImpLayout& l) {
   ImpFew f;
@@ -1055,12 +1056,12 @@ static ImpFew importance_few(const dsk_compress_args& a, const ImpLayout& l) {
   // spread over it, 8 / 8 heads: 859 us in one range, 56 in 32; 40 samples in each of 3 sequences of 5.3K, 240
   // workgroups: 53 against 62 in 2), and as far as their statistics have room.
   const int64_t rows = a.B * n_samp * rps * a.Hkv;
-  f.sums = (size_t)(((int64_t)a.B * n_samp * a.Hkv + 1) / 2);
   int64_t ranges = ((int64_t)a.max_seqlen + kImpFewKeys - 1) / kImpFewKeys;
   if (ranges > kImpFewRanges) ranges = kImpFewRanges;
   if (wgs > 128) ranges = 1;
   else if (ranges * wgs > 1024) ranges = 1024 / wgs;
-  if (ranges > 1 && (int64_t)f.sums + ranges * rows > (int64_t)l.part_rows) ranges = ((int64_t)l.part_rows - (int64_t)f.sums) / rows;
+  const int64_t room = (int64_t)(l.part_rows - l.sum_rows);
+  if (ranges > 1 && ranges * rows > room) ranges = room / rows;
   if (ranges < 1) ranges = 1;
   f.ranges = (int)ranges;
   f.keys = (int)((((int64_t)a.max_seqlen + ranges - 1) / ranges + 31) / 32 * 32);
@@ -1077,9 +1078,9 @@ hipError_t launch_importance(const dsk_compress_args& a, const CompressWs& ws, h
   const ImpLayout l = importance_layout(a.B, n_samp, a.W, a.Hq, a.Hkv);
   const int layers = a.imp_layers > 0 ? a.imp_layers : 1;
   const ImpFew few = importance_few(a, l);
-  if (few.take && few.sums <= l.part_rows) {
+  if (few.take) {
     double* sums = reinterpret_cast<double*>(part);   // of each (sample, KV head), in front of the statistics
-    float4* stats = part + few.sums;
+    float4* stats = part + l.sum_rows;
 #define DSK_IMP_ARGS                                                                                             \
   static_cast<const uint16_t*>(a.K), a.k_stride_tok, a.k_stride_head, static_cast<const uint16_t*>(a.qwin),      \
       a.samp_pos, a.cu_seqlens, n_samp, few.ranges, few.keys, a.W, a.R, a.Hq, G, a.Hkv, a.alpha_imp,         \

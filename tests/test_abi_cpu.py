@@ -334,6 +334,7 @@ def test_compress_needs_the_importance_space_for_that_stage_only(dsk):
     # one workspace for a struct whose stages are run one by one
     full = query(_compress_args(dsk, stages=dsk.DSK_STAGE_CANDIDATES))
     assert full > base and full == query(_compress_args(dsk, stages=dsk.DSK_STAGE_IMPORTANCE))
+    assert full == query(_compress_args(dsk, stages=0, D=0))          # fields that the size does not follow
     a = _compress_args(dsk, stages=dsk.DSK_STAGE_IMPORTANCE, workspace_bytes=full)
     assert dsk.dsk_compress(a, 0, check=False) == dsk.DSK_ERR_ALIGN
     a.workspace_bytes = full - 1
@@ -345,7 +346,7 @@ def test_compress_workspace_does_for_smaller_calls(dsk, Hq, Hkv):
     """A workspace made for the largest batch, sample count and window serves the smaller ones."""
     def size(B, M, W):
         return dsk.dsk_compress_workspace_bytes(_compress_args(dsk, Hq=Hq, Hkv=Hkv, B=B, M=M, W=W, max_seqlen=5))
-    for B in (1, 7, 40, 300):
+    for B in (1, 7, 40, 300, 60000):
         for M in (1, 5, 8, 13):
             for W in range(1, 65):
                 assert size(B, M, W) <= min(size(B + 1, M, W), size(B, M + 1, W))

@@ -386,6 +386,7 @@ def _compare_with_64_bits(B, L, Hq, Hkv, n_class, M, W, R, positions, few, sprea
         (1, 20000, 4, 4, 1, 5, 8, 5000, [19999, 3991, 3992, 3999, 4000]), # five ranges, retained over two
         (2, 20000, 8, 2, 2, 1, 4, 128, [7999, 12345]),                    # two sequences over ranges of 4000
         (1, 131072, 8, 8, 2, 2, 8, 128, [131071, 70000, 4095, 200]),      # 32 ranges
+        (50000, 20, 1, 1, 1, 8, 2, 4, [19, 0]),                           # more sums than statistics of a packed launch
     ])
 def test_importance_few_rows(B, L, Hq, Hkv, n_class, M, W, R, positions):
     """Calls on the kernel for few query rows, whole and in key ranges."""
