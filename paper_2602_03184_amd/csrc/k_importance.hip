@@ -590,6 +590,14 @@ __global__ __launch_bounds__(kImpThreads, 2) void importance_kernel(
 }
 
 // ---- calls with few query rows ------------------------------------------------------------------
+constexpr int kImpQRow = DSK_HEAD_DIM + 8;   // bf16 elements per query row in LDS: 16 rows' 16-byte reads cover all banks
+
+// key ranges that hold keys of a sample
+__device__ __forceinline__ int imp_few_ranges(int last_key, int ranges, int range_keys) {
+  const int n = last_key / range_keys + 1;
+  return n < ranges ? n : ranges;
+}
+
 // The packed kernel pays for its plan, and shares key tiles among kImpRows query rows of a sequence.  Where a
 // sequence has far fewer rows, or few keys, one workgroup per kSamples samples of one KV head does better: its
 // wavefronts take every kWaves-th key tile, straight from memory (one key row per lane), against the
@@ -599,16 +607,12 @@ __global__ __launch_bounds__(kImpThreads, 2) void importance_kernel(
 // statistics of their rows (part) are left to the finishing kernel.
 // grid: (group of kSamples samples, KV head, range x sequence): the ranges are the slowest, so that the few
 // workgroups with work, the first range's, spread over all XCDs
-__device__ __forceinline__ int imp_few_ranges(int last_key, int ranges, int range_keys) {   // that hold a sample's keys
-  const int n = last_key / range_keys + 1;
-  return n < ranges ? n : ranges;
-}
-constexpr int kImpQRow = DSK_HEAD_DIM + 8;   // bf16 elements per query row in LDS: 16 rows' 16-byte reads cover all banks
 template <int kThreads, int kSamples, bool SPLIT>
 __global__ __launch_bounds__(kThreads) void importance_few_kernel(
     const uint16_t* __restrict__ K, int64_t kst, int64_t ksh, const uint16_t* __restrict__ qwin,
-    const int32_t* __restrict__ samp_pos, const int32_t* __restrict__ cu_seqlens, int n_samp, int ranges, int range_keys, int W,
-    int R, int Hq, int G, int Hkv, float alpha, float scale_log2, int B, double* __restrict__ imp_part, float4* __restrict__ part) {
+    const int32_t* __restrict__ samp_pos, const int32_t* __restrict__ cu_seqlens, int n_samp, int ranges,
+    int range_keys, int W, int R, int Hq, int G, int Hkv, float alpha, float scale_log2, int B,
+    double* __restrict__ imp_part, float4* __restrict__ part) {
   constexpr int kWaves = kThreads / DSK_WAVE;
   __shared__ RowStat sm_stat[kSamples][kWaves][32];
   __shared__ __attribute__((aligned(16))) uint16_t sm_q[kSamples][32][kImpQRow];

@@ -419,3 +419,40 @@ def test_importance_ranks_positions_beyond_19_bits():
     L = 600001
     positions = [L - 1, L - 2, L - 10, 524288, 524289, 524287, 300, 64 * 9000 + 55]
     _compare_with_64_bits(1, L, 1, 1, 1, 8, 64, 128, positions, few=False)
+
+
+@pytest.mark.parametrize("B, L, Hkv, n_class, M, few", [(2, 400, 2, 4, 2, True), (1, 30000, 2, 4, 2, True),
+                                                        (1, 9000, 2, 16, 12, False), (3, 3000, 8, 16, 4, False)])
+def test_importance_in_a_graph(B, L, Hkv, n_class, M, few):
+    """The stage recorded once and replayed on other queries, with eager calls on the same workspace in between."""
+    import paper_2602_03184_amd as dsk
+    n, W, R = n_class * M, 8, 128
+    assert _on_the_few_rows_kernel(B, L, Hkv, Hkv, n, W, R) == few
+    g = torch.Generator(device="cuda")
+    g.manual_seed(L)
+    K = torch.randn(Hkv, B * L, 128, generator=g, device="cuda").bfloat16()
+    qs = [torch.randn(B, n, W, Hkv, 128, generator=g, device="cuda").bfloat16() for _ in range(3)]
+    t = torch.randint(R, L - W, (B, n), generator=g, device="cuda", dtype=torch.int32)
+    samp = (t + torch.arange(0, B * L, L, device="cuda", dtype=torch.int32)[:, None]).view(B, n_class, M).contiguous()
+    q = qs[0].clone()
+    comp = dsk.compress(cu_seqlens=dev_i32(np.arange(B + 1) * L), max_seqlen=L, Hq=Hkv, K=K, V=None,
+                        stages=dsk.DSK_STAGE_IMPORTANCE, n_class=n_class, M=M, W=W, R=R, alpha_imp=1.0, samp_pos=samp,
+                        qwin=q, class_weight_q=dev_u8(np.full((B, n_class), 3, np.uint8)))
+    want = []
+    for x in qs:
+        q.copy_(x)
+        dsk.dsk_compress(comp.args)
+        want.append((comp.samp_score.clone(), comp.class_mean.clone(), comp.class_weight_q.clone()))
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        dsk.dsk_compress(comp.args)
+    for x, (score, mean, weight) in [(qs[i], want[i]) for i in (0, 1, 2, 0)]:
+        q.copy_(x)
+        comp.samp_score.fill_(7.0)
+        comp.class_mean.fill_(7.0)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(comp.samp_score, score) and torch.equal(comp.class_mean, mean)
+        assert torch.equal(comp.class_weight_q, weight)
+        dsk.dsk_compress(comp.args)
