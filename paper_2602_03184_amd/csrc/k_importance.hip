@@ -8,9 +8,11 @@
 // holding 16 keys of ONE query row: the softmax statistics (mass of all keys, of the retained region
 // O_t, of the discarded region D_t) accumulate per lane with no cross-lane traffic until the very end.
 //
-// What bounds it: the vector ALU.  Per product of a key tile and a row tile a lane has 16 exponentials
-// (a quarter of the issue rate), 16 multiply-adds and 16 adds = 384 cycles of a SIMD, next to 256 cycles
-// of MFMA, which run in their shadow when the two are interleaved.  Everything else is kept off that path:
+// What bounds it: the vector ALU and the matrix cores together, at the clock that both leave.  Per product of a key
+// tile and a row tile a lane has 16 exponentials (half the issue rate), 16 multiply-adds and 16 adds = 256 cycles of
+// a SIMD, next to 256 cycles of MFMA, which run in their shadow when the two are interleaved; the chip runs at 1.8 to
+// 2.0 GHz meanwhile (2.4 in light kernels), and the products alone would take 150 to 180 ns each on random data, of the
+// 265 they take here.  Everything else is kept off that path:
 //  - The samples of a sequence are ranked by position (latest first) and their rows packed back to back,
 //    so that row tiles are full for any W*G and the samples of a workgroup end at about the same key.
 //  - A workgroup (4 wavefronts x kImpNS row tiles, query operands in registers) shares every key tile
@@ -34,7 +36,10 @@
 //  - Calls with few rows or short sequences run on a kernel of their own, importance_few_kernel below.
 // Measured (stage IMPORTANCE, 32 query / 8 KV heads, W = 8): 128 samples of a 128K sequence 97.7 -> 57.9 us (58 to 66
 // over the GPUs seen), 1024 samples of eight sequences of 24K to 64K tokens 370 -> 243 us, against one workgroup per
-// 3 or 4 consecutive samples with the key tiles fetched by each wavefront.
+// 3 or 4 consecutive samples with the key tiles fetched by each wavefront; then 58.8 -> 55.7 and 233 -> 223 (both on one
+// GPU) from the order of the two workgroups of a CU, key addresses without vector multiplies and kImpItemCost 5 -> 6.
+// Keys straight to LDS three stages ahead (four buffers): 55.9 / 241 against 54.8 / 233 at that stage, latency is not what
+// is missing; two masked tiles' keys on their way instead of one: no change.
 #include <type_traits>
 
 #include "dsk_common.hpp"
@@ -67,7 +72,7 @@ constexpr int kImpWaves = kImpThreads / DSK_WAVE;
 constexpr int kImpNS = kImpRows / 32 / kImpWaves;     // row tiles per wavefront
 constexpr int kImpStage = 64;                         // keys per LDS buffer
 constexpr int kImpMinStages = 4;                      // a piece shorter than this does not pay for its start
-constexpr int kImpItemCost = 5;                       // start of an item and its tiles at the regions' edges, in stages
+constexpr int kImpItemCost = 6;                       // start of an item and its tiles at the regions' edges, in stages
 constexpr float kImpRescaleAt = 64.0f;
 constexpr float kImpHeadroom = 4.0f;                  // log2 units a new reference lies above the largest logit seen
 static_assert(kImpNS == 2, "the row tiles of a wavefront are written out below");
@@ -369,10 +374,12 @@ __global__ __launch_bounds__(kImpThreads, 2) void importance_kernel(
   // the later row tiles of an item have fewer keys: the second workgroup of a CU deals its tiles to the
   // SIMDs the other way round
   const int own_tile = (blockIdx.x * 2 >= gridDim.x ? kImpWaves - 1 - wave : wave) * kImpNS;
+  const bool young = blockIdx.x * 2 >= gridDim.x;   // most likely the second workgroup of its CU
   const int col = lane & 31;        // query row of the tile this lane accumulates; key row of its A operand
   const int hf = lane >> 5;         // channel half / key sub-row selector
   // LDS: chunk c (16 bytes) of key row r lies in slot c ^ (r & 15) of the row
   const int ld_row = tid >> 4, ld_slot = ((tid & 15) ^ ld_row) * 8;   // rows ld_row + 0, 16, 32, 48
+  const unsigned ld_off = ((unsigned)ld_row * (unsigned)kst + (unsigned)(tid & 15) * 8u) * 2u;
   static_assert(kImpThreads == 256 && kImpStage == 64, "a thread stages four 16-byte chunks");
   const int rd_slot = (hf * 8) ^ (col & 15);
 
@@ -386,19 +393,27 @@ __global__ __launch_bounds__(kImpThreads, 2) void importance_kernel(
     const int end = (uint64_t)(item_st + kImpItemCost - at) < x_end - x ? item_st + kImpItemCost : at + (int)(x_end - x);
     const int st_at = at < item_st ? at : item_st;
     const int st_end = end < item_st ? end : item_st;
-    const uint16_t* Kh = K + (int64_t)hk * ksh + (int64_t)seq0 * kst + (tid & 15) * 8;
+    const char* Kh = reinterpret_cast<const char*>(K + (int64_t)hk * ksh + (int64_t)seq0 * kst);     // uniform
 
     // first stage -> registers
     uint4 kreg0, kreg1, kreg2, kreg3;
-    auto load_row = [&](int row) {
-      row = row < L ? row : L - 1;                // stay inside the sequence; masked below
-      return *reinterpret_cast<const uint4*>(Kh + (int64_t)row * kst);
-    };
     auto load_stage = [&](int st) {
-      kreg0 = load_row(st * kImpStage + ld_row);
-      kreg1 = load_row(st * kImpStage + ld_row + 16);
-      kreg2 = load_row(st * kImpStage + ld_row + 32);
-      kreg3 = load_row(st * kImpStage + ld_row + 48);
+      if ((st + 1) * kImpStage <= L) {            // uniform bases + one 32-bit lane offset (kst <= 2^24, host-checked)
+        const char* base = Kh + (int64_t)st * kImpStage * kst * 2;
+        kreg0 = *reinterpret_cast<const uint4*>(base + ld_off);
+        kreg1 = *reinterpret_cast<const uint4*>(base + 32 * kst + ld_off);
+        kreg2 = *reinterpret_cast<const uint4*>(base + 64 * kst + ld_off);
+        kreg3 = *reinterpret_cast<const uint4*>(base + 96 * kst + ld_off);
+      } else {                                    // stay inside the sequence (the stage may lie behind it); masked below
+        auto row_at = [&](int row) {
+          row += st * kImpStage;
+          return *reinterpret_cast<const uint4*>(Kh + ((int64_t)(row < L ? row : L - 1) * kst + (tid & 15) * 8) * 2);
+        };
+        kreg0 = row_at(ld_row);
+        kreg1 = row_at(ld_row + 16);
+        kreg2 = row_at(ld_row + 32);
+        kreg3 = row_at(ld_row + 48);
+      }
     };
     auto store_stage = [&](int buf) {
       *reinterpret_cast<uint4*>(&sm_k[buf][ld_row][ld_slot]) = kreg0;
@@ -524,6 +539,13 @@ __global__ __launch_bounds__(kImpThreads, 2) void importance_kernel(
     for (int st = st_at; st < st_end; ++st) {
       const int buf = (st - st_at) & 1;
       const int k0 = st * kImpStage;
+      // The older of two wavefronts issues first: pieces of the second workgroup of a CU took a third longer than those
+      // of the first, which then left it alone.  Three stages in four the younger one goes first: 58.8 -> 56.4 us,
+      // 233 -> 226 (never, always or every other stage: 58.4 / 57.9 / 56.4 and 232 / 232 / 225).
+      if (young) {
+        if ((st & 3) != 0) __builtin_amdgcn_s_setprio(1);
+        else __builtin_amdgcn_s_setprio(0);
+      }
       half_step(kReady, 0, 1, k0, c0, c1, kf);
       read_keys(kf, buf, 1);
       half_step(kFresh, 1, 0, k0, c1, c0, kf);
