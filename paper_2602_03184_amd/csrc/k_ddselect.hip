@@ -18,7 +18,8 @@
 //            chunk length and the hop-2, -4, -8 .. targets of every position are kept for the emit pass.
 //   chain:   per sequence, hop through the entry maps (staged in LDS) to fix each tile's real
 //            entry and its block / slot offsets; for a single-sequence batch also the totals.
-//   scan:    block and slot bases of the sequences of a batch (B > 1), capacity check.
+//   scan:    block and slot bases of the sequences of a batch of more than kSeqsFolded, capacity check; in smaller
+//            batches the emit pass adds up the sequences in front of its own by itself.
 //   tile<1>: the chunks the chain lays down in the tile are the positions 0, 1, 2 .. hops behind the
 //            tile's real entry; each is found through the hop-2^l tables the first pass kept, ranked
 //            by a workgroup scan and written out.
@@ -35,6 +36,7 @@ constexpr int kTileThreads = 1024;                      // workgroup of the tile
                                                         // threads: 95 / 88 / 86.5 us for the pass at 128K)
 constexpr int kSegPerThread = kSegTile / kTileThreads;  // positions owned by a thread of the tile kernel
 constexpr int kTileWaves = kTileThreads / DSK_WAVE;
+constexpr int kSeqsFolded = kTileThreads;                // sequences whose bases the emit pass forms: one per thread
 constexpr int kChainLdsEntries = 6144;   // uint2 entries staged per chunk in the chain kernel (48 KB)
 
 struct SegParams {
@@ -305,14 +307,15 @@ __device__ __forceinline__ void classify_tokens(const int (&tok)[N], int (&cls)[
 //   clist u16 [2 * kSegTile]   delimiters in reach (overlays the second jump buffer)
 //   ns    u16 [kSegTile]       slots of the chunk starting here
 //   wq    u8  [64]             class -> weight tenths of this sequence
-//   red   i32 [40], then the delimiter ids i32 [64]
+//   red   i32 [40], then the delimiter ids i32 [64], then i32 [3][kTileWaves] sums over the sequences in front
 constexpr size_t kTileJumpBytes =    // jump entries; the vote array (8 bytes per position) and, in the emit pass
     (size_t)kSegTile * 16 > (size_t)kChainLdsEntries * 8 ? (size_t)kSegTile * 16     // that chains for itself, the two
                                                         : (size_t)kChainLdsEntries * 8;   // buffers of the chain scan overlay them
 __host__ __device__ constexpr size_t seg_tile_lds_bytes() {
   return kTileJumpBytes
          + (size_t)kSegTile * 2     // ns
-         + 64 + 448;                // wq, red (reduction words, then 64 delimiter ids)
+         + 64 + 448                 // wq, red (reduction words, then 64 delimiter ids)
+         + 3 * kTileWaves * 4;      // sums over the sequences in front
 }
 static_assert(2 * kTileWaves + 3 <= 40 && (40 + 64) * 4 <= 448, "red fits its slot");
 static_assert(kChainThreads == kTileThreads, "the emit pass runs the chain scan with its own workgroup");
@@ -343,12 +346,52 @@ __global__ __launch_bounds__(kTileThreads) void seg_tile_kernel(
   const int tid = threadIdx.x;
   int seq0, L;
   seq_range(p, s, seq0, L);
-  if (!seq_ok(p, seq0, L)) {
-    if (tid == 0) set_status(dev_status, DSK_ERR_SHAPE);
+  // (emit, batch of up to kSeqsFolded) blocks, slots and candidates of the sequences in front of this one: summed here
+  // instead of by a launch of their own (4.8 of 34 us for eight sequences).  The first tile's workgroup of a sequence
+  // also writes its offsets, whether it has a token or not, that of the last one the totals.
+  const bool fold = MODE == 1 && p.B > 1 && p.B <= kSeqsFolded;
+  int4 before = make_int4(0, 0, 0, 0);
+  int* fsum = red + 112;                                            // [3][kTileWaves]
+  if (fold && tid < s) before = seq_info[tid];
+  auto sum_before = [&]() {                                         // one barrier before `before` is read again
+    const int lane = tid & (DSK_WAVE - 1);
+    const int x = wave_sum_i(before.x), y = wave_sum_i(before.y), z = wave_sum_i(before.z);
+    if (lane == 0) { fsum[tid / DSK_WAVE] = x; fsum[kTileWaves + tid / DSK_WAVE] = y; fsum[2 * kTileWaves + tid / DSK_WAVE] = z; }
+  };
+  auto collect_before = [&]() {
+    static_assert(kTileWaves == 16, "one row of lanes holds the wavefronts' sums");
+    const int lane = tid & 15;
+    before = make_int4(group16_sum_i(fsum[lane]), group16_sum_i(fsum[kTileWaves + lane]),
+                       group16_sum_i(fsum[2 * kTileWaves + lane]), 0);
+  };
+  auto write_offsets = [&](const int4 own) {                        // own: this sequence's blocks, slots, candidates
+    if (j != 0 || tid != 0) return;
+    cu_blocks[s] = before.x;
+    if (cu_slots) cu_slots[s] = before.y;
+    if (cand.tile_count != nullptr) cand.cand_cu[s] = before.z;
+    if (s != p.B - 1) return;
+    const int nb = before.x + own.x, nsl = before.y + own.y, nc = before.z + own.z;
+    cu_blocks[p.B] = nb;
+    if (cu_slots) cu_slots[p.B] = nsl;
+    if (cand.tile_count != nullptr) {
+      cand.cand_cu[p.B] = nc;
+      if (nc > cand.max_cand) set_status(dev_status, DSK_ERR_CAPACITY);
+    }
+    if (nb > p.cap) set_status(dev_status, DSK_ERR_CAPACITY);       // the tables stay self-consistent for the truncated prefix
+    else { block_start[nb] = p.total_tokens; slot_base[nb] = nsl; }
+  };
+  const int p0 = j * kSegTile;
+  const bool seq_valid = seq_ok(p, seq0, L);
+  if (!seq_valid && tid == 0) set_status(dev_status, DSK_ERR_SHAPE);
+  if (!seq_valid || p0 >= L) {
+    if (fold && j == 0) {
+      sum_before();
+      __syncthreads();
+      collect_before();
+      write_offsets(make_int4(0, 0, 0, 0));
+    }
     return;
   }
-  const int p0 = j * kSegTile;
-  if (p0 >= L) return;
   const int p1 = (p0 + kSegTile < L) ? p0 + kSegTile : L;
   const int tlen = p1 - p0;
   const int tile = s * p.tiles_per_seq + j;
@@ -376,7 +419,7 @@ __global__ __launch_bounds__(kTileThreads) void seg_tile_kernel(
       const int i = r * kTileThreads + tid;
       oc1[r] = cand.own_cls[seq0 + p0 + (i < tlen ? i : 0)];
     }
-    if (MODE == 1) cand_o = cand.tile_base[tile] + (p.B == 1 ? 0 : cand.cand_cu[s]);
+    if (MODE == 1) cand_o = cand.tile_base[tile] + (p.B == 1 || fold ? 0 : cand.cand_cu[s]);
     else cand_o = tid < j ? cand.tile_count[tile - j + tid] : 0;     // summed below; j < kTileThreads
   }
   // (emit) where the chain is 2, 4, 8 .. chunks after each of the thread's positions, as the first
@@ -556,6 +599,7 @@ __global__ __launch_bounds__(kTileThreads) void seg_tile_kernel(
       const int i = r * kTileThreads + tid;
       my_len[r] = i < tlen ? (int)seg_len[seq0 + p0 + i] : 0;
     }
+    if (fold) sum_before();
     if (cand.tile_count != nullptr) {
       // rank of every candidate of the tile: positions are owned interleaved (i = r * threads +
       // tid), so the order is row r, then wavefront, then lane
@@ -573,6 +617,10 @@ __global__ __launch_bounds__(kTileThreads) void seg_tile_kernel(
         if (lane == 0) cnt[kSegPerThread * kTileWaves + wave] = part;
       }
       __syncthreads();
+      if (fold) {
+        collect_before();
+        cand_o += before.z;
+      }
       if (MODE == 2) {
         cand_o = 0;
 #pragma unroll
@@ -726,6 +774,12 @@ __global__ __launch_bounds__(kTileThreads) void seg_tile_kernel(
 #pragma unroll
   for (int w = 0; w < kTileWaves; ++w)
     if (w < wave) { ob += red[2 * w]; os += red[2 * w + 1]; }
+  if (fold) {
+    collect_before();
+    write_offsets(sq);
+    sq.z = before.x;
+    sq.w = before.y;
+  }
   int gb = sq.z + info.y + ob + ib - nb_local;
   int gs = sq.w + info.z + os + is - ns_local;
 #pragma unroll
@@ -755,9 +809,9 @@ __global__ __launch_bounds__(kChainThreads) void seg_chain_kernel(
   int n_tiles = (L + kSegTile - 1) / kSegTile;
   if (n_tiles > p.tiles_per_seq) n_tiles = p.tiles_per_seq;
   if (threadIdx.x == 0) { carry[0] = 0; carry[1] = 0; carry[2] = 0; }
+  int n_cand = 0;                                     // of the sequence
   if (cand.tile_count != nullptr) {
-    // candidate lists: offset of every tile's candidates inside its sequence, and the sequence's
-    // total (left in cand_cu[s + 1]; the batch scan turns the totals into offsets)
+    // candidate lists: offset of every tile's candidates inside its sequence, and the sequence's total
     const int lane = threadIdx.x & (DSK_WAVE - 1), wave = threadIdx.x / DSK_WAVE;
     int run = 0;
     for (int j0 = 0; j0 < n_tiles; j0 += kChainThreads) {
@@ -777,14 +831,11 @@ __global__ __launch_bounds__(kChainThreads) void seg_chain_kernel(
       run += total;
       __syncthreads();
     }
-    if (threadIdx.x == 0) {
-      if (p.B == 1) {
-        cand.cand_cu[0] = 0;
-        cand.cand_cu[1] = run;
-        if (run > cand.max_cand) set_status(dev_status, DSK_ERR_CAPACITY);
-      } else {
-        cand.cand_cu[s + 1] = run;
-      }
+    n_cand = run;
+    if (threadIdx.x == 0 && p.B == 1) {
+      cand.cand_cu[0] = 0;
+      cand.cand_cu[1] = run;
+      if (run > cand.max_cand) set_status(dev_status, DSK_ERR_CAPACITY);
     }
   }
   if (p.map_row <= kChainFastSpan) {
@@ -841,7 +892,7 @@ __global__ __launch_bounds__(kChainThreads) void seg_chain_kernel(
   }
   __syncthreads();
   if (threadIdx.x == 0) {
-    seq_info[s] = make_int4(carry[1], carry[2], 0, 0);
+    seq_info[s] = make_int4(carry[1], carry[2], p.B == 1 ? 0 : n_cand, 0);
     if (p.B == 1) {   // single sequence: the batch scan is trivial, finish here
       cu_blocks[0] = 0;
       cu_blocks[1] = carry[1];
@@ -852,24 +903,18 @@ __global__ __launch_bounds__(kChainThreads) void seg_chain_kernel(
   }
 }
 
-// ---- scan over the sequences of the batch (B > 1) ----------------------------------------------
+// ---- scan over the sequences of a batch of more than kSeqsFolded -------------------------------
 __global__ __launch_bounds__(64) void seg_seqscan_kernel(
     int4* __restrict__ seq_info, int B, int cap, int total_tokens, int32_t* __restrict__ cu_blocks,
     int32_t* __restrict__ cu_slots, int32_t* __restrict__ block_start, int32_t* __restrict__ slot_base,
     int32_t* cand_cu, int max_cand, int32_t* dev_status) {
   if (threadIdx.x != 0) return;
-  if (cand_cu != nullptr) {   // per-sequence candidate totals (behind each sequence's entry) -> offsets
-    int run = 0;
-    cand_cu[0] = 0;
-    for (int s = 0; s < B; ++s) {
-      run += cand_cu[s + 1];
-      cand_cu[s + 1] = run;
-    }
-    if (run > max_cand) set_status(dev_status, DSK_ERR_CAPACITY);
-  }
-  int blk = 0, slots = 0;
+  int blk = 0, slots = 0, cands = 0;
+  if (cand_cu != nullptr) cand_cu[0] = 0;
   for (int s = 0; s < B; ++s) {
     int4 v = seq_info[s];
+    cands += v.z;
+    if (cand_cu != nullptr) cand_cu[s + 1] = cands;
     cu_blocks[s] = blk;
     if (cu_slots) cu_slots[s] = slots;
     v.z = blk;
@@ -880,6 +925,7 @@ __global__ __launch_bounds__(64) void seg_seqscan_kernel(
   }
   cu_blocks[B] = blk;
   if (cu_slots) cu_slots[B] = slots;
+  if (cand_cu != nullptr && cands > max_cand) set_status(dev_status, DSK_ERR_CAPACITY);
   if (blk > cap) {
     set_status(dev_status, DSK_ERR_CAPACITY);
     return;   // the tables stay self-consistent for the truncated prefix
@@ -966,7 +1012,7 @@ hipError_t launch_segment(const dsk_compress_args& a, const CompressWs& ws, SegC
                                                                       a.cu_slots, a.block_start, a.slot_base,
                                                                       a.dev_status);
   if ((err = hipGetLastError()) != hipSuccess) return err;
-  if (a.B > 1) {
+  if (a.B > kSeqsFolded || (a.B > 1 && ws.tiles_per_seq == 0)) {   // without a tile there is no emit pass
     seg_seqscan_kernel<<<dim3(1), dim3(64), 0, st>>>(seq_info, a.B, a.max_blocks_total, a.total_tokens,
                                                      a.cu_blocks, a.cu_slots, a.block_start, a.slot_base,
                                                      cand.tile_count ? cand.cand_cu : nullptr, cand.max_cand,

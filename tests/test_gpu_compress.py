@@ -383,3 +383,25 @@ def test_tiles_classify_their_own_tokens(n_class, C, delta):
     _check_tables(lean, case.seg)
     nb = int(case.seg.cu_blocks[-1])
     assert torch.equal(lean.ksum[:, :nb], full.ksum[:, :nb])
+
+
+@pytest.mark.parametrize("B", [2, 1023, 1024, 1025])
+def test_sequence_offsets_with_and_without_a_scan_launch(B):
+    """Batches of up to 1024 sequences form their offsets in the emit pass, larger ones in a launch of their own.
+    Empty sequences (the first and the last among them) have no emit pass of their own but their offsets."""
+    dsk = _dsk()
+    rng = np.random.default_rng(B)
+    seqlens = rng.choice([0, 1, 2, 13, 40, 70], size=B)
+    seqlens[rng.integers(1, B - 1) if B > 2 else 0] = 5000           # several tiles
+    seqlens[0 if B > 2 else 1] = 0
+    seqlens[-1] = 0
+    case = gpu_case(5, B=B, Hq=1, Hkv=1, seqlens=[int(x) for x in seqlens], n_class=5, C=24, delta=12, n_queries=1)
+    for want in (True, False):
+        comp = dsk.compress(**case.compress_kwargs(stages=dsk.DSK_STAGE_CANDIDATES | dsk.DSK_STAGE_SEGMENT,
+                                                   token_ids=case.token_ids, delim_ids=case.delim_ids, want_candidates=want))
+        torch.cuda.synchronize()
+        _check_tables(comp, case.seg)
+    comp = dsk.compress(**case.compress_kwargs(stages=dsk.DSK_STAGE_SEGMENT, cand_pos=dev_i32(case.seg.cand_pos),
+                                               cand_class=dev_u8(case.seg.cand_class), cand_cu=dev_i32(case.seg.cand_cu)))
+    torch.cuda.synchronize()
+    _check_tables(comp, case.seg)
