@@ -18,10 +18,12 @@ constexpr int kSumUnroll = 8;  // row-groups of 4 rows in flight per wave
 // eight sequences, 24K to 64K tokens, 8 heads: 361 -> 345 us for the pass from the larger grid, -> 307 us from
 // these stores.  The first selection that follows reads them from memory instead of the memory-side cache: one
 // sequence of 128K tokens, 8 heads, chunks of 32: pass 66.6 -> 62.6 us, pass and selection 78.4 -> 74.7; chunks of 8:
-// pass unchanged, both 180 -> 183.  (Streaming loads of the rows took another 23 us off, and put 30 us on the
-// decode step that follows, which then finds none of K in the memory-side cache: not used.)
-template <bool MEAN, bool STREAM>
-__device__ __forceinline__ void summarize_block(const uint16_t* base, int len, int64_t stride_tok, unsigned ustride,
+// pass unchanged, both 180 -> 183.
+// STREAM_ROWS: the rows are read past the caches too.  The decode step that follows finds in the memory-side cache
+// what was read last (eight sequences, all rows streamed: pass -23 us, step +30), so the launch streams only what
+// would have left that cache again by its end.
+template <bool MEAN, bool STREAM, bool STREAM_ROWS = false>
+__device__ __forceinline__ void summarize_block(const uint16_t* base, int len, int64_t stride_tok, unsigned ustride8,
                                                 uint16_t* o, int g, int c) {
   // MEAN: mn[] holds this lane's running sums instead
   float mn[8], mx[8];
@@ -36,8 +38,8 @@ __device__ __forceinline__ void summarize_block(const uint16_t* base, int len, i
     for (int u = 0; u < kSumUnroll; ++u) {
       int r = 4 * u + g;
       r = r < last ? r : last;     // a repeated row changes neither min nor max
-      const unsigned byte_off = ((unsigned)r * ustride + (unsigned)(c * 8)) * 2u;
-      v[u] = *reinterpret_cast<const uint4*>(rb + byte_off);
+      const unsigned byte_off = (__umul24((unsigned)r, ustride8) + (unsigned)c) * 16u;   // strides are multiples of 8
+      v[u] = load16<STREAM_ROWS>(rb + byte_off);
     }
 #pragma unroll
     for (int u = 0; u < kSumUnroll; ++u) {
@@ -82,19 +84,27 @@ __device__ __forceinline__ void summarize_block(const uint16_t* base, int len, i
   }
 }
 
+// A cache to summarise: K, and V in the same launch when its summaries are wanted.
+struct SumTensor {
+  const uint16_t* X;
+  int64_t stride_tok, stride_head;
+  uint16_t* out;
+};
+
+// One wavefront per (plane, block); the planes are the heads of K, then those of V, `heads` in all and the slower index,
+// so that the wavefronts for which there is no block come last.  `streamed`: planes from the first one whose rows are
+// read past the caches.
 template <bool MEAN, bool STREAM>
 __global__ __launch_bounds__(kSumThreads) void summaries_kernel(
-    const uint16_t* __restrict__ X, int64_t stride_tok, int64_t stride_head, int Hkv,
-    const int32_t* __restrict__ block_start, const int32_t* __restrict__ cu_blocks, int B,
-    const int32_t* __restrict__ blk_range, int cap, int out_rows, int total_tokens, uint16_t* __restrict__ out,
-    int32_t* dev_status) {
+    SumTensor k, SumTensor v, int Hkv, int heads, int streamed, const int32_t* __restrict__ block_start,
+    const int32_t* __restrict__ cu_blocks, int B, const int32_t* __restrict__ blk_range, int cap, int out_rows,
+    int total_tokens, int32_t* dev_status) {
   const int lane = threadIdx.x & (DSK_WAVE - 1);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / DSK_WAVE);   // wave-uniform: scalar registers
   const int g = lane >> 4;   // row group 0..3
   const int c = lane & 15;   // 16-byte column 0..15
   // blocks [i_lo, i_lo + nblk): the whole table, or the range an incremental update rewrote
-  int i_lo = 0;
-  int nblk = 0;
+  int i_lo = 0, nblk;
   if (blk_range != nullptr) {
     i_lo = blk_range[0];
     int i_hi = blk_range[1];
@@ -106,40 +116,56 @@ __global__ __launch_bounds__(kSumThreads) void summaries_kernel(
     if (nblk > cap) nblk = cap;
   }
   if (nblk <= 0) return;
-  const int64_t items = (int64_t)Hkv * nblk;
-  const int64_t nwaves = (int64_t)gridDim.x * kSumWaves;
+  const int64_t items = (int64_t)heads * nblk;
+  const uint32_t nwaves = gridDim.x * kSumWaves;
   int64_t item = (int64_t)blockIdx.x * kSumWaves + wave;
   if (item >= items) return;
-  int h = (int)(item / nblk);
-  int i = i_lo + (int)(item - (int64_t)h * nblk);
-  int s = __builtin_amdgcn_readfirstlane(block_start[i]);
-  int e = __builtin_amdgcn_readfirstlane(block_start[i + 1]);
-  const unsigned ustride = (unsigned)stride_tok;
+  // plane and block: the first by a division, the next ones by adding the quotient and remainder of the step
+  // (the grid has less than 2^32 wavefronts; the results are uniform, which the compiler does not see)
+  const int step_h = __builtin_amdgcn_readfirstlane((int)(nwaves / (uint32_t)nblk));
+  const int step_i = (int)(nwaves - (uint32_t)step_h * (uint32_t)nblk);
+  int h = __builtin_amdgcn_readfirstlane((int)((uint32_t)item / (uint32_t)nblk));
+  int i = (int)((uint32_t)item - (uint32_t)h * (uint32_t)nblk);
+  int s = __builtin_amdgcn_readfirstlane(block_start[i_lo + i]);
+  int e = __builtin_amdgcn_readfirstlane(block_start[i_lo + i + 1]);
   for (;;) {
-    // the bounds of this wave's next item travel with the rows of the current one
+    // the bounds of this wave's next block travel with the rows of the current one
     const int64_t nitem = item + nwaves;
-    const int64_t pitem = nitem < items ? nitem : item;
-    const int nh = (int)(pitem / nblk);
-    const int ni = i_lo + (int)(pitem - (int64_t)nh * nblk);
-    const int ns = __builtin_amdgcn_readfirstlane(block_start[ni]);
-    const int ne = __builtin_amdgcn_readfirstlane(block_start[ni + 1]);
+    const bool more = nitem < items;
+    int nh = h + step_h, ni = i + step_i;
+    if (ni >= nblk) { ni -= nblk; ++nh; }
+    const int pi = i_lo + (more ? ni : i);
+    const int ns = __builtin_amdgcn_readfirstlane(block_start[pi]);
+    const int ne = __builtin_amdgcn_readfirstlane(block_start[pi + 1]);
     const int len = e - s;
-    uint16_t* o = out + ((int64_t)h * out_rows + i) * (2 * DSK_HEAD_DIM);   // out_rows records per head (>= cap)
+    const bool second = h >= Hkv;
+    const int64_t stride_tok = second ? v.stride_tok : k.stride_tok;
+    const int64_t th = second ? h - Hkv : h;
+    uint16_t* o = (second ? v.out : k.out) + (th * out_rows + i_lo + i) * (2 * DSK_HEAD_DIM);   // out_rows records per head (>= cap)
     if (s < 0 || len <= 0 || e > total_tokens) {   // malformed table: defined output, flag it
       if (lane < 32) reinterpret_cast<uint4*>(o)[lane] = make_uint4(0, 0, 0, 0);
       if (lane == 0) set_status(dev_status, DSK_ERR_SHAPE);
     } else {
-      const uint16_t* base = X + (int64_t)h * stride_head + (int64_t)s * stride_tok;   // uniform
-      summarize_block<MEAN, STREAM>(base, len, stride_tok, ustride, o, g, c);
+      const uint16_t* base = (second ? v.X : k.X) + th * (second ? v.stride_head : k.stride_head) + (int64_t)s * stride_tok;   // uniform
+      const unsigned ustride8 = (unsigned)stride_tok >> 3;
+      if (STREAM && h < streamed) summarize_block<MEAN, STREAM, STREAM>(base, len, stride_tok, ustride8, o, g, c);
+      else summarize_block<MEAN, STREAM>(base, len, stride_tok, ustride8, o, g, c);
     }
-    if (nitem >= items) break;
+    if (!more) break;
     item = nitem; h = nh; i = ni; s = ns; e = ne;
   }
 }
 
+// K's planes, then V's, are read one after the other: of those that end well before the last 256 MB nothing is left in
+// the memory-side cache at the end, so their rows are read past it.  K and V of eight sequences, 362K tokens, 8 heads
+// (1.5 GB), pass / first decode step behind it: 316 / 56.0 us as two launches through the cache, 308 / 56.0 as one,
+// 296 / 56.0 with all but the last 400 MB past it, 294 / 57.7 with all but the last 256 MB.
+constexpr int64_t kSumKeptBytes = 400ll << 20;
+
 template <bool MEAN>
 static hipError_t launch_summaries_impl(const dsk_compress_args& a, hipStream_t st) {
-  const int64_t max_items = (int64_t)a.Hkv * a.max_blocks_total;
+  const int heads = (a.vsum != nullptr ? 2 : 1) * a.Hkv;
+  const int64_t max_items = (int64_t)heads * a.max_blocks_total;
   if (max_items <= 0) return hipSuccess;
   int64_t wgs = (max_items + kSumWaves - 1) / kSumWaves;
   // A wavefront per block where there are many: workgroups dealt out as others end stay close together in
@@ -149,25 +175,20 @@ static hipError_t launch_summaries_impl(const dsk_compress_args& a, hipStream_t 
   // where sequences have a C of their own, below this bound).  Where chunks are C tokens long half of them find no
   // block and leave: 69 920 wavefronts for 32 608 blocks at 128K tokens, C = 30.
   // (C is only a hint here: a call of this stage alone may leave it unset.)
-  int64_t max_wgs = a.C > 0 ? (a.C_per_seq != nullptr ? 4 : 2) * (int64_t)a.Hkv * (a.total_tokens / a.C + a.B) / kSumWaves : 0;
+  int64_t max_wgs = a.C > 0 ? (a.C_per_seq != nullptr ? 4 : 2) * (int64_t)heads * (a.total_tokens / a.C + a.B) / kSumWaves : 0;
   if (max_wgs < 256 * 8) max_wgs = 256 * 8;
-  if (max_wgs > 256 * 128) max_wgs = 256 * 128;
+  if (max_wgs > 256 * 256) max_wgs = 256 * 256;
   if (wgs > max_wgs) wgs = max_wgs;
   const int out_rows = a.sum_stride_blocks > 0 ? a.sum_stride_blocks : a.max_blocks_total;
+  const SumTensor k = {static_cast<const uint16_t*>(a.K), a.k_stride_tok, a.k_stride_head, static_cast<uint16_t*>(a.ksum)};
+  const SumTensor v = {static_cast<const uint16_t*>(a.V), a.v_stride_tok, a.v_stride_head, static_cast<uint16_t*>(a.vsum)};
+  const int64_t plane = (int64_t)a.total_tokens * DSK_HEAD_DIM * 2;
+  const int64_t kept = plane > 0 ? (kSumKeptBytes + plane - 1) / plane : 0;
+  const int streamed = heads > kept ? (int)(heads - kept) : 0;
   summaries_kernel<MEAN, true><<<dim3((unsigned)wgs), dim3(kSumThreads), 0, st>>>(
-      static_cast<const uint16_t*>(a.K), a.k_stride_tok, a.k_stride_head, a.Hkv, a.block_start,
-      a.cu_blocks, a.B, nullptr, a.max_blocks_total, out_rows, a.total_tokens, static_cast<uint16_t*>(a.ksum),
+      k, v, a.Hkv, heads, streamed, a.block_start, a.cu_blocks, a.B, nullptr, a.max_blocks_total, out_rows, a.total_tokens,
       a.dev_status);
-  hipError_t err = hipGetLastError();
-  if (err != hipSuccess) return err;
-  if (a.vsum != nullptr) {
-    summaries_kernel<MEAN, true><<<dim3((unsigned)wgs), dim3(kSumThreads), 0, st>>>(
-        static_cast<const uint16_t*>(a.V), a.v_stride_tok, a.v_stride_head, a.Hkv, a.block_start,
-        a.cu_blocks, a.B, nullptr, a.max_blocks_total, out_rows, a.total_tokens, static_cast<uint16_t*>(a.vsum),
-        a.dev_status);
-    err = hipGetLastError();
-  }
-  return err;
+  return hipGetLastError();
 }
 
 hipError_t launch_summaries(const dsk_compress_args& a, hipStream_t st) {
@@ -182,14 +203,13 @@ hipError_t launch_summaries_range(const void* X, int64_t stride_tok, int64_t str
   if (max_items <= 0) return hipSuccess;
   int64_t wgs = (max_items + kSumWaves - 1) / kSumWaves;
   if (wgs > 256 * 8) wgs = 256 * 8;
+  const SumTensor k = {static_cast<const uint16_t*>(X), stride_tok, stride_head, static_cast<uint16_t*>(out)};
   if (summary_mode == DSK_SUMMARY_MEAN)
     summaries_kernel<true, false><<<dim3((unsigned)wgs), dim3(kSumThreads), 0, st>>>(
-        static_cast<const uint16_t*>(X), stride_tok, stride_head, Hkv, block_start, nullptr, 0, blk_range, cap, cap,
-        total_tokens, static_cast<uint16_t*>(out), dev_status);
+        k, k, Hkv, Hkv, 0, block_start, nullptr, 0, blk_range, cap, cap, total_tokens, dev_status);
   else
     summaries_kernel<false, false><<<dim3((unsigned)wgs), dim3(kSumThreads), 0, st>>>(
-        static_cast<const uint16_t*>(X), stride_tok, stride_head, Hkv, block_start, nullptr, 0, blk_range, cap, cap,
-        total_tokens, static_cast<uint16_t*>(out), dev_status);
+        k, k, Hkv, Hkv, 0, block_start, nullptr, 0, blk_range, cap, cap, total_tokens, dev_status);
   return hipGetLastError();
 }
 
@@ -218,7 +238,7 @@ __global__ __launch_bounds__(kSumThreads) void summaries_batch_ranges_kernel(
       if (lane == 0) set_status(dev_status, DSK_ERR_SHAPE);
     } else {
       const uint16_t* base = X + (int64_t)h * stride_head + ((int64_t)rg.z + s) * stride_tok;
-      summarize_block<MEAN, false>(base, len, stride_tok, (unsigned)stride_tok, o, g, c);
+      summarize_block<MEAN, false>(base, len, stride_tok, (unsigned)stride_tok >> 3, o, g, c);
     }
   }
 }

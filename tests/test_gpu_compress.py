@@ -405,3 +405,33 @@ def test_sequence_offsets_with_and_without_a_scan_launch(B):
                                                cand_class=dev_u8(case.seg.cand_class), cand_cu=dev_i32(case.seg.cand_cu)))
     torch.cuda.synchronize()
     _check_tables(comp, case.seg)
+
+
+@pytest.mark.parametrize("mode", [0, 1])
+@pytest.mark.parametrize("layout", ["hnd", "nhd"])
+def test_summaries_with_rows_read_past_the_caches(layout, mode):
+    """K and V of 492 MB in one launch, of which the first planes are read past the caches, against two launches of
+    246 MB that read nothing past them: the same bits, on both sides of the edge."""
+    dsk = _dsk()
+    L, Hkv = 120001, 8
+    g = torch.Generator(device="cuda")
+    g.manual_seed(7)
+    X = [torch.randn(Hkv, L, 128, generator=g, device="cuda").bfloat16() for _ in range(2)]
+    if layout == "nhd":
+        X = [x.permute(1, 0, 2).contiguous().permute(1, 0, 2) for x in X]
+    ends = np.unique(np.concatenate([[0, L], np.cumsum(np.random.default_rng(3).integers(1, 50, size=6000))]))
+    ends = ends[ends <= L]
+    kw = dict(cu_seqlens=dev_i32([0, L]), max_seqlen=L, Hq=Hkv, Hkv=Hkv, total_tokens=L, stages=dsk.DSK_STAGE_SUMMARIES,
+              block_start=dev_i32(ends), cu_blocks=dev_i32([0, len(ends) - 1]), C_=24, delta=12, b=16, summary_mode=mode)
+    both = dsk.compress(K=X[0], V=X[1], want_vsum=True, **kw)
+    one = [dsk.compress(K=x, V=None, **kw) for x in X]
+    torch.cuda.synchronize()
+    nb = len(ends) - 1
+    assert int(both.dev_status.item()) == 0
+    assert torch.equal(both.ksum[:, :nb], one[0].ksum[:, :nb])
+    assert torch.equal(both.vsum[:, :nb], one[1].ksum[:, :nb])
+    if mode == 0:
+        lens = torch.from_numpy(np.diff(ends)).cuda()
+        for h in (0, 7):
+            want = torch.stack([torch.segment_reduce(X[1][h].float(), how, lengths=lens, axis=0) for how in ("min", "max")], 1)
+            assert torch.equal(both.vsum[h, :nb].float(), want)
