@@ -171,11 +171,11 @@ static hipError_t launch_summaries_impl(const dsk_compress_args& a, hipStream_t 
   // A wavefront per block where there are many: workgroups dealt out as others end stay close together in
   // memory, while a persistent grid of 256 * 8 drifts apart (128K tokens, 8 heads: 79 -> 73 us for the pass
   // with the streamed records).  The capacity may be a multiple of the blocks there are, and an empty workgroup
-  // is not free, so the grid is bounded by wavefronts for twice the blocks of chunks of C tokens (four times
-  // where sequences have a C of their own, below this bound).  Where chunks are C tokens long half of them find no
-  // block and leave: 69 920 wavefronts for 32 608 blocks at 128K tokens, C = 30.
+  // is not free, so the grid is bounded by wavefronts for the blocks of chunks of C tokens (twice as many
+  // where sequences have a C of their own, below this bound); where there are more, wavefronts take two or three.
+  // With twice these grids, 128K tokens and K and V of eight sequences: 71.1 against 70.6 us, 289.4 against 288.8.
   // (C is only a hint here: a call of this stage alone may leave it unset.)
-  int64_t max_wgs = a.C > 0 ? (a.C_per_seq != nullptr ? 4 : 2) * (int64_t)heads * (a.total_tokens / a.C + a.B) / kSumWaves : 0;
+  int64_t max_wgs = a.C > 0 ? (a.C_per_seq != nullptr ? 2 : 1) * (int64_t)heads * (a.total_tokens / a.C + a.B) / kSumWaves : 0;
   if (max_wgs < 256 * 8) max_wgs = 256 * 8;
   if (max_wgs > 256 * 256) max_wgs = 256 * 256;
   if (wgs > max_wgs) wgs = max_wgs;
