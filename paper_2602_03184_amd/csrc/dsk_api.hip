@@ -348,7 +348,7 @@ size_t dsk_select_workspace_bytes(const dsk_select_args* a) {
 size_t dsk_attn_workspace_bytes(const dsk_attn_args* a) {
   if (a == nullptr || a->struct_size != sizeof(dsk_attn_args)) return 0;
   if (a->B < 1 || a->Hq < 1 || a->k < 1) return 0;
-  return attn_ws_layout(*a).total;
+  return attn_ws_layout(*a, /*size_only=*/true).total;
 }
 
 size_t dsk_dense_attn_workspace_bytes(const dsk_dense_attn_args* a) {

@@ -48,7 +48,9 @@ __device__ __forceinline__ void store_attn_out(float* __restrict__ out, uint16_t
 
 // Fold 4*NS already-loaded token rows (K rows kv, V rows vv; row 4u+g in kv[u] of lane group g)
 // into the state.  Rows >= nvalid are padding (their loads were redirected to a real row).
-template <int NS>
+// OWN_SUMS: the rows are summed by themselves before they join the state (with the rescaling in one operation): as many
+// instructions, and no longer chain of sums where a state takes many folds.
+template <int NS, bool OWN_SUMS = false>
 __device__ __forceinline__ void fold_loaded(WaveState& st, const QRow& qf, const uint4 (&kv)[NS],
                                             const uint4 (&vv)[NS], int nvalid, int g, float scale_log2) {
   float z[NS];
@@ -62,6 +64,23 @@ __device__ __forceinline__ void fold_loaded(WaveState& st, const QRow& qf, const
   mloc = fmaxf(fmaxf(rows4_f(mloc, 0), rows4_f(mloc, 1)), fmaxf(rows4_f(mloc, 2), rows4_f(mloc, 3)));
   const float m_new = fmaxf(st.m, mloc);           // finite: nvalid >= 1
   const float alpha = exp2_nonpos(st.m - m_new);         // 0 on the first fold (st.m = -inf)
+  if constexpr (OWN_SUMS) {
+    float l, acc[8];
+#pragma unroll
+    for (int u = 0; u < NS; ++u) {
+      const float p = exp2_nonpos(z[u] - m_new);
+      float f[8];
+      unpack8(vv[u], f);
+      l = u == 0 ? p : l + p;
+#pragma unroll
+      for (int k = 0; k < 8; ++k) acc[k] = u == 0 ? p * f[k] : fmaf(p, f[k], acc[k]);
+    }
+    st.l = fmaf(st.l, alpha, l);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) st.acc[k] = fmaf(st.acc[k], alpha, acc[k]);
+    st.m = m_new;
+    return;
+  }
   st.l *= alpha;
 #pragma unroll
   for (int k = 0; k < 8; ++k) st.acc[k] *= alpha;

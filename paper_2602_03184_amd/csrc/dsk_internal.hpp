@@ -82,9 +82,11 @@ struct AttnWs {
   size_t part_acc;  // f32 [B*Hq*nchunks*D]
   size_t total;
   int nchunks;
-  int slots_per_wg;  // slots one attention workgroup folds into one partial (16; 8 for b > 32, and for b <= 16 in launches of many workgroups)
+  int slots_per_wg;  // slots one attention workgroup folds into one partial (16; 8 for b > 32, and for b <= 16 in launches of
+                     // many workgroups; 32 or more for long lists)
+  bool long_lists;   // attn_long_kernel
 };
-AttnWs attn_ws_layout(const dsk_attn_args& a);
+AttnWs attn_ws_layout(const dsk_attn_args& a, bool size_only = false);   // size_only: total
 hipError_t launch_attn(const dsk_attn_args& a, const AttnWs& ws, hipStream_t st);
 // Fixed-order merge of nchunks partials per (sequence, head); chunk c is valid for
 // c < ceil(min(count, k) / per_chunk) where count = counts[s*Hq+h], or the length of sequence s

@@ -16,7 +16,7 @@
 // The launch is a 1-D grid in which workgroup id = 8 * j + x runs on XCD x: all chunks of all
 // query heads of a (sequence, KV head) group are given the same x, so that rows selected by
 // several heads of the group are fetched into one L2 once (9.3 instead of 10.5 us for the call at
-// 128K / 32 heads against a grid that spread a head's chunks over the XCDs).
+// 128K / 32 heads against a grid that spread a head's chunks over the XCDs; see attn_place).
 #include "dsk_attn_fold.hpp"
 #include "dsk_common.hpp"
 #include "dsk_internal.hpp"
@@ -47,6 +47,55 @@ static bool attn_shared_tiled(const dsk_attn_args& a) {
   const int G = a.Hq / a.Hkv;
   return (a.flags & DSK_ATTN_SHARED_SELECTION) && (G == 2 || G == 4 || G == 8) && a.b <= 32 &&
          (int64_t)a.B * a.Hkv * a.k >= kSharedTiledMinSlots;
+}
+
+// The place of a workgroup of the per-head kernels.  Workgroup id = 8 * j + x runs on XCD x.  The chunks of all heads of a
+// KV group go to one XCD; where the groups are no multiple of 8, each is cut into `split` runs of `run` chunks, which go to
+// XCDs of their own, so that all eight have the same work (28 / 4 heads, one sequence: four groups used half of the chip).
+// Without grouped heads there is nothing to share: the chunks are dealt out over the XCDs in plain order (measured 2 %
+// faster at 40 heads than keeping a head on one XCD).
+struct AttnPlace {
+  int split, run;
+};
+struct AttnAt {
+  int s, hk, h, chunk;   // chunk < 0: nothing to do
+};
+__device__ __forceinline__ AttnAt attn_place(AttnPlace p, int Hq, int G, int n_groups, int nchunks) {
+  AttnAt at;
+  if (G == 1) {
+    const int sh = blockIdx.x / nchunks;
+    at.chunk = blockIdx.x - sh * nchunks;
+    at.s = sh / Hq;
+    at.h = at.hk = sh - at.s * Hq;
+    return at;
+  }
+  const int Hkv = Hq / G;
+  const int per = G * p.run;
+  const int j = blockIdx.x >> 3;
+  const int vl = j / per;
+  const int r = j - vl * per;
+  const int v = vl * 8 + (int)(blockIdx.x & 7);      // (group, run)
+  const int gi = p.split == 1 ? v : v / p.split;
+  const int gq = r / p.run;
+  at.chunk = (v - gi * p.split) * p.run + r - gq * p.run;
+  if (gi >= n_groups || at.chunk >= nchunks) at.chunk = -1;   // padding of the last round of groups, or of the last run
+  at.s = gi / Hkv;
+  at.hk = gi - at.s * Hkv;
+  at.h = at.hk * G + gq;
+  return at;
+}
+static AttnPlace attn_placement(int G, int n_groups, int nchunks) {
+  AttnPlace p = {1, nchunks};
+  if (G == 1) return p;
+  while (p.split < 8 && n_groups * p.split % 8 != 0 && 2 * p.split <= nchunks) p.split *= 2;
+  p.run = (nchunks + p.split - 1) / p.split;
+  return p;
+}
+// workgroups on every XCD
+static int64_t attn_wgs_per_xcd(int G, int n_groups, int nchunks) {
+  const AttnPlace p = attn_placement(G, n_groups, nchunks);
+  if (G == 1) return ((int64_t)n_groups * nchunks + 7) / 8;
+  return ((int64_t)n_groups * p.split + 7) / 8 * G * p.run;
 }
 
 // ordinary (compiler-scheduled) loads; used for slots longer than 32 rows
@@ -95,7 +144,7 @@ __global__ __launch_bounds__(WAVES * DSK_WAVE) void attn_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ K, const uint16_t* __restrict__ V,
     int64_t kst, int64_t ksh, int64_t vst, int64_t vsh, int Hq, int G, int n_groups, int k, int b, int total_tokens,
     const int32_t* __restrict__ sel_start, const int32_t* __restrict__ sel_len,
-    const int32_t* __restrict__ sel_count, int sel_div, float scale_log2, int nchunks,
+    const int32_t* __restrict__ sel_count, int sel_div, float scale_log2, AttnPlace place, int nchunks,
     float2* __restrict__ part_ml, float* __restrict__ part_acc, float* __restrict__ out,
     uint16_t* __restrict__ out_bf16, float* __restrict__ lse) {
   constexpr int kAttnWaves = WAVES;
@@ -104,31 +153,9 @@ __global__ __launch_bounds__(WAVES * DSK_WAVE) void attn_kernel(
   __shared__ float sm_acc[kAttnWaves][DSK_HEAD_DIM];
   constexpr int kSlotsPerWg = kAttnWaves * SPW;
 
-  // workgroup id = 8 * j + x lands on XCD x.  Group gi = s * Hkv + hk takes x = gi % 8; its
-  // G * nchunks workgroups are consecutive in j.
-  // Without grouped heads there is nothing to share: the chunks of a head are dealt out over the
-  // XCDs in plain order (measured 2 % faster at 40 heads than keeping a head on one XCD).
-  int s, hk, h, chunk;
-  if (G == 1) {
-    chunk = blockIdx.x % nchunks;
-    const int sh_lin = blockIdx.x / nchunks;
-    s = sh_lin / Hq;
-    h = hk = sh_lin - s * Hq;
-  } else {
-    const int Hkv = Hq / G;
-    const int per_group = G * nchunks;
-    const int xcd = blockIdx.x & 7;
-    const int j = blockIdx.x >> 3;
-    const int gl = j / per_group;
-    const int r = j - gl * per_group;
-    const int gi = gl * 8 + xcd;
-    if (gi >= n_groups) return;                  // padding of the last round of groups
-    s = gi / Hkv;
-    hk = gi - s * Hkv;
-    const int gq = r / nchunks;
-    chunk = r - gq * nchunks;
-    h = hk * G + gq;
-  }
+  const AttnAt at = attn_place(place, Hq, G, n_groups, nchunks);
+  if (at.chunk < 0) return;
+  const int s = at.s, hk = at.hk, h = at.h, chunk = at.chunk;
   const int64_t sh = (int64_t)s * Hq + h;
   // row of the selection arrays: the head's own, or its KV head's when sel_div = Hq/Hkv heads share one
   const int64_t sr = sel_div == 1 ? sh : (int64_t)s * (Hq / sel_div) + h / sel_div;   // no division on the per-head path
@@ -258,6 +285,132 @@ __global__ __launch_bounds__(WAVES * DSK_WAVE) void attn_kernel(
   const int64_t pbase = sh * nchunks;
   part_acc[(pbase + chunk) * DSK_HEAD_DIM + d] = a;
   if (d == 0) part_ml[pbase + chunk] = make_float2(M, l);
+}
+
+// Long lists: one workgroup of kLongWaves wavefronts for every CU, each with many slots of one head (its whole list where
+// there are that many heads, which leaves nothing to merge).  A wavefront takes every kLongWaves-th slot, one after the
+// other; the spans of 64 slots lie one in each lane.  Few rows in flight are what it gains by: the heads of a group stay
+// close together in their lists, and more of the rows they share come from L2.  Eight sequences, 32 / 8 heads, 128 slots of
+// 16 rows: step 55.0 us with a workgroup per 8 slots and the merge, 50.4 with 8 wavefronts (8 steps that follow on one
+// cache 496 -> 470); with two slots of a wavefront in flight 51.9 / 483, with four 51.8 / 494, 4 wavefronts 56.9 / 530,
+// 12 wavefronts 51.8 / 483, 16 52.6 / 499.  40 / 40 heads, 128K tokens, 256 slots of 16 rows: 40.0 -> 38.7 with 6 chunks a
+// head (240 workgroups), 43.5 with 7 (280: the last 24 have the card to themselves).
+constexpr int kLongWaves = 8;
+template <int NS>
+__global__ __launch_bounds__(kLongWaves * DSK_WAVE) void attn_long_kernel(
+    const uint16_t* __restrict__ q, const uint16_t* __restrict__ K, const uint16_t* __restrict__ V,
+    int64_t kst, int64_t ksh, int64_t vst, int64_t vsh, int Hq, int G, int n_groups, int k, int b, int total_tokens,
+    const int32_t* __restrict__ sel_start, const int32_t* __restrict__ sel_len,
+    const int32_t* __restrict__ sel_count, int sel_div, float scale_log2, AttnPlace place, int nchunks, int slots_per_wg,
+    float2* __restrict__ part_ml, float* __restrict__ part_acc, float* __restrict__ out,
+    uint16_t* __restrict__ out_bf16, float* __restrict__ lse) {
+  __shared__ float sm_m[kLongWaves];
+  __shared__ float sm_l[kLongWaves];
+  __shared__ float sm_acc[kLongWaves][DSK_HEAD_DIM];
+  const AttnAt at = attn_place(place, Hq, G, n_groups, nchunks);
+  if (at.chunk < 0) return;
+  const int64_t sh = (int64_t)at.s * Hq + at.h;
+  const int64_t sr = sel_div == 1 ? sh : (int64_t)at.s * (Hq / sel_div) + at.h / sel_div;   // row of the selection arrays
+  const int slot0 = at.chunk * slots_per_wg;
+  const int lane = threadIdx.x & (DSK_WAVE - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / DSK_WAVE);
+  const int g = lane >> 4;
+  const int c = lane & 15;
+
+  int start = 0, len = 0;                        // of the lane-th slot of the wavefront's current 64
+  auto fetch_spans = [&](int first) {
+    const int j = slot0 + (first + lane) * kLongWaves + wave;
+    start = j < k ? sel_start[sr * k + j] : 0;
+    len = j < k ? sel_len[sr * k + j] : 0;
+  };
+  fetch_spans(0);
+  int count = sel_count[sr];
+  const QRow qf = make_qrow(*reinterpret_cast<const uint4*>(q + sh * DSK_HEAD_DIM + c * 8));
+  if (count > k) count = k;
+  if (total_tokens <= 0) count = 0;
+  if (count <= 0) {                              // nothing selected: chunk 0 writes the defined empty result
+    if (at.chunk == 0 && threadIdx.x < DSK_HEAD_DIM) {
+      store_attn_out(out, out_bf16, sh * DSK_HEAD_DIM + threadIdx.x, 0.0f);
+      if (threadIdx.x == 0 && lse) lse[sh] = -__builtin_inff();
+    }
+    return;
+  }
+  if (slot0 >= count) return;
+  const int own = count - slot0 < slots_per_wg ? count - slot0 : slots_per_wg;     // slots of this workgroup
+  const int n = wave < own ? (own - wave + kLongWaves - 1) / kLongWaves : 0;       // of this wavefront
+  const uint16_t* Kh = K + (int64_t)at.hk * ksh;
+  const uint16_t* Vh = V + (int64_t)at.hk * vsh;
+  const unsigned kst8 = (unsigned)kst >> 3, vst8 = (unsigned)vst >> 3;             // strides: multiples of 8, at most 2^24
+
+  WaveState st;
+  st.m = -__builtin_inff();
+  st.l = 0.0f;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) st.acc[i] = 0.0f;
+  for (int first = 0; first < n; first += DSK_WAVE) {
+    if (first > 0) fetch_spans(first);
+    len = len < b ? len : b;
+    len = len < 4 * NS ? len : 4 * NS;
+    if (!(start >= 0 && len > 0 && start <= total_tokens - len)) { start = 0; len = 0; }   // never read outside K/V
+    const int n_here = n - first < DSK_WAVE ? n - first : DSK_WAVE;
+    for (int r = 0; r < n_here; ++r) {
+      const int nv = __builtin_amdgcn_readlane(len, r);
+      if (nv == 0) continue;
+      const int64_t row0 = __builtin_amdgcn_readlane(start, r);
+      const char* kb = reinterpret_cast<const char*>(Kh + row0 * kst);             // uniform
+      const char* vb = reinterpret_cast<const char*>(Vh + row0 * vst);
+      uint4 kd[NS], vd[NS];
+#pragma unroll
+      for (int u = 0; u < NS; ++u) {
+        const int row = 4 * u + g < nv ? 4 * u + g : nv - 1;
+        kd[u] = *reinterpret_cast<const uint4*>(kb + (__umul24((unsigned)row, kst8) + (unsigned)c) * 16u);
+      }
+#pragma unroll
+      for (int u = 0; u < NS; ++u) {
+        const int row = 4 * u + g < nv ? 4 * u + g : nv - 1;
+        vd[u] = *reinterpret_cast<const uint4*>(vb + (__umul24((unsigned)row, vst8) + (unsigned)c) * 16u);
+      }
+#pragma unroll
+      for (int u = 0; u < NS; ++u) pin_loaded(kd[u]);
+#pragma unroll
+      for (int u = 0; u < NS; ++u) pin_loaded(vd[u]);
+      fold_loaded<NS, true>(st, qf, kd, vd, nv, g, scale_log2);
+    }
+  }
+
+  // lane groups -> wave -> workgroup, as in attn_kernel
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    st.acc[i] += shfl_xor_f(st.acc[i], 16);
+    st.acc[i] += shfl_xor_f(st.acc[i], 32);
+  }
+  st.l += shfl_xor_f(st.l, 16);
+  st.l += shfl_xor_f(st.l, 32);
+  if (lane == 0) { sm_m[wave] = st.m; sm_l[wave] = st.l; }
+  if (g == 0) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) sm_acc[wave][c * 8 + i] = st.acc[i];
+  }
+  __syncthreads();
+  const int d = threadIdx.x;
+  if (d >= DSK_HEAD_DIM) return;
+  float M = sm_m[0];
+#pragma unroll
+  for (int w = 1; w < kLongWaves; ++w) M = fmaxf(M, sm_m[w]);
+  float l = 0.0f, a = 0.0f;
+#pragma unroll
+  for (int w = 0; w < kLongWaves; ++w) {
+    const float f = sm_m[w] == -__builtin_inff() ? 0.0f : exp2f(sm_m[w] - M);   // idle wave
+    l = fmaf(sm_l[w], f, l);
+    a = fmaf(sm_acc[w][d], f, a);
+  }
+  if (count <= slots_per_wg) {                   // the only chunk of this head: finish here
+    store_attn_out(out, out_bf16, sh * DSK_HEAD_DIM + d, l > 0.0f ? a / l : 0.0f);
+    if (d == 0 && lse) lse[sh] = l > 0.0f ? (M + log2f(l)) * kLn2 : -__builtin_inff();
+    return;
+  }
+  part_acc[(sh * nchunks + at.chunk) * DSK_HEAD_DIM + d] = a;
+  if (d == 0) part_ml[sh * nchunks + at.chunk] = make_float2(M, l);
 }
 
 // Shared selection (one slot list per KV head, used by all its query heads): a workgroup per
@@ -494,7 +647,28 @@ __global__ __launch_bounds__(kMergeThreads) void attn_merge_kernel(
   }
 }
 
-AttnWs attn_ws_layout(const dsk_attn_args& a) {
+// Whether a call takes attn_long_kernel, and its chunks per head: those that occupy the CUs most evenly (at least to 85 %,
+// in up to four rounds), the fewest of them within 6 %, with at least kLongMinSlots slots in each.  A caller that merges
+// the partials itself keeps the shorter chunks.
+constexpr int kLongMinSlots = 32;
+constexpr int kCusPerXcd = 32;
+static int attn_long_chunks(const dsk_attn_args& a) {
+  if (a.b > 32 || a.Hkv < 1 || (a.flags & DSK_ATTN_PARTIALS_ONLY) || a.k_stride_tok > kMaxTokenStride ||
+      a.v_stride_tok > kMaxTokenStride)
+    return 0;
+  const int G = a.Hq / a.Hkv, n_groups = a.B * a.Hkv;
+  int best = 0;
+  double best_use = 0.85;
+  for (int ch = 1; ch * kLongMinSlots <= a.k; ++ch) {
+    const int64_t rounds = (attn_wgs_per_xcd(G, n_groups, ch) + kCusPerXcd - 1) / kCusPerXcd;
+    if (rounds > 4) break;
+    const double use = (double)a.B * a.Hq * ch / ((double)rounds * kCusPerXcd * 8);
+    if (best == 0 ? use >= best_use : use > best_use + 0.06) { best = ch; best_use = use; }
+  }
+  return best;
+}
+
+AttnWs attn_ws_layout(const dsk_attn_args& a, bool size_only) {
   AttnWs ws;
   ws.slots_per_wg = attn_shared_tiled(a) ? kSharedWaves * kSharedSpw : attn_slots_per_wg(a.b);
   if (!attn_shared_tiled(a) && a.b <= 16 &&
@@ -505,6 +679,13 @@ AttnWs attn_ws_layout(const dsk_attn_args& a) {
   ws.part_ml = 0;
   ws.part_acc = align_up(n * sizeof(float2));
   ws.total = ws.part_acc + align_up(n * DSK_HEAD_DIM * sizeof(float));
+  // fewer, longer chunks: the space asked for stays that of the shorter ones
+  const int chunks = size_only || attn_shared_tiled(a) ? 0 : attn_long_chunks(a);
+  ws.long_lists = chunks > 0 && chunks < ws.nchunks;
+  if (ws.long_lists) {
+    ws.slots_per_wg = (a.k + chunks - 1) / chunks;
+    ws.nchunks = (a.k + ws.slots_per_wg - 1) / ws.slots_per_wg;
+  }
   return ws;
 }
 
@@ -514,8 +695,9 @@ hipError_t launch_attn(const dsk_attn_args& a, const AttnWs& ws, hipStream_t st)
   float* part_acc = reinterpret_cast<float*>(w + ws.part_acc);
   const float scale = a.scale != 0.0f ? a.scale : 0.08838834764831845f;   // 128^-1/2
   const int n_groups = a.B * a.Hkv;
+  const AttnPlace place = attn_placement(a.Hq / a.Hkv, n_groups, ws.nchunks);
   const dim3 grid(a.Hq == a.Hkv ? (unsigned)(n_groups * ws.nchunks)
-                                : (unsigned)(8 * ((n_groups + 7) / 8) * (a.Hq / a.Hkv) * ws.nchunks));
+                                : (unsigned)(8 * attn_wgs_per_xcd(a.Hq / a.Hkv, n_groups, ws.nchunks)));
 
   const uint16_t* q = static_cast<const uint16_t*>(a.q);
   const uint16_t* K = static_cast<const uint16_t*>(a.K);
@@ -545,10 +727,24 @@ hipError_t launch_attn(const dsk_attn_args& a, const AttnWs& ws, hipStream_t st)
     return launch_attn_merge(part_ml, part_acc, a.sel_count, nullptr, a.B, a.Hq, sel_div, a.k, ws.nchunks,
                              ws.slots_per_wg, a.out, static_cast<uint16_t*>(a.out_bf16), a.lse, st);
   }
+  if (ws.long_lists) {
+#define DSK_LONG_ARGS                                                                                          \
+  q, K, V, a.k_stride_tok, a.k_stride_head, a.v_stride_tok, a.v_stride_head, a.Hq, a.Hq / a.Hkv, n_groups, a.k, a.b, \
+      a.total_tokens, a.sel_start, a.sel_len, a.sel_count, sel_div, scale * kLog2e, place, ws.nchunks, ws.slots_per_wg, \
+      part_ml, part_acc, a.out, static_cast<uint16_t*>(a.out_bf16), a.lse
+    const dim3 block(kLongWaves * DSK_WAVE);
+    if (a.b <= 16) attn_long_kernel<4><<<grid, block, 0, st>>>(DSK_LONG_ARGS);
+    else attn_long_kernel<8><<<grid, block, 0, st>>>(DSK_LONG_ARGS);
+#undef DSK_LONG_ARGS
+    const hipError_t lerr = hipGetLastError();
+    if (lerr != hipSuccess || ws.nchunks <= 1 || a.total_tokens <= 0) return lerr;
+    return launch_attn_merge(part_ml, part_acc, a.sel_count, nullptr, a.B, a.Hq, sel_div, a.k, ws.nchunks,
+                             ws.slots_per_wg, a.out, static_cast<uint16_t*>(a.out_bf16), a.lse, st);
+  }
 #define DSK_ATTN_ARGS                                                                                          \
   q, K, V, a.k_stride_tok, a.k_stride_head, a.v_stride_tok, a.v_stride_head, a.Hq, a.Hq / a.Hkv, n_groups, a.k, a.b, \
-      a.total_tokens, a.sel_start, a.sel_len, a.sel_count, sel_div, scale * kLog2e, ws.nchunks, part_ml, part_acc, a.out, \
-      static_cast<uint16_t*>(a.out_bf16), a.lse
+      a.total_tokens, a.sel_start, a.sel_len, a.sel_count, sel_div, scale * kLog2e, place, ws.nchunks, part_ml, part_acc, \
+      a.out, static_cast<uint16_t*>(a.out_bf16), a.lse
   // Slots of at most 32 rows: workgroups of 8 wavefronts, 2 slots each (16 slots per workgroup).
   // Measured against 4 wavefronts x 2 or 4 slots, 8 x 1 or 4, 16 x 1 or 2 on all configurations:
   // the gather takes 7.3 instead of 8.6 us at 128K / b = 32, and 4.6 instead of 5.6 us at

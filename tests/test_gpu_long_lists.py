@@ -1,0 +1,117 @@
+"""The attention kernel for long lists: a workgroup per CU, each with many slots of one head.  Lists given directly (no
+selection in front), against attention over the same rows in 64 bits."""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+from dsk_testutil import dev_i32, rel_err
+
+pytestmark = pytest.mark.gpu
+
+
+def _lists(rng, B, H, k, b, L, counts):
+    start, length = np.zeros((B, H, k), np.int32), np.zeros((B, H, k), np.int32)
+    for s in range(B):
+        for h in range(H):
+            n = int(counts[s, h])
+            length[s, h, :n] = rng.integers(1, b + 1, size=n)
+            start[s, h, :n] = np.sort(rng.integers(0, L - b, size=n))
+            length[s, h, n:] = b                      # behind the count: not to be read
+    return start, length
+
+
+def _want(q, K, V, start, length, counts, div):
+    B, Hq, _ = q.shape
+    G = Hq // K.shape[0]
+    out, lse = np.zeros((B, Hq, 128)), np.full((B, Hq), -np.inf)
+    qd, Kd, Vd = q.double(), K.double(), V.double()
+    for s in range(B):
+        for h in range(Hq):
+            n = int(counts[s, h // div])
+            if n == 0:
+                continue
+            rows = np.concatenate([np.arange(a, a + l) for a, l in zip(start[s, h // div, :n], length[s, h // div, :n])])
+            rows = torch.from_numpy(rows).cuda()
+            z = Kd[h // G][rows] @ qd[s, h] / math.sqrt(128.0)
+            lse[s, h] = float(torch.logsumexp(z, 0))
+            out[s, h] = (torch.softmax(z, 0) @ Vd[h // G][rows]).cpu().numpy()
+    return out, lse
+
+
+# (B, Hq, Hkv, k, b): one list a head with 32 slots, one more, a slot count beyond the 64 spans of a wavefront; several
+# chunks; runs of chunks on XCDs of their own (4, 2, 1 and 3 groups); heads without groups; several rounds of workgroups
+SHAPES = [(8, 32, 8, 32, 16, True), (8, 32, 8, 33, 16, True), (8, 32, 8, 545, 8, True), (2, 32, 8, 131, 32, True),
+          (1, 28, 4, 257, 16, True), (1, 16, 2, 515, 8, True), (1, 8, 1, 129, 16, False), (1, 40, 40, 200, 16, True),
+          (3, 6, 1, 40, 16, False), (8, 40, 8, 97, 16, True), (3, 16, 2, 16, 32, False), (1, 28, 4, 40, 64, False)]
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,k,b,is_long", SHAPES)
+@pytest.mark.parametrize("layout", ["hnd", "nhd"])
+def test_long_lists(B, Hq, Hkv, k, b, is_long, layout):
+    import paper_2602_03184_amd as dsk
+    rng = np.random.default_rng([B, Hq, Hkv, k, b])
+    g = torch.Generator(device="cuda")
+    g.manual_seed(k)
+    L = 3001
+    K, V = (torch.randn(Hkv, L, 128, generator=g, device="cuda").bfloat16() for _ in range(2))
+    if layout == "nhd":
+        K, V = (x.permute(1, 0, 2).contiguous().permute(1, 0, 2) for x in (K, V))
+    q = torch.randn(B, Hq, 128, generator=g, device="cuda").bfloat16()
+    for shared in (False, True):
+        H = Hkv if shared else Hq
+        if shared and (Hq == Hkv or B * Hkv * k >= 4096):          # those run on a kernel of their own
+            continue
+        counts = np.minimum(k, rng.integers(0, 2 * k, size=(B, H)))
+        counts.flat[-1], counts.flat[0] = 0, k
+        start, length = _lists(rng, B, H, k, b, L, counts)
+        flags = dsk.DSK_ATTN_SHARED_SELECTION if shared else 0
+        att = dsk.make_attn_args(q, K, V, dev_i32(start), dev_i32(length), dev_i32(counts), b, flags=flags, want_bf16=True)
+        lay = dsk.dsk_attn_partials_layout(att.args)
+        assert (lay.slots_per_chunk >= 32) == is_long and lay.nchunks * lay.slots_per_chunk >= k
+        att.out.fill_(7.0)
+        dsk.dsk_sparse_decode_attn(att.args)
+        again = dsk.make_attn_args(q, K, V, dev_i32(start), dev_i32(length), dev_i32(counts), b, flags=flags)
+        dsk.dsk_sparse_decode_attn(again.args)
+        torch.cuda.synchronize()
+        out, lse = _want(q, K, V, start, length, counts, Hq // H)
+        # 32-bit sums of some thousand products and softmax terms: a few 1e-6 of the largest output
+        assert rel_err(att.out.cpu().numpy(), out) <= 1e-5
+        got = att.lse.cpu().numpy()
+        np.testing.assert_allclose(got, lse, rtol=0, atol=1e-5)           # -inf where nothing is selected
+        assert torch.equal(att.out.bfloat16(), att.out_bf16)
+        assert torch.equal(att.out, again.out) and torch.equal(att.lse, again.lse)
+
+
+def test_long_lists_skip_spans_outside_the_cache():
+    """Slots whose span leaves the cache, or is empty, add nothing; a caller that merges itself keeps its short chunks."""
+    import paper_2602_03184_amd as dsk
+    B, Hq, Hkv, k, b, L = 8, 32, 8, 64, 16, 1000
+    rng = np.random.default_rng(5)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(5)
+    K, V = (torch.randn(Hkv, L, 128, generator=g, device="cuda").bfloat16() for _ in range(2))
+    q = torch.randn(B, Hq, 128, generator=g, device="cuda").bfloat16()
+    counts = np.full((B, Hq), k)
+    start, length = _lists(rng, B, Hq, k, b, L, counts)
+    keep = rng.random((B, Hq, k)) < 0.7
+    keep[0, 0] = False                                             # a head with nothing left
+    bad_start = np.where(keep, start, rng.choice([-1, L - 1, L, 2 ** 30], size=start.shape)).astype(np.int32)
+    bad_len = np.where(keep | (bad_start != L - 1), length, 2).astype(np.int32)
+    att = dsk.make_attn_args(q, K, V, dev_i32(bad_start), dev_i32(bad_len), dev_i32(counts), b)
+    dsk.dsk_sparse_decode_attn(att.args)
+    torch.cuda.synchronize()
+    cut = np.zeros((B, Hq), np.int64)
+    s2, l2 = np.zeros_like(start), np.zeros_like(length)
+    for s in range(B):
+        for h in range(Hq):
+            n = cut[s, h] = int(keep[s, h].sum())
+            s2[s, h, :n], l2[s, h, :n] = start[s, h][keep[s, h]], length[s, h][keep[s, h]]
+    out, lse = _want(q, K, V, s2, l2, cut, 1)
+    assert rel_err(att.out.cpu().numpy(), out) <= 1e-5
+    assert np.isinf(att.lse.cpu().numpy()[0, 0]) and float(att.out[0, 0].abs().max()) == 0.0
+    assert dsk.dsk_attn_partials_layout(att.args).nchunks == 1
+    part = dsk.make_attn_args(q, K, V, dev_i32(start), dev_i32(length), dev_i32(counts), b, flags=dsk.DSK_ATTN_PARTIALS_ONLY)
+    assert dsk.dsk_attn_partials_layout(part.args).nchunks > 1
+    assert part.args.workspace_bytes == att.args.workspace_bytes
