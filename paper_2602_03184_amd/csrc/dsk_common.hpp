@@ -66,6 +66,9 @@ __device__ __forceinline__ void pin_loaded(T& v) {
   asm volatile("" : "+v"(v.x), "+v"(v.y), "+v"(v.z), "+v"(v.w)::"memory");
 }
 
+// the same with the vector as one operand: its registers stay together
+__device__ __forceinline__ void pin_loaded(u32x4_t& v) { asm volatile("" : "+v"(v)::"memory"); }
+
 // ---- wavefront (64 lanes) helpers ------------------------------------------------------
 __device__ __forceinline__ float shfl_xor_f(float v, int mask) { return __shfl_xor(v, mask, DSK_WAVE); }
 __device__ __forceinline__ int shfl_xor_i(int v, int mask) { return __shfl_xor(v, mask, DSK_WAVE); }

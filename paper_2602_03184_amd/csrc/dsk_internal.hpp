@@ -77,6 +77,7 @@ hipError_t launch_scores(const dsk_select_args& a, float* scores, int stride, hi
 hipError_t launch_select(const dsk_select_args& a, const float* scores, int stride, hipStream_t st);
 
 // ---- dsk_sparse_decode_attn -----------------------------------------------------------------
+enum class AttnKernel { kShort, kLong, kShared };   // attn_kernel, attn_long_kernel, attn_shared_kernel
 struct AttnWs {
   size_t part_ml;   // float2 [B*Hq*nchunks]  (running max in log2 units, denominator)
   size_t part_acc;  // f32 [B*Hq*nchunks*D]
@@ -84,7 +85,7 @@ struct AttnWs {
   int nchunks;
   int slots_per_wg;  // slots one attention workgroup folds into one partial (16; 8 for b > 32, and for b <= 16 in launches of
                      // many workgroups; 32 or more for long lists)
-  bool long_lists;   // attn_long_kernel
+  AttnKernel kernel;
 };
 AttnWs attn_ws_layout(const dsk_attn_args& a, bool size_only = false);   // size_only: total
 hipError_t launch_attn(const dsk_attn_args& a, const AttnWs& ws, hipStream_t st);

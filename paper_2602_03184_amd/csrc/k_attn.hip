@@ -1,12 +1,13 @@
 // Sparse decode attention over the K/V rows of the selected slots (App. B.2 Steps 2-3):
 // a split-K flash-decode.  The gather is HBM-bound (512 B of K+V per token, ~2 flop/B), so
-// there is no MFMA here: a 256-byte bf16 row is spread over 16 lanes x 16 B and a wavefront
+// there is no MFMA in the kernels per head: a 256-byte bf16 row is spread over 16 lanes x 16 B and a wavefront
 // reads 4 token rows per load instruction.  A wavefront owns SPW slots of at most 4*NS rows; it
 // issues every K and V load of a slot (16 x 16 B per lane, 16 KB per wavefront for 32 rows)
 // before it touches the data, then folds the slot into an online-softmax state (m, l, acc).
 // The wavefronts of a workgroup (8 for slots of up to 32 rows, 2 slots each) merge through LDS
 // into one partial per (sequence, head, chunk of 16 slots); a second small kernel merges the
-// partials of a head in a fixed order.  (Merging inside this kernel -- the workgroup of a head that
+// partials of a head in a fixed order; attn_long_kernel and attn_shared_kernel below take long lists and lists that a
+// KV group shares.  (Merging inside this kernel -- the workgroup of a head that
 // finishes last, found with an arrival counter, folds the head's partials -- was built three ways:
 // write-through partials with a device-scope counter, ordinary stores with a device-scope counter,
 // ordinary stores with a counter that stays in the XCD's L2.  At 128K / 32 heads the attention call
@@ -33,21 +34,16 @@ __host__ __device__ constexpr int attn_slots_per_wg(int b) { return b <= 32 ? 16
 // 32K or 128K tokens: step +0.2 us), so the shape follows the workgroup count.
 constexpr int64_t kAttnSmallWgFrom = 1536;   // workgroups of 16 slots from which 8-slot workgroups are launched
 
-// Shared selection: the tiled kernel (attn_shared_kernel, WAVES x SPW slots per workgroup) takes
-// group widths 2, 4, 8 and slots of at most 32 rows.  It reads every selected row once, where
-// attn_kernel run per query head reads it once per head with all but the first read served by
-// L2; that is as fast while the launch is small (config 3, 1024 selected slots per step:
-// 5.9 us either way, and 8 instead of 16 partials to merge), and slower from a few thousand
-// slots on (8 sequences of config 5, 8192 slots: 15.3 against 18.6 us), so the tiled kernel is
-// used from 4096 slots per step.  Measured against 4 x 1, 8 x 1 and 8 x 2.
-constexpr int kSharedWaves = 4;
-constexpr int kSharedSpw = 2;
-constexpr int64_t kSharedTiledMinSlots = 4096;
-static bool attn_shared_tiled(const dsk_attn_args& a) {
-  const int G = a.Hq / a.Hkv;
-  return (a.flags & DSK_ATTN_SHARED_SELECTION) && (G == 2 || G == 4 || G == 8) && a.b <= 32 &&
-         (int64_t)a.B * a.Hkv * a.k >= kSharedTiledMinSlots;
+// Shared selection: attn_shared_kernel reads every selected row once, where attn_kernel run per query head reads it once
+// per head with all but the first read served by L2, which is as fast while the launch is small (step of 32 / 8 heads at
+// 30K tokens, 128 slots of 16 rows, per head / shared: one sequence 16.2 / 19.3 us, two 20.4 / 21.0, three 24.5 / 22.4).
+constexpr int64_t kSharedMinSlots = 3072;      // selected slots of all lists
+static bool attn_shared(const dsk_attn_args& a) {
+  return (a.flags & DSK_ATTN_SHARED_SELECTION) && a.Hq > a.Hkv && a.b <= 32 && (int64_t)a.B * a.Hkv * a.k >= kSharedMinSlots &&
+         a.k_stride_tok <= kMaxTokenStride && a.v_stride_tok <= kMaxTokenStride;
 }
+// heads of a group that a workgroup takes together
+static int attn_shared_tile(int G) { return G <= 2 ? 2 : G <= 4 ? 4 : 8; }
 
 // The place of a workgroup of the per-head kernels.  Workgroup id = 8 * j + x runs on XCD x.  The chunks of all heads of a
 // KV group go to one XCD; where the groups are no multiple of 8, each is cut into `split` runs of `run` chunks, which go to
@@ -296,6 +292,10 @@ __global__ __launch_bounds__(WAVES * DSK_WAVE) void attn_kernel(
 // 12 wavefronts 51.8 / 483, 16 52.6 / 499.  40 / 40 heads, 128K tokens, 256 slots of 16 rows: 40.0 -> 38.7 with 6 chunks a
 // head (240 workgroups), 43.5 with 7 (280: the last 24 have the card to themselves).
 constexpr int kLongWaves = 8;
+constexpr int kLongMinSlots = 32;       // of a workgroup
+constexpr int kLongMinSlotsShared = 256; // of a list that a group shares: its heads meet in L2 anyway (two sequences of 30K
+                                        // tokens, 28 / 4 heads, 128 slots 20.3 -> 20.8 us; one, 16 / 2, 512 slots 32.3 -> 18.9)
+constexpr int kSharedChunkSlots = 16;   // of a workgroup of attn_shared_kernel
 template <int NS>
 __global__ __launch_bounds__(kLongWaves * DSK_WAVE) void attn_long_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ K, const uint16_t* __restrict__ V,
@@ -351,11 +351,11 @@ __global__ __launch_bounds__(kLongWaves * DSK_WAVE) void attn_long_kernel(
     if (first > 0) fetch_spans(first);
     len = len < b ? len : b;
     len = len < 4 * NS ? len : 4 * NS;
-    if (!(start >= 0 && len > 0 && start <= total_tokens - len)) { start = 0; len = 0; }   // never read outside K/V
-    const int n_here = n - first < DSK_WAVE ? n - first : DSK_WAVE;
-    for (int r = 0; r < n_here; ++r) {
+    // slots that exist and do not leave K/V
+    unsigned long long todo = __ballot(first + lane < n && start >= 0 && len > 0 && start <= total_tokens - len);
+    for (; todo != 0; todo &= todo - 1) {
+      const int r = __builtin_ctzll(todo);
       const int nv = __builtin_amdgcn_readlane(len, r);
-      if (nv == 0) continue;
       const int64_t row0 = __builtin_amdgcn_readlane(start, r);
       const char* kb = reinterpret_cast<const char*>(Kh + row0 * kst);             // uniform
       const char* vb = reinterpret_cast<const char*>(Vh + row0 * vst);
@@ -413,50 +413,110 @@ __global__ __launch_bounds__(kLongWaves * DSK_WAVE) void attn_long_kernel(
   if (d == 0) part_ml[sh * nchunks + at.chunk] = make_float2(M, l);
 }
 
-// Shared selection (one slot list per KV head, used by all its query heads): a workgroup per
-// (chunk of WAVES*SPW slots, KV head x tile of GT query heads, sequence).  Every K/V row a
-// wavefront loads is folded into the GT heads' states, so the group's rows are read once instead
-// of once per query head.  Same partial layout as attn_kernel (one partial per query head and
-// chunk), merged by attn_merge_kernel.
-template <int NS, int SPW, int WAVES, int GT>
-__global__ __launch_bounds__(WAVES * DSK_WAVE) void attn_shared_kernel(
+// ---- shared selection: one slot list per KV head, used by all its query heads -------------------
+// A row is folded into the GT = 2, 4 or 8 heads of the group, which makes the vector ALU the bound of a plain fold: 520
+// instructions per slot of 16 rows and 4 heads.  Here the logits come from the matrix cores (16 rows x up to 16 heads:
+// four 16x16x32 products per 16 rows, of which the heads use GT columns, repeated over the 16), which leaves a lane with
+// four logits of one head instead of every lane with all of them; the weights go back to the rows' lanes by swapping
+// halves and rows of the wavefront (a 4 x 4 transposition of registers and lane groups) and are broadcast inside a row of
+// 16 lanes.  About 250 instructions.  The sums over V stay in fp32 on the vector ALU.
+// A workgroup of kLongWaves wavefronts for every CU, as in attn_long_kernel.  Steps at 30K tokens, 128 slots of 16 rows a
+// list, before (two slots per wavefront, heads in tiles of 2 or 4, other widths per head) and now: eight sequences of
+// 32 / 8 heads 33.1 -> 30.1 us, of 28 / 4 heads 36.4 -> 29.8; 512 slots of 8 rows 62.0 -> 46.8 and 75.5 -> 41.5.
+typedef __attribute__((ext_vector_type(8))) __bf16 attn_bf16x8;
+typedef __attribute__((ext_vector_type(4))) float attn_f32x4;
+typedef __attribute__((ext_vector_type(2))) unsigned attn_u32x2;
+
+// the 4 x 4 transposition: register i of lane group u (16 lanes each) <-> register u of lane group i
+__device__ __forceinline__ void transpose_groups(float (&p)[4]) {
+  auto swap32 = [](float& x, float& y) {   // upper half of x <-> lower half of y
+    const attn_u32x2 r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+    x = __uint_as_float(r.x); y = __uint_as_float(r.y);
+  };
+  auto swap16 = [](float& x, float& y) {   // groups 1 and 3 of x <-> groups 0 and 2 of y
+    const attn_u32x2 r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+    x = __uint_as_float(r.x); y = __uint_as_float(r.y);
+  };
+  swap32(p[0], p[2]); swap32(p[1], p[3]);
+  swap16(p[0], p[1]); swap16(p[2], p[3]);
+}
+// maximum over the four lane groups, in every lane
+__device__ __forceinline__ float groups_max(float v) {
+  attn_u32x2 r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = fmaxf(__uint_as_float(r.x), __uint_as_float(r.y));
+  r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return fmaxf(__uint_as_float(r.x), __uint_as_float(r.y));
+}
+constexpr int kDppRowBcast = 0x150;        // + n: lane n of a row of 16 -> every lane of the row
+
+// acc[j][k] *= lane j of the row: alpha;  acc[j][k] += (lane j of the row: p) * v[k]
+template <int GT, int J = 0>
+__device__ __forceinline__ void rescale(float (&acc)[GT][8], float alpha) {
+  if constexpr (J < GT) {
+    const float a = dpp_f<kDppRowBcast + J>(alpha);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) acc[J][k] *= a;
+    rescale<GT, J + 1>(acc, alpha);
+  }
+}
+template <int GT, int J = 0>
+__device__ __forceinline__ void add_row(float (&acc)[GT][8], float p, const float (&f)[8]) {
+  if constexpr (J < GT) {
+    const float w = dpp_f<kDppRowBcast + J>(p);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) acc[J][k] = fmaf(w, f[k], acc[J][k]);
+    add_row<GT, J + 1>(acc, p, f);
+  }
+}
+
+// NT: 16-row tiles of a slot; GT: query heads of a tile of the group (the last tile of a group may have fewer; the columns
+// of those it does not have repeat its first one).  grid: chunk, fastest, then head tile, KV head, sequence
+template <int NT, int GT>
+__global__ __launch_bounds__(kLongWaves * DSK_WAVE) void attn_shared_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ K, const uint16_t* __restrict__ V,
     int64_t kst, int64_t ksh, int64_t vst, int64_t vsh, int Hq, int G, int k, int b, int total_tokens,
     const int32_t* __restrict__ sel_start, const int32_t* __restrict__ sel_len,
-    const int32_t* __restrict__ sel_count, float scale_log2, int nchunks,
+    const int32_t* __restrict__ sel_count, float scale_log2, int nchunks, int slots_per_wg,
     float2* __restrict__ part_ml, float* __restrict__ part_acc, float* __restrict__ out,
     uint16_t* __restrict__ out_bf16, float* __restrict__ lse) {
-  static_assert(NS > 0, "slots of at most 4*NS rows");
-  __shared__ float sm_m[WAVES][GT];
-  __shared__ float sm_l[WAVES][GT];
-  __shared__ float sm_acc[WAVES][GT][DSK_HEAD_DIM];
-  constexpr int kSlotsPerWg = WAVES * SPW;
-
-  const int chunk = blockIdx.x;
-  const int tiles_g = G / GT;
-  const int hk = blockIdx.y / tiles_g;
-  const int h0 = hk * G + (blockIdx.y % tiles_g) * GT;     // first query head of this tile
-  const int s = blockIdx.z;
-  const int64_t sr = (int64_t)s * (Hq / G) + hk;            // row of the selection arrays
-  const int64_t sh0 = (int64_t)s * Hq + h0;
+  static_assert(GT <= 8 && 16 % GT == 0, "the heads repeat over the 16 columns of a product");
+  __shared__ float sm_m[kLongWaves][GT];
+  __shared__ float sm_l[kLongWaves][GT];
+  __shared__ float sm_acc[kLongWaves][GT][DSK_HEAD_DIM];
+  const int tiles = (G + GT - 1) / GT;
+  const int list = blockIdx.x / nchunks;
+  const int chunk = blockIdx.x - list * nchunks;
+  const int sr = list / tiles;                              // row of the selection arrays: (sequence, KV head)
+  const int hk = sr % (Hq / G);
+  const int h0 = (list - sr * tiles) * GT;
+  const int heads = G - h0 < GT ? G - h0 : GT;              // of this tile
+  const int64_t sh0 = (int64_t)sr * G + h0;                 // first of them, over all sequences
+  const int slot0 = chunk * slots_per_wg;
   const int lane = threadIdx.x & (DSK_WAVE - 1);
-  const int wave = threadIdx.x / DSK_WAVE;
-  const int slot0 = chunk * kSlotsPerWg;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / DSK_WAVE);
+  const int g = lane >> 4;
+  const int c = lane & 15;
 
+  int start = 0, len = 0;                        // of the lane-th slot of the wavefront's current 64
+  auto fetch_spans = [&](int first) {
+    const int j = slot0 + (first + lane) * kLongWaves + wave;
+    start = j < k ? sel_start[(int64_t)sr * k + j] : 0;
+    len = j < k ? sel_len[(int64_t)sr * k + j] : 0;
+  };
+  fetch_spans(0);
   int count = sel_count[sr];
-  int st_[SPW], ln_[SPW];
+  // operand of the queries: column c = head c % GT, channels 32 i + 8 g .. + 8
+  attn_bf16x8 qf[4];
 #pragma unroll
-  for (int r = 0; r < SPW; ++r) {
-    const int j = slot0 + wave + WAVES * r;
-    st_[r] = j < k ? sel_start[sr * k + j] : 0;
-    ln_[r] = j < k ? sel_len[sr * k + j] : 0;
-  }
+  for (int i = 0; i < 4; ++i)
+    qf[i] = *reinterpret_cast<const attn_bf16x8*>(q + (sh0 + (c % GT < heads ? c % GT : 0)) * DSK_HEAD_DIM + 32 * i + 8 * g);
   if (count > k) count = k;
-  if (total_tokens <= 0) count = 0;   // no K/V row exists: not even the redirected loads of skipped slots may run
+  if (total_tokens <= 0) count = 0;   // no K/V row exists
   if (count <= 0) {   // nothing selected: chunk 0 writes the defined empty result of the tile's heads
     if (chunk == 0 && threadIdx.x < DSK_HEAD_DIM) {
 #pragma unroll
       for (int j = 0; j < GT; ++j) {
+        if (j >= heads) break;
         store_attn_out(out, out_bf16, (sh0 + j) * DSK_HEAD_DIM + threadIdx.x, 0.0f);
         if (threadIdx.x == 0 && lse) lse[sh0 + j] = -__builtin_inff();
       }
@@ -464,100 +524,131 @@ __global__ __launch_bounds__(WAVES * DSK_WAVE) void attn_shared_kernel(
     return;
   }
   if (slot0 >= count) return;
-  const int used = (count + kSlotsPerWg - 1) / kSlotsPerWg;
+  const int own = count - slot0 < slots_per_wg ? count - slot0 : slots_per_wg;     // slots of this workgroup
+  const int n = wave < own ? (own - wave + kLongWaves - 1) / kLongWaves : 0;       // of this wavefront
+  const uint16_t* Kh = K + (int64_t)hk * ksh;
+  const uint16_t* Vh = V + (int64_t)hk * vsh;
+  const unsigned kst8 = (unsigned)kst >> 3, vst8 = (unsigned)vst >> 3;             // strides: multiples of 8, at most 2^24
 
-  const int g = lane >> 4;
-  const int c = lane & 15;
-  QRow qf[GT];
+  // of head c % GT: reference, this lane group's part of the denominator; of all heads: channels 8c .. of this group's rows
+  float m = -__builtin_inff(), l = 0.0f, acc[GT][8];
 #pragma unroll
-  for (int j = 0; j < GT; ++j) qf[j] = make_qrow(*reinterpret_cast<const uint4*>(q + (sh0 + j) * DSK_HEAD_DIM + c * 8));
-  const uint16_t* Kh = K + (int64_t)hk * ksh + c * 8;
-  const uint16_t* Vh = V + (int64_t)hk * vsh + c * 8;
+  for (int j = 0; j < GT; ++j)
+#pragma unroll
+    for (int i = 0; i < 8; ++i) acc[j][i] = 0.0f;
 
-  WaveState st[GT];
+  for (int first = 0; first < n; first += DSK_WAVE) {
+    if (first > 0) fetch_spans(first);
+    len = len < b ? len : b;
+    len = len < 16 * NT ? len : 16 * NT;
+    // slots that exist and do not leave K/V
+    unsigned long long todo = __ballot(first + lane < n && start >= 0 && len > 0 && start <= total_tokens - len);
+    for (; todo != 0; todo &= todo - 1) {
+      const int r = __builtin_ctzll(todo);
+      const int nv = __builtin_amdgcn_readlane(len, r);
+      const int64_t row0 = __builtin_amdgcn_readlane(start, r);
+      const char* kb = reinterpret_cast<const char*>(Kh + row0 * kst);             // uniform
+      const char* vb = reinterpret_cast<const char*>(Vh + row0 * vst);
+      // K as operand: row c of the tile, channels 32 i + 8 g .. + 8; V as rows 4 u + g, channels 8 c .. + 8.  Rows behind
+      // the slot's last one repeat it.
+      u32x4_t kd[NT][4], vd[4 * NT];
 #pragma unroll
-  for (int j = 0; j < GT; ++j) {
-    st[j].m = -__builtin_inff();
-    st[j].l = 0.0f;
+      for (int t = 0; t < NT; ++t) {
+        const int row = 16 * t + c < nv ? 16 * t + c : nv - 1;
+        const unsigned at = (__umul24((unsigned)row, kst8) + (unsigned)g) * 16u;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) st[j].acc[i] = 0.0f;
+        for (int i = 0; i < 4; ++i) kd[t][i] = *reinterpret_cast<const u32x4_t*>(kb + at + 64 * i);
+      }
+#pragma unroll
+      for (int u = 0; u < 4 * NT; ++u) {
+        const int row = 4 * u + g < nv ? 4 * u + g : nv - 1;
+        vd[u] = *reinterpret_cast<const u32x4_t*>(vb + (__umul24((unsigned)row, vst8) + (unsigned)c) * 16u);
+      }
+#pragma unroll
+      for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) pin_loaded(kd[t][i]);
+#pragma unroll
+      for (int u = 0; u < 4 * NT; ++u) pin_loaded(vd[u]);
+      // z[t][i]: logit of row 16 t + 4 g + i against head c % GT
+      float z[NT][4];
+      float top = -__builtin_inff();
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+        // four products of 32 channels, added here: as one chain through the accumulator the outputs are 20 % further
+        // from 64 bits than with the packed dot instruction, this way 4 % nearer
+        const attn_f32x4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
+        attn_f32x4 d[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          d[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(attn_bf16x8, kd[t][i]), qf[i], zero, 0, 0, 0);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const float sum = (d[0][i] + d[1][i]) + (d[2][i] + d[3][i]);
+          z[t][i] = 16 * t + 4 * g + i < nv ? sum * scale_log2 : -__builtin_inff();
+          top = fmaxf(top, z[t][i]);
+        }
+      }
+      const float m_new = fmaxf(m, groups_max(top));      // finite: nv >= 1
+      const float alpha = exp2_nonpos(m - m_new);         // 0 on the first fold
+      m = m_new;
+      float part = 0.0f;
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) { z[t][i] = exp2_nonpos(z[t][i] - m_new); part += z[t][i]; }   // 0 for padded rows
+        transpose_groups(z[t]);                           // z[t][u]: weight of row 16 t + 4 u + g
+      }
+      l = fmaf(l, alpha, part);
+      rescale<GT>(acc, alpha);
+#pragma unroll
+      for (int u = 0; u < 4 * NT; ++u) {
+        float f[8];
+        unpack8(make_uint4(vd[u].x, vd[u].y, vd[u].z, vd[u].w), f);
+        add_row<GT>(acc, z[u / 4][u % 4], f);
+      }
+    }
   }
 
-  uint4 kd[SPW][NS], vd[SPW][NS];
-  int nv[SPW];
-#pragma unroll
-  for (int r = 0; r < SPW; ++r) {
-    const int j = slot0 + wave + WAVES * r;
-    int start = st_[r];
-    int len = ln_[r] < b ? ln_[r] : b;
-    len = len < 4 * NS ? len : 4 * NS;
-    const bool ok = j < count && start >= 0 && len > 0 && start <= total_tokens - len;   // never read outside K/V
-    nv[r] = ok ? len : 0;
-    start = ok ? start : 0;
-    len = ok ? len : 1;
-#pragma unroll
-    for (int u = 0; u < NS; ++u) {
-      int row = 4 * u + g;
-      row = row < len ? row : len - 1;
-      kd[r][u] = *reinterpret_cast<const uint4*>(Kh + (int64_t)(start + row) * kst);
-    }
-#pragma unroll
-    for (int u = 0; u < NS; ++u) {
-      int row = 4 * u + g;
-      row = row < len ? row : len - 1;
-      vd[r][u] = *reinterpret_cast<const uint4*>(Vh + (int64_t)(start + row) * vst);
-    }
-  }
-#pragma unroll
-  for (int r = 0; r < SPW; ++r) {
-#pragma unroll
-    for (int u = 0; u < NS; ++u) pin_loaded(kd[r][u]);
-#pragma unroll
-    for (int u = 0; u < NS; ++u) pin_loaded(vd[r][u]);
-    if (nv[r] > 0) {
-#pragma unroll
-      for (int j = 0; j < GT; ++j) fold_loaded<NS>(st[j], qf[j], kd[r], vd[r], nv[r], g, scale_log2);
-    }
-  }
-
+  // lane groups -> wave
 #pragma unroll
   for (int j = 0; j < GT; ++j) {
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-      st[j].acc[i] += shfl_xor_f(st[j].acc[i], 16);
-      st[j].acc[i] += shfl_xor_f(st[j].acc[i], 32);
+      acc[j][i] += shfl_xor_f(acc[j][i], 16);
+      acc[j][i] += shfl_xor_f(acc[j][i], 32);
     }
-    st[j].l += shfl_xor_f(st[j].l, 16);
-    st[j].l += shfl_xor_f(st[j].l, 32);
-    if (lane == 0) { sm_m[wave][j] = st[j].m; sm_l[wave][j] = st[j].l; }
     if (g == 0) {
 #pragma unroll
-      for (int i = 0; i < 8; ++i) sm_acc[wave][j][c * 8 + i] = st[j].acc[i];
+      for (int i = 0; i < 8; ++i) sm_acc[wave][j][c * 8 + i] = acc[j][i];
     }
   }
+  l += shfl_xor_f(l, 16);
+  l += shfl_xor_f(l, 32);
+  if (lane < GT) { sm_m[wave][lane] = m; sm_l[wave][lane] = l; }
   __syncthreads();
 
   // waves -> one partial per head of the tile, fixed order
-  for (int idx = threadIdx.x; idx < GT * DSK_HEAD_DIM; idx += WAVES * DSK_WAVE) {
+  for (int idx = threadIdx.x; idx < heads * DSK_HEAD_DIM; idx += kLongWaves * DSK_WAVE) {
     const int j = idx / DSK_HEAD_DIM;
     const int d = idx % DSK_HEAD_DIM;
     float M = sm_m[0][j];
 #pragma unroll
-    for (int w = 1; w < WAVES; ++w) M = fmaxf(M, sm_m[w][j]);
-    float l = 0.0f, a = 0.0f;
+    for (int w = 1; w < kLongWaves; ++w) M = fmaxf(M, sm_m[w][j]);
+    float ls = 0.0f, a = 0.0f;
 #pragma unroll
-    for (int w = 0; w < WAVES; ++w) {
+    for (int w = 0; w < kLongWaves; ++w) {
       const float f = sm_m[w][j] == -__builtin_inff() ? 0.0f : exp2f(sm_m[w][j] - M);   // idle wave
-      l = fmaf(sm_l[w][j], f, l);
+      ls = fmaf(sm_l[w][j], f, ls);
       a = fmaf(sm_acc[w][j][d], f, a);
     }
     const int64_t sh = sh0 + j;
-    if (used == 1) {
-      store_attn_out(out, out_bf16, sh * DSK_HEAD_DIM + d, l > 0.0f ? a / l : 0.0f);
-      if (d == 0 && lse) lse[sh] = l > 0.0f ? (M + log2f(l)) * kLn2 : -__builtin_inff();
+    if (count <= slots_per_wg) {
+      store_attn_out(out, out_bf16, sh * DSK_HEAD_DIM + d, ls > 0.0f ? a / ls : 0.0f);
+      if (d == 0 && lse) lse[sh] = ls > 0.0f ? (M + log2f(ls)) * kLn2 : -__builtin_inff();
     } else {
       part_acc[(sh * nchunks + chunk) * DSK_HEAD_DIM + d] = a;
-      if (d == 0) part_ml[sh * nchunks + chunk] = make_float2(M, l);
+      if (d == 0) part_ml[sh * nchunks + chunk] = make_float2(M, ls);
     }
   }
 }
@@ -647,44 +738,62 @@ __global__ __launch_bounds__(kMergeThreads) void attn_merge_kernel(
   }
 }
 
-// Whether a call takes attn_long_kernel, and its chunks per head: those that occupy the CUs most evenly (at least to 85 %,
-// in up to four rounds), the fewest of them within 6 %, with at least kLongMinSlots slots in each.  A caller that merges
-// the partials itself keeps the shorter chunks.
-constexpr int kLongMinSlots = 32;
+// Chunks per list for the kernels that want a workgroup on every CU: those that occupy the CUs most evenly (in up to four
+// rounds), the fewest of them within 6 %, with at least min_slots slots in each; 0 if none reaches min_use.
+// per_xcd(ch): workgroups on the busiest XCD.
 constexpr int kCusPerXcd = 32;
-static int attn_long_chunks(const dsk_attn_args& a) {
-  if (a.b > 32 || a.Hkv < 1 || (a.flags & DSK_ATTN_PARTIALS_ONLY) || a.k_stride_tok > kMaxTokenStride ||
-      a.v_stride_tok > kMaxTokenStride)
-    return 0;
-  const int G = a.Hq / a.Hkv, n_groups = a.B * a.Hkv;
+template <typename PerXcd>
+static int attn_even_chunks(PerXcd per_xcd, int64_t lists, int k, int min_slots, double min_use) {
   int best = 0;
-  double best_use = 0.85;
-  for (int ch = 1; ch * kLongMinSlots <= a.k; ++ch) {
-    const int64_t rounds = (attn_wgs_per_xcd(G, n_groups, ch) + kCusPerXcd - 1) / kCusPerXcd;
+  double best_use = 0.0;
+  for (int ch = 1; ch == 1 || ch * min_slots <= k; ++ch) {
+    const int64_t rounds = (per_xcd(ch) + kCusPerXcd - 1) / kCusPerXcd;
+    if (rounds > 4 && best > 0) break;
+    const double use = (double)lists * ch / ((double)rounds * kCusPerXcd * 8);
+    if (use >= min_use && (best == 0 || use > best_use + 0.06)) { best = ch; best_use = use; }
     if (rounds > 4) break;
-    const double use = (double)a.B * a.Hq * ch / ((double)rounds * kCusPerXcd * 8);
-    if (best == 0 ? use >= best_use : use > best_use + 0.06) { best = ch; best_use = use; }
   }
   return best;
 }
 
+// The space asked for is that of short chunks (8 or 16 slots), whatever the call takes.
 AttnWs attn_ws_layout(const dsk_attn_args& a, bool size_only) {
   AttnWs ws;
-  ws.slots_per_wg = attn_shared_tiled(a) ? kSharedWaves * kSharedSpw : attn_slots_per_wg(a.b);
-  if (!attn_shared_tiled(a) && a.b <= 16 &&
-      (int64_t)a.B * a.Hq * ((a.k + ws.slots_per_wg - 1) / ws.slots_per_wg) >= kAttnSmallWgFrom)
-    ws.slots_per_wg = 8;
-  ws.nchunks = (a.k + ws.slots_per_wg - 1) / ws.slots_per_wg;
-  const size_t n = (size_t)a.B * a.Hq * ws.nchunks;
+  const int short_slots = attn_slots_per_wg(a.b);
+  const int G = a.Hkv > 0 ? a.Hq / a.Hkv : 1;
+  const bool many = a.b <= 16 && (int64_t)a.B * a.Hq * ((a.k + short_slots - 1) / short_slots) >= kAttnSmallWgFrom;
+  const bool room8 = many || ((a.flags & DSK_ATTN_SHARED_SELECTION) && (G == 2 || G == 4 || G == 8) && a.b <= 32 &&
+                              (int64_t)a.B * a.Hkv * a.k >= 4096);
+  auto chunks_of = [&](int slots) { return (a.k + slots - 1) / slots; };
+  const int room = chunks_of(room8 ? 8 : short_slots);       // partials of a head
+  const size_t n = (size_t)a.B * a.Hq * room;
   ws.part_ml = 0;
   ws.part_acc = align_up(n * sizeof(float2));
   ws.total = ws.part_acc + align_up(n * DSK_HEAD_DIM * sizeof(float));
-  // fewer, longer chunks: the space asked for stays that of the shorter ones
-  const int chunks = size_only || attn_shared_tiled(a) ? 0 : attn_long_chunks(a);
-  ws.long_lists = chunks > 0 && chunks < ws.nchunks;
-  if (ws.long_lists) {
+  ws.kernel = AttnKernel::kShort;
+  ws.slots_per_wg = many ? 8 : short_slots;
+  ws.nchunks = chunks_of(ws.slots_per_wg);
+  if (size_only || a.Hkv < 1) return ws;
+  // A caller that merges the partials itself keeps short chunks.
+  const bool own_merge = (a.flags & DSK_ATTN_PARTIALS_ONLY) != 0;
+  int chunks = 0;
+  if (attn_shared(a)) {
+    const int tile = attn_shared_tile(G);
+    const int64_t lists = (int64_t)a.B * a.Hkv * ((G + tile - 1) / tile);
+    chunks = own_merge ? room : attn_even_chunks([&](int ch) { return (lists * ch + 7) / 8; }, lists, a.k, kSharedChunkSlots, 0.0);
+    if (chunks > room) chunks = room;
+    ws.kernel = AttnKernel::kShared;
+  } else if (!own_merge && a.b <= 32 && a.k >= ((a.flags & DSK_ATTN_SHARED_SELECTION) ? kLongMinSlotsShared : kLongMinSlots) &&
+             a.k_stride_tok <= kMaxTokenStride && a.v_stride_tok <= kMaxTokenStride) {
+    const int n_groups = a.B * a.Hkv;
+    chunks = attn_even_chunks([&](int ch) { return attn_wgs_per_xcd(G, n_groups, ch); }, (int64_t)a.B * a.Hq, a.k,
+                              kLongMinSlots, 0.85);
+    if (chunks >= ws.nchunks) chunks = 0;
+    if (chunks > 0) ws.kernel = AttnKernel::kLong;
+  }
+  if (chunks > 0) {
     ws.slots_per_wg = (a.k + chunks - 1) / chunks;
-    ws.nchunks = (a.k + ws.slots_per_wg - 1) / ws.slots_per_wg;
+    ws.nchunks = chunks_of(ws.slots_per_wg);
   }
   return ws;
 }
@@ -705,39 +814,36 @@ hipError_t launch_attn(const dsk_attn_args& a, const AttnWs& ws, hipStream_t st)
   // heads that read one row of the selection arrays; the workgroups of a group's heads gather the
   // same rows on one XCD, so only one of them misses in L2
   const int sel_div = (a.flags & DSK_ATTN_SHARED_SELECTION) ? a.Hq / a.Hkv : 1;
-  if (attn_shared_tiled(a)) {
-    const int G = a.Hq / a.Hkv;
-    const int GT = G == 2 ? 2 : 4;
-    const dim3 sgrid((unsigned)ws.nchunks, (unsigned)(a.Hkv * (G / GT)), (unsigned)a.B);
-    const dim3 sblock(kSharedWaves * DSK_WAVE);
-#define DSK_SHARED_ARGS                                                                                        \
-  q, K, V, a.k_stride_tok, a.k_stride_head, a.v_stride_tok, a.v_stride_head, a.Hq, G, a.k, a.b, a.total_tokens, \
-      a.sel_start, a.sel_len, a.sel_count, scale * kLog2e, ws.nchunks, part_ml, part_acc, a.out,                \
-      static_cast<uint16_t*>(a.out_bf16), a.lse
-    if (GT == 2) {
-      if (a.b <= 16) attn_shared_kernel<4, kSharedSpw, kSharedWaves, 2><<<sgrid, sblock, 0, st>>>(DSK_SHARED_ARGS);
-      else attn_shared_kernel<8, kSharedSpw, kSharedWaves, 2><<<sgrid, sblock, 0, st>>>(DSK_SHARED_ARGS);
-    } else {
-      if (a.b <= 16) attn_shared_kernel<4, kSharedSpw, kSharedWaves, 4><<<sgrid, sblock, 0, st>>>(DSK_SHARED_ARGS);
-      else attn_shared_kernel<8, kSharedSpw, kSharedWaves, 4><<<sgrid, sblock, 0, st>>>(DSK_SHARED_ARGS);
-    }
-#undef DSK_SHARED_ARGS
-    hipError_t serr = hipGetLastError();
-    if (serr != hipSuccess || ws.nchunks <= 1 || (a.flags & DSK_ATTN_PARTIALS_ONLY) || a.total_tokens <= 0) return serr;
-    return launch_attn_merge(part_ml, part_acc, a.sel_count, nullptr, a.B, a.Hq, sel_div, a.k, ws.nchunks,
-                             ws.slots_per_wg, a.out, static_cast<uint16_t*>(a.out_bf16), a.lse, st);
-  }
-  if (ws.long_lists) {
-#define DSK_LONG_ARGS                                                                                          \
-  q, K, V, a.k_stride_tok, a.k_stride_head, a.v_stride_tok, a.v_stride_head, a.Hq, a.Hq / a.Hkv, n_groups, a.k, a.b, \
-      a.total_tokens, a.sel_start, a.sel_len, a.sel_count, sel_div, scale * kLog2e, place, ws.nchunks, ws.slots_per_wg, \
-      part_ml, part_acc, a.out, static_cast<uint16_t*>(a.out_bf16), a.lse
+  if (ws.kernel != AttnKernel::kShort) {
     const dim3 block(kLongWaves * DSK_WAVE);
-    if (a.b <= 16) attn_long_kernel<4><<<grid, block, 0, st>>>(DSK_LONG_ARGS);
-    else attn_long_kernel<8><<<grid, block, 0, st>>>(DSK_LONG_ARGS);
+#define DSK_LONG_ARGS                                                                                             \
+  sel_div, scale * kLog2e, place, ws.nchunks, ws.slots_per_wg, part_ml, part_acc, a.out, static_cast<uint16_t*>(a.out_bf16), a.lse
+#define DSK_GATHER_ARGS(...)                                                                                      \
+  q, K, V, a.k_stride_tok, a.k_stride_head, a.v_stride_tok, a.v_stride_head, a.Hq, a.Hq / a.Hkv, __VA_ARGS__ a.k, a.b, \
+      a.total_tokens, a.sel_start, a.sel_len, a.sel_count
+#define DSK_SHARED_ARGS                                                                                           \
+  DSK_GATHER_ARGS(), scale * kLog2e, ws.nchunks, ws.slots_per_wg, part_ml, part_acc, a.out,                       \
+      static_cast<uint16_t*>(a.out_bf16), a.lse
+    if (ws.kernel == AttnKernel::kLong) {
+      if (a.b <= 16) attn_long_kernel<4><<<grid, block, 0, st>>>(DSK_GATHER_ARGS(n_groups,), DSK_LONG_ARGS);
+      else attn_long_kernel<8><<<grid, block, 0, st>>>(DSK_GATHER_ARGS(n_groups,), DSK_LONG_ARGS);
+    } else {
+      const int G = a.Hq / a.Hkv, tile = attn_shared_tile(G);
+      const dim3 sgrid((unsigned)(n_groups * ((G + tile - 1) / tile) * ws.nchunks));
+      switch (tile * 64 + (a.b <= 16 ? 1 : 2)) {
+        case 2 * 64 + 1: attn_shared_kernel<1, 2><<<sgrid, block, 0, st>>>(DSK_SHARED_ARGS); break;
+        case 2 * 64 + 2: attn_shared_kernel<2, 2><<<sgrid, block, 0, st>>>(DSK_SHARED_ARGS); break;
+        case 4 * 64 + 1: attn_shared_kernel<1, 4><<<sgrid, block, 0, st>>>(DSK_SHARED_ARGS); break;
+        case 4 * 64 + 2: attn_shared_kernel<2, 4><<<sgrid, block, 0, st>>>(DSK_SHARED_ARGS); break;
+        case 8 * 64 + 1: attn_shared_kernel<1, 8><<<sgrid, block, 0, st>>>(DSK_SHARED_ARGS); break;
+        default: attn_shared_kernel<2, 8><<<sgrid, block, 0, st>>>(DSK_SHARED_ARGS);
+      }
+    }
 #undef DSK_LONG_ARGS
+#undef DSK_SHARED_ARGS
+#undef DSK_GATHER_ARGS
     const hipError_t lerr = hipGetLastError();
-    if (lerr != hipSuccess || ws.nchunks <= 1 || a.total_tokens <= 0) return lerr;
+    if (lerr != hipSuccess || ws.nchunks <= 1 || (a.flags & DSK_ATTN_PARTIALS_ONLY) || a.total_tokens <= 0) return lerr;
     return launch_attn_merge(part_ml, part_acc, a.sel_count, nullptr, a.B, a.Hq, sel_div, a.k, ws.nchunks,
                              ws.slots_per_wg, a.out, static_cast<uint16_t*>(a.out_bf16), a.lse, st);
   }

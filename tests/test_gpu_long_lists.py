@@ -42,9 +42,12 @@ def _want(q, K, V, start, length, counts, div):
 
 # (B, Hq, Hkv, k, b): one list a head with 32 slots, one more, a slot count beyond the 64 spans of a wavefront; several
 # chunks; runs of chunks on XCDs of their own (4, 2, 1 and 3 groups); heads without groups; several rounds of workgroups
+# (and, where a list is shared: every width and tile of the shared kernel, slots of one and two tiles of 16 rows)
 SHAPES = [(8, 32, 8, 32, 16, True), (8, 32, 8, 33, 16, True), (8, 32, 8, 545, 8, True), (2, 32, 8, 131, 32, True),
           (1, 28, 4, 257, 16, True), (1, 16, 2, 515, 8, True), (1, 8, 1, 129, 16, False), (1, 40, 40, 200, 16, True),
-          (3, 6, 1, 40, 16, False), (8, 40, 8, 97, 16, True), (3, 16, 2, 16, 32, False), (1, 28, 4, 40, 64, False)]
+          (3, 6, 1, 40, 16, False), (8, 40, 8, 97, 16, True), (3, 16, 2, 16, 32, False), (1, 28, 4, 40, 64, False),
+          (4, 16, 8, 97, 32, False), (5, 24, 8, 80, 17, True), (4, 40, 8, 200, 32, True), (12, 56, 8, 33, 9, True),
+          (6, 11, 1, 520, 16, False), (16, 8, 4, 49, 16, False)]
 
 
 @pytest.mark.parametrize("B,Hq,Hkv,k,b,is_long", SHAPES)
@@ -61,7 +64,7 @@ def test_long_lists(B, Hq, Hkv, k, b, is_long, layout):
     q = torch.randn(B, Hq, 128, generator=g, device="cuda").bfloat16()
     for shared in (False, True):
         H = Hkv if shared else Hq
-        if shared and (Hq == Hkv or B * Hkv * k >= 4096):          # those run on a kernel of their own
+        if shared and Hq == Hkv:
             continue
         counts = np.minimum(k, rng.integers(0, 2 * k, size=(B, H)))
         counts.flat[-1], counts.flat[0] = 0, k
@@ -69,7 +72,8 @@ def test_long_lists(B, Hq, Hkv, k, b, is_long, layout):
         flags = dsk.DSK_ATTN_SHARED_SELECTION if shared else 0
         att = dsk.make_attn_args(q, K, V, dev_i32(start), dev_i32(length), dev_i32(counts), b, flags=flags, want_bf16=True)
         lay = dsk.dsk_attn_partials_layout(att.args)
-        assert (lay.slots_per_chunk >= 32) == is_long and lay.nchunks * lay.slots_per_chunk >= k
+        assert shared or (lay.slots_per_chunk >= 32) == is_long
+        assert lay.nchunks * lay.slots_per_chunk >= k
         att.out.fill_(7.0)
         dsk.dsk_sparse_decode_attn(att.args)
         again = dsk.make_attn_args(q, K, V, dev_i32(start), dev_i32(length), dev_i32(counts), b, flags=flags)
