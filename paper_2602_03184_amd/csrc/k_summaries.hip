@@ -93,9 +93,9 @@ struct SumTensor {
 
 // One wavefront per (plane, block); the planes are the heads of K, then those of V, `heads` in all and the slower index,
 // so that the wavefronts for which there is no block come last.  `streamed`: planes from the first one whose rows are
-// read past the caches.
-template <bool MEAN, bool STREAM>
-__global__ __launch_bounds__(kSumThreads) void summaries_kernel(
+// read past the caches.  WAVES: wavefronts per SIMD that the registers leave room for at least (they are 5 with 4).
+template <bool MEAN, bool STREAM, int WAVES>
+__global__ __launch_bounds__(kSumThreads, WAVES) void summaries_kernel(
     SumTensor k, SumTensor v, int Hkv, int heads, int streamed, const int32_t* __restrict__ block_start,
     const int32_t* __restrict__ cu_blocks, int B, const int32_t* __restrict__ blk_range, int cap, int out_rows,
     int total_tokens, int32_t* dev_status) {
@@ -162,7 +162,13 @@ __global__ __launch_bounds__(kSumThreads) void summaries_kernel(
 // 296 / 56.0 with all but the last 400 MB past it, 294 / 57.7 with all but the last 256 MB.
 constexpr int64_t kSumKeptBytes = 400ll << 20;
 
-template <bool MEAN>
+// Short chunks leave most of a wavefront's 32 rows in flight empty, so they want more wavefronts; longer ones lose to the
+// scheduling that the smaller register budget forces.  6 against 5 wavefronts per SIMD, 32 heads at 126K tokens, chunks of 15:
+// 210 against 218 us; 8 heads at 131K, chunks of 16: 73.2 / 76.3, of 18: 74.9 / 74.8, of 20: 75.1 / 73.3, of 30: 74.9 / 72.8.
+// (Where sequences have a C of their own only the largest is known here: two sequences of 14 and 28, 103.9 / 110.1.)
+static bool short_chunks(const dsk_compress_args& a) { return a.C > 0 && a.C <= (a.C_per_seq != nullptr ? 34 : 17); }
+
+template <bool MEAN, int WAVES>
 static hipError_t launch_summaries_impl(const dsk_compress_args& a, hipStream_t st) {
   const int heads = (a.vsum != nullptr ? 2 : 1) * a.Hkv;
   const int64_t max_items = (int64_t)heads * a.max_blocks_total;
@@ -177,7 +183,8 @@ static hipError_t launch_summaries_impl(const dsk_compress_args& a, hipStream_t 
   // (C is only a hint here: a call of this stage alone may leave it unset.)
   int64_t max_wgs = a.C > 0 ? (a.C_per_seq != nullptr ? 2 : 1) * (int64_t)heads * (a.total_tokens / a.C + a.B) / kSumWaves : 0;
   if (max_wgs < 256 * 8) max_wgs = 256 * 8;
-  if (max_wgs > 256 * 256) max_wgs = 256 * 256;
+  const int64_t wgs_cap = WAVES > 4 ? 256 * 128 : 256 * 256;   // 32 heads, chunks of 15: 232 -> 218 us; eight sequences 293 -> 290
+  if (max_wgs > wgs_cap) max_wgs = wgs_cap;
   if (wgs > max_wgs) wgs = max_wgs;
   const int out_rows = a.sum_stride_blocks > 0 ? a.sum_stride_blocks : a.max_blocks_total;
   const SumTensor k = {static_cast<const uint16_t*>(a.K), a.k_stride_tok, a.k_stride_head, static_cast<uint16_t*>(a.ksum)};
@@ -185,14 +192,16 @@ static hipError_t launch_summaries_impl(const dsk_compress_args& a, hipStream_t 
   const int64_t plane = (int64_t)a.total_tokens * DSK_HEAD_DIM * 2;
   const int64_t kept = plane > 0 ? (kSumKeptBytes + plane - 1) / plane : 0;
   const int streamed = heads > kept ? (int)(heads - kept) : 0;
-  summaries_kernel<MEAN, true><<<dim3((unsigned)wgs), dim3(kSumThreads), 0, st>>>(
+  summaries_kernel<MEAN, true, WAVES><<<dim3((unsigned)wgs), dim3(kSumThreads), 0, st>>>(
       k, v, a.Hkv, heads, streamed, a.block_start, a.cu_blocks, a.B, nullptr, a.max_blocks_total, out_rows, a.total_tokens,
       a.dev_status);
   return hipGetLastError();
 }
 
 hipError_t launch_summaries(const dsk_compress_args& a, hipStream_t st) {
-  return a.summary_mode == DSK_SUMMARY_MEAN ? launch_summaries_impl<true>(a, st) : launch_summaries_impl<false>(a, st);
+  if (short_chunks(a))
+    return a.summary_mode == DSK_SUMMARY_MEAN ? launch_summaries_impl<true, 6>(a, st) : launch_summaries_impl<false, 6>(a, st);
+  return a.summary_mode == DSK_SUMMARY_MEAN ? launch_summaries_impl<true, 4>(a, st) : launch_summaries_impl<false, 4>(a, st);
 }
 
 hipError_t launch_summaries_range(const void* X, int64_t stride_tok, int64_t stride_head, int Hkv,
@@ -205,10 +214,10 @@ hipError_t launch_summaries_range(const void* X, int64_t stride_tok, int64_t str
   if (wgs > 256 * 8) wgs = 256 * 8;
   const SumTensor k = {static_cast<const uint16_t*>(X), stride_tok, stride_head, static_cast<uint16_t*>(out)};
   if (summary_mode == DSK_SUMMARY_MEAN)
-    summaries_kernel<true, false><<<dim3((unsigned)wgs), dim3(kSumThreads), 0, st>>>(
+    summaries_kernel<true, false, 4><<<dim3((unsigned)wgs), dim3(kSumThreads), 0, st>>>(
         k, k, Hkv, Hkv, 0, block_start, nullptr, 0, blk_range, cap, cap, total_tokens, dev_status);
   else
-    summaries_kernel<false, false><<<dim3((unsigned)wgs), dim3(kSumThreads), 0, st>>>(
+    summaries_kernel<false, false, 4><<<dim3((unsigned)wgs), dim3(kSumThreads), 0, st>>>(
         k, k, Hkv, Hkv, 0, block_start, nullptr, 0, blk_range, cap, cap, total_tokens, dev_status);
   return hipGetLastError();
 }

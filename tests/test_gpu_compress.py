@@ -407,9 +407,10 @@ def test_sequence_offsets_with_and_without_a_scan_launch(B):
     _check_tables(comp, case.seg)
 
 
+@pytest.mark.parametrize("C", [24, 14])            # kernels for long and short chunks
 @pytest.mark.parametrize("mode", [0, 1])
 @pytest.mark.parametrize("layout", ["hnd", "nhd"])
-def test_summaries_with_rows_read_past_the_caches(layout, mode):
+def test_summaries_with_rows_read_past_the_caches(layout, mode, C):
     """K and V of 492 MB in one launch, of which the first planes are read past the caches, against two launches of
     246 MB that read nothing past them: the same bits, on both sides of the edge."""
     dsk = _dsk()
@@ -422,7 +423,7 @@ def test_summaries_with_rows_read_past_the_caches(layout, mode):
     ends = np.unique(np.concatenate([[0, L], np.cumsum(np.random.default_rng(3).integers(1, 50, size=6000))]))
     ends = ends[ends <= L]
     kw = dict(cu_seqlens=dev_i32([0, L]), max_seqlen=L, Hq=Hkv, Hkv=Hkv, total_tokens=L, stages=dsk.DSK_STAGE_SUMMARIES,
-              block_start=dev_i32(ends), cu_blocks=dev_i32([0, len(ends) - 1]), C_=24, delta=12, b=16, summary_mode=mode)
+              block_start=dev_i32(ends), cu_blocks=dev_i32([0, len(ends) - 1]), C_=C, delta=7, b=16, summary_mode=mode)
     both = dsk.compress(K=X[0], V=X[1], want_vsum=True, **kw)
     one = [dsk.compress(K=x, V=None, **kw) for x in X]
     torch.cuda.synchronize()
