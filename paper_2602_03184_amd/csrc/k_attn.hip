@@ -739,14 +739,15 @@ __global__ __launch_bounds__(kMergeThreads) void attn_merge_kernel(
 }
 
 // Chunks per list for the kernels that want a workgroup on every CU: those that occupy the CUs most evenly (in up to four
-// rounds), the fewest of them within 6 %, with at least min_slots slots in each; 0 if none reaches min_use.
+// rounds), the fewest of them within 6 %, with at least min_slots slots in each (8 more where a list of less than 256 slots is
+// cut: the merge takes back what such chunks gain); 0 if none reaches min_use.
 // per_xcd(ch): workgroups on the busiest XCD.
 constexpr int kCusPerXcd = 32;
 template <typename PerXcd>
 static int attn_even_chunks(PerXcd per_xcd, int64_t lists, int k, int min_slots, double min_use) {
   int best = 0;
   double best_use = 0.0;
-  for (int ch = 1; ch == 1 || ch * min_slots <= k; ++ch) {
+  for (int ch = 1; ch == 1 || ch * (k < 256 ? min_slots + 8 : min_slots) <= k; ++ch) {
     const int64_t rounds = (per_xcd(ch) + kCusPerXcd - 1) / kCusPerXcd;
     if (rounds > 4 && best > 0) break;
     const double use = (double)lists * ch / ((double)rounds * kCusPerXcd * 8);
