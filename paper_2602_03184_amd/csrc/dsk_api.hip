@@ -449,6 +449,7 @@ dsk_status dsk_select_topk(const dsk_select_args* a, void* stream) {
   hipStream_t st = static_cast<hipStream_t>(stream);
   float* scores = static_cast<float*>(a->workspace);
   const int stride = select_score_stride(*a);
+  if (select_scores_itself(*a)) return launch_select_scored(*a, scores, stride, st) == hipSuccess ? DSK_OK : DSK_ERR_LAUNCH;
   if (launch_scores(*a, scores, stride, st) != hipSuccess) return DSK_ERR_LAUNCH;
   if (launch_select(*a, scores, stride, st) != hipSuccess) return DSK_ERR_LAUNCH;
   return DSK_OK;

@@ -75,6 +75,9 @@ hipError_t launch_summaries(const dsk_compress_args& a, hipStream_t st);
 inline int select_score_stride(const dsk_select_args& a) { return (a.max_blocks_total + 3) / 4 * 4; }
 hipError_t launch_scores(const dsk_select_args& a, float* scores, int stride, hipStream_t st);
 hipError_t launch_select(const dsk_select_args& a, const float* scores, int stride, hipStream_t st);
+// short sequences: scores and selection in one launch
+bool select_scores_itself(const dsk_select_args& a);
+hipError_t launch_select_scored(const dsk_select_args& a, float* scores, int stride, hipStream_t st);
 
 // ---- dsk_sparse_decode_attn -----------------------------------------------------------------
 enum class AttnKernel { kShort, kLong, kShared };   // attn_kernel, attn_long_kernel, attn_shared_kernel
