@@ -292,7 +292,8 @@ __global__ __launch_bounds__(WAVES * DSK_WAVE) void attn_kernel(
 // 12 wavefronts 51.8 / 483, 16 52.6 / 499.  40 / 40 heads, 128K tokens, 256 slots of 16 rows: 40.0 -> 38.7 with 6 chunks a
 // head (240 workgroups), 43.5 with 7 (280: the last 24 have the card to themselves).
 constexpr int kLongWaves = 8;
-constexpr int kLongMinSlots = 32;       // of a workgroup
+constexpr int kLongMinSlots = 32;       // of a workgroup; where a list of less than 256 slots is cut, 8 more: the merge takes
+                                        // back what such chunks gain (2 to 8 sequences, 128 slots: 0.2 to 0.4 us slower with 32)
 constexpr int kLongMinSlotsShared = 256; // of a list that a group shares: its heads meet in L2 anyway (two sequences of 30K
                                         // tokens, 28 / 4 heads, 128 slots 20.3 -> 20.8 us; one, 16 / 2, 512 slots 32.3 -> 18.9)
 constexpr int kSharedChunkSlots = 16;   // of a workgroup of attn_shared_kernel
@@ -739,15 +740,15 @@ __global__ __launch_bounds__(kMergeThreads) void attn_merge_kernel(
 }
 
 // Chunks per list for the kernels that want a workgroup on every CU: those that occupy the CUs most evenly (in up to four
-// rounds), the fewest of them within 6 %, with at least min_slots slots in each (8 more where a list of less than 256 slots is
-// cut: the merge takes back what such chunks gain); 0 if none reaches min_use.
+// rounds), the fewest of them within 6 %, with at least min_slots slots in each where there are several; 0 if none
+// reaches min_use.
 // per_xcd(ch): workgroups on the busiest XCD.
 constexpr int kCusPerXcd = 32;
 template <typename PerXcd>
 static int attn_even_chunks(PerXcd per_xcd, int64_t lists, int k, int min_slots, double min_use) {
   int best = 0;
   double best_use = 0.0;
-  for (int ch = 1; ch == 1 || ch * (k < 256 ? min_slots + 8 : min_slots) <= k; ++ch) {
+  for (int ch = 1; ch == 1 || ch * min_slots <= k; ++ch) {
     const int64_t rounds = (per_xcd(ch) + kCusPerXcd - 1) / kCusPerXcd;
     if (rounds > 4 && best > 0) break;
     const double use = (double)lists * ch / ((double)rounds * kCusPerXcd * 8);
@@ -788,7 +789,7 @@ AttnWs attn_ws_layout(const dsk_attn_args& a, bool size_only) {
              a.k_stride_tok <= kMaxTokenStride && a.v_stride_tok <= kMaxTokenStride) {
     const int n_groups = a.B * a.Hkv;
     chunks = attn_even_chunks([&](int ch) { return attn_wgs_per_xcd(G, n_groups, ch); }, (int64_t)a.B * a.Hq, a.k,
-                              kLongMinSlots, 0.85);
+                              a.k < 256 ? kLongMinSlots + 8 : kLongMinSlots, 0.85);
     if (chunks >= ws.nchunks) chunks = 0;
     if (chunks > 0) ws.kernel = AttnKernel::kLong;
   }

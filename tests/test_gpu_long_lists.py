@@ -43,9 +43,9 @@ def _want(q, K, V, start, length, counts, div):
 # (B, Hq, Hkv, k, b): one list a head with 32 slots, one more, a slot count beyond the 64 spans of a wavefront; several
 # chunks; runs of chunks on XCDs of their own (4, 2, 1 and 3 groups); heads without groups; several rounds of workgroups
 # (and, where a list is shared: every width and tile of the shared kernel, slots of one and two tiles of 16 rows)
-SHAPES = [(8, 32, 8, 32, 16, True), (8, 32, 8, 33, 16, True), (8, 32, 8, 545, 8, True), (2, 32, 8, 131, 32, True),
-          (1, 28, 4, 257, 16, True), (1, 16, 2, 515, 8, True), (1, 8, 1, 129, 16, False), (1, 40, 40, 200, 16, True),
-          (3, 6, 1, 40, 16, False), (8, 40, 8, 97, 16, True), (3, 16, 2, 16, 32, False), (1, 28, 4, 40, 64, False),
+SHAPES = [(8, 32, 8, 32, 16, True), (8, 32, 8, 33, 16, True), (8, 32, 8, 545, 8, True), (2, 32, 8, 163, 32, True),
+          (1, 28, 4, 257, 16, True), (1, 16, 2, 515, 8, True), (1, 8, 1, 129, 16, False), (1, 40, 40, 245, 16, True),
+          (3, 6, 1, 40, 16, False), (8, 40, 8, 121, 16, True), (3, 16, 2, 16, 32, False), (1, 28, 4, 40, 64, False),
           (4, 16, 8, 97, 32, False), (5, 24, 8, 80, 17, True), (4, 40, 8, 200, 32, True), (12, 56, 8, 33, 9, True),
           (6, 11, 1, 520, 16, False), (16, 8, 4, 49, 16, False)]
 
