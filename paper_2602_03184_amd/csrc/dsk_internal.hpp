@@ -19,6 +19,15 @@ constexpr int kMaxSamplesPerClass = 64;
 inline size_t align_up(size_t x, size_t a = 256) { return (x + a - 1) / a * a; }
 
 // ---- dsk_compress workspace ---------------------------------------------------------------
+// Rounds of pointer jumping, four times as far each, after which a chain of chunks of at least min_len positions has
+// left a tile of tlen positions
+__host__ __device__ inline int jump_rounds(int tlen, int min_len) {
+  const int hops = (tlen + min_len - 1) / min_len;
+  int rounds = 0;
+  while ((1 << (2 * rounds)) < hops) ++rounds;
+  return rounds;
+}
+
 struct CompressWs {
   size_t tile_map;    // uint2 [n_tiles * map_row]   entry offset -> (exit offset | blocks<<16, slots)
   size_t tile_info;   // int4 [n_tiles]              entry position, block offset, slot offset
@@ -27,7 +36,7 @@ struct CompressWs {
   size_t seg_len;     // u16 [total_tokens]          length of the chunk that would start at each position
   size_t tile_count;  // i32 [n_cand_tiles + 1]      candidates per tile, then exclusive scan
   size_t seg_cand;    // i32 [2 * n_tiles]           candidates per segmentation tile, then their offsets in the sequence
-  size_t seg_jump;    // u16 [jump_levels][jump_stride]  position in the tile 2, 4, 8 .. chunks after each token
+  size_t seg_jump;    // u16 [jump_levels][jump_stride]  position in the tile 4, 16, 64 .. chunks after each token
   size_t imp_plan;    // i32 [ImpLayout::plan_ints]   plan of the importance launch
   size_t imp_part;    // float4 [ImpLayout::part_rows] softmax statistics of a piece's query rows
   size_t without_imp; // bytes that the other stages need
@@ -35,7 +44,7 @@ struct CompressWs {
   int tiles_per_seq;  // ceil(max_seqlen / kSegTile)
   int map_row;        // min(C + delta, kSegTile)
   int n_cand_tiles;   // ceil(total_tokens / kCandTile)
-  int jump_levels;    // doubling levels kept per token: enough for a tile of chunks of C - delta positions
+  int jump_levels;    // levels kept per token: enough for a tile of chunks of C - delta positions
   int jump_stride;    // total_tokens rounded up to 16
 };
 CompressWs compress_ws_layout(const dsk_compress_args& a);

@@ -12,16 +12,16 @@
 //            boundaries of every position's search range, every delimiter in reach "votes" its
 //            packed (score, smaller-e-wins) key into the 2*delta+1 start positions whose range
 //            contains it (64-bit LDS atomic max): work is proportional to delimiters, not
-//            positions.  Then pointer jumping (successor of successor, log2 rounds) gives, for
+//            positions.  Then pointer jumping (successor of successor, log4 rounds) gives, for
 //            every position at once, where the chain leaves the tile and how many blocks / slots
 //            it lays down on the way; the first C+delta of these form the tile's entry map.  The
-//            chunk length and the hop-2, -4, -8 .. targets of every position are kept for the emit pass.
+//            chunk length and the hop-4, -16, -64 .. targets of every position are kept for the emit pass.
 //   chain:   per sequence, hop through the entry maps (staged in LDS) to fix each tile's real
 //            entry and its block / slot offsets; for a single-sequence batch also the totals.
 //   scan:    block and slot bases of the sequences of a batch of more than kSeqsFolded, capacity check; in smaller
 //            batches the emit pass adds up the sequences in front of its own by itself.
 //   tile<1>: the chunks the chain lays down in the tile are the positions 0, 1, 2 .. hops behind the
-//            tile's real entry; each is found through the hop-2^l tables the first pass kept, ranked
+//            tile's real entry; each is found through the hop-4^l tables the first pass kept, ranked
 //            by a workgroup scan and written out.
 //   tile<2>: tile<1> for a single sequence of few tiles, which also chains the tiles in front of
 //            its own by itself: no chain launch.
@@ -50,19 +50,13 @@ struct SegParams {
   int map_row, tiles_per_seq;
   int max_seqlen, total_tokens;
   int B, cap;
-  uint16_t* seg_jump;      // [max_levels][jump_stride] per token: position in its tile 2^(level+1) chunks on
-  int max_levels;          // levels the buffer holds: one less than the doubling rounds of any sequence
+  uint16_t* seg_jump;      // [max_levels][jump_stride] per token: position in its tile 4^(level+1) chunks on
+  int max_levels;          // levels the buffer holds: one less than the rounds of any sequence
   int jump_stride;
 };
 
-constexpr int kMaxJumpLevels = 10;   // kept levels: hops of 2 .. 2^10 chunks; with the chunk itself, 2^11 >= kSegTile
-static_assert((1 << (kMaxJumpLevels + 1)) >= kSegTile, "levels cover a tile of one-position chunks");
-__host__ __device__ inline int jump_rounds(int tlen, int min_len) {
-  const int hops = (tlen + min_len - 1) / min_len;
-  int rounds = 0;
-  while ((1 << rounds) < hops) ++rounds;
-  return rounds;
-}
+constexpr int kMaxJumpLevels = 5;    // kept levels: hops of 4 .. 4^5 chunks; with the chunk itself, 4^6 >= kSegTile
+static_assert((1 << (2 * (kMaxJumpLevels + 1))) >= kSegTile, "levels cover a tile of one-position chunks");
 
 // Candidate lists produced by the segmentation kernels themselves (stage CANDIDATES and stage
 // SEGMENT in one call, weights from a table): the first tile pass classifies and counts the
@@ -279,23 +273,26 @@ __device__ __forceinline__ void chain_prefix_tree(const ChainRows& r, int L, int
   e_out = off; blk_out = blk; sl_out = sl;
 }
 
-// class index of N token ids against the delimiter ids staged in LDS (padded to a multiple of 4
-// entries); the lowest class index wins, as in the candidate stage; 255 = not a delimiter
+// class index of N token ids against the delimiter ids, of which lane c holds that of class c (lanes past the last class
+// that of class 0); the lowest class index wins, as in the candidate stage; 255 = not a delimiter.  Eight classes at a
+// time without a test: those past n_class repeat the id of class 0, which is compared last.  (With the ids in LDS and a
+// branch per class this took most of 3.3 us of the first tile pass, which are 2.3 now.)
 template <int N>
-__device__ __forceinline__ void classify_tokens(const int (&tok)[N], int (&cls)[N], const int32_t* ids, int n_class) {
+__device__ __forceinline__ void classify_tokens(const int (&tok)[N], int (&cls)[N], int lane_id, int n_class) {
 #pragma unroll
   for (int r = 0; r < N; ++r) cls[r] = 255;
-  for (int c4 = (n_class - 1) / 4 * 4; c4 >= 0; c4 -= 4) {
-    const int4 id4 = *reinterpret_cast<const int4*>(ids + c4);      // LDS broadcast read
-    const int idv[4] = {id4.x, id4.y, id4.z, id4.w};
+  for (int c8 = (n_class - 1) / 8 * 8; c8 >= 0; c8 -= 8) {
+    int hit[N];
 #pragma unroll
-    for (int cc = 3; cc >= 0; --cc) {
-      const int c = c4 + cc;
-      if (c < n_class) {
+    for (int r = 0; r < N; ++r) hit[r] = -1;
 #pragma unroll
-        for (int r = 0; r < N; ++r) cls[r] = tok[r] == idv[cc] ? c : cls[r];
-      }
+    for (int c = 7; c >= 0; --c) {
+      const int id = __builtin_amdgcn_readlane(lane_id, c8 + c);
+#pragma unroll
+      for (int r = 0; r < N; ++r) hit[r] = tok[r] == id ? c : hit[r];
     }
+#pragma unroll
+    for (int r = 0; r < N; ++r) cls[r] = hit[r] >= 0 ? c8 + hit[r] : cls[r];
   }
 }
 
@@ -303,18 +300,18 @@ __device__ __forceinline__ void classify_tokens(const int (&tok)[N], int (&cls)[
 // dynamic LDS layout (bytes):
 //   best  u64 [kSegTile]       votes; dead after the successor table is built,
 //   jmp   uint2 [2][kSegTile]  ... so the pointer-jumping entries overlay it:
-//                              x = (position - p0, or exit offset) | chunks << 16, y = slots
+//                              x = 8 * (position - p0), y = chunks << 16 | slots
 //   clist u16 [2 * kSegTile]   delimiters in reach (overlays the second jump buffer)
 //   ns    u16 [kSegTile]       slots of the chunk starting here
 //   wq    u8  [64]             class -> weight tenths of this sequence
-//   red   i32 [40], then the delimiter ids i32 [64], then i32 [3][kTileWaves] sums over the sequences in front
+//   red   i32 [40], then (emit) candidate counts i32 [64], then i32 [3][kTileWaves] sums over the sequences in front
 constexpr size_t kTileJumpBytes =    // jump entries; the vote array (8 bytes per position) and, in the emit pass
     (size_t)kSegTile * 16 > (size_t)kChainLdsEntries * 8 ? (size_t)kSegTile * 16     // that chains for itself, the two
                                                         : (size_t)kChainLdsEntries * 8;   // buffers of the chain scan overlay them
 __host__ __device__ constexpr size_t seg_tile_lds_bytes() {
   return kTileJumpBytes
          + (size_t)kSegTile * 2     // ns
-         + 64 + 448                 // wq, red (reduction words, then 64 delimiter ids)
+         + 64 + 448                 // wq, red (reduction words, then 64 counts)
          + 3 * kTileWaves * 4;      // sums over the sequences in front
 }
 static_assert(2 * kTileWaves + 3 <= 40 && (40 + 64) * 4 <= 448, "red fits its slot");
@@ -422,7 +419,7 @@ __global__ __launch_bounds__(kTileThreads) void seg_tile_kernel(
     if (MODE == 1) cand_o = cand.tile_base[tile] + (p.B == 1 || fold ? 0 : cand.cand_cu[s]);
     else cand_o = tid < j ? cand.tile_count[tile - j + tid] : 0;     // summed below; j < kTileThreads
   }
-  // (emit) where the chain is 2, 4, 8 .. chunks after each of the thread's positions, as the first
+  // (emit) where the chain is 4, 16, 64 .. chunks after each of the thread's positions, as the first
   // pass left it; every level the buffer holds is requested (the count in use depends on the
   // sequence's C and delta, which may still be on their way)
   uint16_t lv[kMaxJumpLevels][kSegPerThread];
@@ -441,45 +438,52 @@ __global__ __launch_bounds__(kTileThreads) void seg_tile_kernel(
     // anything is waited for: they travel with the weight and delimiter-id loads below
     constexpr int kVoteChunk = 2 * kSegTile;                                        // 4 positions per thread
     constexpr int kPerThread = kVoteChunk / kTileThreads;
-    const int e_lo = p0 + C - delta > 1 ? p0 + C - delta : 1;
+    const int lane = tid & (DSK_WAVE - 1);
+    const int e_min = p0 + C - delta > 1 ? p0 + C - delta : 1;
     int e_hi = p1 - 1 + C + delta;
     if (e_hi > L) e_hi = L;
-    int first[kPerThread];
-#pragma unroll
-    for (int r = 0; r < kPerThread; ++r) {
-      int e = e_lo + r * kTileThreads + tid;
-      e = e <= e_hi ? e : e_hi;
-      e = e >= 1 ? e : 1;                              // e_hi >= 1 whenever the tile has a position
-      first[r] = cls_at != nullptr ? (int)cls_at[seq0 + e - 1] : token_ids[seq0 + e - 1];
-    }
-    // candidate lists from this pass: the tile's own positions are classified as well (the
-    // boundaries above start C - delta positions further on)
+    // candidate lists from this pass: the tile's own positions are classified as well -- with the boundaries, which
+    // then start at the tile's first position, where both fit one chunk
     const bool own = cand.tile_count != nullptr;
+    const bool joint = own && e_hi - p0 <= kVoteChunk;
+    const int e_lo = joint ? p0 + 1 : e_min;
+    int first[kPerThread];
+    if (cls_at != nullptr) {
+#pragma unroll
+      for (int r = 0; r < kPerThread; ++r) {
+        int e = e_lo + r * kTileThreads + tid;
+        e = e <= e_hi ? e : e_hi;                        // e_hi >= 1 whenever the tile has a position
+        first[r] = cls_at[seq0 + e - 1];
+      }
+    } else {
+#pragma unroll
+      for (int r = 0; r < kPerThread; ++r) {
+        int e = e_lo + r * kTileThreads + tid;
+        e = e <= e_hi ? e : e_hi;
+        first[r] = token_ids[seq0 + e - 1];
+      }
+    }
     int own_tok[kSegPerThread];
-    if (own) {
+    if (own && !joint) {
 #pragma unroll
       for (int r = 0; r < kSegPerThread; ++r) {
         const int i = r * kTileThreads + tid;
         own_tok[r] = token_ids[seq0 + p0 + (i < tlen ? i : 0)];
       }
     }
-    if (tid < 64) {
-      int w = tid < p.n_class ? p.class_weight_q[s * p.n_class + tid] : 0;
-      if (w > 10) { set_status(dev_status, DSK_ERR_PARAM); w = 10; }
-      wq[tid] = (uint8_t)w;
-    }
-    for (int i = tid; i < kSegTile; i += kTileThreads) best[i] = 0ull;
+    const int lane_id = cls_at == nullptr ? delim_ids[lane < p.n_class ? lane : 0] : 0;
+    int w_own = tid < p.n_class ? p.class_weight_q[s * p.n_class + tid] : 0;          // n_class <= 64
+#pragma unroll
+    for (int r = 0; r < kSegPerThread; ++r) best[r * kTileThreads + tid] = 0ull;
     int* n_list = red;
     if (tid == 0) *n_list = 0;
-    // delimiter ids for the in-kernel classification; the entries past n_class repeat id 0 and are
-    // never compared
-    int32_t* ids = red + 40;                                          // 64 ints behind the reduction words
-    if (cls_at == nullptr && tid < 64) ids[tid] = delim_ids[tid < p.n_class ? tid : 0];
+    if (tid < 64) {
+      if (w_own > 10) { set_status(dev_status, DSK_ERR_PARAM); w_own = 10; }
+      wq[tid] = (uint8_t)w_own;
+    }
     __syncthreads();
 
-    if (own) {
-      int oc[kSegPerThread];
-      classify_tokens<kSegPerThread>(own_tok, oc, ids, p.n_class);
+    auto keep_own = [&](const int (&oc)[kSegPerThread]) {
       int n_wave = 0;
 #pragma unroll
       for (int r = 0; r < kSegPerThread; ++r) {
@@ -487,7 +491,12 @@ __global__ __launch_bounds__(kTileThreads) void seg_tile_kernel(
         if (i < tlen) cand.own_cls[seq0 + p0 + i] = (uint8_t)oc[r];
         n_wave += __popcll(__ballot(i < tlen && oc[r] != 255));
       }
-      if ((tid & (DSK_WAVE - 1)) == 0) red[4 + tid / DSK_WAVE] = n_wave;   // summed once the barriers below have passed
+      if (lane == 0) red[4 + tid / DSK_WAVE] = n_wave;   // summed once the barriers below have passed
+    };
+    if (own && !joint) {
+      int oc[kSegPerThread];
+      classify_tokens<kSegPerThread>(own_tok, oc, lane_id, p.n_class);
+      keep_own(oc);
     }
 
     // votes: boundary e (offered by a delimiter at e-1) can end a chunk that starts at q with
@@ -498,7 +507,6 @@ __global__ __launch_bounds__(kTileThreads) void seg_tile_kernel(
     // that all have one (a dense scan would leave 1 lane in 30 busy).
     {
       uint16_t* clist = reinterpret_cast<uint16_t*>(smem + (size_t)kSegTile * 8);     // free until the jump arrays are built
-      const int lane = tid & (DSK_WAVE - 1);
       for (int e0 = e_lo; e0 <= e_hi; e0 += kVoteChunk) {
         int cb_[kPerThread];
         if (cls_at != nullptr) {
@@ -509,33 +517,54 @@ __global__ __launch_bounds__(kTileThreads) void seg_tile_kernel(
             cb_[r] = e0 == e_lo ? first[r] : (int)cls_at[seq0 + e - 1];
           }
         } else {
-          int tok[kPerThread];
+          // two rows of the workgroup at a time; most wavefronts have nothing in the second two
+          static_assert(kPerThread % kSegPerThread == 0, "rows in pairs");
 #pragma unroll
-          for (int r = 0; r < kPerThread; ++r) {
-            int e = e0 + r * kTileThreads + tid;
-            e = e <= e_hi ? e : e_hi;
-            tok[r] = e0 == e_lo ? first[r] : token_ids[seq0 + e - 1];
+          for (int r0 = 0; r0 < kPerThread; r0 += kSegPerThread) {
+            int tok[kSegPerThread], cls[kSegPerThread];
+#pragma unroll
+            for (int r = 0; r < kSegPerThread; ++r) cb_[r0 + r] = 255;
+            if (e0 + r0 * kTileThreads + __builtin_amdgcn_readfirstlane(tid) > e_hi) continue;
+#pragma unroll
+            for (int r = 0; r < kSegPerThread; ++r) {
+              int e = e0 + (r0 + r) * kTileThreads + tid;
+              e = e <= e_hi ? e : e_hi;
+              tok[r] = e0 == e_lo ? first[r0 + r] : token_ids[seq0 + e - 1];
+            }
+            classify_tokens<kSegPerThread>(tok, cls, lane_id, p.n_class);
+#pragma unroll
+            for (int r = 0; r < kSegPerThread; ++r) cb_[r0 + r] = cls[r];
           }
-          classify_tokens<kPerThread>(tok, cb_, ids, p.n_class);
+          if (joint) {
+            int oc[kSegPerThread];
+#pragma unroll
+            for (int r = 0; r < kSegPerThread; ++r) oc[r] = cb_[r];
+            keep_own(oc);
+          }
         }
         // compaction: position of each delimiter inside its wavefront from ballots, one LDS
         // reservation per wavefront
         unsigned long long bal[kPerThread];
-        int n_wave = 0;
+        int n_wave = 0, wt[kPerThread];
+        const bool few = e0 + kSegPerThread * kTileThreads + __builtin_amdgcn_readfirstlane(tid) > e_hi;
 #pragma unroll
         for (int r = 0; r < kPerThread; ++r) {
-          const int eo = r * kTileThreads + tid;
-          bal[r] = __ballot(e0 + eo <= e_hi && cb_[r] != 255);
+          bal[r] = 0ull;
+          if (r >= kSegPerThread && few) continue;
+          const int e = e0 + r * kTileThreads + tid;
+          bal[r] = __ballot(e >= e_min && e <= e_hi && cb_[r] != 255);
           n_wave += __popcll(bal[r]);
+          wt[r] = wq[cb_[r] & 63];
         }
         int base = 0;
         if (lane == 0 && n_wave > 0) base = atomicAdd(n_list, n_wave);
         base = __builtin_amdgcn_readfirstlane(base);
 #pragma unroll
         for (int r = 0; r < kPerThread; ++r) {
+          if (r >= kSegPerThread && few) continue;
           const int eo = r * kTileThreads + tid;        // e - e0 < 4096: 12 bits, weight 0..10: 4 bits
           if ((bal[r] >> lane) & 1ull) {
-            const int w = cb_[r] < 64 ? wq[cb_[r]] : 0;
+            const int w = cb_[r] < 64 ? wt[r] : 0;
             clist[base + __popcll(bal[r] & ((1ull << lane) - 1ull))] = (uint16_t)((eo << 4) | w);   // at most kVoteChunk entries = 8 KB
           }
           base += __popcll(bal[r]);
@@ -577,6 +606,9 @@ __global__ __launch_bounds__(kTileThreads) void seg_tile_kernel(
     }
     // successor table (registers first: `best` is about to be overlaid).  Lane-interleaved
     // ownership (i = r*threads + tid) keeps these LDS accesses free of bank conflicts.
+    unsigned long long won[kSegPerThread];
+#pragma unroll
+    for (int r = 0; r < kSegPerThread; ++r) won[r] = best[r * kTileThreads + tid];
 #pragma unroll
     for (int r = 0; r < kSegPerThread; ++r) {
       const int i = r * kTileThreads + tid;
@@ -586,7 +618,7 @@ __global__ __launch_bounds__(kTileThreads) void seg_tile_kernel(
         const int s_e = q + C;
         if (s_e >= L) len = L - q;
         else {
-          const unsigned long long key = best[i];
+          const unsigned long long key = won[r];
           len = key ? 0xFFFF - (int)(key & 0xFFFFull) : C;
         }
         seg_len[seq0 + q] = (uint16_t)len;             // chunk lengths stay below 2^16 (C + delta <= 8192)
@@ -604,7 +636,7 @@ __global__ __launch_bounds__(kTileThreads) void seg_tile_kernel(
       // rank of every candidate of the tile: positions are owned interleaved (i = r * threads +
       // tid), so the order is row r, then wavefront, then lane
       const int lane = tid & (DSK_WAVE - 1), wave = tid / DSK_WAVE;
-      int* cnt = red + 40;                                 // [kSegPerThread][kTileWaves]; the id slots are free in this mode
+      int* cnt = red + 40;                                 // [kSegPerThread][kTileWaves]
       unsigned long long bal[kSegPerThread];
 #pragma unroll
       for (int r = 0; r < kSegPerThread; ++r) {
@@ -627,7 +659,7 @@ __global__ __launch_bounds__(kTileThreads) void seg_tile_kernel(
         for (int w = 0; w < kTileWaves; ++w) cand_o += cnt[kSegPerThread * kTileWaves + w];
       }
       static_assert(kSegPerThread * kTileWaves <= DSK_WAVE && (kSegPerThread + 1) * kTileWaves <= 64,
-                    "one lane per (row, wavefront) count; the counts fit the id slots");
+                    "one lane per (row, wavefront) count; the counts fit their words");
       const int c = lane < kSegPerThread * kTileWaves ? cnt[lane] : 0;
       const int ex = wave_incl_scan_i(c, lane) - c;
       if (MODE == 2 && tid == DSK_WAVE - 1 && p0 + kSegTile >= L) {   // last tile: ex + c is the tile's count
@@ -677,15 +709,20 @@ __global__ __launch_bounds__(kTileThreads) void seg_tile_kernel(
     // ceil(len / b): len + b - 1 < 2^16 and b < 2^15 on the multiply path, so the reciprocal is exact
     const int nslot = p.b_inv ? (int)__umulhi((uint32_t)(len + p.b - 1), p.b_inv) : (len + p.b - 1) / p.b;
     ns[i] = (uint16_t)nslot;
-    // level-0 jump: one chunk.  position >= tlen means "left the tile" (i + len <= tlen + C + delta)
-    own[r] = make_uint2((uint32_t)(i + len) | ((i < tlen ? 1u : 0u) << 16), (uint32_t)nslot);
+    // level-0 jump: one chunk.  position >= tlen means "left the tile" (i + len <= tlen + C + delta); the counts of a
+    // chain stay below 2^16 each (its positions do)
+    own[r] = make_uint2((uint32_t)(i + len) * 8u, ((i < tlen ? 1u : 0u) << 16) | (uint32_t)nslot);
     if (MODE == 0) jmp[i] = own[r];
   }
-  // pointer jumping: level r holds 2^r chunks per hop; positions that left the tile are fixed
+  // pointer jumping: level r holds 4^r chunks per hop; positions that left the tile are fixed
   // points.  Every chunk that does not end the sequence has at least C - delta positions, so the
-  // chain crosses the tile in at most ceil(tlen / (C - delta)) hops and as many doublings as cover
+  // chain crosses the tile in at most ceil(tlen / (C - delta)) hops and as many rounds as cover
   // that number finish every position: a fixed round count, no termination vote.  The first pass
   // keeps the target positions of every level (2 bytes per position and level) for the emit pass.
+  // Doubling instead would take as long here (three lookups and a barrier for four times the reach, against two of each),
+  // but the emit pass stages half the levels this way.  128K tokens, inside the kernels: first pass 8.7 -> 6.8 us with
+  // this form of the entries and the classification above, emit pass 7.0 -> 6.2; compression pass 70.6 -> 67.7 us, K and V
+  // of eight sequences 288.7 -> 284.7.
   const int rounds = jump_rounds(tlen, C - delta);       // C - delta >= 1
   if (rounds - 1 > p.max_levels) {                       // cannot happen for a buffer sized by the host's rule
     if (tid == 0) set_status(dev_status, DSK_ERR_WORKSPACE);
@@ -693,28 +730,34 @@ __global__ __launch_bounds__(kTileThreads) void seg_tile_kernel(
   }
   if (MODE == 0) {
     __syncthreads();
-    int cur = 0;
-    for (int round = 0; round < rounds; ++round) {
-      const uint2* js = jmp + cur * kSegTile;
-      uint2* jd = jmp + (cur ^ 1) * kSegTile;
+    const uint32_t left = (uint32_t)tlen * 8u;           // entries: 8 x position (the offset of its own entry), counts
+#pragma unroll
+    for (int round = 0; round <= kMaxJumpLevels; ++round) {
+      if (round >= rounds) break;
+      const unsigned char* js = smem + (round & 1) * (kSegTile * 8);
+      uint2* jd = jmp + ((round & 1) ^ 1) * kSegTile;
+#pragma unroll
+      for (int h = 0; h < 3; ++h) {                      // three hops of this level on
+        uint2 by[kSegPerThread];
+#pragma unroll
+        for (int r = 0; r < kSegPerThread; ++r)
+          by[r] = *reinterpret_cast<const uint2*>(js + (own[r].x < left ? own[r].x : 0u));
+#pragma unroll
+        for (int r = 0; r < kSegPerThread; ++r) {
+          own[r].y += own[r].x < left ? by[r].y : 0u;
+          own[r].x = own[r].x < left ? by[r].x : own[r].x;
+        }
+      }
+      uint16_t* dst = p.seg_jump + (int64_t)round * p.jump_stride + seq0 + p0;
 #pragma unroll
       for (int r = 0; r < kSegPerThread; ++r) {
         const int i = r * kTileThreads + tid;
-        uint2 v = own[r];
-        const int t = (int)(v.x & 0xFFFFu);
-        if (i < tlen && t < tlen) {
-          const uint2 v2 = js[t];
-          v = make_uint2((v2.x & 0xFFFFu) | ((v.x & 0xFFFF0000u) + (v2.x & 0xFFFF0000u)), v.y + v2.y);
-        }
-        jd[i] = v;
-        own[r] = v;
-        if (i < tlen && round < rounds - 1)              // the last level is not hopped from again
-          p.seg_jump[(int64_t)round * p.jump_stride + seq0 + p0 + i] = (uint16_t)(v.x & 0xFFFFu);
+        jd[i] = own[r];
+        if (i < tlen && round < rounds - 1) dst[i] = (uint16_t)(own[r].x >> 3);   // the last level is not hopped from
       }
-      cur ^= 1;
       __syncthreads();
     }
-    const uint2* fj = jmp + cur * kSegTile;
+    const uint2* fj = jmp + (rounds & 1) * kSegTile;
     if (cand.tile_count != nullptr && tid == 0) {
       int n = 0;
 #pragma unroll
@@ -726,7 +769,7 @@ __global__ __launch_bounds__(kTileThreads) void seg_tile_kernel(
       uint2 rv = make_uint2(0u, 0u);
       if (ent < tlen) {
         const uint2 v = fj[ent];
-        rv = make_uint2(((v.x & 0xFFFFu) - (uint32_t)tlen) | (v.x & 0xFFFF0000u), v.y);
+        rv = make_uint2(((v.x >> 3) - (uint32_t)tlen) | (v.y & 0xFFFF0000u), v.y & 0xFFFFu);
       }
       row[ent] = rv;
     }
@@ -734,10 +777,10 @@ __global__ __launch_bounds__(kTileThreads) void seg_tile_kernel(
   }
 
   // emit.  The chunks the chain lays down in this tile are the positions 0, 1, 2 .. hops behind the
-  // tile's entry, and hop counts add up along the chain: with the hop-2^l tables of the first pass
+  // tile's entry, and hop counts add up along the chain: with the hop-4^l tables of the first pass
   // in LDS (hop 1 = the chunk lengths), the thread that owns the n-th chunk finds its position by
-  // one lookup per set bit of n -- no marks, no rounds, no barrier between the lookups.  A chain of
-  // the tile has at most 2^rounds chunks; a thread takes two consecutive n.
+  // d lookups for every digit d of n to the base 4 -- no marks, no rounds, no barrier between the lookups.  A chain of
+  // the tile has at most 4^rounds chunks; a thread takes two consecutive n.
   static_assert(kMaxJumpLevels + 1 <= (int)(kTileJumpBytes / (kSegTile * 2)), "hop tables fit the jump area");
   uint16_t* tab = reinterpret_cast<uint16_t*>(smem);     // [rounds][kSegTile]
 #pragma unroll
@@ -750,17 +793,22 @@ __global__ __launch_bounds__(kTileThreads) void seg_tile_kernel(
   }
   __syncthreads();
   constexpr int kPathPer = 2;
-  static_assert(kPathPer * kTileThreads >= (1 << (kMaxJumpLevels + 1)), "every chunk of a tile has a thread");
+  static_assert(kPathPer * kTileThreads >= kSegTile, "every chunk of a tile has a thread");
   const int e_in = info.x - p0;
   int pos[kPathPer], nsv[kPathPer];
   int nb_local = 0, ns_local = 0;
+  const int n = tid * kPathPer;
+  int q = (e_in >= 0 && e_in < tlen && n < (1 << (2 * rounds))) ? e_in : tlen;
+#pragma unroll
+  for (int l = kMaxJumpLevels; l >= 0; --l) {            // the widest hops first: most threads are past the chain's end
+    if (l >= rounds) continue;
+#pragma unroll
+    for (int h = 1; h <= 3; ++h)
+      if (((n >> (2 * l)) & 3) >= h && q < tlen) q = tab[l * kSegTile + q];
+  }
 #pragma unroll
   for (int r = 0; r < kPathPer; ++r) {
-    const int n = tid * kPathPer + r;
-    int q = (e_in >= 0 && e_in < tlen && n < (1 << rounds)) ? e_in : tlen;
-#pragma unroll
-    for (int l = 0; l <= kMaxJumpLevels; ++l)
-      if (l < rounds && ((n >> l) & 1) && q < tlen) q = tab[l * kSegTile + q];
+    if (r > 0) q = rounds > 0 && q < tlen ? (int)tab[q] : tlen;
     pos[r] = q;
     nsv[r] = q < tlen ? (int)ns[q] : 0;
     if (q < tlen) { ++nb_local; ns_local += nsv[r]; }

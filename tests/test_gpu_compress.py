@@ -385,6 +385,17 @@ def test_tiles_classify_their_own_tokens(n_class, C, delta):
     assert torch.equal(lean.ksum[:, :nb], full.ksum[:, :nb])
 
 
+# the tile's own tokens and the boundaries in reach are 2047 + C + delta positions: classified together up to 4096 of them
+@pytest.mark.parametrize("n_class,C,delta", [(8, 2047, 1), (9, 2048, 1), (64, 1100, 949), (16, 2047, 3), (1, 3000, 2900)])
+def test_tiles_classify_for_the_lists_as_well(n_class, C, delta):
+    dsk = _dsk()
+    case = gpu_case(5, B=3, Hq=1, Hkv=1, seqlens=[9001, 2049, 1], n_class=n_class, C=C, delta=delta, n_queries=1)
+    comp = dsk.compress(**case.compress_kwargs(stages=dsk.DSK_STAGE_CANDIDATES | dsk.DSK_STAGE_SEGMENT,
+                                               token_ids=case.token_ids, delim_ids=case.delim_ids, want_candidates=True))
+    torch.cuda.synchronize()
+    _check_tables(comp, case.seg)
+
+
 @pytest.mark.parametrize("B", [2, 1023, 1024, 1025])
 def test_sequence_offsets_with_and_without_a_scan_launch(B):
     """Batches of up to 1024 sequences form their offsets in the emit pass, larger ones in a launch of their own.
