@@ -541,9 +541,9 @@ dsk_status dsk_dense_decode_attn(const dsk_dense_attn_args* args, void* stream);
  * DSK_STATIC_SCRATCH_BYTES inside the library (one copy per GPU, held until the process ends).
  * The call allocates and frees nothing.
  *   - Size limit: dsk_attn_workspace_bytes(args) must not exceed DSK_STATIC_SCRATCH_BYTES, i.e.
- *     about B * Hq * ceil(k / slots_per_chunk) <= 4000 partials of 520 bytes (configuration 5 of the
- *     benchmark, 8 sequences x 32 heads x 8 chunks, needs 2048); beyond it the call returns
- *     DSK_ERR_WORKSPACE and enqueues nothing.
+ *     about 4100 partials of 520 bytes, counted in chunks of 8 or 16 slots a head whatever
+ *     dsk_attn_partials_layout reports (configuration 5 of the benchmark, 8 sequences x 32 heads x 16
+ *     chunks, needs 4096); beyond it the call returns DSK_ERR_WORKSPACE and enqueues nothing.
  *   - Every call on a GPU uses that GPU's one array, and the array keeps the last call's contents.
  *     Nothing in it has to start at zero (a partial is always written before it is read within a
  *     call), so no clearing is enqueued.  Two calls that overlap on one GPU (different streams, or
