@@ -776,13 +776,14 @@ AttnWs attn_ws_layout(const dsk_attn_args& a, bool size_only) {
   ws.slots_per_wg = many ? 8 : short_slots;
   ws.nchunks = chunks_of(ws.slots_per_wg);
   if (size_only || a.Hkv < 1) return ws;
-  // A caller that merges the partials itself keeps short chunks.
+  // A caller that merges the partials itself keeps short chunks of lists per query head.
   const bool own_merge = (a.flags & DSK_ATTN_PARTIALS_ONLY) != 0;
   int chunks = 0;
   if (attn_shared(a)) {
     const int tile = attn_shared_tile(G);
     const int64_t lists = (int64_t)a.B * a.Hkv * ((G + tile - 1) / tile);
-    chunks = own_merge ? room : attn_even_chunks([&](int ch) { return (lists * ch + 7) / 8; }, lists, a.k, kSharedChunkSlots, 0.0);
+    chunks = attn_even_chunks([&](int ch) { return (lists * ch + 7) / 8; }, lists, a.k, kSharedChunkSlots, 0.0);
+    if (own_merge && chunks < 2) chunks = 2;                 // partials are left where they were left before
     if (chunks > room) chunks = room;
     ws.kernel = AttnKernel::kShared;
   } else if (!own_merge && a.b <= 32 && a.k >= ((a.flags & DSK_ATTN_SHARED_SELECTION) ? kLongMinSlotsShared : kLongMinSlots) &&
