@@ -119,3 +119,33 @@ def test_long_lists_skip_spans_outside_the_cache():
     part = dsk.make_attn_args(q, K, V, dev_i32(start), dev_i32(length), dev_i32(counts), b, flags=dsk.DSK_ATTN_PARTIALS_ONLY)
     assert dsk.dsk_attn_partials_layout(part.args).nchunks > 1
     assert part.args.workspace_bytes == att.args.workspace_bytes
+
+
+# (B, Hq, Hkv, k): chunks of the merged call (4), two where that call needs no merge, one slot more than the chunks divide
+@pytest.mark.parametrize("B,Hq,Hkv,k", [(8, 32, 8, 128), (16, 64, 16, 64), (8, 28, 4, 129)])
+def test_partials_of_shared_lists(B, Hq, Hkv, k):
+    """Partials of a shared list, merged on the host by the documented formula, against the call that merges them."""
+    import paper_2602_03184_amd as dsk
+    rng = np.random.default_rng([B, Hq, k])
+    g = torch.Generator(device="cuda")
+    g.manual_seed(k)
+    L, b = 2001, 16
+    K, V = (torch.randn(Hkv, L, 128, generator=g, device="cuda").bfloat16() for _ in range(2))
+    q = torch.randn(B, Hq, 128, generator=g, device="cuda").bfloat16()
+    counts = np.full((B, Hkv), k)
+    start, length = _lists(rng, B, Hkv, k, b, L, counts)
+    full, part = (dsk.make_attn_args(q, K, V, dev_i32(start), dev_i32(length), dev_i32(counts), b,
+                                     flags=dsk.DSK_ATTN_SHARED_SELECTION | f) for f in (0, dsk.DSK_ATTN_PARTIALS_ONLY))
+    dsk.dsk_sparse_decode_attn(full.args)
+    dsk.dsk_sparse_decode_attn(part.args)
+    torch.cuda.synchronize()
+    lay = dsk.dsk_attn_partials_layout(part.args)
+    assert lay.nchunks == -(-k // lay.slots_per_chunk) and lay.nchunks >= 2
+    assert part.args.workspace_bytes == full.args.workspace_bytes
+    raw = part.keep[-1].view(torch.uint8).cpu().numpy()
+    n = B * Hq * lay.nchunks
+    ml = raw[lay.ml_offset: lay.ml_offset + n * 8].view(np.float32).reshape(B, Hq, lay.nchunks, 2).astype(np.float64)
+    acc = raw[lay.acc_offset: lay.acc_offset + n * 512].view(np.float32).reshape(B, Hq, lay.nchunks, 128).astype(np.float64)
+    w = np.exp2(ml[..., 0] - ml[..., 0].max(-1, keepdims=True))
+    out = (acc * w[..., None]).sum(2) / (ml[..., 1] * w).sum(2)[..., None]
+    assert rel_err(full.out.cpu().numpy(), out) <= 1e-5        # 32-bit sums in two orders, as in test_long_lists
