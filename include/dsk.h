@@ -263,7 +263,7 @@ typedef struct dsk_select_args {
 /* dsk_attn_args.flags: stop after the per-chunk partials (running max in log2 units, denominator,
  * unnormalised numerator) and leave them in the workspace -- for a caller that merges partials
  * itself, e.g. across devices that each hold part of a sequence.  out / lse are then final only
- * for heads whose selection fits one chunk. */
+ * for heads whose selection is empty or fits one chunk (its partial is left as well). */
 #define DSK_ATTN_PARTIALS_ONLY 1u
 /* the sel_* arrays hold one selection per (sequence, KV head) -- [B, Hkv, k] and [B, Hkv], as
  * dsk_select_topk writes them with DSK_SELECT_SHARED_BY_KV_GROUP -- used by all Hq/Hkv query heads
@@ -515,7 +515,8 @@ size_t dsk_reuse_workspace_bytes(const dsk_reuse_args* args);
 /* Where dsk_sparse_decode_attn leaves its split-K partials in args->workspace (what a caller
  * that sets DSK_ATTN_PARTIALS_ONLY reads).  Chunk c of (sequence s, head h) covers the selected
  * slots [c*slots_per_chunk, (c+1)*slots_per_chunk) and is valid for
- * c < ceil(min(sel_count[s,h], k) / slots_per_chunk).  With p = (s*Hq + h)*nchunks + c:
+ * c < ceil(min(sel_count[s,h], k) / slots_per_chunk); with DSK_ATTN_SHARED_SELECTION the count is that of
+ * the head's KV head, and a cache without tokens has no partials.  With p = (s*Hq + h)*nchunks + c:
  *   (m, l)  = ((const float*)(workspace + ml_offset))[2p], [2p+1]   running max of the logits in
  *             log2 units (logit * log2(e)), and sum of 2^(logit2 - m)
  *   acc[d]  = ((const float*)(workspace + acc_offset))[p*D + d]      sum of 2^(logit2 - m) * V[d]

@@ -133,14 +133,14 @@ struct FoldSlots {
 };
 
 // One workgroup of WAVES wavefronts per (chunk of WAVES*SPW slots, head, sequence); writes one partial, or the
-// final result when the head has a single chunk.  NS = 0 selects the generic path for slots
-// longer than 32 rows (2 slots per wave, rows folded 32 at a time).
+// final result when the head has a single chunk (its partial as well for a caller that merges by itself: `leave`).
+// NS = 0 selects the generic path for slots longer than 32 rows (2 slots per wave, rows folded 32 at a time).
 template <int NS, int SPW, int WAVES, bool STAGED = false>
 __global__ __launch_bounds__(WAVES * DSK_WAVE) void attn_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ K, const uint16_t* __restrict__ V,
     int64_t kst, int64_t ksh, int64_t vst, int64_t vsh, int Hq, int G, int n_groups, int k, int b, int total_tokens,
     const int32_t* __restrict__ sel_start, const int32_t* __restrict__ sel_len,
-    const int32_t* __restrict__ sel_count, int sel_div, float scale_log2, AttnPlace place, int nchunks,
+    const int32_t* __restrict__ sel_count, int sel_div, float scale_log2, AttnPlace place, int nchunks, bool leave,
     float2* __restrict__ part_ml, float* __restrict__ part_acc, float* __restrict__ out,
     uint16_t* __restrict__ out_bf16, float* __restrict__ lse) {
   constexpr int kAttnWaves = WAVES;
@@ -276,7 +276,7 @@ __global__ __launch_bounds__(WAVES * DSK_WAVE) void attn_kernel(
   if (used == 1) {   // the only chunk of this head: finish here
     store_attn_out(out, out_bf16, sh * DSK_HEAD_DIM + d, l > 0.0f ? a / l : 0.0f);
     if (d == 0 && lse) lse[sh] = l > 0.0f ? (M + log2f(l)) * kLn2 : -__builtin_inff();
-    return;
+    if (!leave) return;
   }
   const int64_t pbase = sh * nchunks;
   part_acc[(pbase + chunk) * DSK_HEAD_DIM + d] = a;
@@ -421,7 +421,7 @@ __global__ __launch_bounds__(kLongWaves * DSK_WAVE) void attn_long_kernel(
 // four logits of one head instead of every lane with all of them; the weights go back to the rows' lanes by swapping
 // halves and rows of the wavefront (a 4 x 4 transposition of registers and lane groups) and are broadcast inside a row of
 // 16 lanes.  About 250 instructions.  The sums over V stay in fp32 on the vector ALU.
-// A workgroup of kLongWaves wavefronts for every CU, as in attn_long_kernel.  Steps at 30K tokens, 128 slots of 16 rows a
+// A workgroup of kLongWaves wavefronts for every CU, as in attn_long_kernel; `leave` as in attn_kernel.  Steps at 30K tokens, 128 slots of 16 rows a
 // list, before (two slots per wavefront, heads in tiles of 2 or 4, other widths per head) and now: eight sequences of
 // 32 / 8 heads 33.1 -> 30.1 us, of 28 / 4 heads 36.4 -> 29.8; 512 slots of 8 rows 62.0 -> 46.8 and 75.5 -> 41.5.
 typedef __attribute__((ext_vector_type(8))) __bf16 attn_bf16x8;
@@ -477,7 +477,7 @@ __global__ __launch_bounds__(kLongWaves * DSK_WAVE) void attn_shared_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ K, const uint16_t* __restrict__ V,
     int64_t kst, int64_t ksh, int64_t vst, int64_t vsh, int Hq, int G, int k, int b, int total_tokens,
     const int32_t* __restrict__ sel_start, const int32_t* __restrict__ sel_len,
-    const int32_t* __restrict__ sel_count, float scale_log2, int nchunks, int slots_per_wg,
+    const int32_t* __restrict__ sel_count, float scale_log2, int nchunks, int slots_per_wg, bool leave,
     float2* __restrict__ part_ml, float* __restrict__ part_acc, float* __restrict__ out,
     uint16_t* __restrict__ out_bf16, float* __restrict__ lse) {
   static_assert(GT <= 8 && 16 % GT == 0, "the heads repeat over the 16 columns of a product");
@@ -647,7 +647,8 @@ __global__ __launch_bounds__(kLongWaves * DSK_WAVE) void attn_shared_kernel(
     if (count <= slots_per_wg) {
       store_attn_out(out, out_bf16, sh * DSK_HEAD_DIM + d, ls > 0.0f ? a / ls : 0.0f);
       if (d == 0 && lse) lse[sh] = ls > 0.0f ? (M + log2f(ls)) * kLn2 : -__builtin_inff();
-    } else {
+    }
+    if (count > slots_per_wg || leave) {
       part_acc[(sh * nchunks + chunk) * DSK_HEAD_DIM + d] = a;
       if (d == 0) part_ml[sh * nchunks + chunk] = make_float2(M, ls);
     }
@@ -783,7 +784,7 @@ AttnWs attn_ws_layout(const dsk_attn_args& a, bool size_only) {
     const int tile = attn_shared_tile(G);
     const int64_t lists = (int64_t)a.B * a.Hkv * ((G + tile - 1) / tile);
     chunks = attn_even_chunks([&](int ch) { return (lists * ch + 7) / 8; }, lists, a.k, kSharedChunkSlots, 0.0);
-    if (own_merge && chunks < 2) chunks = 2;                 // partials are left where they were left before
+    if (own_merge && chunks < 2) chunks = 2;                 // it is partials that such a caller wants
     if (chunks > room) chunks = room;
     ws.kernel = AttnKernel::kShared;
   } else if (!own_merge && a.b <= 32 && a.k >= ((a.flags & DSK_ATTN_SHARED_SELECTION) ? kLongMinSlotsShared : kLongMinSlots) &&
@@ -817,6 +818,8 @@ hipError_t launch_attn(const dsk_attn_args& a, const AttnWs& ws, hipStream_t st)
   // heads that read one row of the selection arrays; the workgroups of a group's heads gather the
   // same rows on one XCD, so only one of them misses in L2
   const int sel_div = (a.flags & DSK_ATTN_SHARED_SELECTION) ? a.Hq / a.Hkv : 1;
+  // a caller that merges by itself finds the partials of every list that has a slot
+  const bool leave = (a.flags & DSK_ATTN_PARTIALS_ONLY) != 0 && ws.nchunks > 1;
   if (ws.kernel != AttnKernel::kShort) {
     const dim3 block(kLongWaves * DSK_WAVE);
 #define DSK_LONG_ARGS                                                                                             \
@@ -825,7 +828,7 @@ hipError_t launch_attn(const dsk_attn_args& a, const AttnWs& ws, hipStream_t st)
   q, K, V, a.k_stride_tok, a.k_stride_head, a.v_stride_tok, a.v_stride_head, a.Hq, a.Hq / a.Hkv, __VA_ARGS__ a.k, a.b, \
       a.total_tokens, a.sel_start, a.sel_len, a.sel_count
 #define DSK_SHARED_ARGS                                                                                           \
-  DSK_GATHER_ARGS(), scale * kLog2e, ws.nchunks, ws.slots_per_wg, part_ml, part_acc, a.out,                       \
+  DSK_GATHER_ARGS(), scale * kLog2e, ws.nchunks, ws.slots_per_wg, leave, part_ml, part_acc, a.out,                       \
       static_cast<uint16_t*>(a.out_bf16), a.lse
     if (ws.kernel == AttnKernel::kLong) {
       if (a.b <= 16) attn_long_kernel<4><<<grid, block, 0, st>>>(DSK_GATHER_ARGS(n_groups,), DSK_LONG_ARGS);
@@ -852,7 +855,7 @@ hipError_t launch_attn(const dsk_attn_args& a, const AttnWs& ws, hipStream_t st)
   }
 #define DSK_ATTN_ARGS                                                                                          \
   q, K, V, a.k_stride_tok, a.k_stride_head, a.v_stride_tok, a.v_stride_head, a.Hq, a.Hq / a.Hkv, n_groups, a.k, a.b, \
-      a.total_tokens, a.sel_start, a.sel_len, a.sel_count, sel_div, scale * kLog2e, place, ws.nchunks, part_ml, part_acc, \
+      a.total_tokens, a.sel_start, a.sel_len, a.sel_count, sel_div, scale * kLog2e, place, ws.nchunks, leave, part_ml, part_acc, \
       a.out, static_cast<uint16_t*>(a.out_bf16), a.lse
   // Slots of at most 32 rows: workgroups of 8 wavefronts, 2 slots each (16 slots per workgroup).
   // Measured against 4 wavefronts x 2 or 4 slots, 8 x 1 or 4, 16 x 1 or 2 on all configurations:

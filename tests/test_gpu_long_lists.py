@@ -149,3 +149,60 @@ def test_partials_of_shared_lists(B, Hq, Hkv, k):
     w = np.exp2(ml[..., 0] - ml[..., 0].max(-1, keepdims=True))
     out = (acc * w[..., None]).sum(2) / (ml[..., 1] * w).sum(2)[..., None]
     assert rel_err(full.out.cpu().numpy(), out) <= 1e-5        # 32-bit sums in two orders, as in test_long_lists
+
+
+# (B, Hq, Hkv, k, b, shared): chunks of 16, 8 and 8 slots a head; a list that a group shares in short chunks and, from 3072
+# slots on, in two and in more chunks
+SHORT_COUNTS = [(2, 8, 2, 50, 16, False), (8, 32, 8, 128, 16, False), (1, 8, 8, 20, 64, False), (2, 8, 2, 50, 32, True),
+                (8, 32, 8, 128, 16, True), (16, 64, 16, 64, 16, True), (8, 28, 4, 129, 32, True)]
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,k,b,shared", SHORT_COUNTS)
+def test_partials_of_lists_that_fit_one_chunk(B, Hq, Hkv, k, b, shared):
+    """Every list with a slot leaves its partials where the layout says, also one that fits its first chunk: merged by the
+    documented formula they are the merged call's result."""
+    import paper_2602_03184_amd as dsk
+    rng = np.random.default_rng([B, Hq, k, b])
+    g = torch.Generator(device="cuda")
+    g.manual_seed(k)
+    L = 2001
+    K, V = (torch.randn(Hkv, L, 128, generator=g, device="cuda").bfloat16() for _ in range(2))
+    q = torch.randn(B, Hq, 128, generator=g, device="cuda").bfloat16()
+    H = Hkv if shared else Hq
+    flags = dsk.DSK_ATTN_SHARED_SELECTION if shared else 0
+    counts = np.full((B, H), k)
+    start, length = _lists(rng, B, H, k, b, L, counts)
+    cnt = dev_i32(counts)
+    full, part = (dsk.make_attn_args(q, K, V, dev_i32(start), dev_i32(length), cnt, b, flags=flags | f)
+                  for f in (0, dsk.DSK_ATTN_PARTIALS_ONLY))
+    lay = dsk.dsk_attn_partials_layout(part.args)
+    per = lay.slots_per_chunk
+    assert lay.nchunks > 1 and lay.nchunks * per >= k
+    some = np.array([1, per, 0, per + 1, per - 1, k, 2, k + 3])
+    counts = some[np.arange(B * H) % len(some)].reshape(B, H)
+    cnt.copy_(dev_i32(counts))
+    part.keep[-1].fill_(255)                                       # NaN wherever no partial is written
+    dsk.dsk_sparse_decode_attn(full.args)
+    dsk.dsk_sparse_decode_attn(part.args)
+    torch.cuda.synchronize()
+    raw = part.keep[-1].view(torch.uint8).cpu().numpy()
+    n = B * Hq * lay.nchunks
+    ml = raw[lay.ml_offset: lay.ml_offset + n * 8].view(np.float32).reshape(B, Hq, lay.nchunks, 2).astype(np.float64)
+    acc = raw[lay.acc_offset: lay.acc_offset + n * 512].view(np.float32).reshape(B, Hq, lay.nchunks, 128).astype(np.float64)
+    out, lse = full.out.cpu().numpy(), full.lse.cpu().numpy()
+    for s in range(B):
+        for h in range(Hq):
+            c = min(int(counts[s, h // (Hq // H)]), k)
+            used = -(-c // per)
+            assert np.isnan(ml[s, h, used:]).all() and np.isnan(acc[s, h, used:]).all()
+            if c == 0:
+                assert float(part.out[s, h].abs().max()) == 0.0 and float(part.lse[s, h]) == -np.inf
+                continue
+            m, l = ml[s, h, :used].T
+            w = np.exp2(m - m.max())
+            # 32-bit sums in two orders, as in test_long_lists
+            assert rel_err(out[s, h], (acc[s, h, :used] * w[:, None]).sum(0) / (l * w).sum()) <= 1e-5
+            assert abs(lse[s, h] - math.log(2.0) * (m.max() + math.log2((l * w).sum()))) <= 1e-5
+            if used == 1:
+                assert rel_err(part.out[s, h].cpu().numpy(), out[s, h]) <= 1e-5
+                assert abs(float(part.lse[s, h]) - lse[s, h]) <= 1e-5
