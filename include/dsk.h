@@ -522,8 +522,10 @@ size_t dsk_reuse_workspace_bytes(const dsk_reuse_args* args);
  *   acc[d]  = ((const float*)(workspace + acc_offset))[p*D + d]      sum of 2^(logit2 - m) * V[d]
  * The merged result is out = sum_c acc_c 2^(m_c - M) / sum_c l_c 2^(m_c - M), M = max_c m_c, and
  * lse = ln(2) * M + ln(sum_c l_c 2^(m_c - M)) (App. B.2 Step 3, online-softmax split).
- * When nchunks == 1 no partials are written: out / lse are final.  Returns DSK_ERR_SHAPE /
- * DSK_ERR_NULL / DSK_ERR_VERSION on unusable arguments (only geometry fields are read). */
+ * When nchunks == 1 no partials are written: out / lse are final.  Read are B, Hq, Hkv, k, b and
+ * DSK_ATTN_SHARED_SELECTION; the layout is that of a call with DSK_ATTN_PARTIALS_ONLY whether args carries the flag
+ * yet or not (a call without it may cut its lists otherwise).  Returns DSK_ERR_SHAPE / DSK_ERR_NULL /
+ * DSK_ERR_VERSION on unusable arguments. */
 typedef struct dsk_attn_partials {
   size_t ml_offset, acc_offset;    /* bytes from args->workspace */
   int32_t nchunks, slots_per_chunk;

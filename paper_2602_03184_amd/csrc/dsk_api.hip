@@ -404,7 +404,9 @@ dsk_status dsk_attn_partials_layout(const dsk_attn_args* a, dsk_attn_partials* o
   if (a == nullptr || out == nullptr) return DSK_ERR_NULL;
   if (a->struct_size != sizeof(dsk_attn_args)) return DSK_ERR_VERSION;
   if (a->B < 1 || a->Hq < 1 || a->k < 1 || a->b < 1) return DSK_ERR_SHAPE;
-  const AttnWs ws = attn_ws_layout(*a);
+  dsk_attn_args leaving = *a;
+  leaving.flags |= DSK_ATTN_PARTIALS_ONLY;   // a call that merges its partials itself may cut the lists otherwise
+  const AttnWs ws = attn_ws_layout(leaving);
   out->ml_offset = ws.part_ml;
   out->acc_offset = ws.part_acc;
   out->nchunks = ws.nchunks;

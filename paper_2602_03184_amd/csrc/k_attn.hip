@@ -39,8 +39,7 @@ constexpr int64_t kAttnSmallWgFrom = 1536;   // workgroups of 16 slots from whic
 // 30K tokens, 128 slots of 16 rows, per head / shared: one sequence 16.2 / 19.3 us, two 20.4 / 21.0, three 24.5 / 22.4).
 constexpr int64_t kSharedMinSlots = 3072;      // selected slots of all lists
 static bool attn_shared(const dsk_attn_args& a) {
-  return (a.flags & DSK_ATTN_SHARED_SELECTION) && a.Hq > a.Hkv && a.b <= 32 && (int64_t)a.B * a.Hkv * a.k >= kSharedMinSlots &&
-         a.k_stride_tok <= kMaxTokenStride && a.v_stride_tok <= kMaxTokenStride;
+  return (a.flags & DSK_ATTN_SHARED_SELECTION) && a.Hq > a.Hkv && a.b <= 32 && (int64_t)a.B * a.Hkv * a.k >= kSharedMinSlots;
 }
 // heads of a group that a workgroup takes together
 static int attn_shared_tile(int G) { return G <= 2 ? 2 : G <= 4 ? 4 : 8; }
@@ -471,8 +470,10 @@ __device__ __forceinline__ void add_row(float (&acc)[GT][8], float p, const floa
 }
 
 // NT: 16-row tiles of a slot; GT: query heads of a tile of the group (the last tile of a group may have fewer; the columns
-// of those it does not have repeat its first one).  grid: chunk, fastest, then head tile, KV head, sequence
-template <int NT, int GT>
+// of those it does not have repeat its first one).  WIDE: token strides above kMaxTokenStride, row offsets in 64 bits (the
+// chunks, which a caller that merges by itself asks for, do not depend on the strides).
+// grid: chunk, fastest, then head tile, KV head, sequence
+template <int NT, int GT, bool WIDE>
 __global__ __launch_bounds__(kLongWaves * DSK_WAVE) void attn_shared_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ K, const uint16_t* __restrict__ V,
     int64_t kst, int64_t ksh, int64_t vst, int64_t vsh, int Hq, int G, int k, int b, int total_tokens,
@@ -530,6 +531,11 @@ __global__ __launch_bounds__(kLongWaves * DSK_WAVE) void attn_shared_kernel(
   const uint16_t* Kh = K + (int64_t)hk * ksh;
   const uint16_t* Vh = V + (int64_t)hk * vsh;
   const unsigned kst8 = (unsigned)kst >> 3, vst8 = (unsigned)vst >> 3;             // strides: multiples of 8, at most 2^24
+  // 16 bytes at column `col` of row `row`
+  auto at_row = [](const char* base, int row, int64_t stride, unsigned stride8, int col) {
+    if constexpr (WIDE) return base + ((int64_t)row * stride * 2 + col * 16);
+    else return base + (__umul24((unsigned)row, stride8) + (unsigned)col) * 16u;
+  };
 
   // of head c % GT: reference, this lane group's part of the denominator; of all heads: channels 8c .. of this group's rows
   float m = -__builtin_inff(), l = 0.0f, acc[GT][8];
@@ -556,14 +562,14 @@ __global__ __launch_bounds__(kLongWaves * DSK_WAVE) void attn_shared_kernel(
 #pragma unroll
       for (int t = 0; t < NT; ++t) {
         const int row = 16 * t + c < nv ? 16 * t + c : nv - 1;
-        const unsigned at = (__umul24((unsigned)row, kst8) + (unsigned)g) * 16u;
+        const char* from = at_row(kb, row, kst, kst8, g);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) kd[t][i] = *reinterpret_cast<const u32x4_t*>(kb + at + 64 * i);
+        for (int i = 0; i < 4; ++i) kd[t][i] = *reinterpret_cast<const u32x4_t*>(from + 64 * i);
       }
 #pragma unroll
       for (int u = 0; u < 4 * NT; ++u) {
         const int row = 4 * u + g < nv ? 4 * u + g : nv - 1;
-        vd[u] = *reinterpret_cast<const u32x4_t*>(vb + (__umul24((unsigned)row, vst8) + (unsigned)c) * 16u);
+        vd[u] = *reinterpret_cast<const u32x4_t*>(at_row(vb, row, vst, vst8, c));
       }
 #pragma unroll
       for (int t = 0; t < NT; ++t)
@@ -836,14 +842,21 @@ hipError_t launch_attn(const dsk_attn_args& a, const AttnWs& ws, hipStream_t st)
     } else {
       const int G = a.Hq / a.Hkv, tile = attn_shared_tile(G);
       const dim3 sgrid((unsigned)(n_groups * ((G + tile - 1) / tile) * ws.nchunks));
+      const bool wide = a.k_stride_tok > kMaxTokenStride || a.v_stride_tok > kMaxTokenStride;
+#define DSK_SHARED_LAUNCH(NT, GT)                                                                                 \
+  do {                                                                                                            \
+    if (wide) attn_shared_kernel<NT, GT, true><<<sgrid, block, 0, st>>>(DSK_SHARED_ARGS);                         \
+    else attn_shared_kernel<NT, GT, false><<<sgrid, block, 0, st>>>(DSK_SHARED_ARGS);                             \
+  } while (0)
       switch (tile * 64 + (a.b <= 16 ? 1 : 2)) {
-        case 2 * 64 + 1: attn_shared_kernel<1, 2><<<sgrid, block, 0, st>>>(DSK_SHARED_ARGS); break;
-        case 2 * 64 + 2: attn_shared_kernel<2, 2><<<sgrid, block, 0, st>>>(DSK_SHARED_ARGS); break;
-        case 4 * 64 + 1: attn_shared_kernel<1, 4><<<sgrid, block, 0, st>>>(DSK_SHARED_ARGS); break;
-        case 4 * 64 + 2: attn_shared_kernel<2, 4><<<sgrid, block, 0, st>>>(DSK_SHARED_ARGS); break;
-        case 8 * 64 + 1: attn_shared_kernel<1, 8><<<sgrid, block, 0, st>>>(DSK_SHARED_ARGS); break;
-        default: attn_shared_kernel<2, 8><<<sgrid, block, 0, st>>>(DSK_SHARED_ARGS);
+        case 2 * 64 + 1: DSK_SHARED_LAUNCH(1, 2); break;
+        case 2 * 64 + 2: DSK_SHARED_LAUNCH(2, 2); break;
+        case 4 * 64 + 1: DSK_SHARED_LAUNCH(1, 4); break;
+        case 4 * 64 + 2: DSK_SHARED_LAUNCH(2, 4); break;
+        case 8 * 64 + 1: DSK_SHARED_LAUNCH(1, 8); break;
+        default: DSK_SHARED_LAUNCH(2, 8);
       }
+#undef DSK_SHARED_LAUNCH
     }
 #undef DSK_LONG_ARGS
 #undef DSK_SHARED_ARGS

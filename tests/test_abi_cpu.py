@@ -352,3 +352,26 @@ def test_compress_workspace_does_for_smaller_calls(dsk, Hq, Hkv):
                 assert size(B, M, W) <= min(size(B + 1, M, W), size(B, M + 1, W))
                 if W < 64:
                     assert size(B, M, W) <= size(B, M, W + 1), (B, M, W)
+
+
+# (B, Hq, Hkv, k, b): lists per head short and long, shared lists on the kernel of their own and below it, slots of 64 rows
+@pytest.mark.parametrize("B,Hq,Hkv,k,b", [(1, 4, 2, 8, 16), (8, 32, 8, 128, 16), (1, 40, 40, 256, 16), (8, 28, 4, 129, 32),
+                                          (2, 16, 2, 600, 16), (64, 8, 8, 512, 16), (16, 64, 16, 64, 16), (4, 32, 8, 100, 64)])
+@pytest.mark.parametrize("shared", [False, True])
+def test_partials_layout_follows_the_geometry_alone(dsk, B, Hq, Hkv, k, b, shared):
+    """The flag and the strides may be filled in after the layout was asked for; the partials lie inside the workspace."""
+    a = dsk.dsk_attn_args()
+    a.struct_size = C.sizeof(a)
+    a.B, a.Hq, a.Hkv, a.D, a.k, a.b = B, Hq, Hkv, 128, k, b
+    lays = set()
+    for leave in (0, dsk.DSK_ATTN_PARTIALS_ONLY):
+        for stride in (0, 128, 128 * Hkv, (1 << 24) + 8):
+            a.flags = leave | (dsk.DSK_ATTN_SHARED_SELECTION if shared else 0)
+            a.k_stride_tok, a.v_stride_tok = stride, max(stride, 128)
+            lay = dsk.dsk_attn_partials_layout(a)
+            lays.add((lay.ml_offset, lay.acc_offset, lay.nchunks, lay.slots_per_chunk))
+            n = B * Hq * lay.nchunks
+            assert lay.nchunks == -(-k // lay.slots_per_chunk)
+            assert lay.ml_offset + 8 * n <= lay.acc_offset
+            assert lay.acc_offset + 512 * n <= dsk.dsk_attn_workspace_bytes(a)
+    assert len(lays) == 1

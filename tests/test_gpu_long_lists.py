@@ -40,19 +40,29 @@ def _want(q, K, V, start, length, counts, div):
     return out, lse
 
 
-# (B, Hq, Hkv, k, b): one list a head with 32 slots, one more, a slot count beyond the 64 spans of a wavefront; several
-# chunks; runs of chunks on XCDs of their own (4, 2, 1 and 3 groups); heads without groups; several rounds of workgroups
-# (and, where a list is shared: every width and tile of the shared kernel, slots of one and two tiles of 16 rows)
-SHAPES = [(8, 32, 8, 32, 16, True), (8, 32, 8, 33, 16, True), (8, 32, 8, 545, 8, True), (2, 32, 8, 163, 32, True),
-          (1, 28, 4, 257, 16, True), (1, 16, 2, 515, 8, True), (1, 8, 1, 129, 16, False), (1, 40, 40, 245, 16, True),
-          (3, 6, 1, 40, 16, False), (8, 40, 8, 121, 16, True), (3, 16, 2, 16, 32, False), (1, 28, 4, 40, 64, False),
-          (4, 16, 8, 97, 32, False), (5, 24, 8, 80, 17, True), (4, 40, 8, 200, 32, True), (12, 56, 8, 33, 9, True),
-          (6, 11, 1, 520, 16, False), (16, 8, 4, 49, 16, False)]
+# (B, Hq, Hkv, k, b, lists per head on the kernel for long lists, shared lists on the kernel of their own): one list a head
+# with 32 slots, one more, a slot count beyond the 64 spans of a wavefront; several chunks; runs of chunks on XCDs of their
+# own (4, 2, 1 and 3 groups); heads without groups; several rounds of workgroups; every width and tile of the shared kernel,
+# slots of one and two tiles of 16 rows, at the slot counts it starts with and well above them
+SHAPES = [(8, 32, 8, 32, 16, True, False), (8, 32, 8, 33, 16, True, False), (8, 32, 8, 545, 8, True, True),
+          (2, 32, 8, 163, 32, True, False), (1, 28, 4, 257, 16, True, False), (1, 16, 2, 515, 8, True, False),
+          (1, 8, 1, 129, 16, False, False), (1, 40, 40, 245, 16, True, False), (3, 6, 1, 40, 16, False, False),
+          (8, 40, 8, 121, 16, True, True), (3, 16, 2, 16, 32, False, False), (1, 28, 4, 40, 64, False, False),
+          (4, 16, 8, 97, 32, False, True), (5, 24, 8, 83, 17, True, True), (4, 40, 8, 200, 32, True, True),
+          (12, 56, 8, 33, 9, True, True), (6, 11, 1, 520, 16, False, True), (16, 8, 4, 49, 16, False, True),
+          (8, 16, 8, 150, 32, True, True), (8, 24, 8, 139, 17, False, True), (12, 56, 8, 83, 9, True, True),
+          (8, 11, 1, 810, 16, True, True), (16, 8, 4, 121, 16, True, True)]
 
 
-@pytest.mark.parametrize("B,Hq,Hkv,k,b,is_long", SHAPES)
+def _partials_left(att, lay):
+    """Number of partials that a call wrote into a workspace that held NaN."""
+    ml = att.keep[-1].view(torch.uint8).cpu().numpy()[lay.ml_offset: lay.acc_offset].view(np.float32).reshape(-1, 2)
+    return int((~np.isnan(ml[:, 1])).sum())
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,k,b,is_long,on_shared_kernel", SHAPES)
 @pytest.mark.parametrize("layout", ["hnd", "nhd"])
-def test_long_lists(B, Hq, Hkv, k, b, is_long, layout):
+def test_long_lists(B, Hq, Hkv, k, b, is_long, on_shared_kernel, layout):
     import paper_2602_03184_amd as dsk
     rng = np.random.default_rng([B, Hq, Hkv, k, b])
     g = torch.Generator(device="cuda")
@@ -72,10 +82,17 @@ def test_long_lists(B, Hq, Hkv, k, b, is_long, layout):
         flags = dsk.DSK_ATTN_SHARED_SELECTION if shared else 0
         att = dsk.make_attn_args(q, K, V, dev_i32(start), dev_i32(length), dev_i32(counts), b, flags=flags, want_bf16=True)
         lay = dsk.dsk_attn_partials_layout(att.args)
-        assert shared or (lay.slots_per_chunk >= 32) == is_long
         assert lay.nchunks * lay.slots_per_chunk >= k
+        if shared:                                        # the others cut lists that are to be left in parts into 8 or 16
+            assert (lay.slots_per_chunk not in (8, 16)) == on_shared_kernel
         att.out.fill_(7.0)
+        att.keep[-1].fill_(255)
         dsk.dsk_sparse_decode_attn(att.args)
+        torch.cuda.synchronize()
+        if not shared:
+            used = -(-counts // lay.slots_per_chunk)      # of short chunks, as they are left in parts
+            left, short = _partials_left(att, lay), int(used[used > 1].sum())
+            assert left < short if is_long else left == short
         again = dsk.make_attn_args(q, K, V, dev_i32(start), dev_i32(length), dev_i32(counts), b, flags=flags)
         dsk.dsk_sparse_decode_attn(again.args)
         torch.cuda.synchronize()
@@ -104,6 +121,7 @@ def test_long_lists_skip_spans_outside_the_cache():
     bad_start = np.where(keep, start, rng.choice([-1, L - 1, L, 2 ** 30], size=start.shape)).astype(np.int32)
     bad_len = np.where(keep | (bad_start != L - 1), length, 2).astype(np.int32)
     att = dsk.make_attn_args(q, K, V, dev_i32(bad_start), dev_i32(bad_len), dev_i32(counts), b)
+    att.keep[-1].fill_(255)
     dsk.dsk_sparse_decode_attn(att.args)
     torch.cuda.synchronize()
     cut = np.zeros((B, Hq), np.int64)
@@ -115,10 +133,48 @@ def test_long_lists_skip_spans_outside_the_cache():
     out, lse = _want(q, K, V, s2, l2, cut, 1)
     assert rel_err(att.out.cpu().numpy(), out) <= 1e-5
     assert np.isinf(att.lse.cpu().numpy()[0, 0]) and float(att.out[0, 0].abs().max()) == 0.0
-    assert dsk.dsk_attn_partials_layout(att.args).nchunks == 1
+    assert _partials_left(att, dsk.dsk_attn_partials_layout(att.args)) == 0                          # one chunk a list
     part = dsk.make_attn_args(q, K, V, dev_i32(start), dev_i32(length), dev_i32(counts), b, flags=dsk.DSK_ATTN_PARTIALS_ONLY)
     assert dsk.dsk_attn_partials_layout(part.args).nchunks > 1
     assert part.args.workspace_bytes == att.args.workspace_bytes
+
+
+@pytest.mark.parametrize("wide", ["K", "V", "KV"])
+@pytest.mark.parametrize("b", [16, 32])
+def test_token_strides_of_any_size(wide, b):
+    """K and V whose rows lie 2^24 elements and more apart, or as far apart as each likes, per head and shared: the same rows
+    as in a cache without gaps, the partials where the layout says whatever the strides."""
+    import paper_2602_03184_amd as dsk
+    B, Hq, Hkv, k, L = 8, 28, 4, 100, 48
+    rng = np.random.default_rng(b)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(b)
+    K, V = (torch.randn(Hkv, L, 128, generator=g, device="cuda").bfloat16() for _ in range(2))
+    q = torch.randn(B, Hq, 128, generator=g, device="cuda").bfloat16()
+
+    def spread(x, stride):                                         # 1.6 GB for 2^24 + 8
+        y = torch.empty((L - 1) * stride + Hkv * 128, dtype=x.dtype, device="cuda").as_strided((Hkv, L, 128), (128, stride, 1))
+        y.copy_(x)
+        return y
+    Kw = spread(K, (1 << 24) + 8 if "K" in wide else 128 * Hkv + 8)
+    Vw = spread(V, (1 << 24) + 8 if "V" in wide else 128 * Hkv + 64)
+    for shared in (False, True):
+        H = Hkv if shared else Hq
+        counts = np.minimum(k, rng.integers(0, 2 * k, size=(B, H)))
+        counts.flat[0] = k
+        start, length = _lists(rng, B, H, k, b, L, counts)
+        flags = dsk.DSK_ATTN_SHARED_SELECTION if shared else 0
+        args = (dev_i32(start), dev_i32(length), dev_i32(counts), b)
+        att = dsk.sparse_decode_attn(q, Kw, Vw, *args, flags=flags)
+        near, far = (dsk.make_attn_args(q, x, y, *args, flags=flags | dsk.DSK_ATTN_PARTIALS_ONLY) for x, y in ((K, V), (Kw, Vw)))
+        for p in (near, far):
+            p.keep[-1].fill_(255)
+            dsk.dsk_sparse_decode_attn(p.args)
+        torch.cuda.synchronize()
+        out, lse = _want(q, K, V, start, length, counts, Hq // H)
+        assert rel_err(att.out.cpu().numpy(), out) <= 1e-5          # as in test_long_lists
+        np.testing.assert_allclose(att.lse.cpu().numpy(), lse, rtol=0, atol=1e-5)
+        assert torch.equal(near.keep[-1], far.keep[-1])             # same chunks, same sums
 
 
 # (B, Hq, Hkv, k): chunks of the merged call (4), two where that call needs no merge, one slot more than the chunks divide
