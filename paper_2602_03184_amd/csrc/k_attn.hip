@@ -45,12 +45,17 @@ static bool attn_shared(const dsk_attn_args& a) {
 static int attn_shared_tile(int G) { return G <= 2 ? 2 : G <= 4 ? 4 : 8; }
 
 // The place of a workgroup of the per-head kernels.  Workgroup id = 8 * j + x runs on XCD x.  The chunks of all heads of a
-// KV group go to one XCD; where the groups are no multiple of 8, each is cut into `split` runs of `run` chunks, which go to
-// XCDs of their own, so that all eight have the same work (28 / 4 heads, one sequence: four groups used half of the chip).
+// KV group go to one XCD; where the groups are no multiple of 8, each is cut into 2^cut runs of `run` chunks, which go to
+// XCDs of their own, so that all eight have about the same work (28 / 4 heads, one sequence: four groups used half of the
+// chip).  Of the cuts the one with the least work on the busiest XCD, the coarsest of them: cutting until the runs are a
+// multiple of 8 puts more on one where the runs are few (9 / 1 heads, six sequences, 3 chunks: 27 workgroups as they are,
+// 36 in runs of 2 and 1: 10.1 against 11.9 us).
 // Without grouped heads there is nothing to share: the chunks are dealt out over the XCDs in plain order (measured 2 %
 // faster at 40 heads than keeping a head on one XCD).
+// The index arithmetic is in front of every load, so it takes no more than three divisions (the cut is a shift): with five,
+// a step of 17.4 us took 0.1 us longer.
 struct AttnPlace {
-  int split, run;
+  int Hkv, cut, run;
 };
 struct AttnAt {
   int s, hk, h, chunk;   // chunk < 0: nothing to do
@@ -64,33 +69,36 @@ __device__ __forceinline__ AttnAt attn_place(AttnPlace p, int Hq, int G, int n_g
     at.h = at.hk = sh - at.s * Hq;
     return at;
   }
-  const int Hkv = Hq / G;
-  const int per = G * p.run;
-  const int j = blockIdx.x >> 3;
-  const int vl = j / per;
-  const int r = j - vl * per;
-  const int v = vl * 8 + (int)(blockIdx.x & 7);      // (group, run)
-  const int gi = p.split == 1 ? v : v / p.split;
-  const int gq = r / p.run;
-  at.chunk = (v - gi * p.split) * p.run + r - gq * p.run;
-  if (gi >= n_groups || at.chunk >= nchunks) at.chunk = -1;   // padding of the last round of groups, or of the last run
-  at.s = gi / Hkv;
-  at.hk = gi - at.s * Hkv;
+  const unsigned per = G * p.run;
+  const unsigned j = blockIdx.x >> 3;
+  const unsigned vl = j / per;
+  const unsigned r = j - vl * per;
+  const unsigned v = vl * 8 + (blockIdx.x & 7);      // (group, run)
+  const unsigned gi = v >> p.cut;
+  const unsigned gq = r / (unsigned)p.run;
+  at.chunk = (int)((v - (gi << p.cut)) * p.run + r - gq * p.run);
+  if ((int)gi >= n_groups || at.chunk >= nchunks) at.chunk = -1;   // padding of the last round of groups, or of the last run
+  at.s = gi / (unsigned)p.Hkv;
+  at.hk = gi - at.s * p.Hkv;
   at.h = at.hk * G + gq;
   return at;
 }
-static AttnPlace attn_placement(int G, int n_groups, int nchunks) {
-  AttnPlace p = {1, nchunks};
-  if (G == 1) return p;
-  while (p.split < 8 && n_groups * p.split % 8 != 0 && 2 * p.split <= nchunks) p.split *= 2;
-  p.run = (nchunks + p.split - 1) / p.split;
-  return p;
+static AttnPlace attn_placement(int G, int n_groups, int Hkv, int nchunks) {
+  AttnPlace best = {Hkv, 0, nchunks};
+  if (G == 1) return best;
+  int64_t least = (int64_t)(n_groups + 7) / 8 * nchunks;
+  for (int cut = 1; cut <= 3 && (1 << cut) <= nchunks; ++cut) {
+    const int run = (nchunks + (1 << cut) - 1) >> cut;
+    const int64_t most = (((int64_t)n_groups << cut) + 7) / 8 * run;
+    if (most < least) { least = most; best.cut = cut; best.run = run; }
+  }
+  return best;
 }
 // workgroups on every XCD
 static int64_t attn_wgs_per_xcd(int G, int n_groups, int nchunks) {
-  const AttnPlace p = attn_placement(G, n_groups, nchunks);
+  const AttnPlace p = attn_placement(G, n_groups, 1, nchunks);
   if (G == 1) return ((int64_t)n_groups * nchunks + 7) / 8;
-  return ((int64_t)n_groups * p.split + 7) / 8 * G * p.run;
+  return (((int64_t)n_groups << p.cut) + 7) / 8 * G * p.run;
 }
 
 // ordinary (compiler-scheduled) loads; used for slots longer than 32 rows
@@ -153,7 +161,7 @@ __global__ __launch_bounds__(WAVES * DSK_WAVE) void attn_kernel(
   const int s = at.s, hk = at.hk, h = at.h, chunk = at.chunk;
   const int64_t sh = (int64_t)s * Hq + h;
   // row of the selection arrays: the head's own, or its KV head's when sel_div = Hq/Hkv heads share one
-  const int64_t sr = sel_div == 1 ? sh : (int64_t)s * (Hq / sel_div) + h / sel_div;   // no division on the per-head path
+  const int64_t sr = sel_div == 1 ? sh : (int64_t)s * place.Hkv + hk;
   const int lane = threadIdx.x & (DSK_WAVE - 1);
   const int wave = threadIdx.x / DSK_WAVE;
   const int slot0 = chunk * kSlotsPerWg;
@@ -310,7 +318,7 @@ __global__ __launch_bounds__(kLongWaves * DSK_WAVE) void attn_long_kernel(
   const AttnAt at = attn_place(place, Hq, G, n_groups, nchunks);
   if (at.chunk < 0) return;
   const int64_t sh = (int64_t)at.s * Hq + at.h;
-  const int64_t sr = sel_div == 1 ? sh : (int64_t)at.s * (Hq / sel_div) + at.h / sel_div;   // row of the selection arrays
+  const int64_t sr = sel_div == 1 ? sh : (int64_t)at.s * place.Hkv + at.hk;   // row of the selection arrays
   const int slot0 = at.chunk * slots_per_wg;
   const int lane = threadIdx.x & (DSK_WAVE - 1);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / DSK_WAVE);
@@ -814,7 +822,7 @@ hipError_t launch_attn(const dsk_attn_args& a, const AttnWs& ws, hipStream_t st)
   float* part_acc = reinterpret_cast<float*>(w + ws.part_acc);
   const float scale = a.scale != 0.0f ? a.scale : 0.08838834764831845f;   // 128^-1/2
   const int n_groups = a.B * a.Hkv;
-  const AttnPlace place = attn_placement(a.Hq / a.Hkv, n_groups, ws.nchunks);
+  const AttnPlace place = attn_placement(a.Hq / a.Hkv, n_groups, a.Hkv, ws.nchunks);
   const dim3 grid(a.Hq == a.Hkv ? (unsigned)(n_groups * ws.nchunks)
                                 : (unsigned)(8 * attn_wgs_per_xcd(a.Hq / a.Hkv, n_groups, ws.nchunks)));
 
