@@ -754,23 +754,36 @@ __global__ __launch_bounds__(kMergeThreads) void attn_merge_kernel(
   }
 }
 
-// Chunks per list for the kernels that want a workgroup on every CU: those that occupy the CUs most evenly (in up to four
-// rounds), the fewest of them within 6 %, with at least min_slots slots in each where there are several; 0 if none
-// reaches min_use.
+// Chunks per list for the kernels that want a workgroup on every CU: those that occupy the CUs most evenly (in up to
+// max_rounds workgroups a CU; a list that takes more by itself stays whole where several are allowed), the fewest of them
+// within 6 %, with at least min_slots slots in each where there are several; 0 if none reaches min_use.
 // per_xcd(ch): workgroups on the busiest XCD.
 constexpr int kCusPerXcd = 32;
+constexpr int kManyRounds = 4;
 template <typename PerXcd>
-static int attn_even_chunks(PerXcd per_xcd, int64_t lists, int k, int min_slots, double min_use) {
+static int attn_even_chunks(PerXcd per_xcd, int64_t lists, int k, int min_slots, double min_use, int max_rounds) {
   int best = 0;
   double best_use = 0.0;
   for (int ch = 1; ch == 1 || ch * min_slots <= k; ++ch) {
     const int64_t rounds = (per_xcd(ch) + kCusPerXcd - 1) / kCusPerXcd;
-    if (rounds > 4 && best > 0) break;
+    if (rounds > max_rounds && (best > 0 || max_rounds == 1)) break;
     const double use = (double)lists * ch / ((double)rounds * kCusPerXcd * 8);
     if (use >= min_use && (best == 0 || use > best_use + 0.06)) { best = ch; best_use = use; }
-    if (rounds > 4) break;
+    if (rounds > max_rounds) break;
   }
   return best;
+}
+
+// Lists per head on attn_long_kernel: where one workgroup a CU occupies at least 85 % of the CUs.  435 such calls with random
+// heads (1 to 16 a group), batches, lists and shared rows took 0.89 times as long as on attn_kernel in the mean, 1.036 at
+// most; with 75 to 85 % of them it would be 0.92, but a seventh of the calls more than 2 % longer.  (The 6 % above: no
+// slack is as fast, 15 % 1.04 times as long.)  With several workgroups a CU the heads of a group are side by side no longer; that pays where there is little to
+// keep together or attn_kernel does badly: groups of 10 heads and more (713 calls, 0.78, 1.06 at most), lists of up to 1024
+// rows (262 calls, 0.83, 1.02) and slots that leave a quarter and more of the 16 or 32 rows that both kernels have in
+// flight empty (1457 calls, 0.85, 1.05).  The other 1676 took 0.94 in the mean, but an eighth of them more than 2 % longer
+// than on attn_kernel, 13 % at most (48 / 8 heads, six sequences, 175 slots of 16 rows 34.1 -> 38.0 us).
+static bool attn_long_in_rounds(const dsk_attn_args& a, int G) {
+  return G >= 10 || (int64_t)a.k * a.b <= 1024 || a.b <= 12 || (a.b > 16 && a.b <= 24);
 }
 
 // The space asked for is that of short chunks (8 or 16 slots), whatever the call takes.
@@ -797,7 +810,8 @@ AttnWs attn_ws_layout(const dsk_attn_args& a, bool size_only) {
   if (attn_shared(a)) {
     const int tile = attn_shared_tile(G);
     const int64_t lists = (int64_t)a.B * a.Hkv * ((G + tile - 1) / tile);
-    chunks = attn_even_chunks([&](int ch) { return (lists * ch + 7) / 8; }, lists, a.k, kSharedChunkSlots, 0.0);
+    chunks = attn_even_chunks([&](int ch) { return (lists * ch + 7) / 8; }, lists, a.k, kSharedChunkSlots, 0.0,
+                              kManyRounds);
     if (own_merge && chunks < 2) chunks = 2;                 // it is partials that such a caller wants
     if (chunks > room) chunks = room;
     ws.kernel = AttnKernel::kShared;
@@ -805,7 +819,7 @@ AttnWs attn_ws_layout(const dsk_attn_args& a, bool size_only) {
              a.k_stride_tok <= kMaxTokenStride && a.v_stride_tok <= kMaxTokenStride) {
     const int n_groups = a.B * a.Hkv;
     chunks = attn_even_chunks([&](int ch) { return attn_wgs_per_xcd(G, n_groups, ch); }, (int64_t)a.B * a.Hq, a.k,
-                              a.k < 256 ? kLongMinSlots + 8 : kLongMinSlots, 0.85);
+                              a.k < 256 ? kLongMinSlots + 8 : kLongMinSlots, 0.85, attn_long_in_rounds(a, G) ? kManyRounds : 1);
     if (chunks >= ws.nchunks) chunks = 0;
     if (chunks > 0) ws.kernel = AttnKernel::kLong;
   }

@@ -42,16 +42,16 @@ def _want(q, K, V, start, length, counts, div):
 
 # (B, Hq, Hkv, k, b, lists per head on the kernel for long lists, shared lists on the kernel of their own): one list a head
 # with 32 slots, one more, a slot count beyond the 64 spans of a wavefront; several chunks; runs of chunks on XCDs of their
-# own (4, 2, 1 and 3 groups); heads without groups; several rounds of workgroups; every width and tile of the shared kernel,
+# own (4, 2, 1 and 3 groups); heads without groups; several rounds of workgroups and lists too long for them; every width and tile of the shared kernel,
 # slots of one and two tiles of 16 rows, at the slot counts it starts with and well above them
 SHAPES = [(8, 32, 8, 32, 16, True, False), (8, 32, 8, 33, 16, True, False), (8, 32, 8, 545, 8, True, True),
           (2, 32, 8, 163, 32, True, False), (1, 28, 4, 257, 16, True, False), (1, 16, 2, 515, 8, True, False),
           (1, 8, 1, 129, 16, False, False), (1, 40, 40, 245, 16, True, False), (3, 6, 1, 40, 16, False, False),
-          (8, 40, 8, 121, 16, True, True), (3, 16, 2, 16, 32, False, False), (1, 28, 4, 40, 64, False, False),
-          (4, 16, 8, 97, 32, False, True), (5, 24, 8, 83, 17, True, True), (4, 40, 8, 200, 32, True, True),
+          (8, 40, 8, 121, 16, False, True), (3, 16, 2, 16, 32, False, False), (1, 28, 4, 40, 64, False, False),
+          (4, 16, 8, 97, 32, False, True), (5, 24, 8, 83, 17, True, True), (4, 40, 8, 200, 32, False, True),
           (12, 56, 8, 33, 9, True, True), (6, 11, 1, 520, 16, False, True), (16, 8, 4, 49, 16, False, True),
           (8, 16, 8, 150, 32, True, True), (8, 24, 8, 139, 17, False, True), (12, 56, 8, 83, 9, True, True),
-          (8, 11, 1, 810, 16, True, True), (16, 8, 4, 121, 16, True, True)]
+          (8, 11, 1, 810, 16, True, True), (16, 8, 4, 121, 16, True, True), (16, 32, 8, 64, 16, True, True), (16, 32, 8, 65, 16, False, True)]
 
 
 def _partials_left(att, lay):
