@@ -223,7 +223,8 @@ typedef struct dsk_select_args {
                                   still decides what is scored. */
   int32_t max_blocks_per_seq;  /* [host] optional upper bound on the blocks of any ONE sequence (0 = the
                                   bound above).  Picks the workgroup size / register tile of the
-                                  selection kernel; a sequence with more blocks is still selected
+                                  selection kernel, up to 256 also whether the scores are made in the
+                                  same launch; a sequence with more blocks is still selected
                                   correctly, through the memory-resident path. */
   const int32_t* cu_blocks;    /* [dev] [B+1] */
   const int32_t* block_start;  /* [dev] both tables: 16-byte aligned and readable up to a multiple */

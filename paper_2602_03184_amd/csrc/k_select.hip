@@ -620,13 +620,14 @@ constexpr int kScoredPass = kScoredThreads / 32 * kScoredBlocks;        // block
 template <int PASSES, bool FP32>
 __global__ __launch_bounds__(kScoredThreads) void select_scored_kernel(
     const uint16_t* __restrict__ ksum, const uint16_t* __restrict__ q, const int32_t* __restrict__ cu_blocks,
-    const int32_t* __restrict__ block_start, const int32_t* __restrict__ slot_base, int B, int Hq, int Hkv, int cap, int bound, int b, int kcap, const int32_t* __restrict__ budget_per_seq,
-    const int32_t* __restrict__ blocks_used, const int32_t* __restrict__ seq_row0, float* __restrict__ scores, int stride,
-    float* __restrict__ user, int32_t* __restrict__ sel_slot, int32_t* __restrict__ sel_start,
-    int32_t* __restrict__ sel_len, int32_t* __restrict__ sel_count) {
+    const int32_t* __restrict__ block_start, const int32_t* __restrict__ slot_base, int B, int Hq, int Hkv, int cap, int used,
+    int bound, int b, int kcap, const int32_t* __restrict__ budget_per_seq, const int32_t* __restrict__ blocks_used,
+    const int32_t* __restrict__ seq_row0, float* __restrict__ scores, int stride, float* __restrict__ user,
+    int32_t* __restrict__ sel_slot, int32_t* __restrict__ sel_start, int32_t* __restrict__ sel_len,
+    int32_t* __restrict__ sel_count) {
   static_assert(PASSES * kScoredPass <= kScoredThreads, "one block per thread behind the scores");
   __shared__ SelShared sh;
-  __shared__ float sm_score[PASSES * kScoredPass];
+  __shared__ float sm_score[kScoredThreads];
   // workgroup 8 j + x runs on XCD x: so do all heads of a group
   const int G = Hq / Hkv;
   const int j = blockIdx.x >> 3;
@@ -645,20 +646,19 @@ __global__ __launch_bounds__(kScoredThreads) void select_scored_kernel(
   // cu_blocks[0] is 0 by definition: sequence 0 can address its loads before anything arrives
   const int blk0_raw = s == 0 ? 0 : cu_blocks[s];
   const int blk0 = blk0_raw < cap ? (blk0_raw > 0 ? blk0_raw : 0) : cap;
-  const uint16_t* kh = ksum + ((int64_t)hk * cap + blk0) * (2 * DSK_HEAD_DIM) + c * 8;
-  const int last = (cap - blk0 < bound ? cap - blk0 : bound) - 1;     // of the records that may be asked for; -1: none
-  if (last < 0) kh -= 2 * DSK_HEAD_DIM;                                // blk0 == cap: stay inside the table
-  auto record = [&](int i) {
-    i = i < last ? i : last;
-    return *reinterpret_cast<const uint4*>(kh + (int64_t)(i > 0 ? i : 0) * (2 * DSK_HEAD_DIM));
-  };
+  const uint16_t* kh = ksum + (int64_t)hk * cap * (2 * DSK_HEAD_DIM) + c * 8;
+  auto record = [&](int blk) { return *reinterpret_cast<const uint4*>(kh + (int64_t)blk * (2 * DSK_HEAD_DIM)); };
+  const int last = (used - blk0 < bound ? used : blk0 + bound) - 1;    // no record behind it is asked for ahead; used >= 1
   uint4 qv = *reinterpret_cast<const uint4*>(q + sh_idx * DSK_HEAD_DIM + (c & 15) * 8);
   uint4 kv[PASSES][kScoredBlocks];
 #pragma unroll
   for (int p = 0; p < PASSES; ++p)
 #pragma unroll
-    for (int u = 0; u < kScoredBlocks; ++u) kv[p][u] = record(p * kScoredPass + half * kScoredBlocks + u);
-  const int at = blk0 + tid < cap ? blk0 + tid : (cap > 0 ? cap - 1 : 0);
+    for (int u = 0; u < kScoredBlocks; ++u) {
+      const int blk = blk0 + p * kScoredPass + half * kScoredBlocks + u;
+      kv[p][u] = record(blk < last ? blk : last);
+    }
+  const int at = blk0 + tid < cap ? blk0 + tid : cap - 1;
   const int xs[2] = {slot_base[at], slot_base[at + 1]};
   const int xb[2] = {block_start[at], block_start[at + 1]};
   int blk1 = blocks_used != nullptr ? blk0_raw + blocks_used[s] : cu_blocks[s + 1];
@@ -688,29 +688,35 @@ __global__ __launch_bounds__(kScoredThreads) void select_scored_kernel(
     half_wave_reduce<kScoredBlocks, kScoredBlocks, 1>(v, c, u);
     return v[0];
   };
-  if (n > bound) {                      // more blocks than the caller's bound: through memory, as long as it takes
+  if (blk1 - 1 <= last) {
+#pragma unroll
+    for (int p = 0; p < PASSES; ++p) {
+      int u;
+      const float v = score(kv[p], u);
+      if (c < kScoredBlocks) sm_score[p * kScoredPass + half * kScoredBlocks + u] = v;
+    }
+  } else {                              // more blocks than the caller's bounds
+    const bool big = n > kScoredThreads;               // through memory, as long as it takes
     for (int i0 = half * kScoredBlocks; i0 < n; i0 += kScoredPass) {
       uint4 k8[kScoredBlocks];
 #pragma unroll
-      for (int u = 0; u < kScoredBlocks; ++u)
-        k8[u] = *reinterpret_cast<const uint4*>(kh + (int64_t)(i0 + u < n ? i0 + u : n - 1) * (2 * DSK_HEAD_DIM));
+      for (int u = 0; u < kScoredBlocks; ++u) k8[u] = record(blk0 + (i0 + u < n ? i0 + u : n - 1));
       int u;
       const float v = score(k8, u);
       if (c < kScoredBlocks && i0 + u < n) {
-        scores[(int64_t)h * stride + blk0 + i0 + u] = v;
-        if (user) user[(int64_t)h * cap + blk0 + i0 + u] = v;
+        if (!big) sm_score[i0 + u] = v;
+        else {
+          scores[(int64_t)h * stride + blk0 + i0 + u] = v;
+          if (user) user[(int64_t)h * cap + blk0 + i0 + u] = v;
+        }
       }
     }
-    __syncthreads();
-    select_big<kScoredThreads>(sh, scores, stride, cu_blocks, block_start, slot_base, cap, Hq, b, k, kcap, 0, blk1, row0,
-                               h, s, sel_slot, sel_start, sel_len, sel_count);
-    return;
-  }
-#pragma unroll
-  for (int p = 0; p < PASSES; ++p) {
-    int u;
-    const float v = score(kv[p], u);
-    if (c < kScoredBlocks) sm_score[p * kScoredPass + half * kScoredBlocks + u] = v;
+    if (big) {
+      __syncthreads();
+      select_big<kScoredThreads>(sh, scores, stride, cu_blocks, block_start, slot_base, cap, Hq, b, k, kcap, 0, blk1, row0,
+                                 h, s, sel_slot, sel_start, sel_len, sel_count);
+      return;
+    }
   }
   __syncthreads();
   const float f[1] = {sm_score[tid < n ? tid : 0]};
@@ -725,10 +731,19 @@ static int select_bound(const dsk_select_args& a) {
   return bound;
 }
 
+// Where it is taken: the heads of a group run on one XCD, so it is the workgroups there that count.  Selection alone, two
+// launches / one, us: up to 32 workgroups on an XCD 0.65 to 0.9 of the time in 900 calls (32 / 8 heads, one sequence of 68
+// blocks 7.7 / 5.6); 33 to 64 of them 0.8 to 0.95, but 1.05 with 8 blocks a sequence where only the batch's blocks are
+// known and 256 are asked for; from 80 on longer (40 / 40 heads, 16 sequences 7.2 / 8.0; 128 / 1, one 9.0 / 13.9; 128 / 8, 32
+// sequences 14.3 / 38.7).  The scores of blocks that a region has in reserve are wanted by a caller only with the array.
 constexpr int kScoredMax = 2 * kScoredPass;
+constexpr int64_t kScoredPerXcd = 64, kScoredPerXcdUnknown = 32;
 bool select_scores_itself(const dsk_select_args& a) {
   const bool per_head = !(a.flags & DSK_SELECT_SHARED_BY_KV_GROUP) || a.Hq == a.Hkv;
-  return per_head && select_bound(a) <= kScoredMax && ((int64_t)a.B * a.Hkv + 7) * (a.Hq / a.Hkv) <= 0x7FFFFFFF;   // a 1-D grid
+  const bool known = a.B == 1 || a.max_blocks_per_seq > 0;
+  const int64_t per_xcd = ((int64_t)a.B * a.Hkv + 7) / 8 * (a.Hq / a.Hkv);
+  return per_head && select_bound(a) <= kScoredMax && per_xcd <= (known ? kScoredPerXcd : kScoredPerXcdUnknown) &&
+         (a.blocks_used == nullptr || a.scores == nullptr);
 }
 
 hipError_t launch_select_scored(const dsk_select_args& a, float* scores, int stride, hipStream_t st) {
@@ -737,8 +752,8 @@ hipError_t launch_select_scored(const dsk_select_args& a, float* scores, int str
   const dim3 grid((unsigned)(8 * ((n_groups + 7) / 8) * G));
 #define DSK_SEL_ARGS                                                                                            \
   static_cast<const uint16_t*>(a.ksum), static_cast<const uint16_t*>(a.q), a.cu_blocks, a.block_start, a.slot_base, a.B, a.Hq, \
-      a.Hkv, a.max_blocks_total, bound, a.b, a.budget / a.b, a.budget_per_seq, a.blocks_used, a.seq_row0, scores,   \
-      stride, a.scores, a.sel_slot, a.sel_start, a.sel_len, a.sel_count
+      a.Hkv, a.max_blocks_total, a.max_blocks_used > 0 ? a.max_blocks_used : a.max_blocks_total, bound, a.b, a.budget / a.b,  \
+      a.budget_per_seq, a.blocks_used, a.seq_row0, scores, stride, a.scores, a.sel_slot, a.sel_start, a.sel_len, a.sel_count
 #define DSK_SEL_PASSES(fp32)                                                                                    \
   do {                                                                                                          \
     if (bound <= kScoredPass) select_scored_kernel<1, fp32><<<grid, dim3(kScoredThreads), 0, st>>>(DSK_SEL_ARGS); \

@@ -83,5 +83,24 @@ def test_beyond_the_tile_and_regions():
     t.blocks_used, t.seq_row0 = dev_i32([199, 0, 255]), dev_i32([1000, 50, 7])
     two, one = _run(t, q, 640), _run(t, q, 640, max_blocks_per_seq=255)
     assert all(torch.equal(x, y) for x, y in zip(one[:4], two[:4]))
-    used = np.r_[0:199, 300:555]
-    assert torch.equal(one[4][:, used], two[4][:, used])
+    assert torch.equal(one[4][:, :556], two[4][:, :556])                   # what a region has in reserve is scored too
+
+
+@pytest.mark.parametrize("blocks", [[257], [300, 20], [511, 512], [20, 513, 200]], ids=str)
+@pytest.mark.parametrize("Hq,Hkv", [(8, 2), (6, 2)])
+def test_sequences_that_outgrow_the_bounds(blocks, Hq, Hkv):
+    """A sequence with a few more blocks than the caller's bounds say: up to 512 they are scored into the workgroup's own
+    memory, beyond that through the workspace."""
+    rng = np.random.default_rng([Hq, len(blocks), max(blocks)])
+    t = _tables(rng, blocks, Hq, Hkv, 16, room=2000)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(3)
+    q = torch.randn(t.B, Hq, 128, generator=g, device="cuda").bfloat16()
+    n = sum(blocks)
+    two = _run(t, q, 37 * 16)
+    for kw in (dict(max_blocks_per_seq=250), dict(max_blocks_per_seq=100), dict(max_blocks_used=n - 7, max_blocks_per_seq=256),
+               dict(max_blocks_used=19, max_blocks_per_seq=256)):
+        one = _run(t, q, 37 * 16, **kw)
+        for x, y in zip(one[:4], two[:4]):
+            assert torch.equal(x, y), kw
+        assert torch.equal(one[4][:, :n], two[4][:, :n]), kw
