@@ -162,11 +162,29 @@ __global__ __launch_bounds__(kSumThreads, WAVES) void summaries_kernel(
 // 296 / 56.0 with all but the last 400 MB past it, 294 / 57.7 with all but the last 256 MB.
 constexpr int64_t kSumKeptBytes = 400ll << 20;
 
-// Short chunks leave most of a wavefront's 32 rows in flight empty, so they want more wavefronts; longer ones lose to the
-// scheduling that the smaller register budget forces.  6 against 5 wavefronts per SIMD, 32 heads at 126K tokens, chunks of 15:
-// 210 against 218 us; 8 heads at 131K, chunks of 16: 73.2 / 76.3, of 18: 74.9 / 74.8, of 20: 75.1 / 73.3, of 30: 74.9 / 72.8.
-// (Where sequences have a C of their own only the largest is known here: two sequences of 14 and 28, 103.9 / 110.1.)
-static bool short_chunks(const dsk_compress_args& a) { return a.C > 0 && a.C <= (a.C_per_seq != nullptr ? 34 : 17); }
+// wavefronts for the blocks of chunks of C tokens (C is only a hint here: a call of this stage alone may leave it unset)
+static int64_t expected_waves(const dsk_compress_args& a) {
+  return a.C > 0 ? (a.vsum != nullptr ? 2 : 1) * (int64_t)a.Hkv * (a.total_tokens / a.C + a.B) : 0;
+}
+
+// Wavefronts per SIMD.  Short chunks leave most of a wavefront's 32 rows in flight empty, so they want 6 of them; long ones
+// lose to the scheduling that the smaller register budget forces, except in launches of few rounds.  6 against 5, 32 heads at
+// 126K tokens, chunks of 15: 210 against 218 us; 8 heads at 131K, chunks of 16: 73.2 / 76.3, of 18: 74.9 / 74.8, of 20: 75.1 /
+// 73.3, of 30: 74.9 / 72.8.  Chunks of 18 to 50, by wavefronts, mean of 13 to 73 launches: up to 6 K 0.97, to 18 K 0.98, to
+// 30 K 0.99, to 50 K 1.015, above 1.03 (8 heads at 18K tokens, chunks of 24: 9.3 / 10.2 us).
+// Where sequences have a C of their own only the largest is known here, but the capacity of the tables follows the shortest
+// chunk there may be, C - delta of some sequence: against that of the largest it tells how short the shortest C is, unless
+// delta leaves chunks of every C nearly alike short; half of the sum of both stands for the mean.  Two sequences of 60K
+// tokens, 8 heads, C of 14 and 28: 43.4 / 47.7, 18 and 34: 41.4 / 44.4, 24 and 24: 42.6 / 40.9.
+static bool six_waves(const dsk_compress_args& a) {
+  if (a.C <= 0) return false;
+  if (a.C <= 17 || expected_waves(a) <= 30 * 1024) return true;
+  if (a.C_per_seq == nullptr) return false;
+  const int64_t min_chunk = a.C - a.delta;
+  if (3 * min_chunk < a.C) return a.C <= 34;
+  const int64_t shortest = (int64_t)a.C * a.total_tokens / (min_chunk * a.max_blocks_total);
+  return shortest <= 18 && a.C + shortest <= 52;
+}
 
 template <bool MEAN, int WAVES>
 static hipError_t launch_summaries_impl(const dsk_compress_args& a, hipStream_t st) {
@@ -180,8 +198,7 @@ static hipError_t launch_summaries_impl(const dsk_compress_args& a, hipStream_t 
   // is not free, so the grid is bounded by wavefronts for the blocks of chunks of C tokens (twice as many
   // where sequences have a C of their own, below this bound); where there are more, wavefronts take two or three.
   // With twice these grids, 128K tokens and K and V of eight sequences: 71.1 against 70.6 us, 289.4 against 288.8.
-  // (C is only a hint here: a call of this stage alone may leave it unset.)
-  int64_t max_wgs = a.C > 0 ? (a.C_per_seq != nullptr ? 2 : 1) * (int64_t)heads * (a.total_tokens / a.C + a.B) / kSumWaves : 0;
+  int64_t max_wgs = (a.C_per_seq != nullptr ? 2 : 1) * expected_waves(a) / kSumWaves;
   if (max_wgs < 256 * 8) max_wgs = 256 * 8;
   const int64_t wgs_cap = WAVES > 4 ? 256 * 128 : 256 * 256;   // 32 heads, chunks of 15: 232 -> 218 us; eight sequences 293 -> 290
   if (max_wgs > wgs_cap) max_wgs = wgs_cap;
@@ -199,7 +216,7 @@ static hipError_t launch_summaries_impl(const dsk_compress_args& a, hipStream_t 
 }
 
 hipError_t launch_summaries(const dsk_compress_args& a, hipStream_t st) {
-  if (short_chunks(a))
+  if (six_waves(a))
     return a.summary_mode == DSK_SUMMARY_MEAN ? launch_summaries_impl<true, 6>(a, st) : launch_summaries_impl<false, 6>(a, st);
   return a.summary_mode == DSK_SUMMARY_MEAN ? launch_summaries_impl<true, 4>(a, st) : launch_summaries_impl<false, 4>(a, st);
 }
