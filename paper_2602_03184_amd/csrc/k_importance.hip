@@ -36,9 +36,9 @@
 //  - Calls with few rows or short sequences run on a kernel of their own, importance_few_kernel below.
 // Measured (stage IMPORTANCE, 32 query / 8 KV heads, W = 8): 128 samples of a 128K sequence 97.7 -> 57.9 us (58 to 66
 // over the GPUs seen), 1024 samples of eight sequences of 24K to 64K tokens 370 -> 243 us, against one workgroup per
-// 3 or 4 consecutive samples with the key tiles fetched by each wavefront; then 58.8 -> 55.7 and 233 -> 223 (both on one
-// GPU) from the order of the two workgroups of a CU, key addresses without vector multiplies and kImpItemCost 5 -> 6.
-// Keys straight to LDS three stages ahead (four buffers): 55.9 / 241 against 54.8 / 233 at that stage, latency is not what
+// 3 or 4 consecutive samples with the key tiles fetched by each wavefront; then 58.5 -> 55.0 and 235 -> 222 (both on one
+// GPU) from key addresses without vector multiplies and the order of the two workgroups of a CU.  (A kImpItemCost of 6 did
+// as well in these two, but took up to 8 % longer with 32 heads without groups.)  Keys straight to LDS three stages ahead (four buffers): 55.9 / 241 against 54.8 / 233 at that stage, latency is not what
 // is missing; two masked tiles' keys on their way instead of one: no change.
 #include <type_traits>
 
@@ -72,7 +72,7 @@ constexpr int kImpWaves = kImpThreads / DSK_WAVE;
 constexpr int kImpNS = kImpRows / 32 / kImpWaves;     // row tiles per wavefront
 constexpr int kImpStage = 64;                         // keys per LDS buffer
 constexpr int kImpMinStages = 4;                      // a piece shorter than this does not pay for its start
-constexpr int kImpItemCost = 6;                       // start of an item and its tiles at the regions' edges, in stages
+constexpr int kImpItemCost = 5;                       // start of an item and its tiles at the regions' edges, in stages
 constexpr float kImpRescaleAt = 64.0f;
 constexpr float kImpHeadroom = 4.0f;                  // log2 units a new reference lies above the largest logit seen
 static_assert(kImpNS == 2, "the row tiles of a wavefront are written out below");
@@ -374,7 +374,11 @@ __global__ __launch_bounds__(kImpThreads, 2) void importance_kernel(
   // the later row tiles of an item have fewer keys: the second workgroup of a CU deals its tiles to the
   // SIMDs the other way round
   const int own_tile = (blockIdx.x * 2 >= gridDim.x ? kImpWaves - 1 - wave : wave) * kImpNS;
-  const bool young = blockIdx.x * 2 >= gridDim.x;   // most likely the second workgroup of its CU
+  // Most likely the second workgroup of its CU, which goes first in three stages of four (below): where a row tile holds rows
+  // of one sample and pieces are long.  Row tiles that samples share leave much work behind the stages, at each wavefront's
+  // own pace, and a priority then costs as often as it gains (250 calls with 1 to 20 rows a sample, or 40, 56, 72 ..: 0.90 to
+  // 1.12 of the time without); with short pieces it is up to 4 % slower too.
+  const bool young = rps % 32 == 0 && line.per >= 8 && blockIdx.x * 2 >= gridDim.x;
   const int col = lane & 31;        // query row of the tile this lane accumulates; key row of its A operand
   const int hf = lane >> 5;         // channel half / key sub-row selector
   // LDS: chunk c (16 bytes) of key row r lies in slot c ^ (r & 15) of the row
@@ -540,8 +544,9 @@ __global__ __launch_bounds__(kImpThreads, 2) void importance_kernel(
       const int buf = (st - st_at) & 1;
       const int k0 = st * kImpStage;
       // The older of two wavefronts issues first: pieces of the second workgroup of a CU took a third longer than those
-      // of the first, which then left it alone.  Three stages in four the younger one goes first: 58.8 -> 56.4 us,
-      // 233 -> 226 (never, always or every other stage: 58.4 / 57.9 / 56.4 and 232 / 232 / 225).
+      // of the first, which then left it alone.  Three stages in four the younger one goes first: 57.8 -> 55.0 us,
+      // 232 -> 222 for the two cases above; 212 calls with 32, 64 and 128 rows a sample 0.99 -> 0.97 of the time with
+      // multiplied addresses in the mean, 1.02 at most.
       if (young) {
         if ((st & 3) != 0) __builtin_amdgcn_s_setprio(1);
         else __builtin_amdgcn_s_setprio(0);
@@ -556,6 +561,7 @@ __global__ __launch_bounds__(kImpThreads, 2) void importance_kernel(
       read_keys(kf, buf ^ 1, 0);                  // past the end: old keys, their products are not used
       half_step(kFresh, 1, 0, k0 + 32, c1, c0, kf);
     }
+    __builtin_amdgcn_s_setprio(0);
     // the mixed tiles: each wavefront on its own, so that it holds up no other one
     auto next_mixed = [&](int p, int tile) {
       while (tile < 2 * st_end && tile * 32 <= last[p] && kind_of(p, tile * 32) != 3) ++tile;
