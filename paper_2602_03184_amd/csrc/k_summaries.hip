@@ -94,27 +94,16 @@ struct SumTensor {
 // One wavefront per (plane, block); the planes are the heads of K, then those of V, `heads` in all and the slower index,
 // so that the wavefronts for which there is no block come last.  `streamed`: planes from the first one whose rows are
 // read past the caches.  WAVES: wavefronts per SIMD that the registers leave room for at least (they are 5 with 4).
-template <bool MEAN, bool STREAM, int WAVES>
+template <bool MEAN, int WAVES>
 __global__ __launch_bounds__(kSumThreads, WAVES) void summaries_kernel(
     SumTensor k, SumTensor v, int Hkv, int heads, int streamed, const int32_t* __restrict__ block_start,
-    const int32_t* __restrict__ cu_blocks, int B, const int32_t* __restrict__ blk_range, int cap, int out_rows,
-    int total_tokens, int32_t* dev_status) {
+    const int32_t* __restrict__ cu_blocks, int B, int cap, int out_rows, int total_tokens, int32_t* dev_status) {
   const int lane = threadIdx.x & (DSK_WAVE - 1);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / DSK_WAVE);   // wave-uniform: scalar registers
   const int g = lane >> 4;   // row group 0..3
   const int c = lane & 15;   // 16-byte column 0..15
-  // blocks [i_lo, i_lo + nblk): the whole table, or the range an incremental update rewrote
-  int i_lo = 0, nblk;
-  if (blk_range != nullptr) {
-    i_lo = blk_range[0];
-    int i_hi = blk_range[1];
-    if (i_hi > cap) i_hi = cap;
-    if (i_lo < 0) i_lo = 0;
-    nblk = i_hi - i_lo;
-  } else {
-    nblk = cu_blocks[B];
-    if (nblk > cap) nblk = cap;
-  }
+  int nblk = cu_blocks[B];
+  if (nblk > cap) nblk = cap;
   if (nblk <= 0) return;
   const int64_t items = (int64_t)heads * nblk;
   const uint32_t nwaves = gridDim.x * kSumWaves;
@@ -126,30 +115,30 @@ __global__ __launch_bounds__(kSumThreads, WAVES) void summaries_kernel(
   const int step_i = (int)(nwaves - (uint32_t)step_h * (uint32_t)nblk);
   int h = __builtin_amdgcn_readfirstlane((int)((uint32_t)item / (uint32_t)nblk));
   int i = (int)((uint32_t)item - (uint32_t)h * (uint32_t)nblk);
-  int s = __builtin_amdgcn_readfirstlane(block_start[i_lo + i]);
-  int e = __builtin_amdgcn_readfirstlane(block_start[i_lo + i + 1]);
+  int s = __builtin_amdgcn_readfirstlane(block_start[i]);
+  int e = __builtin_amdgcn_readfirstlane(block_start[i + 1]);
   for (;;) {
     // the bounds of this wave's next block travel with the rows of the current one
     const int64_t nitem = item + nwaves;
     const bool more = nitem < items;
     int nh = h + step_h, ni = i + step_i;
     if (ni >= nblk) { ni -= nblk; ++nh; }
-    const int pi = i_lo + (more ? ni : i);
+    const int pi = more ? ni : i;
     const int ns = __builtin_amdgcn_readfirstlane(block_start[pi]);
     const int ne = __builtin_amdgcn_readfirstlane(block_start[pi + 1]);
     const int len = e - s;
     const bool second = h >= Hkv;
     const int64_t stride_tok = second ? v.stride_tok : k.stride_tok;
     const int64_t th = second ? h - Hkv : h;
-    uint16_t* o = (second ? v.out : k.out) + (th * out_rows + i_lo + i) * (2 * DSK_HEAD_DIM);   // out_rows records per head (>= cap)
+    uint16_t* o = (second ? v.out : k.out) + (th * out_rows + i) * (2 * DSK_HEAD_DIM);   // out_rows records per head (>= cap)
     if (s < 0 || len <= 0 || e > total_tokens) {   // malformed table: defined output, flag it
       if (lane < 32) reinterpret_cast<uint4*>(o)[lane] = make_uint4(0, 0, 0, 0);
       if (lane == 0) set_status(dev_status, DSK_ERR_SHAPE);
     } else {
       const uint16_t* base = (second ? v.X : k.X) + th * (second ? v.stride_head : k.stride_head) + (int64_t)s * stride_tok;   // uniform
       const unsigned ustride8 = (unsigned)stride_tok >> 3;
-      if (STREAM && h < streamed) summarize_block<MEAN, STREAM, STREAM>(base, len, stride_tok, ustride8, o, g, c);
-      else summarize_block<MEAN, STREAM>(base, len, stride_tok, ustride8, o, g, c);
+      if (h < streamed) summarize_block<MEAN, true, true>(base, len, stride_tok, ustride8, o, g, c);
+      else summarize_block<MEAN, true>(base, len, stride_tok, ustride8, o, g, c);
     }
     if (!more) break;
     item = nitem; h = nh; i = ni; s = ns; e = ne;
@@ -209,9 +198,8 @@ static hipError_t launch_summaries_impl(const dsk_compress_args& a, hipStream_t 
   const int64_t plane = (int64_t)a.total_tokens * DSK_HEAD_DIM * 2;
   const int64_t kept = plane > 0 ? (kSumKeptBytes + plane - 1) / plane : 0;
   const int streamed = heads > kept ? (int)(heads - kept) : 0;
-  summaries_kernel<MEAN, true, WAVES><<<dim3((unsigned)wgs), dim3(kSumThreads), 0, st>>>(
-      k, v, a.Hkv, heads, streamed, a.block_start, a.cu_blocks, a.B, nullptr, a.max_blocks_total, out_rows, a.total_tokens,
-      a.dev_status);
+  summaries_kernel<MEAN, WAVES><<<dim3((unsigned)wgs), dim3(kSumThreads), 0, st>>>(
+      k, v, a.Hkv, heads, streamed, a.block_start, a.cu_blocks, a.B, a.max_blocks_total, out_rows, a.total_tokens, a.dev_status);
   return hipGetLastError();
 }
 
@@ -221,21 +209,53 @@ hipError_t launch_summaries(const dsk_compress_args& a, hipStream_t st) {
   return a.summary_mode == DSK_SUMMARY_MEAN ? launch_summaries_impl<true, 4>(a, st) : launch_summaries_impl<false, 4>(a, st);
 }
 
+// Summaries of the blocks [blk_range[0], blk_range[1]) that an incremental update rewrote: few, so the chain of loads in front
+// of the rows is what counts.  grid: (group of kSumWaves heads, block), so that nothing has to be divided.
+template <bool MEAN>
+__global__ __launch_bounds__(kSumThreads) void summaries_range_kernel(
+    const uint16_t* __restrict__ X, int64_t stride_tok, int64_t stride_head, int Hkv,
+    const int32_t* __restrict__ block_start, const int32_t* __restrict__ blk_range, int cap, int total_tokens,
+    uint16_t* __restrict__ out, int32_t* dev_status) {
+  const int lane = threadIdx.x & (DSK_WAVE - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / DSK_WAVE);
+  const int g = lane >> 4, c = lane & 15;
+  const int h = (int)blockIdx.x * kSumWaves + wave;
+  int lo = blk_range[0], hi = blk_range[1];
+  if (hi > cap) hi = cap;
+  if (lo < 0) lo = 0;
+  if (h >= Hkv) return;
+  for (int64_t b = (int64_t)lo + blockIdx.y; b < hi; b += gridDim.y) {
+    const int i = (int)b;
+    const int s = __builtin_amdgcn_readfirstlane(block_start[i]);
+    const int e = __builtin_amdgcn_readfirstlane(block_start[i + 1]);
+    const int len = e - s;
+    uint16_t* o = out + ((int64_t)h * cap + i) * (2 * DSK_HEAD_DIM);
+    if (s < 0 || len <= 0 || e > total_tokens) {   // malformed table: defined output, flag it
+      if (lane < 32) reinterpret_cast<uint4*>(o)[lane] = make_uint4(0, 0, 0, 0);
+      if (lane == 0) set_status(dev_status, DSK_ERR_SHAPE);
+    } else {
+      const uint16_t* base = X + (int64_t)h * stride_head + (int64_t)s * stride_tok;
+      summarize_block<MEAN, false>(base, len, stride_tok, (unsigned)stride_tok >> 3, o, g, c);
+    }
+  }
+}
+
 hipError_t launch_summaries_range(const void* X, int64_t stride_tok, int64_t stride_head, int Hkv,
                                   const int32_t* block_start, const int32_t* blk_range, int max_blocks_in_range,
                                   int cap, int total_tokens, int summary_mode, void* out, int32_t* dev_status,
                                   hipStream_t st) {
-  const int64_t max_items = (int64_t)Hkv * max_blocks_in_range;
-  if (max_items <= 0) return hipSuccess;
-  int64_t wgs = (max_items + kSumWaves - 1) / kSumWaves;
-  if (wgs > 256 * 8) wgs = 256 * 8;
-  const SumTensor k = {static_cast<const uint16_t*>(X), stride_tok, stride_head, static_cast<uint16_t*>(out)};
+  if (Hkv <= 0 || max_blocks_in_range <= 0) return hipSuccess;
+  const int groups = (Hkv + kSumWaves - 1) / kSumWaves;
+  const int most = groups < 256 * 8 ? 256 * 8 / groups : 1;    // a long range: at most about 2048 workgroups
+  const dim3 grid((unsigned)groups, (unsigned)(max_blocks_in_range < most ? max_blocks_in_range : most));
   if (summary_mode == DSK_SUMMARY_MEAN)
-    summaries_kernel<true, false, 4><<<dim3((unsigned)wgs), dim3(kSumThreads), 0, st>>>(
-        k, k, Hkv, Hkv, 0, block_start, nullptr, 0, blk_range, cap, cap, total_tokens, dev_status);
+    summaries_range_kernel<true><<<grid, dim3(kSumThreads), 0, st>>>(
+        static_cast<const uint16_t*>(X), stride_tok, stride_head, Hkv, block_start, blk_range, cap, total_tokens,
+        static_cast<uint16_t*>(out), dev_status);
   else
-    summaries_kernel<false, false, 4><<<dim3((unsigned)wgs), dim3(kSumThreads), 0, st>>>(
-        k, k, Hkv, Hkv, 0, block_start, nullptr, 0, blk_range, cap, cap, total_tokens, dev_status);
+    summaries_range_kernel<false><<<grid, dim3(kSumThreads), 0, st>>>(
+        static_cast<const uint16_t*>(X), stride_tok, stride_head, Hkv, block_start, blk_range, cap, total_tokens,
+        static_cast<uint16_t*>(out), dev_status);
   return hipGetLastError();
 }
 

@@ -103,6 +103,21 @@ def test_decode_loop_one_token_at_a_time_then_bursts():
     np.testing.assert_array_equal(want, seq.oracle_table(seq.L))
 
 
+@pytest.mark.parametrize("Hkv", [1, 5])
+def test_a_range_of_more_blocks_than_the_launch_has_workgroups(Hkv):
+    """Thousands of rewritten blocks in one update: a workgroup of the summaries takes several of them."""
+    rng = np.random.default_rng(Hkv)
+    L, C, delta = 12000, 4, 2
+    tok = np.where(rng.random(L) < 0.2, rng.integers(0, 3, L), 99)
+    bits = [bf16_bits_of(torch.from_numpy(rng.standard_normal((Hkv, L, 128)).astype(np.float32)).bfloat16()) for _ in range(2)]
+    seq = _Seq(bits[0], bits[1], tok, [0, 1, 2], [9, 5, 7], 50, C, delta, 5, 10, 4, want_vsum=True)
+    want, i0 = seq.append(L - 50)
+    assert len(want) - i0 > 2048
+    seq.check_tables(want, i0)
+    seq.check_summaries(want)
+    seq.check_summaries(want, vsum=True)
+
+
 def test_append_with_gqa_heads_and_v_summaries_then_decode():
     dsk = _dsk()
     case = gpu_case(2, seqlens=[6000])
