@@ -83,7 +83,7 @@ hipError_t launch_summaries(const dsk_compress_args& a, hipStream_t st);
 // block scores live in the workspace as rows of `stride` = round_up(max_blocks_total, 4) floats
 inline int select_score_stride(const dsk_select_args& a) { return (a.max_blocks_total + 3) / 4 * 4; }
 hipError_t launch_scores(const dsk_select_args& a, float* scores, int stride, hipStream_t st);
-hipError_t launch_select(const dsk_select_args& a, const float* scores, int stride, hipStream_t st);
+hipError_t launch_select(const dsk_select_args& a, float* scores, int stride, hipStream_t st);
 // short sequences: scores and selection in one launch
 bool select_scores_itself(const dsk_select_args& a);
 hipError_t launch_select_scored(const dsk_select_args& a, float* scores, int stride, hipStream_t st);

@@ -326,30 +326,225 @@ __device__ __noinline__ void select_big(
   }
 }
 
-// The selection of one (sequence, head) from registers: thread t holds the scores f, slot bases xs and starts xb of the blocks
-// [t * PT - shift, + PT) of the sequence's n (shift < PT; entries outside it are ignored).
-template <int PT, int THREADS>
-__device__ __forceinline__ void select_core(SelShared& sh, const float* f, const int* xs, const int* xb, int shift, int n,
-                                            int k, int kcap, int b, int row0, int64_t obase, int64_t sh_idx,
-                                            int32_t* __restrict__ sel_slot, int32_t* __restrict__ sel_start,
-                                            int32_t* __restrict__ sel_len, int32_t* __restrict__ sel_count) {
+// What the selection needs to score the blocks itself
+struct ScoredBy {
+  const uint16_t* ksum;
+  const uint16_t* q;
+  float* user;         // the caller's array for the scores, or NULL
+  int B, Hkv;
+  int used, bound;     // blocks of all sequences, of one
+};
+
+// Short sequences.  Up to kScoredMax blocks, a list per query head: the workgroup of a list scores its blocks itself, which saves the launch of
+// the score kernel and the way of the scores through memory.  Every head of a group reads the summaries (all heads of a
+// group on one XCD, so that they meet in its L2), which costs as much as the launch from some 256 blocks on.  A
+// half-wavefront scores 8 consecutive blocks at a time as in the score kernel (same sums, same bits), the loads of all
+// blocks in flight at once.  Whole decode step in a graph, two launches / one: one head, 68 blocks 13.8 / 11.8 us, 170
+// 13.7 / 12.5, 300 14.5 / 14.6, 400 13.7 / 14.1; 32 / 8 heads 68 blocks 15.2 / 12.7, 170 15.1 / 13.5, 300 16.2 / 15.9.  (A list
+// per KV head would have a wavefront score all of its group's heads, one after the other: 15.4 / 19.6 at 400 blocks.)
+constexpr int kScoredThreads = 512;
+constexpr int kScoredBlocks = 8;                                        // of a half-wavefront
+constexpr int kScoredPass = kScoredThreads / 32 * kScoredBlocks;        // blocks of a pass
+
+// workgroup 8 j + x runs on XCD x: so do all heads of a group; false: a workgroup of the last round without a group
+__device__ __forceinline__ bool scored_place(const ScoredBy& by, int Hq, int& s, int& hk, int& h) {
+  const int G = Hq / by.Hkv;
+  const int j = blockIdx.x >> 3;
+  const int gi = j / G * 8 + (int)(blockIdx.x & 7);
+  if (gi >= by.B * by.Hkv) return false;
+  s = gi / by.Hkv;
+  hk = gi - s * by.Hkv;
+  h = hk * G + j % G;
+  return true;
+}
+
+// Scores the n blocks of sequence s from blk0 on against query head h; thread t gets block t's score, slot bases and starts.
+// More than a block a thread: the scores are left in memory (select_big takes them from there).  false: no block.
+template <int PASSES, bool FP32>
+__device__ __forceinline__ bool scored_load(const ScoredBy& by, float* scores, int stride, const int32_t* cu_blocks,
+                                            const int32_t* block_start, const int32_t* slot_base, int cap,
+                                            const int32_t* blocks_used, const int32_t* seq_row0, int s, int hk, int h,
+                                            int64_t sh_idx, int blk0_raw, int blk0, float4* fv, int4* iv, int4* bv, int& blk1,
+                                            int& n, int& row0) {
+  static_assert(PASSES * kScoredPass <= kScoredThreads, "one block per thread behind the scores");
+  __shared__ float sm_score[kScoredThreads];
+  const int tid = threadIdx.x;
+  const int half = tid >> 5;
+  const int c = tid & 31;
+  const bool is_max = c >= 16;
+  const uint16_t* kh = by.ksum + (int64_t)hk * cap * (2 * DSK_HEAD_DIM) + c * 8;
+  auto record = [&](int blk) { return *reinterpret_cast<const uint4*>(kh + (int64_t)blk * (2 * DSK_HEAD_DIM)); };
+  const int last = (by.used - blk0 < by.bound ? by.used : blk0 + by.bound) - 1;    // no record behind it is asked for ahead; by.used >= 1
+  uint4 qv = *reinterpret_cast<const uint4*>(by.q + sh_idx * DSK_HEAD_DIM + (c & 15) * 8);
+  uint4 kv[PASSES][kScoredBlocks];
+#pragma unroll
+  for (int p = 0; p < PASSES; ++p)
+#pragma unroll
+    for (int u = 0; u < kScoredBlocks; ++u) {
+      const int blk = blk0 + p * kScoredPass + half * kScoredBlocks + u;
+      kv[p][u] = record(blk < last ? blk : last);
+    }
+  const int at = blk0 + tid < cap ? blk0 + tid : cap - 1;
+  iv[0].x = slot_base[at]; iv[0].y = slot_base[at + 1];
+  bv[0].x = block_start[at]; bv[0].y = block_start[at + 1];
+  blk1 = blocks_used != nullptr ? blk0_raw + blocks_used[s] : cu_blocks[s + 1];
+  row0 = seq_row0 != nullptr ? seq_row0[s] : 0;
+  pin_loaded(qv);
+#pragma unroll
+  for (int p = 0; p < PASSES; ++p)
+#pragma unroll
+    for (int u = 0; u < kScoredBlocks; ++u) pin_loaded(kv[p][u]);
+  if (blk1 > cap) blk1 = cap;
+  n = blk1 - blk0;
+  if (n <= 0) return false;
+  // scores of a half-wavefront's 8 blocks, one in each of its first 8 lanes: block index `u`
+  auto score = [&](const uint4 (&k8)[kScoredBlocks], int& u) {
+    float v[kScoredBlocks];
+    score_parts<kScoredBlocks, FP32>(k8, qv, is_max, v);
+    u = 0;
+    half_wave_reduce<kScoredBlocks, kScoredBlocks, 1>(v, c, u);
+    return v[0];
+  };
+  if (blk1 - 1 <= last) {
+#pragma unroll
+    for (int p = 0; p < PASSES; ++p) {
+      int u;
+      const float v = score(kv[p], u);
+      if (c < kScoredBlocks) sm_score[p * kScoredPass + half * kScoredBlocks + u] = v;
+    }
+  } else {                              // more blocks than the caller's bounds
+    const bool big = n > kScoredThreads;               // through memory, as long as it takes
+    for (int i0 = half * kScoredBlocks; i0 < n; i0 += kScoredPass) {
+      uint4 k8[kScoredBlocks];
+#pragma unroll
+      for (int u = 0; u < kScoredBlocks; ++u) k8[u] = record(blk0 + (i0 + u < n ? i0 + u : n - 1));
+      int u;
+      const float v = score(k8, u);
+      if (c < kScoredBlocks && i0 + u < n) {
+        if (!big) sm_score[i0 + u] = v;
+        else {
+          scores[(int64_t)h * stride + blk0 + i0 + u] = v;
+          if (by.user) by.user[(int64_t)h * cap + blk0 + i0 + u] = v;
+        }
+      }
+    }
+    if (big) {
+      __syncthreads();
+      return true;
+    }
+  }
+  __syncthreads();
+  fv[0].x = sm_score[tid < n ? tid : 0];
+  if (by.user && tid < n) by.user[(int64_t)h * cap + blk0 + tid] = fv[0].x;
+  return true;
+}
+
+// One (sequence, head).  Thread t holds the scores, slot bases and starts of the blocks [t * PT - shift, + PT) of the
+// sequence's n (shift < PT; entries outside it are ignored).
+// scores: rows of `stride` floats (stride % 4 == 0, stride >= cap, base 16-byte aligned);
+// slot_base, block_start: 16-byte aligned, readable up to a multiple of 4 entries past cap.
+// PASSES > 0 (PT = 1): the blocks are scored here, see above.  (One kernel for both: with the selection in a function of its
+// own the compiler orders the longer sequences' instances otherwise, 0.05 us a call.)
+template <int PT, int THREADS, int PASSES = 0, bool FP32 = false>
+__global__ __launch_bounds__(THREADS) void select_kernel(
+    float* __restrict__ scores, int stride, const int32_t* __restrict__ cu_blocks,
+    const int32_t* __restrict__ block_start, const int32_t* __restrict__ slot_base, int cap, int Hq,
+    int b, int kcap, const int32_t* __restrict__ budget_per_seq, const int32_t* __restrict__ blocks_used,
+    const int32_t* __restrict__ seq_row0, int32_t* __restrict__ sel_slot, int32_t* __restrict__ sel_start,
+    int32_t* __restrict__ sel_len, int32_t* __restrict__ sel_count, ScoredBy by) {
+  static_assert(PASSES > 0 ? PT == 1 && THREADS == kScoredThreads : PT == 4 || PT == 8, "register tile");
   constexpr int NW = THREADS / DSK_WAVE;
   constexpr int kSelPerThread = PT;
+  constexpr int kSelVecs = (PT + 3) / 4;
+  __shared__ SelShared sh;
+  int h = blockIdx.x;
+  int s = blockIdx.y;
+  int hk = 0;
+  if constexpr (PASSES > 0) {
+    if (!scored_place(by, Hq, s, hk, h)) return;
+  }
   const int tid = threadIdx.x;
   const int lane = tid & (DSK_WAVE - 1);
   const int wave = tid / DSK_WAVE;
+  const int64_t sh_idx = (int64_t)s * Hq + h;
+  const int64_t obase = sh_idx * kcap;
+  // slots to take: kcap, or this sequence's own budget (clamped to 1..kcap slots)
+  int k = kcap;
+  if (budget_per_seq != nullptr) {
+    int ks = budget_per_seq[s] / b;
+    ks = ks < 1 ? 1 : ks;
+    k = ks < kcap ? ks : kcap;
+  }
+
+  // cu_blocks[0] is 0 by definition: sequence 0 can address its loads before anything arrives
+  const int blk0_raw = s == 0 ? 0 : cu_blocks[s];
+  const int blk0 = blk0_raw < cap ? (blk0_raw > 0 ? blk0_raw : 0) : cap;
+  float4 fv[kSelVecs];
+  int4 iv[kSelVecs + 1], bv[kSelVecs + 1];
+  int shift = 0, blk1, n, row0;
+  if constexpr (PASSES > 0) {
+    if (!scored_load<PASSES, FP32>(by, scores, stride, cu_blocks, block_start, slot_base, cap, blocks_used, seq_row0, s, hk, h,
+                                   sh_idx, blk0_raw, blk0, fv, iv, bv, blk1, n, row0))
+      n = 0;
+  } else {
+    shift = blk0 & 3;                                 // same for scores rows (stride % 4 == 0)
+    const int v_first = (blk0 - shift) / 4 + tid * kSelVecs;   // thread t owns vectors [v_first, v_first + kSelVecs)
+    const int max_vec_sc = stride / 4 - 1;              // clamp to the buffers, mask by index later
+    const int max_vec_sb = cap / 4;
+    const float4* sc4 = reinterpret_cast<const float4*>(scores + (int64_t)h * stride);
+    const int4* sb4 = reinterpret_cast<const int4*>(slot_base);
+    const int4* bs4 = reinterpret_cast<const int4*>(block_start);
+#pragma unroll
+    for (int u = 0; u < kSelVecs; ++u) {
+      const int v = v_first + u;
+      fv[u] = sc4[v < max_vec_sc ? v : max_vec_sc];
+    }
+#pragma unroll
+    for (int u = 0; u < kSelVecs + 1; ++u) {
+      const int v = v_first + u;
+      iv[u] = sb4[v < max_vec_sb ? v : max_vec_sb];
+    }
+#pragma unroll
+    for (int u = 0; u < kSelVecs + 1; ++u) {
+      const int v = v_first + u;
+      bv[u] = bs4[v < max_vec_sb ? v : max_vec_sb];
+    }
+    // tables with a region per sequence: the blocks in use and the sequence's first K/V row
+    blk1 = blocks_used != nullptr ? blk0_raw + blocks_used[s] : cu_blocks[s + 1];
+    row0 = seq_row0 != nullptr ? seq_row0[s] : 0;
+#pragma unroll
+    for (int u = 0; u < kSelVecs; ++u) pin_loaded(fv[u]);              // all vector loads in flight together
+#pragma unroll
+    for (int u = 0; u < kSelVecs + 1; ++u) pin_loaded(iv[u]);
+#pragma unroll
+    for (int u = 0; u < kSelVecs + 1; ++u) pin_loaded(bv[u]);
+    if (blk1 > cap) blk1 = cap;
+    n = blk1 - blk0;
+  }
+  if (n <= 0) {
+    write_padding(0, kcap, obase, sh_idx, sel_slot, sel_start, sel_len, sel_count);
+    return;
+  }
+  if (PASSES > 0 ? n > THREADS : !sel_fits_tile(n, PT, THREADS)) {   // too many blocks for the register tile
+    select_big<THREADS>(sh, scores, stride, cu_blocks, block_start, slot_base, cap, Hq, b, k, kcap, PASSES > 0 ? 0 : PT, blk1,
+                        row0, h, s, sel_slot, sel_start, sel_len, sel_count);
+    return;
+  }
+
   // registers: key[r], w[r] of block i = tid*PT + r - shift (w = 0 marks "no block")
   uint32_t key[kSelPerThread];
   int w[kSelPerThread];
   uint32_t kmin = 0xFFFFFFFFu, kmax = 0u;
   int nslots = 0;
   {
+    const float* f = reinterpret_cast<const float*>(fv);
+    const int* x = reinterpret_cast<const int*>(iv);
 #pragma unroll
     for (int r = 0; r < kSelPerThread; ++r) {
       const int i = tid * kSelPerThread + r - shift;
       const bool ok = i >= 0 && i < n;
       key[r] = float_key(f[r]);
-      int wr = xs[r + 1] - xs[r];
+      int wr = x[r + 1] - x[r];
       wr = (ok && wr > 0) ? wr : 0;                   // malformed table: never count backwards
       w[r] = wr;
       kmin = (ok && key[r] < kmin) ? key[r] : kmin;
@@ -497,6 +692,8 @@ __device__ __forceinline__ void select_core(SelShared& sh, const float* f, const
       w[r] = take;                                       // from here on: slots taken from block r
     }
   }
+  const int* xs = reinterpret_cast<const int*>(iv);
+  const int* xb = reinterpret_cast<const int*>(bv);
   for (int base = 0; base < n_work; base += kSelWork) {
     int e = e0 - base, o = off;
 #pragma unroll
@@ -526,203 +723,7 @@ __device__ __forceinline__ void select_core(SelShared& sh, const float* f, const
       }
     }
     if (base + kSelWork < n_work) __syncthreads();       // the list is refilled for another round
-  }
-}
-
-// scores: rows of `stride` floats (stride % 4 == 0, stride >= cap, base 16-byte aligned);
-// slot_base, block_start: 16-byte aligned, readable up to a multiple of 4 entries past cap.
-template <int PT, int THREADS>
-__global__ __launch_bounds__(THREADS) void select_kernel(
-    const float* __restrict__ scores, int stride, const int32_t* __restrict__ cu_blocks,
-    const int32_t* __restrict__ block_start, const int32_t* __restrict__ slot_base, int cap, int Hq,
-    int b, int kcap, const int32_t* __restrict__ budget_per_seq, const int32_t* __restrict__ blocks_used,
-    const int32_t* __restrict__ seq_row0, int32_t* __restrict__ sel_slot, int32_t* __restrict__ sel_start,
-    int32_t* __restrict__ sel_len, int32_t* __restrict__ sel_count) {
-  static_assert(PT == 4 || PT == 8, "register tile");
-  constexpr int kSelVecs = PT / 4;
-  __shared__ SelShared sh;
-  const int h = blockIdx.x;
-  const int s = blockIdx.y;
-  const int tid = threadIdx.x;
-  const int64_t sh_idx = (int64_t)s * Hq + h;
-  const int64_t obase = sh_idx * kcap;
-  // slots to take: kcap, or this sequence's own budget (clamped to 1..kcap slots)
-  int k = kcap;
-  if (budget_per_seq != nullptr) {
-    int ks = budget_per_seq[s] / b;
-    ks = ks < 1 ? 1 : ks;
-    k = ks < kcap ? ks : kcap;
-  }
-
-  // cu_blocks[0] is 0 by definition: sequence 0 can address its loads before anything arrives
-  const int blk0_raw = s == 0 ? 0 : cu_blocks[s];
-  const int blk0 = blk0_raw < cap ? (blk0_raw > 0 ? blk0_raw : 0) : cap;
-  const int shift = blk0 & 3;                         // same for scores rows (stride % 4 == 0)
-  const int v_first = (blk0 - shift) / 4 + tid * kSelVecs;   // thread t owns vectors [v_first, v_first + kSelVecs)
-  const int max_vec_sc = stride / 4 - 1;              // clamp to the buffers, mask by index later
-  const int max_vec_sb = cap / 4;
-  const float4* sc4 = reinterpret_cast<const float4*>(scores + (int64_t)h * stride);
-  const int4* sb4 = reinterpret_cast<const int4*>(slot_base);
-  const int4* bs4 = reinterpret_cast<const int4*>(block_start);
-  float4 fv[kSelVecs];
-  int4 iv[kSelVecs + 1], bv[kSelVecs + 1];
-#pragma unroll
-  for (int u = 0; u < kSelVecs; ++u) {
-    const int v = v_first + u;
-    fv[u] = sc4[v < max_vec_sc ? v : max_vec_sc];
-  }
-#pragma unroll
-  for (int u = 0; u < kSelVecs + 1; ++u) {
-    const int v = v_first + u;
-    iv[u] = sb4[v < max_vec_sb ? v : max_vec_sb];
-  }
-#pragma unroll
-  for (int u = 0; u < kSelVecs + 1; ++u) {
-    const int v = v_first + u;
-    bv[u] = bs4[v < max_vec_sb ? v : max_vec_sb];
-  }
-  // tables with a region per sequence: the blocks in use and the sequence's first K/V row
-  int blk1 = blocks_used != nullptr ? blk0_raw + blocks_used[s] : cu_blocks[s + 1];
-  const int row0 = seq_row0 != nullptr ? seq_row0[s] : 0;
-#pragma unroll
-  for (int u = 0; u < kSelVecs; ++u) pin_loaded(fv[u]);              // all vector loads in flight together
-#pragma unroll
-  for (int u = 0; u < kSelVecs + 1; ++u) pin_loaded(iv[u]);
-#pragma unroll
-  for (int u = 0; u < kSelVecs + 1; ++u) pin_loaded(bv[u]);
-  if (blk1 > cap) blk1 = cap;
-  const int n = blk1 - blk0;
-  if (n <= 0) {
-    write_padding(0, kcap, obase, sh_idx, sel_slot, sel_start, sel_len, sel_count);
-    return;
-  }
-  if (!sel_fits_tile(n, PT, THREADS)) {                            // too many blocks for the register tile
-    select_big<THREADS>(sh, scores, stride, cu_blocks, block_start, slot_base, cap, Hq, b, k, kcap, PT, blk1, row0, h, s,
-                        sel_slot, sel_start, sel_len, sel_count);
-    return;
-  }
-  select_core<PT, THREADS>(sh, reinterpret_cast<const float*>(fv), reinterpret_cast<const int*>(iv),
-                           reinterpret_cast<const int*>(bv), shift, n, k, kcap, b, row0, obase, sh_idx, sel_slot, sel_start,
-                           sel_len, sel_count);
-}
-
-// ---- short sequences ---------------------------------------------------------------------------------
-// Up to kScoredMax blocks, a list per query head: the workgroup of a list scores its blocks itself, which saves the launch of
-// the score kernel and the way of the scores through memory.  Every head of a group reads the summaries (all heads of a
-// group on one XCD, so that they meet in its L2), which costs as much as the launch from some 256 blocks on.  A
-// half-wavefront scores 8 consecutive blocks at a time as in the score kernel (same sums, same bits), the loads of all
-// blocks in flight at once.  Whole decode step in a graph, two launches / one: one head, 68 blocks 13.8 / 11.8 us, 170
-// 13.7 / 12.5, 300 14.5 / 14.6, 400 13.7 / 14.1; 32 / 8 heads 68 blocks 15.2 / 12.7, 170 15.1 / 13.5, 300 16.2 / 15.9.  (A list
-// per KV head would have a wavefront score all of its group's heads, one after the other: 15.4 / 19.6 at 400 blocks.)
-constexpr int kScoredThreads = 512;
-constexpr int kScoredBlocks = 8;                                        // of a half-wavefront
-constexpr int kScoredPass = kScoredThreads / 32 * kScoredBlocks;        // blocks of a pass
-template <int PASSES, bool FP32>
-__global__ __launch_bounds__(kScoredThreads) void select_scored_kernel(
-    const uint16_t* __restrict__ ksum, const uint16_t* __restrict__ q, const int32_t* __restrict__ cu_blocks,
-    const int32_t* __restrict__ block_start, const int32_t* __restrict__ slot_base, int B, int Hq, int Hkv, int cap, int used,
-    int bound, int b, int kcap, const int32_t* __restrict__ budget_per_seq, const int32_t* __restrict__ blocks_used,
-    const int32_t* __restrict__ seq_row0, float* __restrict__ scores, int stride, float* __restrict__ user,
-    int32_t* __restrict__ sel_slot, int32_t* __restrict__ sel_start, int32_t* __restrict__ sel_len,
-    int32_t* __restrict__ sel_count) {
-  static_assert(PASSES * kScoredPass <= kScoredThreads, "one block per thread behind the scores");
-  __shared__ SelShared sh;
-  __shared__ float sm_score[kScoredThreads];
-  // workgroup 8 j + x runs on XCD x: so do all heads of a group
-  const int G = Hq / Hkv;
-  const int j = blockIdx.x >> 3;
-  const int gi = j / G * 8 + (int)(blockIdx.x & 7);
-  if (gi >= B * Hkv) return;
-  const int s = gi / Hkv;
-  const int hk = gi - s * Hkv;
-  const int h = hk * G + j % G;
-  const int tid = threadIdx.x;
-  const int half = tid >> 5;
-  const int c = tid & 31;
-  const bool is_max = c >= 16;
-  const int64_t sh_idx = (int64_t)s * Hq + h;
-  const int64_t obase = sh_idx * kcap;
-
-  // cu_blocks[0] is 0 by definition: sequence 0 can address its loads before anything arrives
-  const int blk0_raw = s == 0 ? 0 : cu_blocks[s];
-  const int blk0 = blk0_raw < cap ? (blk0_raw > 0 ? blk0_raw : 0) : cap;
-  const uint16_t* kh = ksum + (int64_t)hk * cap * (2 * DSK_HEAD_DIM) + c * 8;
-  auto record = [&](int blk) { return *reinterpret_cast<const uint4*>(kh + (int64_t)blk * (2 * DSK_HEAD_DIM)); };
-  const int last = (used - blk0 < bound ? used : blk0 + bound) - 1;    // no record behind it is asked for ahead; used >= 1
-  uint4 qv = *reinterpret_cast<const uint4*>(q + sh_idx * DSK_HEAD_DIM + (c & 15) * 8);
-  uint4 kv[PASSES][kScoredBlocks];
-#pragma unroll
-  for (int p = 0; p < PASSES; ++p)
-#pragma unroll
-    for (int u = 0; u < kScoredBlocks; ++u) {
-      const int blk = blk0 + p * kScoredPass + half * kScoredBlocks + u;
-      kv[p][u] = record(blk < last ? blk : last);
-    }
-  const int at = blk0 + tid < cap ? blk0 + tid : cap - 1;
-  const int xs[2] = {slot_base[at], slot_base[at + 1]};
-  const int xb[2] = {block_start[at], block_start[at + 1]};
-  int blk1 = blocks_used != nullptr ? blk0_raw + blocks_used[s] : cu_blocks[s + 1];
-  const int row0 = seq_row0 != nullptr ? seq_row0[s] : 0;
-  int k = kcap;
-  if (budget_per_seq != nullptr) {
-    int ks = budget_per_seq[s] / b;
-    ks = ks < 1 ? 1 : ks;
-    k = ks < kcap ? ks : kcap;
-  }
-  pin_loaded(qv);
-#pragma unroll
-  for (int p = 0; p < PASSES; ++p)
-#pragma unroll
-    for (int u = 0; u < kScoredBlocks; ++u) pin_loaded(kv[p][u]);
-  if (blk1 > cap) blk1 = cap;
-  const int n = blk1 - blk0;
-  if (n <= 0) {
-    write_padding(0, kcap, obase, sh_idx, sel_slot, sel_start, sel_len, sel_count);
-    return;
-  }
-  // scores of a half-wavefront's 8 blocks, one in each of its first 8 lanes: block index `u`
-  auto score = [&](const uint4 (&k8)[kScoredBlocks], int& u) {
-    float v[kScoredBlocks];
-    score_parts<kScoredBlocks, FP32>(k8, qv, is_max, v);
-    u = 0;
-    half_wave_reduce<kScoredBlocks, kScoredBlocks, 1>(v, c, u);
-    return v[0];
-  };
-  if (blk1 - 1 <= last) {
-#pragma unroll
-    for (int p = 0; p < PASSES; ++p) {
-      int u;
-      const float v = score(kv[p], u);
-      if (c < kScoredBlocks) sm_score[p * kScoredPass + half * kScoredBlocks + u] = v;
-    }
-  } else {                              // more blocks than the caller's bounds
-    const bool big = n > kScoredThreads;               // through memory, as long as it takes
-    for (int i0 = half * kScoredBlocks; i0 < n; i0 += kScoredPass) {
-      uint4 k8[kScoredBlocks];
-#pragma unroll
-      for (int u = 0; u < kScoredBlocks; ++u) k8[u] = record(blk0 + (i0 + u < n ? i0 + u : n - 1));
-      int u;
-      const float v = score(k8, u);
-      if (c < kScoredBlocks && i0 + u < n) {
-        if (!big) sm_score[i0 + u] = v;
-        else {
-          scores[(int64_t)h * stride + blk0 + i0 + u] = v;
-          if (user) user[(int64_t)h * cap + blk0 + i0 + u] = v;
-        }
-      }
-    }
-    if (big) {
-      __syncthreads();
-      select_big<kScoredThreads>(sh, scores, stride, cu_blocks, block_start, slot_base, cap, Hq, b, k, kcap, 0, blk1, row0,
-                                 h, s, sel_slot, sel_start, sel_len, sel_count);
-      return;
-    }
-  }
-  __syncthreads();
-  const float f[1] = {sm_score[tid < n ? tid : 0]};
-  if (user && tid < n) user[(int64_t)h * cap + blk0 + tid] = f[0];
-  select_core<1, kScoredThreads>(sh, f, xs, xb, 0, n, k, kcap, b, row0, obase, sh_idx, sel_slot, sel_start, sel_len, sel_count);
-}
+  }}
 
 // an upper bound on the blocks of a sequence, as far as the caller gave one
 static int select_bound(const dsk_select_args& a) {
@@ -750,14 +751,15 @@ hipError_t launch_select_scored(const dsk_select_args& a, float* scores, int str
   const int G = a.Hq / a.Hkv, bound = select_bound(a);
   const int64_t n_groups = (int64_t)a.B * a.Hkv;
   const dim3 grid((unsigned)(8 * ((n_groups + 7) / 8) * G));
+  const ScoredBy by = {static_cast<const uint16_t*>(a.ksum), static_cast<const uint16_t*>(a.q), a.scores, a.B, a.Hkv,
+                       a.max_blocks_used > 0 ? a.max_blocks_used : a.max_blocks_total, bound};
 #define DSK_SEL_ARGS                                                                                            \
-  static_cast<const uint16_t*>(a.ksum), static_cast<const uint16_t*>(a.q), a.cu_blocks, a.block_start, a.slot_base, a.B, a.Hq, \
-      a.Hkv, a.max_blocks_total, a.max_blocks_used > 0 ? a.max_blocks_used : a.max_blocks_total, bound, a.b, a.budget / a.b,  \
-      a.budget_per_seq, a.blocks_used, a.seq_row0, scores, stride, a.scores, a.sel_slot, a.sel_start, a.sel_len, a.sel_count
+  scores, stride, a.cu_blocks, a.block_start, a.slot_base, a.max_blocks_total, a.Hq, a.b, a.budget / a.b, a.budget_per_seq, \
+      a.blocks_used, a.seq_row0, a.sel_slot, a.sel_start, a.sel_len, a.sel_count, by
 #define DSK_SEL_PASSES(fp32)                                                                                    \
   do {                                                                                                          \
-    if (bound <= kScoredPass) select_scored_kernel<1, fp32><<<grid, dim3(kScoredThreads), 0, st>>>(DSK_SEL_ARGS); \
-    else select_scored_kernel<2, fp32><<<grid, dim3(kScoredThreads), 0, st>>>(DSK_SEL_ARGS);                    \
+    if (bound <= kScoredPass) select_kernel<1, kScoredThreads, 1, fp32><<<grid, dim3(kScoredThreads), 0, st>>>(DSK_SEL_ARGS); \
+    else select_kernel<1, kScoredThreads, 2, fp32><<<grid, dim3(kScoredThreads), 0, st>>>(DSK_SEL_ARGS);                    \
   } while (0)
   if (G == 1 || G == 2 || G == 4 || G == 8) DSK_SEL_PASSES(false);
   else DSK_SEL_PASSES(true);
@@ -766,7 +768,7 @@ hipError_t launch_select_scored(const dsk_select_args& a, float* scores, int str
   return hipGetLastError();
 }
 
-hipError_t launch_select(const dsk_select_args& a, const float* scores, int stride, hipStream_t st) {
+hipError_t launch_select(const dsk_select_args& a, float* scores, int stride, hipStream_t st) {
   const int k = a.budget / a.b;
   // selecting heads: the query heads, or the KV heads when a group shares its selection
   const int Hsel = (a.flags & DSK_SELECT_SHARED_BY_KV_GROUP) ? a.Hkv : a.Hq;
@@ -776,7 +778,7 @@ hipError_t launch_select(const dsk_select_args& a, const float* scores, int stri
   const int bound = select_bound(a);
 #define DSK_SEL_ARGS                                                                                          \
   scores, stride, a.cu_blocks, a.block_start, a.slot_base, a.max_blocks_total, Hsel, a.b, k, a.budget_per_seq, a.blocks_used, \
-      a.seq_row0, a.sel_slot, a.sel_start, a.sel_len, a.sel_count
+      a.seq_row0, a.sel_slot, a.sel_start, a.sel_len, a.sel_count, ScoredBy{}
   if (sel_fits_tile(bound, 4, 256)) select_kernel<4, 256><<<grid, dim3(256), 0, st>>>(DSK_SEL_ARGS);
   else if (sel_fits_tile(bound, 4, 512)) select_kernel<4, 512><<<grid, dim3(512), 0, st>>>(DSK_SEL_ARGS);
   else if (sel_fits_tile(bound, 4, 1024)) select_kernel<4, 1024><<<grid, dim3(1024), 0, st>>>(DSK_SEL_ARGS);
