@@ -93,9 +93,12 @@ struct SumTensor {
 
 // One wavefront per (plane, block); the planes are the heads of K, then those of V, `heads` in all and the slower index,
 // so that the wavefronts for which there is no block come last.  `streamed`: planes from the first one whose rows are
-// read past the caches.  WAVES: wavefronts per SIMD that the registers leave room for at least (they are 5 with 4).
+// read past the caches.  WAVES: wavefronts per SIMD that the compiler schedules for, 4 (96 or 104 registers) or 6 (80).  The
+// upper bound holds it to the first: of its own accord it takes one schedule or the other with any change of the code, 67.7
+// or 70.5 us for the pass over one sequence of 128K tokens, 285 or 295 for K and V of eight.
 template <bool MEAN, int WAVES>
-__global__ __launch_bounds__(kSumThreads, WAVES) void summaries_kernel(
+__attribute__((amdgpu_waves_per_eu(WAVES, WAVES == 4 ? 4 : 8)))
+__global__ __launch_bounds__(kSumThreads) void summaries_kernel(
     SumTensor k, SumTensor v, int Hkv, int heads, int streamed, const int32_t* __restrict__ block_start,
     const int32_t* __restrict__ cu_blocks, int B, int cap, int out_rows, int total_tokens, int32_t* dev_status) {
   const int lane = threadIdx.x & (DSK_WAVE - 1);

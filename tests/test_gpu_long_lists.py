@@ -262,3 +262,54 @@ def test_partials_of_lists_that_fit_one_chunk(B, Hq, Hkv, k, b, shared):
             if used == 1:
                 assert rel_err(part.out[s, h].cpu().numpy(), out[s, h]) <= 1e-5
                 assert abs(float(part.lse[s, h]) - lse[s, h]) <= 1e-5
+
+
+# chunks a list in several wavefronts: short chunks, long lists, shared lists in tiles of 4 and 8 heads, slots of two tiles
+@pytest.mark.parametrize("B,Hq,Hkv,k,b,shared", [(2, 8, 2, 50, 16, False), (8, 32, 8, 128, 16, False), (8, 32, 8, 128, 32, False),
+                                                 (8, 32, 8, 128, 16, True), (8, 56, 8, 128, 32, True)])
+def test_values_that_are_not_finite_stay_where_they_are(B, Hq, Hkv, k, b, shared):
+    """A NaN in a query, a row of K or a row of V, or an infinity in V, shows in the outputs that depend on it and in no other:
+    not in the other heads of a group, whose logits share matrix products, nor in other lists or channels.  Where a logit is
+    NaN no sum of weights is above zero and the result is that of an empty list, on every kernel."""
+    import paper_2602_03184_amd as dsk
+    rng = np.random.default_rng([B, Hq, k, b])
+    g = torch.Generator(device="cuda")
+    g.manual_seed(b)
+    L = 4001
+    K, V = (torch.randn(Hkv, L, 128, generator=g, device="cuda").bfloat16() for _ in range(2))
+    q = torch.randn(B, Hq, 128, generator=g, device="cuda").bfloat16()
+    H, G = (Hkv if shared else Hq), Hq // Hkv
+    counts = np.full((B, H), k)
+    start, length = _lists(rng, B, H, k, b, L - 200, counts)       # the last rows are in the lists below only
+    # rows L-1, L-2, L-3 as the only row of a slot and L-10 inside one
+    lists = {"K": (0, 0), "V": (0, 1), "inf": (1, 0), "inside": (1, 1)}
+    for (s, h), row, n, at in zip(lists.values(), (L - 1, L - 2, L - 3, L - 12), (1, 1, 1, 5), (0, k - 1, 9, 30)):
+        start[s, h, at], length[s, h, at] = row, n
+    out0, lse0 = _want(q, K, V, start, length, counts, G if shared else 1)
+    kv = lambda h: h if shared else h // G                          # KV head of a list
+    K[kv(0), L - 1, 7] = float("nan")
+    V[kv(1), L - 2, 5] = float("nan")
+    V[kv(0), L - 3, 9] = float("inf")
+    K[kv(1), L - 10, 100] = float("nan")
+    q[0, Hq - 1, 3] = float("nan")
+    att = dsk.make_attn_args(q, K, V, dev_i32(start), dev_i32(length), dev_i32(counts), b,
+                             flags=dsk.DSK_ATTN_SHARED_SELECTION if shared else 0)
+    dsk.dsk_sparse_decode_attn(att.args)
+    torch.cuda.synchronize()
+    out, lse = att.out.cpu().numpy(), att.lse.cpu().numpy()
+    bad, bad_lse = np.zeros(out.shape, bool), np.zeros(lse.shape, bool)
+
+    def heads(name):
+        s, h = lists[name]
+        return s, slice(h * G, (h + 1) * G) if shared else h
+    for name in ("K", "inside"):
+        bad[heads(name)], bad_lse[heads(name)] = True, True
+    bad[heads("V") + (5,)] = True
+    bad[heads("inf") + (9,)] = True
+    bad[0, Hq - 1], bad_lse[0, Hq - 1] = True, True
+    empty = np.broadcast_to(bad_lse[..., None], out.shape)
+    np.testing.assert_array_equal(~np.isfinite(out), bad & ~empty)
+    np.testing.assert_array_equal(lse == -np.inf, bad_lse)
+    assert not out[empty].any()
+    assert rel_err(out[~bad], out0[~bad]) <= 1e-5                  # as in test_long_lists
+    np.testing.assert_allclose(lse[~bad_lse], lse0[~bad_lse], rtol=0, atol=1e-5)
