@@ -292,12 +292,12 @@ __global__ __launch_bounds__(WAVES * DSK_WAVE) void attn_kernel(
 
 // Long lists: one workgroup of kLongWaves wavefronts for every CU, each with many slots of one head (its whole list where
 // there are that many heads, which leaves nothing to merge).  A wavefront takes every kLongWaves-th slot, one after the
-// other; the spans of 64 slots lie one in each lane.  Few rows in flight are what it gains by: the heads of a group stay
-// close together in their lists, and more of the rows they share come from L2.  Eight sequences, 32 / 8 heads, 128 slots of
-// 16 rows: step 55.0 us with a workgroup per 8 slots and the merge, 50.4 with 8 wavefronts (8 steps that follow on one
-// cache 496 -> 470); with two slots of a wavefront in flight 51.9 / 483, with four 51.8 / 494, 4 wavefronts 56.9 / 530,
-// 12 wavefronts 51.8 / 483, 16 52.6 / 499.  40 / 40 heads, 128K tokens, 256 slots of 16 rows: 40.0 -> 38.7 with 6 chunks a
-// head (240 workgroups), 43.5 with 7 (280: the last 24 have the card to themselves).
+// other; the spans of 64 slots lie one in each lane.  What it gains is the merge and the starts of the many workgroups:
+// eight sequences, 32 / 8 heads, 128 slots of 16 rows, take 31.3 us without a merge against 32.5 and 4.8 with a workgroup per
+// 8 slots, from the same 146 MB of HBM (145) with the same third of the requests served by L2; step 55.0 -> 50.4 us (8 steps
+// that follow on one cache 496 -> 470).  With two slots of a wavefront in flight 51.9 / 483, with four 51.8 / 494, 4
+// wavefronts 56.9 / 530, 12 wavefronts 51.8 / 483, 16 52.6 / 499.  40 / 40 heads, 128K tokens, 256 slots of 16 rows: 40.0 ->
+// 38.7 with 6 chunks a head (240 workgroups), 43.5 with 7 (280: the last 24 have the card to themselves).
 constexpr int kLongWaves = 8;
 constexpr int kLongMinSlots = 32;       // of a workgroup; where a list of less than 256 slots is cut, 8 more: the merge takes
                                         // back what such chunks gain (2 to 8 sequences, 128 slots: 0.2 to 0.4 us slower with 32)
@@ -428,9 +428,11 @@ __global__ __launch_bounds__(kLongWaves * DSK_WAVE) void attn_long_kernel(
 // four logits of one head instead of every lane with all of them; the weights go back to the rows' lanes by swapping
 // halves and rows of the wavefront (a 4 x 4 transposition of registers and lane groups) and are broadcast inside a row of
 // 16 lanes.  About 250 instructions.  The sums over V stay in fp32 on the vector ALU.
-// A workgroup of kLongWaves wavefronts for every CU, as in attn_long_kernel; `leave` as in attn_kernel.  Steps at 30K tokens, 128 slots of 16 rows a
-// list, before (two slots per wavefront, heads in tiles of 2 or 4, other widths per head) and now: eight sequences of
-// 32 / 8 heads 33.1 -> 30.1 us, of 28 / 4 heads 36.4 -> 29.8; 512 slots of 8 rows 62.0 -> 46.8 and 75.5 -> 41.5.
+// A workgroup of kLongWaves wavefronts for every CU, as in attn_long_kernel; `leave` as in attn_kernel.  Steps at 30K tokens,
+// 128 slots of 16 rows a list, before (two slots per wavefront, heads in tiles of 2 or 4, other widths per head) and now:
+// eight sequences of 32 / 8 heads 33.1 -> 30.1 us, of 28 / 4 heads 36.4 -> 29.8; 512 slots of 8 rows 62.0 -> 46.8 and 75.5 ->
+// 41.5.  Random calls of 3072 slots and more, now / before, mean and largest by heads a group: 2 0.90 1.01, 3 0.71 0.90, 4
+// 0.75 0.86, 5 0.57 0.85, 6 0.56 0.81, 7 0.50 0.72, 8 0.62 0.79, 9 and more 0.45 0.92.
 typedef __attribute__((ext_vector_type(8))) __bf16 attn_bf16x8;
 typedef __attribute__((ext_vector_type(4))) float attn_f32x4;
 typedef __attribute__((ext_vector_type(2))) unsigned attn_u32x2;
@@ -777,8 +779,9 @@ static int attn_even_chunks(PerXcd per_xcd, int64_t lists, int k, int min_slots,
 // Lists per head on attn_long_kernel: where one workgroup a CU occupies at least 85 % of the CUs.  435 such calls with random
 // heads (1 to 16 a group), batches, lists and shared rows took 0.89 times as long as on attn_kernel in the mean, 1.036 at
 // most; with 75 to 85 % of them it would be 0.92, but a seventh of the calls more than 2 % longer.  (The 6 % above: no
-// slack is as fast, 15 % 1.04 times as long.)  With several workgroups a CU the heads of a group are side by side no longer; that pays where there is little to
-// keep together or attn_kernel does badly: groups of 10 heads and more (713 calls, 0.78, 1.06 at most), lists of up to 1024
+// slack is as fast, 15 % 1.04 times as long.)  With several workgroups a CU the heads of a group are side by side no longer
+// and fetch more of their common rows anew (198 -> 237 MB in the last example); that pays where there is little to keep
+// together or attn_kernel does badly: groups of 10 heads and more (713 calls, 0.78, 1.06 at most), lists of up to 1024
 // rows (262 calls, 0.83, 1.02) and slots that leave a quarter and more of the 16 or 32 rows that both kernels have in
 // flight empty (1457 calls, 0.85, 1.05).  The other 1676 took 0.94 in the mean, but an eighth of them more than 2 % longer
 // than on attn_kernel, 13 % at most (48 / 8 heads, six sequences, 175 slots of 16 rows 34.1 -> 38.0 us).

@@ -8,11 +8,11 @@
 // holding 16 keys of ONE query row: the softmax statistics (mass of all keys, of the retained region
 // O_t, of the discarded region D_t) accumulate per lane with no cross-lane traffic until the very end.
 //
-// What bounds it: the vector ALU and the matrix cores together, at the clock that both leave.  Per product of a key
-// tile and a row tile a lane has 16 exponentials (half the issue rate), 16 multiply-adds and 16 adds = 256 cycles of
-// a SIMD, next to 256 cycles of MFMA, which run in their shadow when the two are interleaved; the chip runs at 1.8 to
-// 2.0 GHz meanwhile (2.4 in light kernels), and the products alone would take 150 to 180 ns each on random data, of the
-// 265 they take here.  Everything else is kept off that path:
+// What bounds it: vector and matrix instructions next to each other, at the clock that the data leave.  Counted for 1024
+// samples of eight sequences: per product of a key tile and a row tile 256 cycles of MFMA and 350 of vector issue (72
+// instructions of a wavefront, the 16 exponentials taking two slots each), of 727 cycles that a SIMD spends, starts and
+// waits included (matrix cores 35 % busy, vector ALU 48 %).  On zeros the same call takes the same cycles at 2.33 GHz, on
+// random data at 1.97: 211 and 251 us.  Everything else is kept off that path:
 //  - The samples of a sequence are ranked by position (latest first) and their rows packed back to back,
 //    so that row tiles are full for any W*G and the samples of a workgroup end at about the same key.
 //  - A workgroup (4 wavefronts x kImpNS row tiles, query operands in registers) shares every key tile
@@ -25,8 +25,8 @@
 //  - The exponentials are taken relative to a reference that is only moved when a tile's sum exceeds
 //    kImpRescaleAt (at first, and seldom afterwards), so the usual tile has no maximum and no rescaling.
 //  - The products of the next tile are issued in between the exponentials of the current one; with both
-//    workgroups of a CU at work a product takes about 585 cycles of a SIMD (440 when the other one idles).
-//    Holding the products of both row tiles at once spilled registers, leaving the MFMAs in front of the
+//    workgroups of a CU at work a product takes about 585 cycles of a SIMD inside the loop (440 when the other one
+//    idles).  Holding the products of both row tiles at once spilled registers, leaving the MFMAs in front of the
 //    branch on the kind of a tile serialised them (1.2 instead of 0.8 us per key tile).
 //  - Tiles that cross a region's edge of some row (2.5 times the work) are left out of that loop and done by
 //    each wavefront on its own, so that it does not hold up the others at a barrier.  A row tile of one sample has
@@ -38,8 +38,9 @@
 // over the GPUs seen), 1024 samples of eight sequences of 24K to 64K tokens 370 -> 243 us, against one workgroup per
 // 3 or 4 consecutive samples with the key tiles fetched by each wavefront; then 58.5 -> 55.0 and 235 -> 222 (both on one
 // GPU) from key addresses without vector multiplies and the order of the two workgroups of a CU.  (A kImpItemCost of 6 did
-// as well in these two, but took up to 8 % longer with 32 heads without groups.)  Keys straight to LDS three stages ahead (four buffers): 55.9 / 241 against 54.8 / 233 at that stage, latency is not what
-// is missing; two masked tiles' keys on their way instead of one: no change.
+// as well in these two, but took up to 8 % longer with 32 heads without groups.)  Keys straight to LDS three stages ahead
+// (four buffers): 55.9 / 241 against 54.8 / 233 at that stage, latency is not what is missing; two masked tiles' keys on
+// their way instead of one: no change.
 #include <type_traits>
 
 #include "dsk_common.hpp"
@@ -376,8 +377,9 @@ __global__ __launch_bounds__(kImpThreads, 2) void importance_kernel(
   const int own_tile = (blockIdx.x * 2 >= gridDim.x ? kImpWaves - 1 - wave : wave) * kImpNS;
   // Most likely the second workgroup of its CU, which goes first in three stages of four (below): where a row tile holds rows
   // of one sample and pieces are long.  Row tiles that samples share leave much work behind the stages, at each wavefront's
-  // own pace, and a priority then costs as often as it gains (250 calls with 1 to 20 rows a sample, or 40, 56, 72 ..: 0.90 to
-  // 1.12 of the time without); with short pieces it is up to 4 % slower too.
+  // own pace, and a priority then costs as often as it gains.  600 random calls, time against none, mean / largest: 32, 64 ..
+  // rows a sample, pieces of 8 stages and more 0.97 / 0.99, shorter ones 1.00 / 1.02; up to 20 rows, 64 stages and more 0.985
+  // / 1.01 (1.09 among 52 others), fewer 0.99 / 1.07; 40, 56, 72 .. rows 1.00 / 1.10.
   const bool young = rps % 32 == 0 && line.per >= 8 && blockIdx.x * 2 >= gridDim.x;
   const int col = lane & 31;        // query row of the tile this lane accumulates; key row of its A operand
   const int hf = lane >> 5;         // channel half / key sub-row selector
