@@ -780,13 +780,22 @@ static int attn_even_chunks(PerXcd per_xcd, int64_t lists, int k, int min_slots,
 // heads (1 to 16 a group), batches, lists and shared rows took 0.89 times as long as on attn_kernel in the mean, 1.036 at
 // most; with 75 to 85 % of them it would be 0.92, but a seventh of the calls more than 2 % longer.  (The 6 % above: no
 // slack is as fast, 15 % 1.04 times as long.)  With several workgroups a CU the heads of a group are side by side no longer
-// and fetch more of their common rows anew (198 -> 237 MB in the last example); that pays where there is little to keep
-// together or attn_kernel does badly: groups of 10 heads and more (713 calls, 0.78, 1.06 at most), lists of up to 1024
-// rows (262 calls, 0.83, 1.02) and slots that leave a quarter and more of the 16 or 32 rows that both kernels have in
-// flight empty (1457 calls, 0.85, 1.05).  The other 1676 took 0.94 in the mean, but an eighth of them more than 2 % longer
-// than on attn_kernel, 13 % at most (48 / 8 heads, six sequences, 175 slots of 16 rows 34.1 -> 38.0 us).
-static bool attn_long_in_rounds(const dsk_attn_args& a, int G) {
-  return G >= 10 || (int64_t)a.k * a.b <= 1024 || a.b <= 12 || (a.b > 16 && a.b <= 24);
+// and fetch more of their common rows anew (198 -> 237 MB in the last example).  That pays, time on attn_kernel = 1, mean and
+// largest,
+//  - in groups of 10 heads and more: 713 calls 0.78, 1.06;
+//  - for lists of up to 1024 rows: 262 calls 0.83, 1.02;
+//  - for slots that leave a quarter and more of the 16 or 32 rows that both kernels have in flight empty: 1457 calls 0.85, 1.05;
+//  - for whole lists (nothing to merge) of slots of up to 16 rows, 293 calls 0.90, 1.035; of larger ones up to 2700 rows, 118
+//    calls 0.90, 1.02;
+//  - where the lists of a group have more than 100 000 rows together, 88 calls 0.87, 1.01, or, if the last round is full to
+//    95 %, more than 75 000, 102 calls 0.88, 1.04, or there are 8 heads and more, 104 calls 0.85, 1.04.
+// The other 1000 took 0.97 in the mean, but a fifth of them more than 2 % longer than on attn_kernel, 13 % at most (48 / 8
+// heads, six sequences, 175 slots of 16 rows 34.1 -> 38.0 us).
+static bool attn_long_in_rounds(const dsk_attn_args& a, int G, int chunks, double use) {
+  const int64_t rows = (int64_t)a.k * a.b;
+  return G >= 10 || rows <= 1024 || a.b <= 12 || (a.b > 16 && a.b <= 24) ||
+         (chunks == 1 && (a.b <= 16 || rows <= 2700)) || G * rows > 100000 ||
+         (use >= 0.95 && (G * rows > 75000 || G >= 8));
 }
 
 // The space asked for is that of short chunks (8 or 16 slots), whatever the call takes.
@@ -821,8 +830,14 @@ AttnWs attn_ws_layout(const dsk_attn_args& a, bool size_only) {
   } else if (!own_merge && a.b <= 32 && a.k >= ((a.flags & DSK_ATTN_SHARED_SELECTION) ? kLongMinSlotsShared : kLongMinSlots) &&
              a.k_stride_tok <= kMaxTokenStride && a.v_stride_tok <= kMaxTokenStride) {
     const int n_groups = a.B * a.Hkv;
-    chunks = attn_even_chunks([&](int ch) { return attn_wgs_per_xcd(G, n_groups, ch); }, (int64_t)a.B * a.Hq, a.k,
-                              a.k < 256 ? kLongMinSlots + 8 : kLongMinSlots, 0.85, attn_long_in_rounds(a, G) ? kManyRounds : 1);
+    auto even = [&](int max_rounds) {
+      return attn_even_chunks([&](int ch) { return attn_wgs_per_xcd(G, n_groups, ch); }, (int64_t)a.B * a.Hq, a.k,
+                              a.k < 256 ? kLongMinSlots + 8 : kLongMinSlots, 0.85, max_rounds);
+    };
+    chunks = even(kManyRounds);
+    const int64_t rounds = (attn_wgs_per_xcd(G, n_groups, chunks) + kCusPerXcd - 1) / kCusPerXcd;
+    if (rounds > 1 && !attn_long_in_rounds(a, G, chunks, (double)a.B * a.Hq * chunks / (double)(rounds * kCusPerXcd * 8)))
+      chunks = even(1);
     if (chunks >= ws.nchunks) chunks = 0;
     if (chunks > 0) ws.kernel = AttnKernel::kLong;
   }

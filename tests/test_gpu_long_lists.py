@@ -51,7 +51,7 @@ SHAPES = [(8, 32, 8, 32, 16, True, False), (8, 32, 8, 33, 16, True, False), (8, 
           (4, 16, 8, 97, 32, False, True), (5, 24, 8, 83, 17, True, True), (4, 40, 8, 200, 32, False, True),
           (12, 56, 8, 33, 9, True, True), (6, 11, 1, 520, 16, False, True), (16, 8, 4, 49, 16, False, True),
           (8, 16, 8, 150, 32, True, True), (8, 24, 8, 139, 17, False, True), (12, 56, 8, 83, 9, True, True),
-          (8, 11, 1, 810, 16, True, True), (16, 8, 4, 121, 16, True, True), (16, 32, 8, 64, 16, True, True), (16, 32, 8, 65, 16, False, True)]
+          (8, 11, 1, 810, 16, True, True), (16, 8, 4, 121, 16, True, True), (16, 32, 8, 64, 16, True, True), (16, 32, 8, 65, 16, True, True), (16, 32, 8, 100, 32, False, True)]
 
 
 def _partials_left(att, lay):
