@@ -335,10 +335,10 @@ struct ScoredBy {
   int used, bound;     // blocks of all sequences, of one
 };
 
-// Short sequences.  Up to kScoredMax blocks, a list per query head: the workgroup of a list scores its blocks itself, which saves the launch of
-// the score kernel and the way of the scores through memory.  Every head of a group reads the summaries (all heads of a
-// group on one XCD, so that they meet in its L2), which costs as much as the launch from some 256 blocks on.  A
-// half-wavefront scores 8 consecutive blocks at a time as in the score kernel (same sums, same bits), the loads of all
+// Short sequences.  Up to kScoredMax blocks, a list per query head: the workgroup of a list scores its blocks itself, which
+// saves the launch of the score kernel and the way of the scores through memory.  Every head of a group reads the summaries
+// (all heads of a group on one XCD, so that they meet in its L2), which costs as much as the launch from some 256 blocks on.
+// A half-wavefront scores 8 consecutive blocks at a time as in the score kernel (same sums, same bits), the loads of all
 // blocks in flight at once.  Whole decode step in a graph, two launches / one: one head, 68 blocks 13.8 / 11.8 us, 170
 // 13.7 / 12.5, 300 14.5 / 14.6, 400 13.7 / 14.1; 32 / 8 heads 68 blocks 15.2 / 12.7, 170 15.1 / 13.5, 300 16.2 / 15.9.  (A list
 // per KV head would have a wavefront score all of its group's heads, one after the other: 15.4 / 19.6 at 400 blocks.)
@@ -374,7 +374,8 @@ __device__ __forceinline__ bool scored_load(const ScoredBy& by, float* scores, i
   const bool is_max = c >= 16;
   const uint16_t* kh = by.ksum + (int64_t)hk * cap * (2 * DSK_HEAD_DIM) + c * 8;
   auto record = [&](int blk) { return *reinterpret_cast<const uint4*>(kh + (int64_t)blk * (2 * DSK_HEAD_DIM)); };
-  const int last = (by.used - blk0 < by.bound ? by.used : blk0 + by.bound) - 1;    // no record behind it is asked for ahead; by.used >= 1
+  // no record behind it is asked for ahead (used >= 1, bound >= 1)
+  const int last = (by.used - blk0 < by.bound ? by.used : blk0 + by.bound) - 1;
   uint4 qv = *reinterpret_cast<const uint4*>(by.q + sh_idx * DSK_HEAD_DIM + (c & 15) * 8);
   uint4 kv[PASSES][kScoredBlocks];
 #pragma unroll
