@@ -819,31 +819,30 @@ __global__ __launch_bounds__(kThreads) void importance_few_kernel(
   }
 }
 
-// what the finishing kernels end with, on the sum of a sample's rows (thread m < M: the class's m-th
-// sample, have: its position is not -1): sample scores, class mean, class weight; sums in sample order
+// what the finishing kernels end with, on the sum of a sample's rows (thread m < M <= 64: the class's m-th
+// sample, have: its position is not -1): sample scores, class mean, class weight; sums in sample order.  The first
+// wavefront alone: with the scores in LDS, a barrier and one thread that adds them this took 2400 cycles instead of 1600.
 __device__ __forceinline__ void imp_class_weight(double sum_rows, bool have, int c, int s, int n_class, int M, int n_rows,
                                                  float alpha, uint8_t* class_weight_q, float* class_mean,
                                                  float* samp_score, float* samp_score_sum, int layers) {
-  __shared__ float sm_score[kMaxSamplesPerClass];
-  __shared__ int sm_have[kMaxSamplesPerClass];
+  static_assert(kMaxSamplesPerClass <= DSK_WAVE, "a lane per sample");
+  if (threadIdx.x >= DSK_WAVE) return;
+  float st = 0.0f;
   if ((int)threadIdx.x < M) {
     const int64_t js = ((int64_t)s * n_class + c) * M + threadIdx.x;
-    float st = (float)(sum_rows / n_rows);
+    st = (float)(sum_rows / n_rows);
     if (samp_score) samp_score[js] = have ? st : __builtin_nanf("");
     if (samp_score_sum != nullptr && have) {      // expectation over layers: this layer joins the running sum
       const float tot = samp_score_sum[js] + st;
       samp_score_sum[js] = tot;
       st = tot / (float)layers;
     }
-    sm_score[threadIdx.x] = st;
-    sm_have[threadIdx.x] = have ? 1 : 0;
   }
-  __syncthreads();
-  if (threadIdx.x != 0) return;
+  unsigned long long left = __ballot((int)threadIdx.x < M && have);
+  const int cnt = __popcll(left);
   float sum = 0.0f;
-  int cnt = 0;
-  for (int i = 0; i < M; ++i)
-    if (sm_have[i]) { sum += sm_score[i]; ++cnt; }
+  for (; left != 0; left &= left - 1) sum += __int_as_float(__builtin_amdgcn_readlane(__float_as_int(st), __builtin_ctzll(left)));
+  if (threadIdx.x != 0) return;
   const int64_t cs = (int64_t)s * n_class + c;
   if (cnt > 0) {
     const float mean = sum / (float)cnt;
@@ -878,54 +877,65 @@ __global__ __launch_bounds__(DSK_WAVE) void importance_few_finalize_kernel(
 
 constexpr int kImpFinThreads = 1024;
 constexpr int kImpFinWaves = kImpFinThreads / DSK_WAVE;
-constexpr int kImpFinRows = 2;       // rows of a lane in flight together,
-constexpr int kImpFinBatch = 8;      // and pieces of each
+constexpr int kImpFinRows = 2;       // rows of a lane in flight together
 // The rows idx, idx + stride .. of a sample's n_rows: their pieces' statistics merged, the row values summed.
 // locate(row, n): the first of the row's n pieces, `pitch` entries apart.
+// What bounds it is how fast one CU takes them in, so no more pieces are requested than some row of the wavefront has, to
+// the next even number: with 8 at a time whatever there is, this was 9100 of the finishing kernel's 15500 cycles (128
+// samples of 128K tokens, 5 pieces a row), now 8100 of 13600; 8600 of 14700 and 6500 of 11500 (eight sequences, 2 pieces).
 template <typename Locate>
 __device__ __forceinline__ float imp_rows_sum(Locate locate, int pitch, int idx, int stride, int n_rows, float alpha) {
   float sum = 0.0f;
-  for (; idx < n_rows; idx += kImpFinRows * stride) {
+  while (__any(idx < n_rows)) {
     const float4* rows[kImpFinRows];
-    int n[kImpFinRows], most = 0;
+    int n[kImpFinRows];
+    int most = 0;
     RowStat a[kImpFinRows];
 #pragma unroll
     for (int i = 0; i < kImpFinRows; ++i) {
       const bool own = idx + i * stride < n_rows;
-      rows[i] = locate(own ? idx + i * stride : idx, n[i]);
+      rows[i] = locate(own ? idx + i * stride : 0, n[i]);
       n[i] = own ? n[i] : 0;
       most = n[i] > most ? n[i] : most;
       a[i] = {-__builtin_inff(), 0.0f, 0.0f, 0.0f};
     }
-    for (int w = 0; w < most; w += kImpFinBatch) {
-      float4 v[kImpFinRows][kImpFinBatch];
+    most = (int)wave_max_u((uint32_t)most);
+    auto merge = [&](auto batch, int w) {                // pieces w .. of each row
+      constexpr int kBatch = decltype(batch)::value;
+      float4 v[kImpFinRows][kBatch];
 #pragma unroll
       for (int i = 0; i < kImpFinRows; ++i)
 #pragma unroll
-        for (int j = 0; j < kImpFinBatch; ++j) v[i][j] = rows[i][(int64_t)(w + j < n[i] ? w + j : 0) * pitch];
+        for (int j = 0; j < kBatch; ++j) v[i][j] = rows[i][(int64_t)(w + j < n[i] ? w + j : 0) * pitch];
 #pragma unroll
       for (int i = 0; i < kImpFinRows; ++i)
 #pragma unroll
-        for (int j = 0; j < kImpFinBatch; ++j) pin_loaded(v[i][j]);
+        for (int j = 0; j < kBatch; ++j) pin_loaded(v[i][j]);
 #pragma unroll
       for (int i = 0; i < kImpFinRows; ++i) {
         float m = a[i].m;
 #pragma unroll
-        for (int j = 0; j < kImpFinBatch; ++j) m = fmaxf(m, w + j < n[i] ? v[i][j].x : -__builtin_inff());
+        for (int j = 0; j < kBatch; ++j) m = fmaxf(m, w + j < n[i] ? v[i][j].x : -__builtin_inff());
         const float ref = m == -__builtin_inff() ? 0.0f : m;     // no key anywhere yet: all factors 0
         const float f = __builtin_amdgcn_exp2f(a[i].m - ref);
         a[i] = {m, a[i].zt * f, a[i].zo * f, a[i].zd * f};
 #pragma unroll
-        for (int j = 0; j < kImpFinBatch; ++j) {
+        for (int j = 0; j < kBatch; ++j) {
           const float g = w + j < n[i] ? __builtin_amdgcn_exp2f(v[i][j].x - ref) : 0.0f;
           a[i].zt = fmaf(v[i][j].y, g, a[i].zt);
           a[i].zo = fmaf(v[i][j].z, g, a[i].zo);
           a[i].zd = fmaf(v[i][j].w, g, a[i].zd);
         }
       }
-    }
+    };
+    int w = 0;
+    for (; most - w > 6; w += 8) merge(std::integral_constant<int, 8>{}, w);
+    if (most - w > 4) merge(std::integral_constant<int, 6>{}, w);
+    else if (most - w > 2) merge(std::integral_constant<int, 4>{}, w);
+    else if (most > w) merge(std::integral_constant<int, 2>{}, w);
 #pragma unroll
     for (int i = 0; i < kImpFinRows; ++i) sum += a[i].zt > 0.0f ? (a[i].zo - alpha * a[i].zd) / a[i].zt : 0.0f;
+    idx += kImpFinRows * stride;
   }
   return sum;
 }
@@ -955,6 +965,9 @@ __global__ __launch_bounds__(kImpFinThreads) void importance_finalize_kernel(
   // everything that does not depend on the plan's values goes out in one round trip
   if (threadIdx.x <= items && threadIdx.x < kImpFinItems) sm_item[threadIdx.x] = pl.item_at[threadIdx.x];
   const bool have = (int)threadIdx.x < M && samp_pos[(int64_t)s * n_samp + c * M + threadIdx.x] >= 0;
+  const int per_sample = M < kImpFinWaves ? kImpFinWaves / M : 1;   // wavefronts of one sample
+  const int m_first = wave / per_sample;
+  const int rk_first = m_first < M ? rank[c * M + m_first] : -1;
   static_assert(kImpFinItems <= kImpFinThreads, "one load each");
   auto item_at = [&](int i) { return (uint32_t)(i < kImpFinItems ? sm_item[i] : pl.item_at[i]); };
   ImpLine line;
@@ -965,9 +978,8 @@ __global__ __launch_bounds__(kImpFinThreads) void importance_finalize_kernel(
     line.extra = (uint32_t)(T % nw);
   }
   __syncthreads();
-  const int per_sample = M < kImpFinWaves ? kImpFinWaves / M : 1;   // wavefronts of one sample
-  for (int m = wave / per_sample; m < M; m += kImpFinWaves / per_sample) {
-    const int rk = rank[c * M + m];
+  for (int m = m_first; m < M; m += kImpFinWaves / per_sample) {
+    const int rk = m == m_first ? rk_first : rank[c * M + m];
     float sum = 0.0f;
     if (rk >= 0 && nw > 0) {
       sum = imp_rows_sum(

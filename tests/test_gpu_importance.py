@@ -413,6 +413,12 @@ def test_importance_packed_rows(B, L, Hq, Hkv, n_class, M, W, R, spread, imp_sca
     _compare_with_64_bits(B, L, Hq, Hkv, n_class, M, W, R, positions, few=False, spread=spread, imp_scale=imp_scale)
 
 
+@pytest.mark.parametrize("L", [300, 600, 1000, 1400, 1900, 2300, 4000, 9000])
+def test_importance_rows_of_many_pieces(L):
+    """Two groups of query rows, cut into pieces of four stages: 2 to 37 pieces a row for the finishing kernel."""
+    _compare_with_64_bits(1, L, 8, 1, 2, 2, 16, 64, [L - 17, L - 18, L - 40], few=False)
+
+
 def test_importance_ranks_positions_beyond_19_bits():
     """A sequence of more than 2^19 tokens: the sort keys leave out the lowest bit of a position, so neighbours
     tie and an item's length counts from the later one."""
