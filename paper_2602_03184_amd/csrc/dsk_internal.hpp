@@ -120,10 +120,10 @@ struct DenseWs {
 DenseWs dense_ws_layout(const dsk_dense_attn_args& a);
 hipError_t launch_dense_attn(const dsk_dense_attn_args& a, const DenseWs& ws, hipStream_t st);
 
-// summaries of the blocks [blk_range[0], blk_range[1]) only (device-resident range)
+// summaries of the blocks [blk_range[0], blk_range[1]) only (device-resident range); chunk: their usual length, C
 hipError_t launch_summaries_range(const void* X, int64_t stride_tok, int64_t stride_head, int Hkv,
                                   const int32_t* block_start, const int32_t* blk_range, int max_blocks_in_range,
-                                  int cap, int total_tokens, int summary_mode, void* out, int32_t* dev_status,
+                                  int cap, int total_tokens, int chunk, int summary_mode, void* out, int32_t* dev_status,
                                   hipStream_t st);
 // incremental update: workspace = int32 {first recomputed block, new block count}
 hipError_t launch_append(const dsk_append_args& a, hipStream_t st);
@@ -131,7 +131,7 @@ hipError_t launch_append(const dsk_append_args& a, hipStream_t st);
 // entry, end, first K/V row, new length}
 hipError_t launch_summaries_batch_ranges(const void* X, int64_t stride_tok, int64_t stride_head, int Hkv, int B,
                                          const int32_t* block_start, const void* ranges, int max_blocks_in_range,
-                                         int out_rows, int summary_mode, void* out, int32_t* dev_status,
+                                         int out_rows, int chunk, int summary_mode, void* out, int32_t* dev_status,
                                          hipStream_t st);
 hipError_t launch_append_batch(const dsk_append_batch_args& a, hipStream_t st);
 

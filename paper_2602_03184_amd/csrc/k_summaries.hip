@@ -22,27 +22,27 @@ constexpr int kSumUnroll = 8;  // row-groups of 4 rows in flight per wave
 // STREAM_ROWS: the rows are read past the caches too.  The decode step that follows finds in the memory-side cache
 // what was read last (eight sequences, all rows streamed: pass -23 us, step +30), so the launch streams only what
 // would have left that cache again by its end.
-template <bool MEAN, bool STREAM, bool STREAM_ROWS = false>
+template <bool MEAN, bool STREAM, bool STREAM_ROWS = false, int kUnroll = kSumUnroll>
 __device__ __forceinline__ void summarize_block(const uint16_t* base, int len, int64_t stride_tok, unsigned ustride8,
                                                 uint16_t* o, int g, int c) {
   // MEAN: mn[] holds this lane's running sums instead
   float mn[8], mx[8];
 #pragma unroll
   for (int k = 0; k < 8; ++k) { mn[k] = MEAN ? 0.0f : __builtin_inff(); mx[k] = -__builtin_inff(); }
-  for (int r0 = 0; r0 < len; r0 += 4 * kSumUnroll) {
+  for (int r0 = 0; r0 < len; r0 += 4 * kUnroll) {
     // scalar 64-bit base of this row batch + 32-bit lane offsets (stride_tok <= 2^24, host-checked)
     const char* rb = reinterpret_cast<const char*>(base + (int64_t)r0 * stride_tok);
     const int last = len - 1 - r0;
-    uint4 v[kSumUnroll];
+    uint4 v[kUnroll];
 #pragma unroll
-    for (int u = 0; u < kSumUnroll; ++u) {
+    for (int u = 0; u < kUnroll; ++u) {
       int r = 4 * u + g;
       r = r < last ? r : last;     // a repeated row changes neither min nor max
       const unsigned byte_off = (__umul24((unsigned)r, ustride8) + (unsigned)c) * 16u;   // strides are multiples of 8
       v[u] = load16<STREAM_ROWS>(rb + byte_off);
     }
 #pragma unroll
-    for (int u = 0; u < kSumUnroll; ++u) {
+    for (int u = 0; u < kUnroll; ++u) {
       float f[8];
       unpack8(v[u], f);
       if constexpr (MEAN) {
@@ -82,6 +82,19 @@ __device__ __forceinline__ void summarize_block(const uint16_t* base, int len, i
                     make_uint4(pack_bf16_exact(mx[0], mx[1]), pack_bf16_exact(mx[2], mx[3]),
                                pack_bf16_exact(mx[4], mx[5]), pack_bf16_exact(mx[6], mx[7])));
   }
+}
+
+// The same where wavefronts are few and the latency of the rows is what counts.  LONG: up to 96 rows in flight, for chunks of
+// more than kSumRowsAhead.  (MEAN: a lane adds its rows in token order, whatever is in flight.)  A token appended to each of
+// eight sequences, chunks of 16 to 64, 8 heads: 4.8 -> 4.0 us for the launch, 8 decode steps 471.8 -> 467.9.  Where chunks are
+// shorter the registers are only a burden.
+constexpr int kSumRowsAhead = 4 * kSumUnroll;
+template <bool MEAN, bool LONG>
+__device__ __forceinline__ void summarize_few(const uint16_t* base, int len, int64_t stride_tok, unsigned ustride8,
+                                              uint16_t* o, int g, int c) {
+  if (!LONG || len <= kSumRowsAhead) summarize_block<MEAN, false>(base, len, stride_tok, ustride8, o, g, c);
+  else if (len <= 2 * kSumRowsAhead) summarize_block<MEAN, false, false, 2 * kSumUnroll>(base, len, stride_tok, ustride8, o, g, c);
+  else summarize_block<MEAN, false, false, 3 * kSumUnroll>(base, len, stride_tok, ustride8, o, g, c);
 }
 
 // A cache to summarise: K, and V in the same launch when its summaries are wanted.
@@ -214,7 +227,7 @@ hipError_t launch_summaries(const dsk_compress_args& a, hipStream_t st) {
 
 // Summaries of the blocks [blk_range[0], blk_range[1]) that an incremental update rewrote: few, so the chain of loads in front
 // of the rows is what counts.  grid: (group of kSumWaves heads, block), so that nothing has to be divided.
-template <bool MEAN>
+template <bool MEAN, bool LONG>
 __global__ __launch_bounds__(kSumThreads) void summaries_range_kernel(
     const uint16_t* __restrict__ X, int64_t stride_tok, int64_t stride_head, int Hkv,
     const int32_t* __restrict__ block_start, const int32_t* __restrict__ blk_range, int cap, int total_tokens,
@@ -238,34 +251,35 @@ __global__ __launch_bounds__(kSumThreads) void summaries_range_kernel(
       if (lane == 0) set_status(dev_status, DSK_ERR_SHAPE);
     } else {
       const uint16_t* base = X + (int64_t)h * stride_head + (int64_t)s * stride_tok;
-      summarize_block<MEAN, false>(base, len, stride_tok, (unsigned)stride_tok >> 3, o, g, c);
+      summarize_few<MEAN, LONG>(base, len, stride_tok, (unsigned)stride_tok >> 3, o, g, c);
     }
   }
 }
 
 hipError_t launch_summaries_range(const void* X, int64_t stride_tok, int64_t stride_head, int Hkv,
                                   const int32_t* block_start, const int32_t* blk_range, int max_blocks_in_range,
-                                  int cap, int total_tokens, int summary_mode, void* out, int32_t* dev_status,
+                                  int cap, int total_tokens, int chunk, int summary_mode, void* out, int32_t* dev_status,
                                   hipStream_t st) {
   if (Hkv <= 0 || max_blocks_in_range <= 0) return hipSuccess;
   const int groups = (Hkv + kSumWaves - 1) / kSumWaves;
   const int most = groups < 256 * 8 ? 256 * 8 / groups : 1;    // a long range: at most about 2048 workgroups
   const dim3 grid((unsigned)groups, (unsigned)(max_blocks_in_range < most ? max_blocks_in_range : most));
-  if (summary_mode == DSK_SUMMARY_MEAN)
-    summaries_range_kernel<true><<<grid, dim3(kSumThreads), 0, st>>>(
-        static_cast<const uint16_t*>(X), stride_tok, stride_head, Hkv, block_start, blk_range, cap, total_tokens,
-        static_cast<uint16_t*>(out), dev_status);
-  else
-    summaries_range_kernel<false><<<grid, dim3(kSumThreads), 0, st>>>(
-        static_cast<const uint16_t*>(X), stride_tok, stride_head, Hkv, block_start, blk_range, cap, total_tokens,
-        static_cast<uint16_t*>(out), dev_status);
+#define DSK_RANGE(mean, lng)                                                                                          \
+  summaries_range_kernel<mean, lng><<<grid, dim3(kSumThreads), 0, st>>>(                                                  \
+      static_cast<const uint16_t*>(X), stride_tok, stride_head, Hkv, block_start, blk_range, cap, total_tokens,           \
+      static_cast<uint16_t*>(out), dev_status)
+  const bool lng = chunk > kSumRowsAhead;
+  if (summary_mode == DSK_SUMMARY_MEAN) { if (lng) DSK_RANGE(true, true); else DSK_RANGE(true, false); }
+  else if (lng) DSK_RANGE(false, true);
+  else DSK_RANGE(false, false);
+#undef DSK_RANGE
   return hipGetLastError();
 }
 
 // Summaries of the blocks a batched incremental update rewrote.  ranges[s] = {first rewritten
 // entry, end, first K/V row of sequence s, its length}; block_start counts from the sequence's first
 // token.  grid: (rewritten block, sequence, group of kSumWaves heads): one wavefront per head.
-template <bool MEAN>
+template <bool MEAN, bool LONG>
 __global__ __launch_bounds__(kSumThreads) void summaries_batch_ranges_kernel(
     const uint16_t* __restrict__ X, int64_t stride_tok, int64_t stride_head, int Hkv,
     const int32_t* __restrict__ block_start, const int4* __restrict__ ranges, int out_rows,
@@ -287,25 +301,26 @@ __global__ __launch_bounds__(kSumThreads) void summaries_batch_ranges_kernel(
       if (lane == 0) set_status(dev_status, DSK_ERR_SHAPE);
     } else {
       const uint16_t* base = X + (int64_t)h * stride_head + ((int64_t)rg.z + s) * stride_tok;
-      summarize_block<MEAN, false>(base, len, stride_tok, (unsigned)stride_tok >> 3, o, g, c);
+      summarize_few<MEAN, LONG>(base, len, stride_tok, (unsigned)stride_tok >> 3, o, g, c);
     }
   }
 }
 
 hipError_t launch_summaries_batch_ranges(const void* X, int64_t stride_tok, int64_t stride_head, int Hkv, int B,
                                          const int32_t* block_start, const void* ranges, int max_blocks_in_range,
-                                         int out_rows, int summary_mode, void* out, int32_t* dev_status,
+                                         int out_rows, int chunk, int summary_mode, void* out, int32_t* dev_status,
                                          hipStream_t st) {
   if (max_blocks_in_range <= 0 || B <= 0) return hipSuccess;
   const dim3 grid((unsigned)max_blocks_in_range, (unsigned)B, (unsigned)((Hkv + kSumWaves - 1) / kSumWaves));
-  if (summary_mode == DSK_SUMMARY_MEAN)
-    summaries_batch_ranges_kernel<true><<<grid, dim3(kSumThreads), 0, st>>>(
-        static_cast<const uint16_t*>(X), stride_tok, stride_head, Hkv, block_start, static_cast<const int4*>(ranges),
-        out_rows, static_cast<uint16_t*>(out), dev_status);
-  else
-    summaries_batch_ranges_kernel<false><<<grid, dim3(kSumThreads), 0, st>>>(
-        static_cast<const uint16_t*>(X), stride_tok, stride_head, Hkv, block_start, static_cast<const int4*>(ranges),
-        out_rows, static_cast<uint16_t*>(out), dev_status);
+#define DSK_RANGES(mean, lng)                                                                                         \
+  summaries_batch_ranges_kernel<mean, lng><<<grid, dim3(kSumThreads), 0, st>>>(                                           \
+      static_cast<const uint16_t*>(X), stride_tok, stride_head, Hkv, block_start, static_cast<const int4*>(ranges),       \
+      out_rows, static_cast<uint16_t*>(out), dev_status)
+  const bool lng = chunk > kSumRowsAhead;
+  if (summary_mode == DSK_SUMMARY_MEAN) { if (lng) DSK_RANGES(true, true); else DSK_RANGES(true, false); }
+  else if (lng) DSK_RANGES(false, true);
+  else DSK_RANGES(false, false);
+#undef DSK_RANGES
   return hipGetLastError();
 }
 

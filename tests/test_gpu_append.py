@@ -7,7 +7,8 @@ import pytest
 import torch
 
 from oracle import dynsplit_oracle as O
-from dsk_testutil import bf16_bits_of, canon_zero, dev_bf16, dev_i32, dev_u8, gpu_case, oracle_summaries
+from dsk_testutil import (assert_bf16_of, bf16_bits_of, canon_zero, dev_bf16, dev_i32, dev_u8, gpu_case, oracle_means_bf16,
+                          oracle_summaries)
 
 pytestmark = pytest.mark.gpu
 
@@ -169,6 +170,29 @@ def test_append_edge_parameters(C, delta, a_num, everywhere):
     seq.check_summaries(want)
     if everywhere and delta == C - 1 and a_num == 10:
         assert len(want) - 1 == seq.L - C + 1             # one-token chunks, then the last chunk of C tokens
+
+
+@pytest.mark.parametrize("C", [32, 33, 64, 65, 96, 97, 200])
+@pytest.mark.parametrize("mean", [False, True])
+def test_append_chunk_lengths_around_the_rows_in_flight(C, mean):
+    """Whole chunks of C tokens (no delimiter, delta 0) and an open one that grows: 32, 64 or 96 rows at a time."""
+    rng = np.random.default_rng(C)
+    L = 6 * C + 9
+    K = (rng.standard_normal((3, L, 128)).astype(np.float32).view(np.uint32) >> 16).astype(np.uint16)
+    V = K[::-1].copy()
+    seq = _Seq(K, V, np.full(L, 7), [1, 2], np.array([9, 5], np.uint8), 2 * C - 3, C, 0, 5, 10, 16, want_vsum=True,
+               summary_mode=int(mean))
+    for n in (1, 2, 1, 33, C - 1, 1, 2 * C + 5):
+        want, i0 = seq.append(n)
+        seq.check_tables(want, i0)
+        if not mean:
+            seq.check_summaries(want)
+            seq.check_summaries(want, vsum=True)
+            continue
+        for bits, sums in ((K, seq.comp.ksum), (V, seq.comp.vsum)):
+            got = bf16_bits_of(sums)[:, : len(want) - 1]
+            np.testing.assert_array_equal(got[:, :, 0], got[:, :, 1])
+            assert_bf16_of(got[:, :, 0], oracle_means_bf16(bits[:, : seq.L], want, range(3)))
 
 
 def test_append_from_an_empty_sequence():
