@@ -3,9 +3,9 @@
 //
 // Every fixed-length slot inherits the score of its semantic block, so the k best slots are
 // found on the block scores with each block weighted by its slot count.  Thread t of the 256,
-// 512 or 1024 (by the host's bound on the block count) owns PT (4 or 8) consecutive blocks [t*PT, t*PT+PT) of the sequence: their keys (order-preserving
-// integer images of the scores) and slot counts live in registers, fetched with 16-byte loads
-// that are all in flight at once.
+// 512 or 1024 (by the host's bound on the block count) owns PT (4, 6, 8, 12 or 16) consecutive blocks [t*PT, t*PT+PT) of the
+// sequence: their keys (order-preserving integer images of the scores) and slot counts live in registers, fetched with
+// 16-byte loads (8-byte ones for 6 blocks) that are all in flight at once.
 //   1. key range and slot total (workgroup reduction);
 //   2. one slot-count-weighted LDS histogram over the top 10 bits of (key - smallest key) finds the
 //      bin that holds the k-th best slot; the few blocks of that bin are ranked against each
@@ -31,7 +31,7 @@ namespace dsk {
 
 constexpr int kSelMaxThreads = 1024;                    // workgroups of 256, 512 or 1024 threads by block count
 constexpr int kSelMaxWaves = kSelMaxThreads / DSK_WAVE;
-constexpr int kSelMaxPerThread = 8;                     // blocks per thread: 4 or 8 (register tile of 4096 or 8192)
+constexpr int kSelMaxPerThread = 16;                    // blocks per thread: 4, 6, 8, 12 or 16 (register tile of 1024 to 16384)
 constexpr int kSelWork = 1024;                          // chosen blocks staged in LDS per emission round
 
 // does a sequence of n blocks fit a register tile of `per_thread` blocks per thread whatever
@@ -326,6 +326,12 @@ __device__ __noinline__ void select_big(
   }
 }
 
+// vectors that a thread of PT consecutive blocks reads its table entries in
+template <int W> struct SelVec { typedef float4 F; typedef int4 I; };
+template <> struct SelVec<2> { typedef float2 F; typedef int2 I; };
+__device__ __forceinline__ void pin_loaded(float2& v) { asm volatile("" : "+v"(v.x), "+v"(v.y)::"memory"); }
+__device__ __forceinline__ void pin_loaded(int2& v) { asm volatile("" : "+v"(v.x), "+v"(v.y)::"memory"); }
+
 // What the selection needs to score the blocks itself
 struct ScoredBy {
   const uint16_t* ksum;
@@ -453,10 +459,11 @@ __global__ __launch_bounds__(THREADS) void select_kernel(
     int b, int kcap, const int32_t* __restrict__ budget_per_seq, const int32_t* __restrict__ blocks_used,
     const int32_t* __restrict__ seq_row0, int32_t* __restrict__ sel_slot, int32_t* __restrict__ sel_start,
     int32_t* __restrict__ sel_len, int32_t* __restrict__ sel_count, ScoredBy by) {
-  static_assert(PASSES > 0 ? PT == 1 && THREADS == kScoredThreads : PT == 4 || PT == 8, "register tile");
+  static_assert(PASSES > 0 ? PT == 1 && THREADS == kScoredThreads : PT == 4 || PT == 6 || PT == 8 || PT == 12 || PT == 16, "register tile");
   constexpr int NW = THREADS / DSK_WAVE;
   constexpr int kSelPerThread = PT;
-  constexpr int kSelVecs = (PT + 3) / 4;
+  constexpr int kVec = PT == 6 ? 2 : 4;                  // entries of a load
+  constexpr int kSelVecs = (PT + kVec - 1) / kVec;
   __shared__ SelShared sh;
   int h = blockIdx.x;
   int s = blockIdx.y;
@@ -480,21 +487,23 @@ __global__ __launch_bounds__(THREADS) void select_kernel(
   // cu_blocks[0] is 0 by definition: sequence 0 can address its loads before anything arrives
   const int blk0_raw = s == 0 ? 0 : cu_blocks[s];
   const int blk0 = blk0_raw < cap ? (blk0_raw > 0 ? blk0_raw : 0) : cap;
-  float4 fv[kSelVecs];
-  int4 iv[kSelVecs + 1], bv[kSelVecs + 1];
+  typedef typename SelVec<kVec>::F VecF;
+  typedef typename SelVec<kVec>::I VecI;
+  VecF fv[kSelVecs];
+  VecI iv[kSelVecs + 1], bv[kSelVecs + 1];
   int shift = 0, blk1, n, row0;
   if constexpr (PASSES > 0) {
     if (!scored_load<PASSES, FP32>(by, scores, stride, cu_blocks, block_start, slot_base, cap, blocks_used, seq_row0, s, hk, h,
                                    sh_idx, blk0_raw, blk0, fv, iv, bv, blk1, n, row0))
       n = 0;
   } else {
-    shift = blk0 & 3;                                 // same for scores rows (stride % 4 == 0)
-    const int v_first = (blk0 - shift) / 4 + tid * kSelVecs;   // thread t owns vectors [v_first, v_first + kSelVecs)
-    const int max_vec_sc = stride / 4 - 1;              // clamp to the buffers, mask by index later
-    const int max_vec_sb = cap / 4;
-    const float4* sc4 = reinterpret_cast<const float4*>(scores + (int64_t)h * stride);
-    const int4* sb4 = reinterpret_cast<const int4*>(slot_base);
-    const int4* bs4 = reinterpret_cast<const int4*>(block_start);
+    shift = blk0 & (kVec - 1);                                 // same for scores rows (stride % 4 == 0)
+    const int v_first = (blk0 - shift) / kVec + tid * kSelVecs;   // thread t owns vectors [v_first, v_first + kSelVecs)
+    const int max_vec_sc = stride / kVec - 1;              // clamp to the buffers, mask by index later
+    const int max_vec_sb = cap / kVec;
+    const VecF* sc4 = reinterpret_cast<const VecF*>(scores + (int64_t)h * stride);
+    const VecI* sb4 = reinterpret_cast<const VecI*>(slot_base);
+    const VecI* bs4 = reinterpret_cast<const VecI*>(block_start);
 #pragma unroll
     for (int u = 0; u < kSelVecs; ++u) {
       const int v = v_first + u;
@@ -775,15 +784,24 @@ hipError_t launch_select(const dsk_select_args& a, float* scores, int stride, hi
   const int Hsel = (a.flags & DSK_SELECT_SHARED_BY_KV_GROUP) ? a.Hkv : a.Hq;
   const dim3 grid((unsigned)Hsel, (unsigned)a.B);
   // a sequence has at most `bound` blocks: the smallest register tile that holds them all does
-  // the least per-thread work (larger sequences than the tile still work, through select_big)
+  // the least per-thread work (larger sequences than the tile still work, through select_big).  Decode step of 32 / 8 heads,
+  // one sequence of 4369 blocks, 8 / 6 blocks a thread 24.4 / 24.0 us, eight steps of a batch on either side of 4096 471 / 467
+  // (5 a thread, each entry a load of its own: 24.6); select_big / 12 or 16 a thread: 9362 blocks 47.2 / 31.4, 13107 57.6 /
+  // 36.4, 16375 83 / 37.7.  The capacity of the tables alone says too little for those: with chunks of C +- C/2 tokens it is
+  // twice the blocks there are, and a sequence of less than 8 K blocks is better off with 8 a thread.
   const int bound = select_bound(a);
+  const bool known = a.max_blocks_per_seq > 0 || (a.B == 1 && a.max_blocks_used > 0);
 #define DSK_SEL_ARGS                                                                                          \
   scores, stride, a.cu_blocks, a.block_start, a.slot_base, a.max_blocks_total, Hsel, a.b, k, a.budget_per_seq, a.blocks_used, \
       a.seq_row0, a.sel_slot, a.sel_start, a.sel_len, a.sel_count, ScoredBy{}
   if (sel_fits_tile(bound, 4, 256)) select_kernel<4, 256><<<grid, dim3(256), 0, st>>>(DSK_SEL_ARGS);
   else if (sel_fits_tile(bound, 4, 512)) select_kernel<4, 512><<<grid, dim3(512), 0, st>>>(DSK_SEL_ARGS);
   else if (sel_fits_tile(bound, 4, 1024)) select_kernel<4, 1024><<<grid, dim3(1024), 0, st>>>(DSK_SEL_ARGS);
-  else select_kernel<kSelMaxPerThread, kSelMaxThreads><<<grid, dim3(kSelMaxThreads), 0, st>>>(DSK_SEL_ARGS);
+  else if (sel_fits_tile(bound, 6, 1024)) select_kernel<6, 1024><<<grid, dim3(1024), 0, st>>>(DSK_SEL_ARGS);
+  else if (!known || sel_fits_tile(bound, 8, 1024) || !sel_fits_tile(bound, kSelMaxPerThread, 1024))
+    select_kernel<8, 1024><<<grid, dim3(1024), 0, st>>>(DSK_SEL_ARGS);
+  else if (sel_fits_tile(bound, 12, 1024)) select_kernel<12, 1024><<<grid, dim3(1024), 0, st>>>(DSK_SEL_ARGS);
+  else select_kernel<kSelMaxPerThread, 1024><<<grid, dim3(1024), 0, st>>>(DSK_SEL_ARGS);
 #undef DSK_SEL_ARGS
   return hipGetLastError();
 }
