@@ -105,6 +105,39 @@ def test_long_lists(B, Hq, Hkv, k, b, is_long, on_shared_kernel, layout):
         assert torch.equal(att.out, again.out) and torch.equal(att.lse, again.lse)
 
 
+@pytest.mark.parametrize("b", [33, 48, 64, 65, 100, 128])
+@pytest.mark.parametrize("B,Hq,Hkv,k,shared", [(2, 6, 2, 21, False), (1, 28, 4, 8, False), (3, 8, 8, 9, False), (2, 8, 2, 17, True)])
+def test_slots_of_more_than_32_rows(b, B, Hq, Hkv, k, shared):
+    """Slots around the 16 and 32 rows that are on their way at first, and of the rows behind them; spans outside the cache."""
+    import paper_2602_03184_amd as dsk
+    rng = np.random.default_rng([b, B, Hq, k])
+    g = torch.Generator(device="cuda")
+    g.manual_seed(b)
+    L, H = 1500, Hkv if shared else Hq
+    K, V = (torch.randn(Hkv, L, 128, generator=g, device="cuda").bfloat16() for _ in range(2))
+    q = torch.randn(B, Hq, 128, generator=g, device="cuda").bfloat16()
+    counts = rng.integers(1, k + 1, size=(B, H))
+    counts[0, 0], counts[0, -1] = k, 0
+    start, length = _lists(rng, B, H, k, b, L, counts)
+    edges = np.array([1, 15, 16, 17, 31, 32, 33, 48, 49, 63, 64, b - 1, b])
+    length[:, :, ::2] = rng.choice(edges[edges <= b], size=length[:, :, ::2].shape)
+    start[:, :, 1::4] = L - length[:, :, 1::4]                             # ends with the cache
+    bad = (start.copy(), length.copy())
+    if k > 8:
+        bad[0][:, :, 3], bad[0][:, :, 6] = L - length[:, :, 3] + 1, -1     # leave the cache: skipped
+        bad[1][:, :, 7] = 0
+        keep = np.array([j for j in range(k) if j not in (3, 6, 7)])
+    else:
+        keep = np.arange(k)
+    n_kept = np.array([[int((keep < counts[s, h]).sum()) for h in range(H)] for s in range(B)])
+    args = dsk.make_attn_args(q, K, V, dev_i32(bad[0]), dev_i32(bad[1]), dev_i32(counts), b,
+                              flags=dsk.DSK_ATTN_SHARED_SELECTION if shared else 0)
+    dsk.dsk_sparse_decode_attn(args.args)
+    want, want_lse = _want(q, K, V, start[:, :, keep], length[:, :, keep], n_kept, Hq // H)
+    assert rel_err(args.out.cpu().numpy(), want) <= 1e-5                   # sums of 32 bits
+    np.testing.assert_allclose(args.lse.cpu().numpy(), want_lse, rtol=0, atol=1e-5)   # -inf where nothing is selected
+
+
 def test_long_lists_skip_spans_outside_the_cache():
     """Slots whose span leaves the cache, or is empty, add nothing; a caller that merges itself keeps its short chunks."""
     import paper_2602_03184_amd as dsk
