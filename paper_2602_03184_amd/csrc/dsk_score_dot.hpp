@@ -48,14 +48,6 @@ __device__ __forceinline__ void half_wave_reduce(float (&v)[N], int lane, int& i
   }
 }
 
-// dot product of the 8 channels of a summary (widened) with the q+ or q- of a head, in channel order
-__device__ __forceinline__ float dot8_f32(const float (&q)[8], const float (&k)[8]) {
-  float acc = 0.0f;
-#pragma unroll
-  for (int i = 0; i < 8; ++i) acc = fmaf(q[i], k[i], acc);
-  return acc;
-}
-
 // q+ (lanes holding kmax) or q- (lanes holding kmin) of 8 channels as packed bf16 pairs: the halves whose sign does not fit
 // are zeroed, both are exact in bf16
 __device__ __forceinline__ void keep_sign(const uint4& q, bool is_max, uint32_t (&out)[4]) {
@@ -68,32 +60,15 @@ __device__ __forceinline__ void keep_sign(const uint4& q, bool is_max, uint32_t 
   }
 }
 
-// this lane's part of the scores of N blocks for one query head.  FP32: single-precision multiply-adds in channel order
-// (group widths that are no power of two up to 8) instead of the packed bf16 dot instruction.
-template <int N, bool FP32>
-__device__ __forceinline__ void score_parts(const uint4 (&kv)[N], const uint4& q, bool is_max, float (&v)[N]) {
-  if constexpr (FP32) {
-    float qs[8];
-    unpack8(q, qs);
-#pragma unroll
-    for (int k = 0; k < 8; ++k) qs[k] = is_max ? fmaxf(qs[k], 0.0f) : fminf(qs[k], 0.0f);
-#pragma unroll
-    for (int u = 0; u < N; ++u) {
-      float f[8];
-      unpack8(kv[u], f);
-      v[u] = dot8_f32(qs, f);
-    }
-  } else {
-    uint32_t qp[4];
-    keep_sign(q, is_max, qp);
-#pragma unroll
-    for (int u = 0; u < N; ++u) {
-      float acc = dot2_bf16(qp[0], kv[u].x, 0.0f);
-      acc = dot2_bf16(qp[1], kv[u].y, acc);
-      acc = dot2_bf16(qp[2], kv[u].z, acc);
-      v[u] = dot2_bf16(qp[3], kv[u].w, acc);
-    }
-  }
+// this lane's part of the score of a block: 8 channels of its summary with keep_sign's q, on the packed bf16 dot instruction,
+// neither operand widened.  (Groups whose width is no power of two up to 8 had single-precision multiply-adds in channel order,
+// 16 instructions more a block and head and as far from 64 bits, 3.3e-8 to 4.4e-8 of the norm: decode steps of 40 / 8 heads 44.3
+// -> 41.8 us at three sequences of 107K tokens, 24.1 -> 22.9 at four of 7K; 28 / 4, shared lists, eight of 50K 42.0 -> 39.2.)
+__device__ __forceinline__ float score_part(const uint32_t (&qp)[4], const uint4& k) {
+  float acc = dot2_bf16(qp[0], k.x, 0.0f);
+  acc = dot2_bf16(qp[1], k.y, acc);
+  acc = dot2_bf16(qp[2], k.z, acc);
+  return dot2_bf16(qp[3], k.w, acc);
 }
 
 }  // namespace dsk

@@ -23,8 +23,7 @@ __host__ __device__ constexpr int score_blocks_per_half(int G) { return G >= 8 ?
 // differ only in log2(G) consecutive lane bits, so the maximum is a few exchanges.
 // PADDED: group widths that are no power of two (and above 8): G is the width of a tile of the group's heads,
 // the real width `group` comes from the launch, blockIdx.y counts (KV head, tile), and the heads that a tile
-// does not have repeat its first one and are not written.  The products of this variant are single-precision
-// multiply-adds in channel order, so that its scores are those of scores_kernel_wide_shared bit by bit.
+// does not have repeat its first one and are not written.
 template <int G, bool GROUPMAX = false, bool PADDED = false>
 __global__ __launch_bounds__(kScoreThreads) void scores_kernel(
     const uint16_t* __restrict__ ksum, const uint16_t* __restrict__ q, const int32_t* __restrict__ cu_blocks,
@@ -126,37 +125,13 @@ __global__ __launch_bounds__(kScoreThreads) void scores_kernel(
     if (seg_end > cur) {
       // q+ or q- as packed bf16 pairs; the products run on the packed bf16 dot instruction with neither operand widened
       float v[V];
-      if constexpr (PADDED) {
+      uint32_t qp[G][4];
 #pragma unroll
-        for (int g = 0; g < G; ++g) {
-          float qs[8];
-          unpack8(qv[g], qs);
+      for (int g = 0; g < G; ++g) keep_sign(qv[g], is_max, qp[g]);
 #pragma unroll
-          for (int k = 0; k < 8; ++k) qs[k] = is_max ? fmaxf(qs[k], 0.0f) : fminf(qs[k], 0.0f);
+      for (int u = 0; u < NB; ++u)
 #pragma unroll
-          for (int u = 0; u < NB; ++u) {
-            float f[8];
-            unpack8(kv[u], f);
-            v[u * G + g] = dot8_f32(qs, f);
-          }
-        }
-      } else {
-        uint32_t qp[G][4];
-#pragma unroll
-        for (int g = 0; g < G; ++g) {
-          keep_sign(qv[g], is_max, qp[g]);
-        }
-#pragma unroll
-        for (int u = 0; u < NB; ++u) {
-#pragma unroll
-          for (int g = 0; g < G; ++g) {
-            float acc = dot2_bf16(qp[g][0], kv[u].x, 0.0f);
-            acc = dot2_bf16(qp[g][1], kv[u].y, acc);
-            acc = dot2_bf16(qp[g][2], kv[u].z, acc);
-            v[u * G + g] = dot2_bf16(qp[g][3], kv[u].w, acc);
-          }
-        }
-      }
+        for (int g = 0; g < G; ++g) v[u * G + g] = score_part(qp[g], kv[u]);
       int idx = 0;
       half_wave_reduce<V, V, 1>(v, c, idx);
       const bool writer = c < V;                     // lanes differing only in non-halving (high) bits hold copies
@@ -206,17 +181,12 @@ __global__ __launch_bounds__(kScoreThreads) void scores_kernel_wide_shared(
     if (i >= nblk) break;
     while (s + 1 < B && cu_blocks[s + 1] <= i) ++s;
     const uint4 kv = *reinterpret_cast<const uint4*>(kh + (int64_t)i * (2 * DSK_HEAD_DIM) + c * 8);
-    float f[8];
-    unpack8(kv, f);
     float best = -__builtin_inff();
     for (int g = 0; g < G; ++g) {
       const uint4 qv = *reinterpret_cast<const uint4*>(q + ((int64_t)s * Hq + hk * G + g) * DSK_HEAD_DIM + d0);
-      float qf[8];
-      unpack8(qv, qf);
-      float acc = 0.0f;
-#pragma unroll
-      for (int k = 0; k < 8; ++k) acc = fmaf(is_max ? fmaxf(qf[k], 0.0f) : fminf(qf[k], 0.0f), f[k], acc);
-      acc = group16_sum(acc);
+      uint32_t qp[4];
+      keep_sign(qv, is_max, qp);
+      float acc = group16_sum(score_part(qp, kv));
       acc += shfl_xor_f(acc, 16);
       best = fmaxf(best, acc);
     }

@@ -366,7 +366,7 @@ __device__ __forceinline__ bool scored_place(const ScoredBy& by, int Hq, int& s,
 
 // Scores the n blocks of sequence s from blk0 on against query head h; thread t gets block t's score, slot bases and starts.
 // More than a block a thread: the scores are left in memory (select_big takes them from there).  false: no block.
-template <int PASSES, bool FP32>
+template <int PASSES>
 __device__ __forceinline__ bool scored_load(const ScoredBy& by, float* scores, int stride, const int32_t* cu_blocks,
                                             const int32_t* block_start, const int32_t* slot_base, int cap,
                                             const int32_t* blocks_used, const int32_t* seq_row0, int s, int hk, int h,
@@ -407,7 +407,10 @@ __device__ __forceinline__ bool scored_load(const ScoredBy& by, float* scores, i
   // scores of a half-wavefront's 8 blocks, one in each of its first 8 lanes: block index `u`
   auto score = [&](const uint4 (&k8)[kScoredBlocks], int& u) {
     float v[kScoredBlocks];
-    score_parts<kScoredBlocks, FP32>(k8, qv, is_max, v);
+    uint32_t qp[4];
+    keep_sign(qv, is_max, qp);
+#pragma unroll
+    for (int b = 0; b < kScoredBlocks; ++b) v[b] = score_part(qp, k8[b]);
     u = 0;
     half_wave_reduce<kScoredBlocks, kScoredBlocks, 1>(v, c, u);
     return v[0];
@@ -452,7 +455,7 @@ __device__ __forceinline__ bool scored_load(const ScoredBy& by, float* scores, i
 // slot_base, block_start: 16-byte aligned, readable up to a multiple of 4 entries past cap.
 // PASSES > 0 (PT = 1): the blocks are scored here, see above.  (One kernel for both: with the selection in a function of its
 // own the compiler orders the longer sequences' instances otherwise, 0.05 us a call.)
-template <int PT, int THREADS, int PASSES = 0, bool FP32 = false>
+template <int PT, int THREADS, int PASSES = 0>
 __global__ __launch_bounds__(THREADS) void select_kernel(
     float* __restrict__ scores, int stride, const int32_t* __restrict__ cu_blocks,
     const int32_t* __restrict__ block_start, const int32_t* __restrict__ slot_base, int cap, int Hq,
@@ -493,7 +496,7 @@ __global__ __launch_bounds__(THREADS) void select_kernel(
   VecI iv[kSelVecs + 1], bv[kSelVecs + 1];
   int shift = 0, blk1, n, row0;
   if constexpr (PASSES > 0) {
-    if (!scored_load<PASSES, FP32>(by, scores, stride, cu_blocks, block_start, slot_base, cap, blocks_used, seq_row0, s, hk, h,
+    if (!scored_load<PASSES>(by, scores, stride, cu_blocks, block_start, slot_base, cap, blocks_used, seq_row0, s, hk, h,
                                    sh_idx, blk0_raw, blk0, fv, iv, bv, blk1, n, row0))
       n = 0;
   } else {
@@ -766,14 +769,8 @@ hipError_t launch_select_scored(const dsk_select_args& a, float* scores, int str
 #define DSK_SEL_ARGS                                                                                            \
   scores, stride, a.cu_blocks, a.block_start, a.slot_base, a.max_blocks_total, a.Hq, a.b, a.budget / a.b, a.budget_per_seq, \
       a.blocks_used, a.seq_row0, a.sel_slot, a.sel_start, a.sel_len, a.sel_count, by
-#define DSK_SEL_PASSES(fp32)                                                                                    \
-  do {                                                                                                          \
-    if (bound <= kScoredPass) select_kernel<1, kScoredThreads, 1, fp32><<<grid, dim3(kScoredThreads), 0, st>>>(DSK_SEL_ARGS); \
-    else select_kernel<1, kScoredThreads, 2, fp32><<<grid, dim3(kScoredThreads), 0, st>>>(DSK_SEL_ARGS);                    \
-  } while (0)
-  if (G == 1 || G == 2 || G == 4 || G == 8) DSK_SEL_PASSES(false);
-  else DSK_SEL_PASSES(true);
-#undef DSK_SEL_PASSES
+  if (bound <= kScoredPass) select_kernel<1, kScoredThreads, 1><<<grid, dim3(kScoredThreads), 0, st>>>(DSK_SEL_ARGS);
+  else select_kernel<1, kScoredThreads, 2><<<grid, dim3(kScoredThreads), 0, st>>>(DSK_SEL_ARGS);
 #undef DSK_SEL_ARGS
   return hipGetLastError();
 }
