@@ -50,15 +50,17 @@ __device__ __forceinline__ void store_attn_out(float* __restrict__ out, uint16_t
 // into the state.  Rows >= nvalid are padding (their loads were redirected to a real row).
 // OWN_SUMS: the rows are summed by themselves before they join the state (with the rescaling in one operation): as many
 // instructions, and no longer chain of sums where a state takes many folds.
-template <int NS, bool OWN_SUMS = false>
+// SLOTS = 2: the rows are those of two slots, half of them each, of which nvalid and nvalid2 (>= 0) are real.
+template <int NS, bool OWN_SUMS = false, int SLOTS = 1>
 __device__ __forceinline__ void fold_loaded(WaveState& st, const QRow& qf, const uint4 (&kv)[NS],
-                                            const uint4 (&vv)[NS], int nvalid, int g, float scale_log2) {
+                                            const uint4 (&vv)[NS], int nvalid, int g, float scale_log2, int nvalid2 = 0) {
+  constexpr int kPer = NS / SLOTS;
   float z[NS];
   float mloc = -__builtin_inff();
 #pragma unroll
   for (int u = 0; u < NS; ++u) {
     const float d = group16_sum(dot8_bf16(qf, kv[u])) * scale_log2;
-    z[u] = (4 * u + g < nvalid) ? d : -__builtin_inff();
+    z[u] = (4 * (u % kPer) + g < (u < kPer ? nvalid : nvalid2)) ? d : -__builtin_inff();
     mloc = fmaxf(mloc, z[u]);
   }
   mloc = fmaxf(fmaxf(rows4_f(mloc, 0), rows4_f(mloc, 1)), fmaxf(rows4_f(mloc, 2), rows4_f(mloc, 3)));

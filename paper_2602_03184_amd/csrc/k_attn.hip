@@ -318,7 +318,10 @@ constexpr int kLongMinSlots = 32;       // of a workgroup; where a list of less 
 constexpr int kLongMinSlotsShared = 256; // of a list that a group shares: its heads meet in L2 anyway (two sequences of 30K
                                         // tokens, 28 / 4 heads, 128 slots 20.3 -> 20.8 us; one, 16 / 2, 512 slots 32.3 -> 18.9)
 constexpr int kSharedChunkSlots = 16;   // of a workgroup of attn_shared_kernel
-template <int NS>
+// SLOTS = 2 (slots of up to 8 rows): two slots in the 16 rows that a wavefront has in flight.  Decode steps with such slots:
+// 28 / 4 heads, 130K tokens, 357 slots 23.5 -> 21.9 us; 16 / 2, eight sequences of 15K, 176 slots 27.5 -> 24.3; 32 / 32, three of
+// 31K, 636 slots 63.7 -> 63.1 (at the rate of the memory).
+template <int NS, int SLOTS = 1>
 __global__ __launch_bounds__(kLongWaves * DSK_WAVE) void attn_long_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ K, const uint16_t* __restrict__ V,
     int64_t kst, int64_t ksh, int64_t vst, int64_t vsh, int Hq, int G, int n_groups, int k, int b, int total_tokens,
@@ -372,31 +375,39 @@ __global__ __launch_bounds__(kLongWaves * DSK_WAVE) void attn_long_kernel(
   for (int first = 0; first < n; first += DSK_WAVE) {
     if (first > 0) fetch_spans(first);
     len = len < b ? len : b;
-    len = len < 4 * NS ? len : 4 * NS;
+    len = len < 4 * NS / SLOTS ? len : 4 * NS / SLOTS;
     // slots that exist and do not leave K/V
     unsigned long long todo = __ballot(first + lane < n && start >= 0 && len > 0 && start <= total_tokens - len);
-    for (; todo != 0; todo &= todo - 1) {
-      const int r = __builtin_ctzll(todo);
-      const int nv = __builtin_amdgcn_readlane(len, r);
-      const int64_t row0 = __builtin_amdgcn_readlane(start, r);
-      const char* kb = reinterpret_cast<const char*>(Kh + row0 * kst);             // uniform
-      const char* vb = reinterpret_cast<const char*>(Vh + row0 * vst);
+    for (; todo != 0; todo &= todo - 1) {      // of 0: 0
+      int nv[SLOTS];
+      const char *kb[SLOTS], *vb[SLOTS];                                           // uniform
+#pragma unroll
+      for (int i = 0; i < SLOTS; ++i) {
+        const bool have = i == 0 || todo != 0;
+        const int r = __builtin_ctzll(have ? todo : 1ull);
+        nv[i] = have ? __builtin_amdgcn_readlane(len, r) : 0;
+        const int64_t row0 = __builtin_amdgcn_readlane(start, r);
+        kb[i] = have ? reinterpret_cast<const char*>(Kh + row0 * kst) : kb[0];     // none left: the first one's rows again
+        vb[i] = have ? reinterpret_cast<const char*>(Vh + row0 * vst) : vb[0];
+        if (i + 1 < SLOTS) todo &= todo - 1;
+      }
+      constexpr int kPer = NS / SLOTS;
+      auto row_of = [&](int u) {
+        const int row = 4 * (u % kPer) + g, most = (u >= kPer && nv[SLOTS - 1] > 0 ? nv[SLOTS - 1] : nv[0]) - 1;
+        return (unsigned)(row < most ? row : most);
+      };
       uint4 kd[NS], vd[NS];
 #pragma unroll
-      for (int u = 0; u < NS; ++u) {
-        const int row = 4 * u + g < nv ? 4 * u + g : nv - 1;
-        kd[u] = *reinterpret_cast<const uint4*>(kb + (__umul24((unsigned)row, kst8) + (unsigned)c) * 16u);
-      }
+      for (int u = 0; u < NS; ++u)
+        kd[u] = *reinterpret_cast<const uint4*>(kb[u / kPer] + (__umul24(row_of(u), kst8) + (unsigned)c) * 16u);
 #pragma unroll
-      for (int u = 0; u < NS; ++u) {
-        const int row = 4 * u + g < nv ? 4 * u + g : nv - 1;
-        vd[u] = *reinterpret_cast<const uint4*>(vb + (__umul24((unsigned)row, vst8) + (unsigned)c) * 16u);
-      }
+      for (int u = 0; u < NS; ++u)
+        vd[u] = *reinterpret_cast<const uint4*>(vb[u / kPer] + (__umul24(row_of(u), vst8) + (unsigned)c) * 16u);
 #pragma unroll
       for (int u = 0; u < NS; ++u) pin_loaded(kd[u]);
 #pragma unroll
       for (int u = 0; u < NS; ++u) pin_loaded(vd[u]);
-      fold_loaded<NS, true>(st, qf, kd, vd, nv, g, scale_log2);
+      fold_loaded<NS, true, SLOTS>(st, qf, kd, vd, nv[0], g, scale_log2, nv[SLOTS - 1]);
     }
   }
 
@@ -497,7 +508,9 @@ __device__ __forceinline__ void add_row(float (&acc)[GT][8], float p, const floa
 // of those it does not have repeat its first one).  WIDE: token strides above kMaxTokenStride, row offsets in 64 bits (the
 // chunks, which a caller that merges by itself asks for, do not depend on the strides).
 // grid: chunk, fastest, then head tile, KV head, sequence
-template <int NT, int GT, bool WIDE>
+// SLOTS = 2 (NT = 1, slots of up to 8 rows): a tile holds the rows of two slots: 28 / 4 heads, eight sequences of 50K tokens, 311
+// slots 39.2 -> 35.8 us.
+template <int NT, int GT, bool WIDE, int SLOTS = 1>
 __global__ __launch_bounds__(kLongWaves * DSK_WAVE) void attn_shared_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ K, const uint16_t* __restrict__ V,
     int64_t kst, int64_t ksh, int64_t vst, int64_t vsh, int Hq, int G, int k, int b, int total_tokens,
@@ -506,6 +519,8 @@ __global__ __launch_bounds__(kLongWaves * DSK_WAVE) void attn_shared_kernel(
     float2* __restrict__ part_ml, float* __restrict__ part_acc, float* __restrict__ out,
     uint16_t* __restrict__ out_bf16, float* __restrict__ lse) {
   static_assert(GT <= 8 && 16 % GT == 0, "the heads repeat over the 16 columns of a product");
+  static_assert(SLOTS == 1 || (SLOTS == 2 && NT == 1), "two slots in one tile");
+  constexpr int kSlotRows = 16 * NT / SLOTS;
   __shared__ float sm_m[kLongWaves][GT];
   __shared__ float sm_l[kLongWaves][GT];
   __shared__ float sm_acc[kLongWaves][GT][DSK_HEAD_DIM];
@@ -571,30 +586,42 @@ __global__ __launch_bounds__(kLongWaves * DSK_WAVE) void attn_shared_kernel(
   for (int first = 0; first < n; first += DSK_WAVE) {
     if (first > 0) fetch_spans(first);
     len = len < b ? len : b;
-    len = len < 16 * NT ? len : 16 * NT;
+    len = len < kSlotRows ? len : kSlotRows;
     // slots that exist and do not leave K/V
     unsigned long long todo = __ballot(first + lane < n && start >= 0 && len > 0 && start <= total_tokens - len);
-    for (; todo != 0; todo &= todo - 1) {
-      const int r = __builtin_ctzll(todo);
-      const int nv = __builtin_amdgcn_readlane(len, r);
-      const int64_t row0 = __builtin_amdgcn_readlane(start, r);
-      const char* kb = reinterpret_cast<const char*>(Kh + row0 * kst);             // uniform
-      const char* vb = reinterpret_cast<const char*>(Vh + row0 * vst);
-      // K as operand: row c of the tile, channels 32 i + 8 g .. + 8; V as rows 4 u + g, channels 8 c .. + 8.  Rows behind
-      // the slot's last one repeat it.
+    for (; todo != 0; todo &= todo - 1) {      // of 0: 0
+      int nv[SLOTS];
+      const char *kb[SLOTS], *vb[SLOTS];                                           // uniform
+#pragma unroll
+      for (int i = 0; i < SLOTS; ++i) {
+        const bool have = i == 0 || todo != 0;
+        const int r = __builtin_ctzll(have ? todo : 1ull);
+        nv[i] = have ? __builtin_amdgcn_readlane(len, r) : 0;
+        const int64_t row0 = __builtin_amdgcn_readlane(start, r);
+        kb[i] = have ? reinterpret_cast<const char*>(Kh + row0 * kst) : kb[0];     // none left: the first one's rows again
+        vb[i] = have ? reinterpret_cast<const char*>(Vh + row0 * vst) : vb[0];
+        if (i + 1 < SLOTS) todo &= todo - 1;
+      }
+      // row of its slot for row x of the tiles, one of the second slot where x is behind the first; those behind a slot's last
+      // row repeat it
+      auto second = [&](int x) { return SLOTS == 2 && x >= kSlotRows; };
+      auto slot_row = [&](int x) {
+        const int row = SLOTS == 2 ? x & (kSlotRows - 1) : x;
+        const int most = (second(x) && nv[SLOTS - 1] > 0 ? nv[SLOTS - 1] : nv[0]) - 1;
+        return row < most ? row : most;
+      };
+      auto real_row = [&](int x) { return (SLOTS == 2 ? x & (kSlotRows - 1) : x) < (second(x) ? nv[SLOTS - 1] : nv[0]); };
+      // K as operand: row c of the tile, channels 32 i + 8 g .. + 8; V as rows 4 u + g, channels 8 c .. + 8
       u32x4_t kd[NT][4], vd[4 * NT];
 #pragma unroll
       for (int t = 0; t < NT; ++t) {
-        const int row = 16 * t + c < nv ? 16 * t + c : nv - 1;
-        const char* from = at_row(kb, row, kst, kst8, g);
+        const char* from = at_row(second(c) ? kb[SLOTS - 1] : kb[0], slot_row(16 * t + c), kst, kst8, g);
 #pragma unroll
         for (int i = 0; i < 4; ++i) kd[t][i] = *reinterpret_cast<const u32x4_t*>(from + 64 * i);
       }
 #pragma unroll
-      for (int u = 0; u < 4 * NT; ++u) {
-        const int row = 4 * u + g < nv ? 4 * u + g : nv - 1;
-        vd[u] = *reinterpret_cast<const u32x4_t*>(at_row(vb, row, vst, vst8, c));
-      }
+      for (int u = 0; u < 4 * NT; ++u)
+        vd[u] = *reinterpret_cast<const u32x4_t*>(at_row(SLOTS == 2 && u >= 2 ? vb[SLOTS - 1] : vb[0], slot_row(4 * u + g), vst, vst8, c));
 #pragma unroll
       for (int t = 0; t < NT; ++t)
 #pragma unroll
@@ -616,7 +643,7 @@ __global__ __launch_bounds__(kLongWaves * DSK_WAVE) void attn_shared_kernel(
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           const float sum = (d[0][i] + d[1][i]) + (d[2][i] + d[3][i]);
-          z[t][i] = 16 * t + 4 * g + i < nv ? sum * scale_log2 : -__builtin_inff();
+          z[t][i] = real_row(16 * t + 4 * g + i) ? sum * scale_log2 : -__builtin_inff();
           top = fmaxf(top, z[t][i]);
         }
       }
@@ -891,7 +918,8 @@ hipError_t launch_attn(const dsk_attn_args& a, const AttnWs& ws, hipStream_t st)
   DSK_GATHER_ARGS(), scale * kLog2e, ws.nchunks, ws.slots_per_wg, leave, part_ml, part_acc, a.out,                       \
       static_cast<uint16_t*>(a.out_bf16), a.lse
     if (ws.kernel == AttnKernel::kLong) {
-      if (a.b <= 16) attn_long_kernel<4><<<grid, block, 0, st>>>(DSK_GATHER_ARGS(n_groups,), DSK_LONG_ARGS);
+      if (a.b <= 8) attn_long_kernel<4, 2><<<grid, block, 0, st>>>(DSK_GATHER_ARGS(n_groups,), DSK_LONG_ARGS);
+      else if (a.b <= 16) attn_long_kernel<4><<<grid, block, 0, st>>>(DSK_GATHER_ARGS(n_groups,), DSK_LONG_ARGS);
       else attn_long_kernel<8><<<grid, block, 0, st>>>(DSK_GATHER_ARGS(n_groups,), DSK_LONG_ARGS);
     } else {
       const int G = a.Hq / a.Hkv, tile = attn_shared_tile(G);
@@ -899,7 +927,8 @@ hipError_t launch_attn(const dsk_attn_args& a, const AttnWs& ws, hipStream_t st)
       const bool wide = a.k_stride_tok > kMaxTokenStride || a.v_stride_tok > kMaxTokenStride;
 #define DSK_SHARED_LAUNCH(NT, GT)                                                                                 \
   do {                                                                                                            \
-    if (wide) attn_shared_kernel<NT, GT, true><<<sgrid, block, 0, st>>>(DSK_SHARED_ARGS);                         \
+    if (NT == 1 && !wide && a.b <= 8) attn_shared_kernel<1, GT, false, 2><<<sgrid, block, 0, st>>>(DSK_SHARED_ARGS); \
+    else if (wide) attn_shared_kernel<NT, GT, true><<<sgrid, block, 0, st>>>(DSK_SHARED_ARGS);                         \
     else attn_shared_kernel<NT, GT, false><<<sgrid, block, 0, st>>>(DSK_SHARED_ARGS);                             \
   } while (0)
       switch (tile * 64 + (a.b <= 16 ? 1 : 2)) {
@@ -928,7 +957,11 @@ hipError_t launch_attn(const dsk_attn_args& a, const AttnWs& ws, hipStream_t st)
   // Measured against 4 wavefronts x 2 or 4 slots, 8 x 1 or 4, 16 x 1 or 2 on all configurations:
   // the gather takes 7.3 instead of 8.6 us at 128K / b = 32, and 4.6 instead of 5.6 us at
   // 32K / b = 16 (half as many workgroups to dispatch and half as many partials to merge).
-  if (a.b <= 16 && ws.slots_per_wg == 8) attn_kernel<4, 2, 4, false><<<grid, dim3(256), 0, st>>>(DSK_ATTN_ARGS);
+  // Slots of up to 8 rows: half of the loads (32 / 8 heads at 5.6K tokens, 54 slots 13.4 -> 12.65 us, at 11K, eight sequences
+  // 21.1 -> 20.4; workgroups of 4 wavefronts x 4 slots 12.9 and 20.8).
+  if (a.b <= 8 && ws.slots_per_wg == 8) attn_kernel<2, 2, 4, false><<<grid, dim3(256), 0, st>>>(DSK_ATTN_ARGS);
+  else if (a.b <= 8) attn_kernel<2, 2, 8, false><<<grid, dim3(512), 0, st>>>(DSK_ATTN_ARGS);
+  else if (a.b <= 16 && ws.slots_per_wg == 8) attn_kernel<4, 2, 4, false><<<grid, dim3(256), 0, st>>>(DSK_ATTN_ARGS);
   else if (a.b <= 16) attn_kernel<4, 2, 8, false><<<grid, dim3(512), 0, st>>>(DSK_ATTN_ARGS);
   else if (a.b <= 32) attn_kernel<8, 2, 8, true><<<grid, dim3(512), 0, st>>>(DSK_ATTN_ARGS);
   else attn_kernel<8, 1, 8, true, true><<<grid, dim3(512), 0, st>>>(DSK_ATTN_ARGS);

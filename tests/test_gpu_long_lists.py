@@ -105,10 +105,7 @@ def test_long_lists(B, Hq, Hkv, k, b, is_long, on_shared_kernel, layout):
         assert torch.equal(att.out, again.out) and torch.equal(att.lse, again.lse)
 
 
-@pytest.mark.parametrize("b", [33, 48, 64, 65, 100, 128])
-@pytest.mark.parametrize("B,Hq,Hkv,k,shared", [(2, 6, 2, 21, False), (1, 28, 4, 8, False), (3, 8, 8, 9, False), (2, 8, 2, 17, True)])
-def test_slots_of_more_than_32_rows(b, B, Hq, Hkv, k, shared):
-    """Slots around the 16 and 32 rows that are on their way at first, and of the rows behind them; spans outside the cache."""
+def _spans_in_and_outside_the_cache(b, B, Hq, Hkv, k, shared):
     import paper_2602_03184_amd as dsk
     rng = np.random.default_rng([b, B, Hq, k])
     g = torch.Generator(device="cuda")
@@ -119,7 +116,7 @@ def test_slots_of_more_than_32_rows(b, B, Hq, Hkv, k, shared):
     counts = rng.integers(1, k + 1, size=(B, H))
     counts[0, 0], counts[0, -1] = k, 0
     start, length = _lists(rng, B, H, k, b, L, counts)
-    edges = np.array([1, 15, 16, 17, 31, 32, 33, 48, 49, 63, 64, b - 1, b])
+    edges = np.array([1, 2, 4, 5, 7, 8, 15, 16, 17, 31, 32, 33, 48, 49, 63, 64, b - 1, b])
     length[:, :, ::2] = rng.choice(edges[edges <= b], size=length[:, :, ::2].shape)
     start[:, :, 1::4] = L - length[:, :, 1::4]                             # ends with the cache
     bad = (start.copy(), length.copy())
@@ -136,6 +133,22 @@ def test_slots_of_more_than_32_rows(b, B, Hq, Hkv, k, shared):
     want, want_lse = _want(q, K, V, start[:, :, keep], length[:, :, keep], n_kept, Hq // H)
     assert rel_err(args.out.cpu().numpy(), want) <= 1e-5                   # sums of 32 bits
     np.testing.assert_allclose(args.lse.cpu().numpy(), want_lse, rtol=0, atol=1e-5)   # -inf where nothing is selected
+
+
+@pytest.mark.parametrize("b", [33, 48, 64, 65, 100, 128])
+@pytest.mark.parametrize("B,Hq,Hkv,k,shared", [(2, 6, 2, 21, False), (1, 28, 4, 8, False), (3, 8, 8, 9, False), (2, 8, 2, 17, True)])
+def test_slots_of_more_than_32_rows(b, B, Hq, Hkv, k, shared):
+    """Slots around the 16 and 32 rows that are on their way at first, and of the rows behind them."""
+    _spans_in_and_outside_the_cache(b, B, Hq, Hkv, k, shared)
+
+
+@pytest.mark.parametrize("b", [1, 5, 8])
+@pytest.mark.parametrize("B,Hq,Hkv,k,shared", [(1, 4, 2, 21, False), (24, 32, 8, 31, False), (8, 32, 8, 67, False), (4, 8, 8, 600, False),
+                                               (8, 32, 8, 99, True), (8, 16, 2, 203, True), (16, 4, 2, 131, True)])
+def test_slots_of_up_to_8_rows(b, B, Hq, Hkv, k, shared):
+    """Two slots in a wavefront's 16 rows: odd numbers of them, skipped ones in between; workgroups of 8 and 16 slots, the kernels
+    for long and for shared lists with 2, 4 and 8 heads a tile."""
+    _spans_in_and_outside_the_cache(b, B, Hq, Hkv, k, shared)
 
 
 def test_long_lists_skip_spans_outside_the_cache():
