@@ -119,7 +119,7 @@ __device__ __forceinline__ void fold_rows(WaveState& st, const QRow& qf, const u
     r = r < nvalid ? r : nvalid - 1;
     vv[u] = *reinterpret_cast<const uint4*>(vbase + (int64_t)r * vst);
   }
-  fold_loaded<NS>(st, qf, kv, vv, nvalid, g, scale_log2);
+  fold_loaded<NS, true>(st, qf, kv, vv, nvalid, g, scale_log2);
 }
 
 // compile-time loop over the slots of a wave: wait for slot S's K and V, fold, recurse
@@ -141,11 +141,15 @@ struct FoldSlots {
 
 // One workgroup of WAVES wavefronts per (chunk of WAVES*SPW slots, head, sequence); writes one partial, or the
 // final result when the head has a single chunk (its partial as well for a caller that merges by itself: `leave`).
-// REST: slots may have more than 4*NS rows; those behind are folded afterwards, 32 at a time.  A wavefront per slot, the first
-// 32 rows of all slots of the workgroup on their way together, half of the loads for slots that have 16 rows: chunks are
-// seldom as long as such a slot.  Decode steps of slots of 64 rows against two slots a wavefront, one after the other: 40 / 40
-// heads at 9.5K tokens 17.7 -> 15.6 us, 32 / 8 heads, three sequences 16.4 -> 15.7, 40 / 8, two of 24K 25.2 -> 24.3, 8 / 8, two
-// of 12K 19.0 -> 17.1; twelve drawn steps 1.04 times as fast (two slots a wavefront with loads ahead: 0.99 and 1.00 times).
+// REST: slots may have more than 4*NS rows; those behind are folded afterwards, 32 at a time.  The first 32 rows of a slot are
+// requested together, half of the loads for slots that have 16 rows: chunks are seldom as long as such a slot.
+// Up to kAttnWavePerSlotTo workgroups latency counts: a wavefront per slot, the rows of all slots of the workgroup on their way
+// at once.  In larger launches the other workgroups hide it, and half as many wavefronts with two slots each leave room for more
+// of them.  Decode steps of slots of 64 rows, a wavefront a slot / two slots a wavefront: 160 workgroups 15.9 / 17.2 us, 384
+// 17.7 / 17.9, 512 29.3 / 29.7 and 23.4 / 23.4, 1024 35.4 / 33.7 and 40.3 / 39.6, 1536 38.7 / 38.4 and 37.0 / 38.2, 1920 43.4 /
+// 40.9, 2560 54.3 / 52.8, 3072 65.3 / 61.5, 4096 84.9 / 82.1, 5120 81.8 / 72.8.  (Two slots a wavefront through loads that the
+// compiler placed: 17.8, 17.6, 28.7 and 23.6, 36.3 and 39.6, 40.9 and 39.3, 43.6, 57.5, 67.3, 87.9, 78.2.)
+constexpr int kAttnWavePerSlotTo = 512;
 template <int NS, int SPW, int WAVES, bool STAGED = false, bool REST = false>
 __global__ __launch_bounds__(WAVES * DSK_WAVE) void attn_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ K, const uint16_t* __restrict__ V,
@@ -247,7 +251,7 @@ __global__ __launch_bounds__(WAVES * DSK_WAVE) void attn_kernel(
         for (int u = 0; u < NS; ++u) pin_loaded(kd[r][u]);
 #pragma unroll
         for (int u = 0; u < NS; ++u) pin_loaded(vd[r][u]);
-        if (nv[r] > 0) fold_loaded<NS>(st, qf, kd[r], vd[r], nv[r], g, scale_log2);
+        if (nv[r] > 0) fold_loaded<NS, REST>(st, qf, kd[r], vd[r], nv[r], g, scale_log2);
       }
     }
     if constexpr (!STAGED) FoldSlots<NS, SPW, 0>::run(st, qf, kd, vd, nv, g, scale_log2);
@@ -964,7 +968,8 @@ hipError_t launch_attn(const dsk_attn_args& a, const AttnWs& ws, hipStream_t st)
   else if (a.b <= 16 && ws.slots_per_wg == 8) attn_kernel<4, 2, 4, false><<<grid, dim3(256), 0, st>>>(DSK_ATTN_ARGS);
   else if (a.b <= 16) attn_kernel<4, 2, 8, false><<<grid, dim3(512), 0, st>>>(DSK_ATTN_ARGS);
   else if (a.b <= 32) attn_kernel<8, 2, 8, true><<<grid, dim3(512), 0, st>>>(DSK_ATTN_ARGS);
-  else attn_kernel<8, 1, 8, true, true><<<grid, dim3(512), 0, st>>>(DSK_ATTN_ARGS);
+  else if ((int64_t)a.B * a.Hq * ws.nchunks <= kAttnWavePerSlotTo) attn_kernel<8, 1, 8, true, true><<<grid, dim3(512), 0, st>>>(DSK_ATTN_ARGS);
+  else attn_kernel<8, 2, 4, true, true><<<grid, dim3(256), 0, st>>>(DSK_ATTN_ARGS);
 #undef DSK_ATTN_ARGS
   hipError_t err = hipGetLastError();
   // a cache without tokens: every head already holds the defined empty result, no partial exists
