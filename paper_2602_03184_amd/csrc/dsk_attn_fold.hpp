@@ -35,9 +35,20 @@ __device__ __forceinline__ float dot8_bf16(const QRow& q, const uint4& k) {
   return dot2_bf16(q.p[3], k.w, d);
 }
 
-// 2^x for x <= 0 on the hardware exponential alone: results below the normal range come out as
+// 2^x for x <= 2 on the hardware exponential alone: results below the normal range come out as
 // 0, which is what a softmax weight that small is worth; -inf gives 0.
-__device__ __forceinline__ float exp2_nonpos(float x) { return __builtin_amdgcn_exp2f(x); }
+__device__ __forceinline__ float exp2_small(float x) { return __builtin_amdgcn_exp2f(x); }
+
+// Reference of a state whose exponents are one multiply-add each, z * scale - reference, from its largest logit.  The exponent of
+// the largest row is then what rounding took from its logit: at most half a unit in the last place, which all weights of the state
+// have alike.  Beyond kPlainLogits (in log2 units) that could take all weights out of range, so the reference goes down by as much
+// as rounding can have put on and more, and the exponents are bounded by kMostExponent: rows that close to the largest (within
+// the rounding of such logits) count alike.  An infinite logit stays the reference.
+constexpr float kPlainLogits = 16777216.0f;
+constexpr float kMostExponent = 2.0f;
+__device__ __forceinline__ float fma_reference(float m) {
+  return fmaf(__builtin_amdgcn_fmed3f(fabsf(m) - kPlainLogits, 0.0f, 3.0e38f), -1.1920929e-7f, m);   // 2^-23
+}
 
 // one channel of a finished attention output: fp32 always, a nearest-even bf16 copy on request
 __device__ __forceinline__ void store_attn_out(float* __restrict__ out, uint16_t* __restrict__ out_bf16, int64_t idx,
@@ -56,25 +67,24 @@ template <int NS, bool OWN_SUMS = false, int SLOTS = 1>
 __device__ __forceinline__ void fold_loaded(WaveState& st, const QRow& qf, const uint4 (&kv)[NS],
                                             const uint4 (&vv)[NS], int nvalid, int g, float scale_log2, int nvalid2 = 0) {
   constexpr int kPer = NS / SLOTS;
-  // z[u]: logit; OWN_SUMS: what scale_log2 makes the logit of
-  const float none = OWN_SUMS && scale_log2 < 0.0f ? __builtin_inff() : -__builtin_inff();
-  float z[NS];
+  float z[NS];                                           // logit; OWN_SUMS: what scale_log2 (> 0) makes the logit of
   float mloc = -__builtin_inff();
 #pragma unroll
   for (int u = 0; u < NS; ++u) {
     float d = group16_sum(dot8_bf16(qf, kv[u]));
     if constexpr (!OWN_SUMS) d *= scale_log2;
-    z[u] = (4 * (u % kPer) + g < (u < kPer ? nvalid : nvalid2)) ? d : none;
-    mloc = fmaxf(mloc, OWN_SUMS ? z[u] * scale_log2 : z[u]);
+    z[u] = (4 * (u % kPer) + g < (u < kPer ? nvalid : nvalid2)) ? d : -__builtin_inff();
+    mloc = fmaxf(mloc, z[u]);
   }
   mloc = fmaxf(fmaxf(rows4_f(mloc, 0), rows4_f(mloc, 1)), fmaxf(rows4_f(mloc, 2), rows4_f(mloc, 3)));
+  if constexpr (OWN_SUMS) mloc = fma_reference(mloc * scale_log2);
   const float m_new = fmaxf(st.m, mloc);           // finite: nvalid >= 1
-  const float alpha = exp2_nonpos(st.m - m_new);         // 0 on the first fold (st.m = -inf)
+  const float alpha = exp2_small(st.m - m_new);          // 0 on the first fold (st.m = -inf)
   if constexpr (OWN_SUMS) {
     float l, acc[8];
 #pragma unroll
     for (int u = 0; u < NS; ++u) {
-      const float p = exp2_nonpos(fmaf(z[u], scale_log2, -m_new));
+      const float p = exp2_small(__builtin_elementwise_minimum(fmaf(z[u], scale_log2, -m_new), kMostExponent));   // a NaN stays
       float f[8];
       unpack8(vv[u], f);
       l = u == 0 ? p : l + p;
@@ -92,7 +102,7 @@ __device__ __forceinline__ void fold_loaded(WaveState& st, const QRow& qf, const
   for (int k = 0; k < 8; ++k) st.acc[k] *= alpha;
 #pragma unroll
   for (int u = 0; u < NS; ++u) {
-    const float p = exp2_nonpos(z[u] - m_new);          // 0 for padded rows
+    const float p = exp2_small(z[u] - m_new);          // 0 for padded rows
     st.l += p;
     float f[8];
     unpack8(vv[u], f);

@@ -652,13 +652,13 @@ __global__ __launch_bounds__(kLongWaves * DSK_WAVE) void attn_shared_kernel(
         }
       }
       const float m_new = fmaxf(m, groups_max(top));      // finite: nv >= 1
-      const float alpha = exp2_nonpos(m - m_new);         // 0 on the first fold
+      const float alpha = exp2_small(m - m_new);         // 0 on the first fold
       m = m_new;
       float part = 0.0f;
 #pragma unroll
       for (int t = 0; t < NT; ++t) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) { z[t][i] = exp2_nonpos(z[t][i] - m_new); part += z[t][i]; }   // 0 for padded rows
+        for (int i = 0; i < 4; ++i) { z[t][i] = exp2_small(z[t][i] - m_new); part += z[t][i]; }   // 0 for padded rows
         transpose_groups(z[t]);                           // z[t][u]: weight of row 16 t + 4 u + g
       }
       l = fmaf(l, alpha, part);

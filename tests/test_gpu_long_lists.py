@@ -312,6 +312,52 @@ def test_partials_of_lists_that_fit_one_chunk(B, Hq, Hkv, k, b, shared):
                 assert abs(float(part.lse[s, h]) - lse[s, h]) <= 1e-5
 
 
+# short chunks of one and of several, long lists whole and in chunks, slots of more than 32 rows in small and in large launches;
+# shared lists in tiles of 2, 4 and 8 heads
+LOGIT_LISTS = [(1, 4, 2, 7, 8, False), (2, 8, 2, 50, 16, False), (2, 8, 2, 50, 32, False), (8, 32, 8, 65, 8, False),
+               (8, 32, 8, 33, 16, False), (2, 32, 8, 163, 32, False), (1, 40, 40, 245, 16, False), (2, 8, 2, 5, 64, False),
+               (1, 28, 4, 40, 64, False), (3, 28, 4, 61, 40, False), (8, 32, 8, 33, 64, False), (8, 16, 8, 203, 8, True),
+               (8, 32, 8, 128, 16, True), (8, 56, 8, 128, 32, True)]
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,k,b,shared", LOGIT_LISTS)
+@pytest.mark.parametrize("scale,size", [(1e6, 1.0), (1e9, 1.0), (1e12, 1.0), (0.0, 2e5)])
+def test_logits_of_any_size(B, Hq, Hkv, k, b, shared, scale, size):
+    """Logits up to 1e14, far beyond where neighbours of 32 bits lie one apart: all the weight is on the best row of a list
+    (rows that are well apart), on every kernel."""
+    import paper_2602_03184_amd as dsk
+    rng = np.random.default_rng([B, Hq, k, b])
+    g = torch.Generator(device="cuda")
+    g.manual_seed(k + b)
+    L, H, G = 3001, Hkv if shared else Hq, Hq // Hkv
+    K, V = (torch.randn(Hkv, L, 128, generator=g, device="cuda").bfloat16() for _ in range(2))
+    K, q = (K.float() * size).bfloat16(), (torch.randn(B, Hq, 128, generator=g, device="cuda") * size).bfloat16()
+    counts = np.full((B, H), k)
+    start, length = _lists(rng, B, H, k, b, L, counts)
+    att = dsk.make_attn_args(q, K, V, dev_i32(start), dev_i32(length), dev_i32(counts), b, scale=scale,
+                             flags=dsk.DSK_ATTN_SHARED_SELECTION if shared else 0)
+    dsk.dsk_sparse_decode_attn(att.args)
+    torch.cuda.synchronize()
+    out, lse = att.out.cpu().numpy(), att.lse.cpu().numpy()
+    by = scale or 1.0 / math.sqrt(128.0)
+    Kd, qd, checked = K.double(), q.double(), 0
+    heads = rng.permutation(B * Hq)[:32]
+    for s, h in zip(heads // Hq, heads % Hq):
+        at = h // G if shared else h
+        rows = np.unique(np.concatenate([np.arange(a, a + n) for a, n in zip(start[s, at], length[s, at])]))
+        z = (Kd[h // G][torch.from_numpy(rows).cuda()] @ qd[s, h]).cpu().numpy()
+        first, second = np.sort(z)[::-1][:2]
+        # a dot is a sum of 128 products of some size^2 in 32 bits, wrong by some 1e-5 size^2 at most
+        if (first - second) * by < 200.0 or first - second < 1e-2 * size * size:
+            continue
+        checked += 1
+        times = sum(int(a <= rows[z.argmax()] < a + n) for a, n in zip(start[s, at], length[s, at]))
+        want = V[h // G, int(rows[z.argmax()])].float().cpu().numpy()
+        assert rel_err(out[s, h], want) <= 1e-6                    # weights of 1 and 0; the same row in several slots
+        assert abs(lse[s, h] - (first * by + math.log(times))) <= 1e-5 * abs(first * by)
+    assert checked >= len(heads) // 2
+
+
 # chunks a list in several wavefronts: short chunks, long lists, shared lists in tiles of 4 and 8 heads, slots of two tiles
 @pytest.mark.parametrize("B,Hq,Hkv,k,b,shared", [(2, 8, 2, 50, 16, False), (8, 32, 8, 128, 16, False), (8, 32, 8, 128, 32, False),
                                                  (8, 32, 8, 128, 16, True), (8, 56, 8, 128, 32, True)])
