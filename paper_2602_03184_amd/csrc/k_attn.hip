@@ -101,7 +101,7 @@ static int64_t attn_wgs_per_xcd(int G, int n_groups, int nchunks) {
   return (((int64_t)n_groups << p.cut) + 7) / 8 * G * p.run;
 }
 
-// ordinary (compiler-scheduled) loads; used for slots longer than 32 rows
+// up to 4*NS rows of a slot of more than 32, the loads placed by the compiler
 template <int NS>
 __device__ __forceinline__ void fold_rows(WaveState& st, const QRow& qf, const uint16_t* __restrict__ kbase,
                                           const uint16_t* __restrict__ vbase, int64_t kst, int64_t vst,
@@ -141,15 +141,19 @@ struct FoldSlots {
 
 // One workgroup of WAVES wavefronts per (chunk of WAVES*SPW slots, head, sequence); writes one partial, or the
 // final result when the head has a single chunk (its partial as well for a caller that merges by itself: `leave`).
-// REST: slots may have more than 4*NS rows; those behind are folded afterwards, 32 at a time.  The first 32 rows of a slot are
-// requested together, half of the loads for slots that have 16 rows: chunks are seldom as long as such a slot.
-// Up to kAttnWavePerSlotTo workgroups latency counts: a wavefront per slot, the rows of all slots of the workgroup on their way
-// at once.  In larger launches the other workgroups hide it, and half as many wavefronts with two slots each leave room for more
-// of them.  Decode steps of slots of 64 rows, a wavefront a slot / two slots a wavefront: 160 workgroups 15.9 / 17.2 us, 384
-// 17.7 / 17.9, 512 29.3 / 29.7 and 23.4 / 23.4, 1024 35.4 / 33.7 and 40.3 / 39.6, 1536 38.7 / 38.4 and 37.0 / 38.2, 1920 43.4 /
-// 40.9, 2560 54.3 / 52.8, 3072 65.3 / 61.5, 4096 84.9 / 82.1, 5120 81.8 / 72.8.  (Two slots a wavefront through loads that the
-// compiler placed: 17.8, 17.6, 28.7 and 23.6, 36.3 and 39.6, 40.9 and 39.3, 43.6, 57.5, 67.3, 87.9, 78.2.)
-constexpr int kAttnWavePerSlotTo = 512;
+// REST: slots may have more than 4*NS rows; those behind are folded afterwards, 32 at a time; half of the loads for slots that
+// have 16 rows: chunks are seldom as long as such a slot.  The compiler places these loads: all requested before the first one is
+// waited for, decode steps of slots of 64 rows take 46.3 instead of 45.1 us (16 / 2 heads, eight sequences of 30K tokens, 128
+// slots), 73.4 instead of 72.4 (40 / 8, eight of 9K), 29.4 instead of 28.8 (8 / 8, four of 40K).
+// A wavefront per slot where latency counts: in launches of up to kAttnWavePerSlotTo workgroups, and for slots of more than
+// kAttnTwoSlotsTo rows, which keep a wavefront busy for several round trips.  Otherwise the other workgroups hide the latency,
+// and half as many wavefronts with two slots each leave room for more of them.  Steps of slots of 64 rows, a wavefront a slot /
+// two slots a wavefront, by workgroups: 160 15.7 / 16.7 us, 512 28.8 / 28.6, 26.8 / 26.9 and 23.5 / 23.3, 640 32.0 / 32.4 and
+// 26.7 / 26.3, 1024 38.5 / 39.2, 34.5 / 34.7 and 32.3 / 32.0, 1536 35.9 / 37.6 and 38.0 / 38.2, 1920 42.1 / 40.7, 2048 79.2 / 80.7
+// and 43.0 / 40.9, 2560 53.8 / 52.7, 3072 63.2 / 60.9, 4096 85.8 / 81.9 and 69.2 / 60.6, 5120 80.2 / 72.5; of 100 to 256 rows, 2048
+// and more workgroups: 69.5 / 71.3, 78.7 / 83.3, 62.5 / 64.7, 61.4 / 76.5.
+constexpr int kAttnWavePerSlotTo = 1536;
+constexpr int kAttnTwoSlotsTo = 64;
 template <int NS, int SPW, int WAVES, bool STAGED = false, bool REST = false>
 __global__ __launch_bounds__(WAVES * DSK_WAVE) void attn_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ K, const uint16_t* __restrict__ V,
@@ -219,7 +223,6 @@ __global__ __launch_bounds__(WAVES * DSK_WAVE) void attn_kernel(
       if constexpr (!REST) len = len < 4 * NS ? len : 4 * NS;
       const bool ok = j < count && start >= 0 && len > 0 && start <= total_tokens - len;   // never read outside K/V
       if constexpr (REST) {
-        st_[r] = start;
         ln_[r] = ok ? len : 0;             // of the whole slot, for the rows behind
         len = len < 4 * NS ? len : 4 * NS;
       }
@@ -246,11 +249,13 @@ __global__ __launch_bounds__(WAVES * DSK_WAVE) void attn_kernel(
         row = row < len ? row : len - 1;
         vd[r][u] = *reinterpret_cast<const uint4*>(Vh + (int64_t)(start + row) * vst);
       }
-      if constexpr (STAGED) {
+      if constexpr (STAGED && !REST) {
 #pragma unroll
         for (int u = 0; u < NS; ++u) pin_loaded(kd[r][u]);
 #pragma unroll
         for (int u = 0; u < NS; ++u) pin_loaded(vd[r][u]);
+      }
+      if constexpr (STAGED) {
         if (nv[r] > 0) fold_loaded<NS, REST>(st, qf, kd[r], vd[r], nv[r], g, scale_log2);
       }
     }
@@ -968,7 +973,8 @@ hipError_t launch_attn(const dsk_attn_args& a, const AttnWs& ws, hipStream_t st)
   else if (a.b <= 16 && ws.slots_per_wg == 8) attn_kernel<4, 2, 4, false><<<grid, dim3(256), 0, st>>>(DSK_ATTN_ARGS);
   else if (a.b <= 16) attn_kernel<4, 2, 8, false><<<grid, dim3(512), 0, st>>>(DSK_ATTN_ARGS);
   else if (a.b <= 32) attn_kernel<8, 2, 8, true><<<grid, dim3(512), 0, st>>>(DSK_ATTN_ARGS);
-  else if ((int64_t)a.B * a.Hq * ws.nchunks <= kAttnWavePerSlotTo) attn_kernel<8, 1, 8, true, true><<<grid, dim3(512), 0, st>>>(DSK_ATTN_ARGS);
+  else if (a.b > kAttnTwoSlotsTo || (int64_t)a.B * a.Hq * ws.nchunks <= kAttnWavePerSlotTo)
+    attn_kernel<8, 1, 8, true, true><<<grid, dim3(512), 0, st>>>(DSK_ATTN_ARGS);
   else attn_kernel<8, 2, 4, true, true><<<grid, dim3(256), 0, st>>>(DSK_ATTN_ARGS);
 #undef DSK_ATTN_ARGS
   hipError_t err = hipGetLastError();

@@ -136,11 +136,13 @@ def _spans_in_and_outside_the_cache(b, B, Hq, Hkv, k, shared):
 
 
 @pytest.mark.parametrize("b", [33, 48, 64, 65, 100, 128])
-@pytest.mark.parametrize("B,Hq,Hkv,k,shared", [(2, 6, 2, 21, False), (1, 28, 4, 8, False), (3, 8, 8, 9, False), (2, 8, 2, 17, True),
-                                               (16, 16, 4, 16, False), (9, 19, 1, 21, False), (12, 40, 8, 12, True), (33, 16, 16, 7, False)])
-def test_slots_of_more_than_32_rows(b, B, Hq, Hkv, k, shared):
-    """Slots around the 16 and 32 rows that are on their way at first, and of the rows behind them; launches of up to 512
-    workgroups and of more."""
+@pytest.mark.parametrize("B,Hq,Hkv,k,shared,large", [(2, 6, 2, 21, False, False), (1, 28, 4, 8, False, False), (3, 8, 8, 9, False, False),
+                                                     (2, 8, 2, 17, True, False), (4, 32, 8, 96, False, False), (9, 19, 1, 66, False, True),
+                                                     (8, 16, 4, 97, True, True), (12, 16, 16, 71, False, True)])
+def test_slots_of_more_than_32_rows(b, B, Hq, Hkv, k, shared, large):
+    """Slots around the 16 and 32 rows that are folded first, and of the rows behind them; launches of up to 1536 workgroups of 8
+    slots and of more, where slots of up to 64 rows go two to a wavefront."""
+    assert (B * Hq * -(-k // 8) > 1536) == large
     _spans_in_and_outside_the_cache(b, B, Hq, Hkv, k, shared)
 
 
