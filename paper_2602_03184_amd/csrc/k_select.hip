@@ -5,7 +5,7 @@
 // found on the block scores with each block weighted by its slot count.  Thread t of the 256,
 // 512 or 1024 (by the host's bound on the block count) owns PT (4, 6, 8, 12 or 16) consecutive blocks [t*PT, t*PT+PT) of the
 // sequence: their keys (order-preserving integer images of the scores) and slot counts live in registers, fetched with
-// 16-byte loads (8-byte ones for 6 blocks) that are all in flight at once.
+// 16-byte loads (8-byte ones for 6 blocks) that are all in flight at once (12 and 16: but for the block starts).
 //   1. key range and slot total (workgroup reduction);
 //   2. one slot-count-weighted LDS histogram over the top 10 bits of (key - smallest key) finds the
 //      bin that holds the k-th best slot; the few blocks of that bin are ranked against each
@@ -455,9 +455,9 @@ __device__ __forceinline__ bool scored_load(const ScoredBy& by, float* scores, i
 // slot_base, block_start: 16-byte aligned, readable up to a multiple of 4 entries past cap.
 // PASSES > 0 (PT = 1): the blocks are scored here, see above.  (One kernel for both: with the selection in a function of its
 // own the compiler orders the longer sequences' instances otherwise, 0.05 us a call.)
-template <int PT, int THREADS, int PASSES = 0>
-__global__ __launch_bounds__(THREADS) void select_kernel(
-    float* __restrict__ scores, int stride, const int32_t* __restrict__ cu_blocks,
+template <int PT, int THREADS, int PASSES>
+__device__ __forceinline__ void select_tile(
+    SelShared& sh, float* __restrict__ scores, int stride, const int32_t* __restrict__ cu_blocks,
     const int32_t* __restrict__ block_start, const int32_t* __restrict__ slot_base, int cap, int Hq,
     int b, int kcap, const int32_t* __restrict__ budget_per_seq, const int32_t* __restrict__ blocks_used,
     const int32_t* __restrict__ seq_row0, int32_t* __restrict__ sel_slot, int32_t* __restrict__ sel_start,
@@ -467,7 +467,9 @@ __global__ __launch_bounds__(THREADS) void select_kernel(
   constexpr int kSelPerThread = PT;
   constexpr int kVec = PT == 6 ? 2 : 4;                  // entries of a load
   constexpr int kSelVecs = (PT + kVec - 1) / kVec;
-  __shared__ SelShared sh;
+  // The starts of so many blocks would not fit the registers with the rest (20 of 1024 threads' 128): those of the chosen blocks
+  // are fetched when their slots are written (sequence of 13005 blocks, selection with them in the tile 27.0 us, so 25.2)
+  constexpr bool kLateStarts = PT >= 12;
   int h = blockIdx.x;
   int s = blockIdx.y;
   int hk = 0;
@@ -517,10 +519,12 @@ __global__ __launch_bounds__(THREADS) void select_kernel(
       const int v = v_first + u;
       iv[u] = sb4[v < max_vec_sb ? v : max_vec_sb];
     }
+    if constexpr (!kLateStarts) {
 #pragma unroll
-    for (int u = 0; u < kSelVecs + 1; ++u) {
-      const int v = v_first + u;
-      bv[u] = bs4[v < max_vec_sb ? v : max_vec_sb];
+      for (int u = 0; u < kSelVecs + 1; ++u) {
+        const int v = v_first + u;
+        bv[u] = bs4[v < max_vec_sb ? v : max_vec_sb];
+      }
     }
     // tables with a region per sequence: the blocks in use and the sequence's first K/V row
     blk1 = blocks_used != nullptr ? blk0_raw + blocks_used[s] : cu_blocks[s + 1];
@@ -529,8 +533,10 @@ __global__ __launch_bounds__(THREADS) void select_kernel(
     for (int u = 0; u < kSelVecs; ++u) pin_loaded(fv[u]);              // all vector loads in flight together
 #pragma unroll
     for (int u = 0; u < kSelVecs + 1; ++u) pin_loaded(iv[u]);
+    if constexpr (!kLateStarts) {
 #pragma unroll
-    for (int u = 0; u < kSelVecs + 1; ++u) pin_loaded(bv[u]);
+      for (int u = 0; u < kSelVecs + 1; ++u) pin_loaded(bv[u]);
+    }
     if (blk1 > cap) blk1 = cap;
     n = blk1 - blk0;
   }
@@ -713,7 +719,8 @@ __global__ __launch_bounds__(THREADS) void select_kernel(
     for (int r = 0; r < kSelPerThread; ++r) {
       const bool on = (on_mask >> r) & 1u;
       if (on && e >= 0 && e < kSelWork) {                  // few lanes per step: masked LDS writes
-        sh.work[e] = make_int4(xb[r], xb[r + 1], xs[r], o);
+        if constexpr (kLateStarts) sh.work[e] = make_int4(blk0 + tid * kSelPerThread + r - shift, 0, xs[r], o);
+        else sh.work[e] = make_int4(xb[r], xb[r + 1], xs[r], o);
         sh.work_take[e] = w[r];
       }
       e += on ? 1 : 0;
@@ -722,7 +729,12 @@ __global__ __launch_bounds__(THREADS) void select_kernel(
     __syncthreads();
     const int n_round = n_work - base < kSelWork ? n_work - base : kSelWork;
     for (int j = tid; j < n_round; j += THREADS) {
-      const int4 wk = sh.work[j];
+      int4 wk = sh.work[j];
+      if constexpr (kLateStarts) {
+        const int at = wk.x;
+        wk.x = block_start[at];
+        wk.y = block_start[at + 1];
+      }
       const int take = sh.work_take[j];
       for (int jj = 0; jj < take; ++jj) {
         const int oo = wk.w + jj;
@@ -736,7 +748,43 @@ __global__ __launch_bounds__(THREADS) void select_kernel(
       }
     }
     if (base + kSelWork < n_work) __syncthreads();       // the list is refilled for another round
-  }}
+  }
+}
+
+template <int PT, int THREADS, int PASSES = 0>
+__global__ __launch_bounds__(THREADS) void select_kernel(
+    float* __restrict__ scores, int stride, const int32_t* __restrict__ cu_blocks,
+    const int32_t* __restrict__ block_start, const int32_t* __restrict__ slot_base, int cap, int Hq,
+    int b, int kcap, const int32_t* __restrict__ budget_per_seq, const int32_t* __restrict__ blocks_used,
+    const int32_t* __restrict__ seq_row0, int32_t* __restrict__ sel_slot, int32_t* __restrict__ sel_start,
+    int32_t* __restrict__ sel_len, int32_t* __restrict__ sel_count, ScoredBy by) {
+  __shared__ SelShared sh;
+  select_tile<PT, THREADS, PASSES>(sh, scores, stride, cu_blocks, block_start, slot_base, cap, Hq, b, kcap, budget_per_seq,
+                                   blocks_used, seq_row0, sel_slot, sel_start, sel_len, sel_count, by);
+}
+
+// Where the bound asks for more than 8 blocks a thread: the tile by the blocks that the sequence has, as a bound may be far above
+// them.  dsk_select_topk of 8118 blocks of 32 / 8 heads, tile by a bound of 12285 or 16381 blocks / by the length: 19.1 / 17.4 and
+// 27.7 / 19.6 us; of 9265, 13005 and 16205 blocks with a bound that fits: 17.2 / 17.2, 27.0 / 25.2, 29.3 / 27.4 (read from memory
+// in every pass, as beyond 16381 blocks: 35.1, 48.7, 75.3).  Of the 16 blocks a thread some are in scratch memory (64 bytes a lane).
+__global__ __launch_bounds__(kSelMaxThreads) void select_by_length_kernel(
+    float* __restrict__ scores, int stride, const int32_t* __restrict__ cu_blocks,
+    const int32_t* __restrict__ block_start, const int32_t* __restrict__ slot_base, int cap, int Hq,
+    int b, int kcap, const int32_t* __restrict__ budget_per_seq, const int32_t* __restrict__ blocks_used,
+    const int32_t* __restrict__ seq_row0, int32_t* __restrict__ sel_slot, int32_t* __restrict__ sel_start,
+    int32_t* __restrict__ sel_len, int32_t* __restrict__ sel_count, ScoredBy by) {
+  __shared__ SelShared sh;
+  const int s = blockIdx.y;
+  const int blk0 = s == 0 ? 0 : cu_blocks[s];
+  const int n = blocks_used != nullptr ? blocks_used[s] : cu_blocks[s + 1] - blk0;
+#define DSK_TILE(PT)                                                                                                        \
+  select_tile<PT, kSelMaxThreads, 0>(sh, scores, stride, cu_blocks, block_start, slot_base, cap, Hq, b, kcap, budget_per_seq, \
+                                     blocks_used, seq_row0, sel_slot, sel_start, sel_len, sel_count, by)
+  if (sel_fits_tile(n, 8, kSelMaxThreads)) DSK_TILE(8);
+  else if (sel_fits_tile(n, 12, kSelMaxThreads)) DSK_TILE(12);
+  else DSK_TILE(kSelMaxPerThread);
+#undef DSK_TILE
+}
 
 // an upper bound on the blocks of a sequence, as far as the caller gave one
 static int select_bound(const dsk_select_args& a) {
@@ -782,12 +830,9 @@ hipError_t launch_select(const dsk_select_args& a, float* scores, int stride, hi
   const dim3 grid((unsigned)Hsel, (unsigned)a.B);
   // a sequence has at most `bound` blocks: the smallest register tile that holds them all does
   // the least per-thread work (larger sequences than the tile still work, through select_big).  Decode step of 32 / 8 heads,
-  // one sequence of 4369 blocks, 8 / 6 blocks a thread 24.4 / 24.0 us, eight steps of a batch on either side of 4096 471 / 467
-  // (5 a thread, each entry a load of its own: 24.6); select_big / 12 or 16 a thread: 9362 blocks 47.2 / 31.4, 13107 57.6 /
-  // 36.4, 16375 83 / 37.7.  The capacity of the tables alone says too little for those: with chunks of C +- C/2 tokens it is
-  // twice the blocks there are, and a sequence of less than 8 K blocks is better off with 8 a thread.
+  // one sequence of 4369 blocks, 8 / 6 blocks a thread 24.4 / 24.0 us, eight sequences on either side of 4096 no difference
+  // (5 a thread, each entry a load of its own: 24.6).
   const int bound = select_bound(a);
-  const bool known = a.max_blocks_per_seq > 0 || (a.B == 1 && a.max_blocks_used > 0);
 #define DSK_SEL_ARGS                                                                                          \
   scores, stride, a.cu_blocks, a.block_start, a.slot_base, a.max_blocks_total, Hsel, a.b, k, a.budget_per_seq, a.blocks_used, \
       a.seq_row0, a.sel_slot, a.sel_start, a.sel_len, a.sel_count, ScoredBy{}
@@ -795,10 +840,8 @@ hipError_t launch_select(const dsk_select_args& a, float* scores, int stride, hi
   else if (sel_fits_tile(bound, 4, 512)) select_kernel<4, 512><<<grid, dim3(512), 0, st>>>(DSK_SEL_ARGS);
   else if (sel_fits_tile(bound, 4, 1024)) select_kernel<4, 1024><<<grid, dim3(1024), 0, st>>>(DSK_SEL_ARGS);
   else if (sel_fits_tile(bound, 6, 1024)) select_kernel<6, 1024><<<grid, dim3(1024), 0, st>>>(DSK_SEL_ARGS);
-  else if (!known || sel_fits_tile(bound, 8, 1024) || !sel_fits_tile(bound, kSelMaxPerThread, 1024))
-    select_kernel<8, 1024><<<grid, dim3(1024), 0, st>>>(DSK_SEL_ARGS);
-  else if (sel_fits_tile(bound, 12, 1024)) select_kernel<12, 1024><<<grid, dim3(1024), 0, st>>>(DSK_SEL_ARGS);
-  else select_kernel<kSelMaxPerThread, 1024><<<grid, dim3(1024), 0, st>>>(DSK_SEL_ARGS);
+  else if (sel_fits_tile(bound, 8, 1024)) select_kernel<8, 1024><<<grid, dim3(1024), 0, st>>>(DSK_SEL_ARGS);
+  else select_by_length_kernel<<<grid, dim3(kSelMaxThreads), 0, st>>>(DSK_SEL_ARGS);
 #undef DSK_SEL_ARGS
   return hipGetLastError();
 }

@@ -28,7 +28,9 @@ def test_every_register_tile_selects_alike(blocks, b):
     q = torch.randn(t.B, 2, 128, generator=g, device="cuda").bfloat16()
     for budget in (b, 129 * b, 3000 * b):                                  # several rounds of the list of chosen blocks
         memory = _run(t, q, budget, max_blocks_per_seq=300)                # outgrown: read from memory
-        for kw in (dict(max_blocks_per_seq=max(blocks)), dict(max_blocks_per_seq=max(blocks) + 1), dict()):
+        # bounds that fit, and one that leaves the tile to the length of the sequence
+        for kw in (dict(max_blocks_per_seq=max(blocks)), dict(max_blocks_per_seq=max(blocks) + 1), dict(max_blocks_per_seq=16381),
+                   dict()):
             got = _run(t, q, budget, **kw)
             for name, x, y in zip(("slot", "start", "len", "count"), got, memory):
                 assert torch.equal(x, y), (name, budget, kw)
