@@ -22,9 +22,11 @@ constexpr int kSumUnroll = 8;  // row-groups of 4 rows in flight per wave
 // STREAM_ROWS: the rows are read past the caches too.  The decode step that follows finds in the memory-side cache
 // what was read last (eight sequences, all rows streamed: pass -23 us, step +30), so the launch streams only what
 // would have left that cache again by its end.
+// kUnroll: row-groups in flight; those behind the first kSumUnroll are left out, four at a time, where the block has no row for them.
 template <bool MEAN, bool STREAM, bool STREAM_ROWS = false, int kUnroll = kSumUnroll>
 __device__ __forceinline__ void summarize_block(const uint16_t* base, int len, int64_t stride_tok, unsigned ustride8,
                                                 uint16_t* o, int g, int c) {
+  static_assert((4 * kUnroll - 1) * kMaxTokenStride * 2 + 256 <= (int64_t)1 << 32, "byte offsets of the rows in 32 bits");
   // MEAN: mn[] holds this lane's running sums instead
   float mn[8], mx[8];
 #pragma unroll
@@ -32,10 +34,11 @@ __device__ __forceinline__ void summarize_block(const uint16_t* base, int len, i
   for (int r0 = 0; r0 < len; r0 += 4 * kUnroll) {
     // scalar 64-bit base of this row batch + 32-bit lane offsets (stride_tok <= 2^24, host-checked)
     const char* rb = reinterpret_cast<const char*>(base + (int64_t)r0 * stride_tok);
-    const int last = len - 1 - r0;
+    const int last = __builtin_amdgcn_readfirstlane(len - 1 - r0);
     uint4 v[kUnroll];
 #pragma unroll
     for (int u = 0; u < kUnroll; ++u) {
+      if (u >= kSumUnroll && u % 4 == 0 && 4 * u > last) break;    // uniform: no row left
       int r = 4 * u + g;
       r = r < last ? r : last;     // a repeated row changes neither min nor max
       const unsigned byte_off = (__umul24((unsigned)r, ustride8) + (unsigned)c) * 16u;   // strides are multiples of 8
@@ -43,6 +46,7 @@ __device__ __forceinline__ void summarize_block(const uint16_t* base, int len, i
     }
 #pragma unroll
     for (int u = 0; u < kUnroll; ++u) {
+      if (u >= kSumUnroll && u % 4 == 0 && 4 * u > last) break;
       float f[8];
       unpack8(v[u], f);
       if constexpr (MEAN) {
@@ -84,16 +88,17 @@ __device__ __forceinline__ void summarize_block(const uint16_t* base, int len, i
   }
 }
 
-// The same where wavefronts are few and the latency of the rows is what counts.  LONG: up to 96 rows in flight, for chunks of
-// more than kSumRowsAhead.  (MEAN: a lane adds its rows in token order, whatever is in flight.)  A token appended to each of
-// eight sequences, chunks of 16 to 64, 8 heads: 4.8 -> 4.0 us for the launch, 8 decode steps 471.8 -> 467.9.  Where chunks are
-// shorter the registers are only a burden.
+// The same where wavefronts are few and the latency of the rows is what counts.  LONG: up to 96 rows in flight, for blocks of more
+// than kSumRowsAhead where chunks are of more than that and up to kSumLongTo.  (MEAN: a lane adds its rows in token order, whatever
+// is in flight.)  Steps of an update of eight sequences, 8 heads, without / with it: chunks of 33 tokens 9.74 / 9.59 us, 40 9.58 /
+// 9.42, 64 9.98 / 10.02; of 84 10.6 / 11.0, 120 10.97 / 11.4, one sequence 9.34 / 9.52 (11.8, 12.0 and 10.4 when every round
+// handled 96 rows, whatever a block had left); where chunks are shorter the registers are only a burden.
 constexpr int kSumRowsAhead = 4 * kSumUnroll;
+constexpr int kSumLongTo = 64;
 template <bool MEAN, bool LONG>
 __device__ __forceinline__ void summarize_few(const uint16_t* base, int len, int64_t stride_tok, unsigned ustride8,
                                               uint16_t* o, int g, int c) {
   if (!LONG || len <= kSumRowsAhead) summarize_block<MEAN, false>(base, len, stride_tok, ustride8, o, g, c);
-  else if (len <= 2 * kSumRowsAhead) summarize_block<MEAN, false, false, 2 * kSumUnroll>(base, len, stride_tok, ustride8, o, g, c);
   else summarize_block<MEAN, false, false, 3 * kSumUnroll>(base, len, stride_tok, ustride8, o, g, c);
 }
 
@@ -268,7 +273,7 @@ hipError_t launch_summaries_range(const void* X, int64_t stride_tok, int64_t str
   summaries_range_kernel<mean, lng><<<grid, dim3(kSumThreads), 0, st>>>(                                                  \
       static_cast<const uint16_t*>(X), stride_tok, stride_head, Hkv, block_start, blk_range, cap, total_tokens,           \
       static_cast<uint16_t*>(out), dev_status)
-  const bool lng = chunk > kSumRowsAhead;
+  const bool lng = chunk > kSumRowsAhead && chunk <= kSumLongTo;
   if (summary_mode == DSK_SUMMARY_MEAN) { if (lng) DSK_RANGE(true, true); else DSK_RANGE(true, false); }
   else if (lng) DSK_RANGE(false, true);
   else DSK_RANGE(false, false);
@@ -316,7 +321,7 @@ hipError_t launch_summaries_batch_ranges(const void* X, int64_t stride_tok, int6
   summaries_batch_ranges_kernel<mean, lng><<<grid, dim3(kSumThreads), 0, st>>>(                                           \
       static_cast<const uint16_t*>(X), stride_tok, stride_head, Hkv, block_start, static_cast<const int4*>(ranges),       \
       out_rows, static_cast<uint16_t*>(out), dev_status)
-  const bool lng = chunk > kSumRowsAhead;
+  const bool lng = chunk > kSumRowsAhead && chunk <= kSumLongTo;
   if (summary_mode == DSK_SUMMARY_MEAN) { if (lng) DSK_RANGES(true, true); else DSK_RANGES(true, false); }
   else if (lng) DSK_RANGES(false, true);
   else DSK_RANGES(false, false);

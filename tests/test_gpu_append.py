@@ -175,7 +175,7 @@ def test_append_edge_parameters(C, delta, a_num, everywhere):
 @pytest.mark.parametrize("C", [32, 33, 64, 65, 96, 97, 200])
 @pytest.mark.parametrize("mean", [False, True])
 def test_append_chunk_lengths_around_the_rows_in_flight(C, mean):
-    """Whole chunks of C tokens (no delimiter, delta 0) and an open one that grows: 32, 64 or 96 rows at a time."""
+    """Whole chunks of C tokens (no delimiter, delta 0) and an open one that grows: up to 32 rows at a time, or up to 96 (C up to 64)."""
     rng = np.random.default_rng(C)
     L = 6 * C + 9
     K = (rng.standard_normal((3, L, 128)).astype(np.float32).view(np.uint32) >> 16).astype(np.uint16)
@@ -193,6 +193,30 @@ def test_append_chunk_lengths_around_the_rows_in_flight(C, mean):
             got = bf16_bits_of(sums)[:, : len(want) - 1]
             np.testing.assert_array_equal(got[:, :, 0], got[:, :, 1])
             assert_bf16_of(got[:, :, 0], oracle_means_bf16(bits[:, : seq.L], want, range(3)))
+
+
+@pytest.mark.parametrize("mean", [False, True])
+def test_append_chunks_of_more_rows_than_are_in_flight(mean):
+    """Chunks of 65 to 127 tokens around C = 64, each up to its delimiter: one or two rounds of up to 96 rows, of which 16 at a
+    time are left out where a block has none."""
+    rng = np.random.default_rng(7)
+    lens = [97, 112, 113, 127, 96, 81, 80, 65, 128 - 1, 99, 111, 126]
+    ends = np.cumsum(lens)
+    L = int(ends[-1]) + 40
+    K = (rng.standard_normal((3, L, 128)).astype(np.float32).view(np.uint32) >> 16).astype(np.uint16)
+    tok = np.full(L, 7)
+    tok[ends - 1] = 1
+    seq = _Seq(K, K, tok, [1, 2], np.array([9, 5], np.uint8), 5, 64, 63, 10, 10, 16, summary_mode=int(mean))
+    for n in [1, 300, 1, 150, 250, 1, 1] + [L]:
+        want, i0 = seq.append(min(n, L - seq.L))
+        seq.check_tables(want, i0)
+        if not mean:
+            seq.check_summaries(want)
+            continue
+        got = bf16_bits_of(seq.comp.ksum)[:, : len(want) - 1]
+        np.testing.assert_array_equal(got[:, :, 0], got[:, :, 1])
+        assert_bf16_of(got[:, :, 0], oracle_means_bf16(K[:, : seq.L], want, range(3)))
+    assert set(np.diff(want)) >= {97, 112, 113, 127}
 
 
 def test_append_from_an_empty_sequence():
