@@ -141,19 +141,21 @@ struct FoldSlots {
 
 // One workgroup of WAVES wavefronts per (chunk of WAVES*SPW slots, head, sequence); writes one partial, or the
 // final result when the head has a single chunk (its partial as well for a caller that merges by itself: `leave`).
-// REST: slots may have more than 4*NS rows; those behind are folded afterwards, 32 at a time; half of the loads for slots that
-// have 16 rows: chunks are seldom as long as such a slot.  The compiler places these loads: all requested before the first one is
-// waited for, decode steps of slots of 64 rows take 46.3 instead of 45.1 us (16 / 2 heads, eight sequences of 30K tokens, 128
-// slots), 73.4 instead of 72.4 (40 / 8, eight of 9K), 29.4 instead of 28.8 (8 / 8, four of 40K).
-// A wavefront per slot where latency counts: in launches of up to kAttnWavePerSlotTo workgroups, and for slots of more than
-// kAttnTwoSlotsTo rows, which keep a wavefront busy for several round trips.  Otherwise the other workgroups hide the latency,
-// and half as many wavefronts with two slots each leave room for more of them.  Steps of slots of 64 rows, a wavefront a slot /
-// two slots a wavefront, by workgroups: 160 15.7 / 16.7 us, 512 28.8 / 28.6, 26.8 / 26.9 and 23.5 / 23.3, 640 32.0 / 32.4 and
-// 26.7 / 26.3, 1024 38.5 / 39.2, 34.5 / 34.7 and 32.3 / 32.0, 1536 35.9 / 37.6 and 38.0 / 38.2, 1920 42.1 / 40.7, 2048 79.2 / 80.7
-// and 43.0 / 40.9, 2560 53.8 / 52.7, 3072 63.2 / 60.9, 4096 85.8 / 81.9 and 69.2 / 60.6, 5120 80.2 / 72.5; of 100 to 256 rows, 2048
-// and more workgroups: 69.5 / 71.3, 78.7 / 83.3, 62.5 / 64.7, 61.4 / 76.5.
-constexpr int kAttnWavePerSlotTo = 1536;
-constexpr int kAttnTwoSlotsTo = 64;
+// REST: slots of more than 32 rows: the first 32 of every slot of the wavefront, then those behind, 32 at a time (STAGED: slot by
+// slot); half of the loads where there are no more than 16: chunks are seldom as long as such a slot.  The compiler places the
+// loads: with all 32 rows requested before the first one is waited for launches of 385 workgroups and more took 2 to 4 % longer.
+// A wavefront per slot where a CU has no more than one workgroup, so that the latency of its loads counts, and for lists per head
+// of slots of kAttnOneSlotFrom rows and more, which keep a wavefront busy for several round trips.  Otherwise the other workgroups
+// hide it, and half as many wavefronts with two slots each leave room for more of them.  Attention alone, slots of 40 to 64 rows,
+// 170 random calls, time in units of two slots a wavefront, slot by slot, with each weight added to the state by itself, mean and
+// largest: a wavefront per slot / two slots a wavefront up to 256 workgroups 0.91 1.00 / 0.94 0.99, 257 to 512 0.97 1.04 / 0.96
+// 1.03, 513 to 1024 1.03 1.10 / 0.99 1.06, 1025 to 2048 1.03 1.13 / 0.95 1.04, more 1.09 1.14 / 0.93 1.00.  Decode steps of slots of
+// 128 to 256 rows, chunks as long, 800 to 2048 workgroups: 82.5 / 86.7 us, 60.5 / 65.0, 62.4 / 76.7, 52.6 / 56.2; with chunks of 20
+// to 40 tokens, or shared lists (35.2 / 31.2), the other way round.  Without grouped heads, where nothing comes from L2, slot by
+// slot: 512 workgroups 28.6 / 29.2, 27.0 / 27.7 and 28.4 / 29.1 us against the first rows of both slots first; with grouped heads
+// 1 to 2 % slower, or 9 % where most slots have rows behind the 32.
+constexpr int kAttnWavePerSlotTo = 256;
+constexpr int kAttnOneSlotFrom = 128;
 template <int NS, int SPW, int WAVES, bool STAGED = false, bool REST = false>
 __global__ __launch_bounds__(WAVES * DSK_WAVE) void attn_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ K, const uint16_t* __restrict__ V,
@@ -211,8 +213,37 @@ __global__ __launch_bounds__(WAVES * DSK_WAVE) void attn_kernel(
 #pragma unroll
   for (int i = 0; i < 8; ++i) st.acc[i] = 0.0f;
 
-  {
-    // all K/V loads of the first 4*NS rows of the wave's SPW slots go out now (STAGED: of a slot)
+  if constexpr (REST) {
+    // rows r0 .. r0 + 31 of a slot of len rows (r0 < len)
+    auto fold_part = [&](int start, int len, int r0) {
+      const int nvr = len - r0;
+      const uint16_t* kb = Kh + (int64_t)(start + r0) * kst;
+      const uint16_t* vb = Vh + (int64_t)(start + r0) * vst;
+      if (nvr > 16) fold_rows<8>(st, qf, kb, vb, kst, vst, nvr < 32 ? nvr : 32, g, scale_log2);
+      else fold_rows<4>(st, qf, kb, vb, kst, vst, nvr, g, scale_log2);
+    };
+#pragma unroll
+    for (int r = 0; r < SPW; ++r) {
+      const int j = slot0 + wave + kAttnWaves * r;
+      const int start = st_[r];
+      int len = ln_[r];
+      if (len > b) len = b;
+      ln_[r] = 0;
+      if (j >= count || start < 0 || len <= 0 || start > total_tokens - len) continue;   // never read outside K/V
+      if constexpr (STAGED) {
+        for (int r0 = 0; r0 < len; r0 += 32) fold_part(start, len, r0);
+      } else {
+        fold_part(start, len, 0);
+        ln_[r] = len;                    // for the rows behind
+      }
+    }
+    if constexpr (!STAGED) {
+#pragma unroll
+      for (int r = 0; r < SPW; ++r)
+        for (int r0 = 32; r0 < ln_[r]; r0 += 32) fold_part(st_[r], ln_[r], r0);
+    }
+  } else {
+    // every slot has at most 4*NS rows: all K/V loads of the wave's SPW slots go out now (STAGED: of a slot)
     uint4 kd[SPW][NS], vd[SPW][NS];
     int nv[SPW];
 #pragma unroll
@@ -220,23 +251,11 @@ __global__ __launch_bounds__(WAVES * DSK_WAVE) void attn_kernel(
       const int j = slot0 + wave + kAttnWaves * r;
       int start = st_[r];
       int len = ln_[r] < b ? ln_[r] : b;
-      if constexpr (!REST) len = len < 4 * NS ? len : 4 * NS;
+      len = len < 4 * NS ? len : 4 * NS;
       const bool ok = j < count && start >= 0 && len > 0 && start <= total_tokens - len;   // never read outside K/V
-      if constexpr (REST) {
-        ln_[r] = ok ? len : 0;             // of the whole slot, for the rows behind
-        len = len < 4 * NS ? len : 4 * NS;
-      }
       nv[r] = ok ? len : 0;
       start = ok ? start : 0;            // a skipped slot reads row 0 (harmless) so that the loads
       len = ok ? len : 1;                // below stay unconditional
-      if constexpr (REST) {              // half of the loads where half of the rows are there
-        if (__builtin_amdgcn_readfirstlane(len) <= 2 * NS) {
-          const uint16_t* kb = Kh + (int64_t)start * kst;
-          const uint16_t* vb = Vh + (int64_t)start * vst;
-          if (ok) fold_rows<NS / 2>(st, qf, kb, vb, kst, vst, len, g, scale_log2);
-          continue;
-        }
-      }
 #pragma unroll
       for (int u = 0; u < NS; ++u) {
         int row = 4 * u + g;
@@ -249,30 +268,15 @@ __global__ __launch_bounds__(WAVES * DSK_WAVE) void attn_kernel(
         row = row < len ? row : len - 1;
         vd[r][u] = *reinterpret_cast<const uint4*>(Vh + (int64_t)(start + row) * vst);
       }
-      if constexpr (STAGED && !REST) {
+      if constexpr (STAGED) {
 #pragma unroll
         for (int u = 0; u < NS; ++u) pin_loaded(kd[r][u]);
 #pragma unroll
         for (int u = 0; u < NS; ++u) pin_loaded(vd[r][u]);
-      }
-      if constexpr (STAGED) {
-        if (nv[r] > 0) fold_loaded<NS, REST>(st, qf, kd[r], vd[r], nv[r], g, scale_log2);
+        if (nv[r] > 0) fold_loaded<NS>(st, qf, kd[r], vd[r], nv[r], g, scale_log2);
       }
     }
     if constexpr (!STAGED) FoldSlots<NS, SPW, 0>::run(st, qf, kd, vd, nv, g, scale_log2);
-  }
-  if constexpr (REST) {
-#pragma unroll
-    for (int r = 0; r < SPW; ++r) {
-      const int len = ln_[r];
-      for (int r0 = 4 * NS; r0 < len; r0 += 32) {
-        const int nvr = len - r0;
-        const uint16_t* kb = Kh + (int64_t)(st_[r] + r0) * kst;
-        const uint16_t* vb = Vh + (int64_t)(st_[r] + r0) * vst;
-        if (nvr > 16) fold_rows<8>(st, qf, kb, vb, kst, vst, nvr < 32 ? nvr : 32, g, scale_log2);
-        else fold_rows<4>(st, qf, kb, vb, kst, vst, nvr, g, scale_log2);
-      }
-    }
   }
 
   // lane groups -> wave
@@ -973,9 +977,10 @@ hipError_t launch_attn(const dsk_attn_args& a, const AttnWs& ws, hipStream_t st)
   else if (a.b <= 16 && ws.slots_per_wg == 8) attn_kernel<4, 2, 4, false><<<grid, dim3(256), 0, st>>>(DSK_ATTN_ARGS);
   else if (a.b <= 16) attn_kernel<4, 2, 8, false><<<grid, dim3(512), 0, st>>>(DSK_ATTN_ARGS);
   else if (a.b <= 32) attn_kernel<8, 2, 8, true><<<grid, dim3(512), 0, st>>>(DSK_ATTN_ARGS);
-  else if (a.b > kAttnTwoSlotsTo || (int64_t)a.B * a.Hq * ws.nchunks <= kAttnWavePerSlotTo)
-    attn_kernel<8, 1, 8, true, true><<<grid, dim3(512), 0, st>>>(DSK_ATTN_ARGS);
-  else attn_kernel<8, 2, 4, true, true><<<grid, dim3(256), 0, st>>>(DSK_ATTN_ARGS);
+  else if ((a.b >= kAttnOneSlotFrom && sel_div == 1) || (int64_t)a.B * a.Hq * ws.nchunks <= kAttnWavePerSlotTo)
+    attn_kernel<8, 1, 8, false, true><<<grid, dim3(512), 0, st>>>(DSK_ATTN_ARGS);
+  else if (a.Hq == a.Hkv) attn_kernel<8, 2, 4, true, true><<<grid, dim3(256), 0, st>>>(DSK_ATTN_ARGS);
+  else attn_kernel<8, 2, 4, false, true><<<grid, dim3(256), 0, st>>>(DSK_ATTN_ARGS);
 #undef DSK_ATTN_ARGS
   hipError_t err = hipGetLastError();
   // a cache without tokens: every head already holds the defined empty result, no partial exists
