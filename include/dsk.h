@@ -519,7 +519,7 @@ size_t dsk_reuse_workspace_bytes(const dsk_reuse_args* args);
  * c < ceil(min(sel_count[s,h], k) / slots_per_chunk); with DSK_ATTN_SHARED_SELECTION the count is that of
  * the head's KV head, and a cache without tokens has no partials.  With p = (s*Hq + h)*nchunks + c:
  *   (m, l)  = ((const float*)(workspace + ml_offset))[2p], [2p+1]   running max of the logits in
- *             log2 units (logit * log2(e)), from 2^24 on up to 2^-23 of it less, and sum of 2^(logit2 - m)
+ *             log2 units (logit * log2(e)), and sum of 2^(logit2 - m)
  *   acc[d]  = ((const float*)(workspace + acc_offset))[p*D + d]      sum of 2^(logit2 - m) * V[d]
  * The merged result is out = sum_c acc_c 2^(m_c - M) / sum_c l_c 2^(m_c - M), M = max_c m_c, and
  * lse = ln(2) * M + ln(sum_c l_c 2^(m_c - M)) (App. B.2 Step 3, online-softmax split).

@@ -35,20 +35,24 @@ __device__ __forceinline__ float dot8_bf16(const QRow& q, const uint4& k) {
   return dot2_bf16(q.p[3], k.w, d);
 }
 
-// 2^x for x <= 2 on the hardware exponential alone: results below the normal range come out as
+// 2^x on the hardware exponential alone, for x <= 0 or not far above: results below the normal range come out as
 // 0, which is what a softmax weight that small is worth; -inf gives 0.
 __device__ __forceinline__ float exp2_small(float x) { return __builtin_amdgcn_exp2f(x); }
 
-// Reference of a state whose exponents are one multiply-add each, z * scale - reference, from its largest logit.  The exponent of
-// the largest row is then what rounding took from its logit: at most half a unit in the last place, which all weights of the state
-// have alike.  Beyond kPlainLogits (in log2 units) that could take all weights out of range, so the reference goes down by as much
-// as rounding can have put on and more, and the exponents are bounded by kMostExponent: rows that close to the largest (within
-// the rounding of such logits) count alike.  An infinite logit stays the reference.
-constexpr float kPlainLogits = 16777216.0f;
-constexpr float kMostExponent = 2.0f;
-__device__ __forceinline__ float fma_reference(float m) {
-  return fmaf(__builtin_amdgcn_fmed3f(fabsf(m) - kPlainLogits, 0.0f, 3.0e38f), -1.1920929e-7f, m);   // 2^-23
-}
+// Exponents of one multiply-add each, z * scale - m, where m is the largest logit as rounded.  The exponent of the largest row is
+// what rounding took from its logit: at most half a unit in the last place, which all weights of a state have alike.  From 2^30 on
+// (log2 units) that is more than 32, and from 2^31 on it would take the weights out of range: scale and m are halved until m is
+// below 2^30, where logits that differ at all are still 64 apart and all the weight is on the largest.
+struct FmaExponent {
+  float scale, m;
+  __device__ __forceinline__ FmaExponent(float scale_log2, float largest) {
+    const int e = __builtin_amdgcn_frexp_expf(largest) - 30;     // of an infinity or NaN: 0
+    const int over = e > 0 ? e : 0;
+    scale = ldexpf(scale_log2, -over);
+    m = ldexpf(largest, -over);
+  }
+  __device__ __forceinline__ float of(float z) const { return fmaf(z, scale, -m); }
+};
 
 // one channel of a finished attention output: fp32 always, a nearest-even bf16 copy on request
 __device__ __forceinline__ void store_attn_out(float* __restrict__ out, uint16_t* __restrict__ out_bf16, int64_t idx,
@@ -77,14 +81,15 @@ __device__ __forceinline__ void fold_loaded(WaveState& st, const QRow& qf, const
     mloc = fmaxf(mloc, z[u]);
   }
   mloc = fmaxf(fmaxf(rows4_f(mloc, 0), rows4_f(mloc, 1)), fmaxf(rows4_f(mloc, 2), rows4_f(mloc, 3)));
-  if constexpr (OWN_SUMS) mloc = fma_reference(mloc * scale_log2);
+  if constexpr (OWN_SUMS) mloc *= scale_log2;            // rounding keeps the order
   const float m_new = fmaxf(st.m, mloc);           // finite: nvalid >= 1
   const float alpha = exp2_small(st.m - m_new);          // 0 on the first fold (st.m = -inf)
   if constexpr (OWN_SUMS) {
+    const FmaExponent exponent(scale_log2, m_new);
     float l, acc[8];
 #pragma unroll
     for (int u = 0; u < NS; ++u) {
-      const float p = exp2_small(__builtin_elementwise_minimum(fmaf(z[u], scale_log2, -m_new), kMostExponent));   // a NaN stays
+      const float p = exp2_small(exponent.of(z[u]));
       float f[8];
       unpack8(vv[u], f);
       l = u == 0 ? p : l + p;
