@@ -182,3 +182,39 @@ def test_scores_of_any_group_width(Hq, Hkv, shared, lens):
                 want, tol = best, best_tol
             got = sel.scores[h // G if shared else h, cub[s]: cub[s + 1]].double().cpu()
             assert bool(((got - want).abs() <= tol).all()), (s, h, float((got - want).abs().max()))
+
+
+# every width of the tiles, and the kernel for shared lists of more than 8 heads; in the selection's launch and in one of their own
+@pytest.mark.parametrize("n_blocks", [90, 700])
+@pytest.mark.parametrize("G", [1, 2, 3, 4, 5, 6, 7, 8, 12])
+def test_a_nan_in_a_query_stays_with_its_head(G, n_blocks):
+    """A query with a NaN, of either sign, has NaN for all its scores, whatever the width of the group; the scores of the other
+    heads are the same bits as without it, a list that the group shares goes by theirs."""
+    from test_gpu_select_short import _run, _tables
+    rng = np.random.default_rng([G, n_blocks])
+    t = _tables(rng, [n_blocks, 5], 2 * G, 2, 16, room=8)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(G)
+    q = torch.randn(2, 2 * G, 128, generator=g, device="cuda").bfloat16()
+    kw = dict(max_blocks_per_seq=n_blocks)
+    clean = _run(t, q, 320, **kw)
+    bad = G // 2                                          # in the first sequence, first group
+    for sign in (1.0, -1.0):
+        q2 = q.clone()
+        q2[0, bad, 77] = float(np.copysign(np.nan, sign))
+        got = _run(t, q2, 320, **kw)
+        assert bool(got[4][bad, :n_blocks].isnan().all())
+        same = torch.ones_like(got[4], dtype=torch.bool)
+        same[bad, :n_blocks] = False
+        assert torch.equal(got[4][same], clean[4][same])
+        for x, y in zip(got[:4], clean[:4]):
+            keep = torch.ones(2, 2 * G, dtype=torch.bool)
+            keep[0, bad] = False
+            assert torch.equal(x[keep.cuda()], y[keep.cuda()])
+        assert int(got[3][0, bad]) == int(clean[3][0, bad])
+        slots = got[0][0, bad, : int(got[3][0, bad])].cpu().numpy()
+        assert (np.diff(slots) > 0).all() and slots[0] >= 0
+        if G > 1:
+            shared = _run(t, q2, 320, shared=True, **kw)
+            others = [h for h in range(G) if h != bad]
+            assert torch.equal(shared[4][0, :n_blocks], clean[4][others, :n_blocks].amax(0))

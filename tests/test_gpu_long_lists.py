@@ -105,7 +105,8 @@ def test_long_lists(B, Hq, Hkv, k, b, is_long, on_shared_kernel, layout):
         assert torch.equal(att.out, again.out) and torch.equal(att.lse, again.lse)
 
 
-def _spans_in_and_outside_the_cache(b, B, Hq, Hkv, k, shared):
+def _spans_in_and_outside_the_cache(b, B, Hq, Hkv, k, shared, kernel):
+    """kernel: the one that is to run, "8" and "16" the one for short chunks of so many slots."""
     import paper_2602_03184_amd as dsk
     rng = np.random.default_rng([b, B, Hq, k])
     g = torch.Generator(device="cuda")
@@ -129,7 +130,17 @@ def _spans_in_and_outside_the_cache(b, B, Hq, Hkv, k, shared):
     n_kept = np.array([[int((keep < counts[s, h]).sum()) for h in range(H)] for s in range(B)])
     args = dsk.make_attn_args(q, K, V, dev_i32(bad[0]), dev_i32(bad[1]), dev_i32(counts), b,
                               flags=dsk.DSK_ATTN_SHARED_SELECTION if shared else 0)
+    args.keep[-1].fill_(255)
     dsk.dsk_sparse_decode_attn(args.args)
+    torch.cuda.synchronize()
+    lay = dsk.dsk_attn_partials_layout(args.args)
+    if kernel == "shared":
+        assert lay.slots_per_chunk not in (8, 16)
+    else:                                                                  # the long lists' kernel leaves fewer partials
+        used = -(-counts // lay.slots_per_chunk) * (Hq // H)
+        left, short = _partials_left(args, lay), int(used[used > Hq // H].sum())
+        assert left < short if kernel == "long" else left == short
+        assert kernel == "long" or lay.slots_per_chunk == int(kernel)
     want, want_lse = _want(q, K, V, start[:, :, keep], length[:, :, keep], n_kept, Hq // H)
     assert rel_err(args.out.cpu().numpy(), want) <= 1e-5                   # sums of 32 bits
     np.testing.assert_allclose(args.lse.cpu().numpy(), want_lse, rtol=0, atol=1e-5)   # -inf where nothing is selected
@@ -143,16 +154,17 @@ def test_slots_of_more_than_32_rows(b, B, Hq, Hkv, k, shared, large):
     """Slots around the 16 and 32 rows that are folded first, and of the rows behind them; launches of up to 256 workgroups of 8
     slots and of more, where slots of up to 127 rows, and of shared lists, go two to a wavefront."""
     assert (B * Hq * -(-k // 8) > 256) == large
-    _spans_in_and_outside_the_cache(b, B, Hq, Hkv, k, shared)
+    _spans_in_and_outside_the_cache(b, B, Hq, Hkv, k, shared, "8")
 
 
 @pytest.mark.parametrize("b", [1, 5, 8])
-@pytest.mark.parametrize("B,Hq,Hkv,k,shared", [(1, 4, 2, 21, False), (24, 32, 8, 31, False), (8, 32, 8, 67, False), (4, 8, 8, 600, False),
-                                               (8, 32, 8, 99, True), (8, 16, 2, 203, True), (16, 4, 2, 131, True)])
-def test_slots_of_up_to_8_rows(b, B, Hq, Hkv, k, shared):
+@pytest.mark.parametrize("B,Hq,Hkv,k,shared,kernel", [(1, 4, 2, 21, False, "16"), (24, 32, 8, 31, False, "8"), (8, 32, 8, 67, False, "long"),
+                                                      (4, 8, 8, 600, False, "long"), (8, 32, 8, 99, True, "shared"),
+                                                      (8, 16, 2, 203, True, "shared"), (16, 4, 2, 131, True, "shared")])
+def test_slots_of_up_to_8_rows(b, B, Hq, Hkv, k, shared, kernel):
     """Two slots in a wavefront's 16 rows: odd numbers of them, skipped ones in between; workgroups of 8 and 16 slots, the kernels
     for long and for shared lists with 2, 4 and 8 heads a tile."""
-    _spans_in_and_outside_the_cache(b, B, Hq, Hkv, k, shared)
+    _spans_in_and_outside_the_cache(b, B, Hq, Hkv, k, shared, kernel)
 
 
 def test_long_lists_skip_spans_outside_the_cache():
@@ -360,9 +372,12 @@ def test_logits_of_any_size(B, Hq, Hkv, k, b, shared, scale, size):
     assert checked >= len(heads) // 2
 
 
-# chunks a list in several wavefronts: short chunks, long lists, shared lists in tiles of 4 and 8 heads, slots of two tiles
+# chunks a list in several wavefronts: short chunks, long lists, shared lists in tiles of 4 and 8 heads, slots of two tiles; slots of
+# which a wavefront takes two at a time (an odd number of them), or which lie in one or two to a wavefront beyond 32 rows
 @pytest.mark.parametrize("B,Hq,Hkv,k,b,shared", [(2, 8, 2, 50, 16, False), (8, 32, 8, 128, 16, False), (8, 32, 8, 128, 32, False),
-                                                 (8, 32, 8, 128, 16, True), (8, 56, 8, 128, 32, True)])
+                                                 (8, 32, 8, 128, 16, True), (8, 56, 8, 128, 32, True), (2, 8, 2, 51, 8, False),
+                                                 (12, 32, 8, 35, 8, False), (8, 32, 8, 121, 8, False), (8, 32, 8, 121, 8, True),
+                                                 (2, 8, 2, 51, 64, False), (8, 32, 8, 121, 64, False)])
 def test_values_that_are_not_finite_stay_where_they_are(B, Hq, Hkv, k, b, shared):
     """A NaN in a query, a row of K or a row of V, or an infinity in V, shows in the outputs that depend on it and in no other:
     not in the other heads of a group, whose logits share matrix products, nor in other lists or channels.  Where a logit is
