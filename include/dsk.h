@@ -242,7 +242,8 @@ typedef struct dsk_select_args {
   int32_t* sel_start;          /* [dev] [B, Hq, k] first global token of the slot */
   int32_t* sel_len;            /* [dev] [B, Hq, k] tokens in the slot (1..b); 0 padding */
   int32_t* sel_count;          /* [dev] [B, Hq] number of selected slots */
-  float* scores;               /* [dev] optional out [Hq, max_blocks_total] block scores */
+  float* scores;               /* [dev] optional out [Hq, max_blocks_total] block scores.  A NaN in a query makes
+                                  all scores of its head NaN; a group's shared scores are the largest of the others */
   /* Tables with a region per sequence (dsk_append_tokens_batch); both NULL for the packed tables of
      a batched dsk_compress.  cu_blocks then holds the region starts, and */
   const int32_t* blocks_used;  /* [dev] optional [B]: sequence s has blocks cu_blocks[s] .. +blocks_used[s]-1
@@ -258,7 +259,8 @@ typedef struct dsk_select_args {
  * dsk_sparse_decode_attn -- attention of one decode query per (sequence, head) over the
  * tokens of the selected slots (App. B.2 Steps 2-3):
  *   z_t = q.K[hk,t] * scale;  out = sum_t softmax(z)_t V[hk,t];  lse = log sum_t exp(z_t)
- * fp32 accumulation, split over slots with an online-softmax merge in a fixed order.
+ * fp32 accumulation, split over slots with an online-softmax merge in a fixed order.  How lists are cut, and with it the
+ * last bits, follows B, Hq, Hkv, k, b and the flags; the same call gives the same bits.
  * A (sequence, head) with no selected token gets out = 0 and lse = -inf.
  * ---------------------------------------------------------------------------------------- */
 /* dsk_attn_args.flags: stop after the per-chunk partials (running max in log2 units, denominator,

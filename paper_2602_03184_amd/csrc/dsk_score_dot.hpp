@@ -49,7 +49,7 @@ __device__ __forceinline__ void half_wave_reduce(float (&v)[N], int lane, int& i
 }
 
 // q+ (lanes holding kmax) or q- (lanes holding kmin) of 8 channels as packed bf16 pairs: the halves whose sign does not fit
-// are zeroed, both are exact in bf16
+// are zeroed, both are exact in bf16 (a NaN stays in one of them)
 __device__ __forceinline__ void keep_sign(const uint4& q, bool is_max, uint32_t (&out)[4]) {
   const uint32_t wds[4] = {q.x, q.y, q.z, q.w};
 #pragma unroll

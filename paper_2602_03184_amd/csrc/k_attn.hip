@@ -844,7 +844,8 @@ static int attn_even_chunks(PerXcd per_xcd, int64_t lists, int k, int min_slots,
 //  - where the lists of a group have more than 100 000 rows together, 88 calls 0.87, 1.01, or, if the last round is full to
 //    95 %, more than 75 000, 102 calls 0.88, 1.04, or there are 8 heads and more, 104 calls 0.85, 1.04.
 // The other 1000 took 0.97 in the mean, but a fifth of them more than 2 % longer than on attn_kernel, 13 % at most (48 / 8
-// heads, six sequences, 175 slots of 16 rows 34.1 -> 38.0 us).
+// heads, six sequences, 175 slots of 16 rows 34.1 -> 38.0 us).  Slots of up to 8 rows, measured again with two of them in flight on
+// both kernels: 97 calls that take this one 0.91, 1.03; with one round only 1.03 of the time as chosen, 1.40 at most.
 static bool attn_long_in_rounds(const dsk_attn_args& a, int G, int chunks, double use) {
   const int64_t rows = (int64_t)a.k * a.b;
   return G >= 10 || rows <= 1024 || a.b <= 12 || (a.b > 16 && a.b <= 24) ||

@@ -941,8 +941,8 @@ __device__ __forceinline__ float imp_rows_sum(Locate locate, int pitch, int idx,
 }
 
 // grid: (class, sequence).  The wavefronts are dealt to the class's samples; their lanes merge the pieces
-// of the sample's rows over all KV heads and sum the row values, thread 0 then adds the sample scores in
-// sample order (every sum in a fixed order).
+// of the sample's rows over all KV heads and sum the row values, the first wavefront then adds the sample
+// scores in sample order (every sum in a fixed order).
 constexpr int kImpFinItems = 1024;   // items whose places on the line are fetched ahead
 __global__ __launch_bounds__(kImpFinThreads) void importance_finalize_kernel(
     int32_t* __restrict__ plan, const float4* __restrict__ part, const int32_t* __restrict__ samp_pos,
