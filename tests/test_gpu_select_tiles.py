@@ -4,6 +4,7 @@ import numpy as np
 import pytest
 import torch
 
+from dsk_testutil import dev_i32
 from test_gpu_select_short import _run, _tables
 
 pytestmark = pytest.mark.gpu
@@ -38,3 +39,25 @@ def test_every_register_tile_selects_alike(blocks, b):
             for h in range(2):
                 n = int(got[3][s, h])
                 np.testing.assert_array_equal(got[0][s, h, :n].cpu().numpy(), _sorted_slots(t, got[4][h], s, budget // b))
+
+
+def test_tiles_by_the_length_of_regions():
+    """Tables with a region per sequence under a bound for the largest tile: the tile goes by the blocks in use, not by the region."""
+    rng = np.random.default_rng(12)
+    sizes, used = [9000, 13000, 17000, 4000], [8100, 12285, 16900, 0]
+    t = _tables(rng, sizes, 2, 1, 8, room=100)
+    ends = np.concatenate([[0], np.cumsum(sizes)])
+    base = t.block_start.clone()
+    for lo, hi in zip(ends, ends[1:]):                                     # inside a region positions and slots count from 0
+        t.block_start[lo:hi] = base[lo:hi] - base[lo]
+        t.slot_base[lo:hi] -= t.slot_base[lo].clone()
+    t.blocks_used, t.seq_row0 = dev_i32(used), dev_i32([5, 0, 100000, 7])
+    g = torch.Generator(device="cuda")
+    g.manual_seed(6)
+    q = torch.randn(4, 2, 128, generator=g, device="cuda").bfloat16()
+    for budget in (8, 1500 * 8):
+        memory = _run(t, q, budget, max_blocks_per_seq=300)
+        for kw in (dict(max_blocks_per_seq=16381), dict()):
+            for x, y in zip(_run(t, q, budget, **kw)[:4], memory):
+                assert torch.equal(x, y), (budget, kw)
+        assert memory[3].cpu().tolist() == [[min(budget // 8, 1500)] * 2] * 3 + [[0, 0]]
