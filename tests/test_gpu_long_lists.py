@@ -148,7 +148,8 @@ def _spans_in_and_outside_the_cache(b, B, Hq, Hkv, k, shared, kernel):
 
 @pytest.mark.parametrize("b", [33, 48, 64, 65, 100, 127, 128])
 @pytest.mark.parametrize("B,Hq,Hkv,k,shared,large", [(2, 6, 2, 21, False, False), (1, 28, 4, 8, False, False), (3, 8, 8, 9, False, False),
-                                                     (2, 8, 2, 17, True, False), (16, 16, 4, 8, False, False), (9, 19, 1, 21, False, True),
+                                                     (2, 8, 2, 17, True, False), (16, 16, 4, 8, False, False), (16, 16, 4, 16, False, True),
+                                                     (9, 19, 1, 21, False, True),
                                                      (12, 40, 8, 12, True, True), (33, 16, 16, 7, False, True)])
 def test_slots_of_more_than_32_rows(b, B, Hq, Hkv, k, shared, large):
     """Slots around the 16 and 32 rows that are folded first, and of the rows behind them; launches of up to 256 workgroups of 8
